@@ -1,7 +1,8 @@
 // Element-wise glue between convolution layers (activation, residual add, channel concat and
 // their gradients).  Not part of the paper's method; they exist so that a whole network can
 // run on the library's own kernels.  All are bandwidth-bound streaming kernels over
-// [rows][channels] tensors, 8 elements (16 bytes) per lane for the 16-bit types.
+// [rows][channels] tensors: a lane moves 16 bytes at a time (one element at a time they were bound by the
+// number of memory instructions: 400k x 32 f16, gradient through a ReLU, 20.0 -> 14.5 us).
 #include "common.h"
 
 #include <algorithm>
@@ -9,53 +10,86 @@
 namespace spc {
 namespace {
 
-template <typename T> __device__ __forceinline__ float to_f(T v) { return (float)v; }
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 enum EwOp { EW_RELU = 0, EW_ADD = 1, EW_ADD_RELU = 2, EW_RELU_BWD = 3 };
 
-// out[i] = op(a[i], b[i]); RELU: max(a,0); ADD: a+b; ADD_RELU: max(a+b,0); RELU_BWD: b > 0 ? a : 0
-template <typename T, int OP>
-__global__ void __launch_bounds__(256) k_ew(const T* a, const T* b, T* out,  // (out may alias a or b: no __restrict__)
-                                            long long n) {
-  const long long stride = (long long)gridDim.x * blockDim.x;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const float x = to_f(a[i]);
-    const float y = (OP == EW_RELU) ? 0.f : to_f(b[i]);
-    float r;
-    if (OP == EW_RELU) r = x > 0.f ? x : 0.f;
-    else if (OP == EW_ADD) r = x + y;
-    else if (OP == EW_ADD_RELU) r = (x + y) > 0.f ? (x + y) : 0.f;
-    else r = y > 0.f ? x : 0.f;
-    out[i] = (T)r;
-  }
+template <typename T, int OP> __device__ __forceinline__ T ew_one(T a, T b) {
+  const float x = (float)a;
+  const float y = (OP == EW_RELU) ? 0.f : (float)b;
+  float r;
+  if (OP == EW_RELU) r = x > 0.f ? x : 0.f;
+  else if (OP == EW_ADD) r = x + y;
+  else if (OP == EW_ADD_RELU) r = (x + y) > 0.f ? (x + y) : 0.f;
+  else r = y > 0.f ? x : 0.f;
+  return (T)r;
 }
 
-// dst[r][dst_off + c] = src[r][src_off + c] for c < cols (channel concat / split)
-template <typename T>
-__global__ void __launch_bounds__(256) k_copy_cols(const T* __restrict__ src, int src_ld, int src_off, T* __restrict__ dst,
-                                                   int dst_ld, int dst_off, int cols, long long rows) {
-  const long long total = rows * cols;
+// out[i] = op(a[i], b[i]); RELU: max(a,0); ADD: a+b; ADD_RELU: max(a+b,0); RELU_BWD: b > 0 ? a : 0.
+// (out may alias a or b: no __restrict__.)  Vectors [0, nv) of 16 bytes, one per thread, then the elements that
+// fill no vector, or every element where a pointer is not 16-byte aligned (nv = 0).
+template <typename T, int OP>
+__global__ void __launch_bounds__(256) k_ew(const T* a, const T* b, T* out, long long nv, long long n) {
+  constexpr int W = 16 / sizeof(T);
+  typedef T vec __attribute__((ext_vector_type(W)));
   const long long stride = (long long)gridDim.x * blockDim.x;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
-    const long long r = i / cols;
-    const int c = (int)(i - r * cols);
-    dst[r * dst_ld + dst_off + c] = src[r * src_ld + src_off + c];
+  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  for (long long i = t; i < nv; i += stride) {
+    const vec x = reinterpret_cast<const vec*>(a)[i];
+    vec y = x, r;
+    if (OP != EW_RELU) y = reinterpret_cast<const vec*>(b)[i];
+#pragma unroll
+    for (int j = 0; j < W; ++j) r[j] = ew_one<T, OP>(x[j], y[j]);
+    reinterpret_cast<vec*>(out)[i] = r;
+  }
+  for (long long i = nv * W + t; i < n; i += stride) out[i] = ew_one<T, OP>(a[i], OP == EW_RELU ? a[i] : b[i]);
+}
+
+// dst[r][dst_off + c] = src[r][src_off + c] for c < cols (channel concat / split), in units of V: row lengths,
+// offsets and column count are multiples of it.
+template <typename V, typename I>
+__global__ void __launch_bounds__(256) k_copy_cols(const V* __restrict__ src, int src_ld, int src_off, V* __restrict__ dst,
+                                                   int dst_ld, int dst_off, int cols, I total) {
+  const I stride = (I)gridDim.x * blockDim.x;
+  for (I i = (I)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
+    const I r = i / (I)cols;
+    const int c = (int)(i - r * (I)cols);
+    dst[(long long)r * dst_ld + dst_off + c] = src[(long long)r * src_ld + src_off + c];
   }
 }
 
 template <typename T>
 int launch_ew(int op, const void* a, const void* b, void* out, long long n, hipStream_t st) {
-  const unsigned blocks = (unsigned)std::min<long long>((n + 255) / 256, 8192);
+  constexpr long long W = 16 / sizeof(T);
+  const bool aligned = (((size_t)a | (size_t)(op == EW_RELU ? a : b) | (size_t)out) & 15) == 0;
+  const long long nv = aligned ? n / W : 0;
+  const long long threads = nv > 0 ? std::max(nv, n - nv * W) : n;
+  const unsigned blocks = (unsigned)std::min<long long>((threads + 255) / 256, 1 << 16);
   const T* pa = (const T*)a;
   const T* pb = (const T*)b;
   T* po = (T*)out;
   switch (op) {
-    case EW_RELU: hipLaunchKernelGGL((k_ew<T, EW_RELU>), dim3(blocks), dim3(256), 0, st, pa, pb, po, n); break;
-    case EW_ADD: hipLaunchKernelGGL((k_ew<T, EW_ADD>), dim3(blocks), dim3(256), 0, st, pa, pb, po, n); break;
-    case EW_ADD_RELU: hipLaunchKernelGGL((k_ew<T, EW_ADD_RELU>), dim3(blocks), dim3(256), 0, st, pa, pb, po, n); break;
-    case EW_RELU_BWD: hipLaunchKernelGGL((k_ew<T, EW_RELU_BWD>), dim3(blocks), dim3(256), 0, st, pa, pb, po, n); break;
+    case EW_RELU: hipLaunchKernelGGL((k_ew<T, EW_RELU>), dim3(blocks), dim3(256), 0, st, pa, pb, po, nv, n); break;
+    case EW_ADD: hipLaunchKernelGGL((k_ew<T, EW_ADD>), dim3(blocks), dim3(256), 0, st, pa, pb, po, nv, n); break;
+    case EW_ADD_RELU: hipLaunchKernelGGL((k_ew<T, EW_ADD_RELU>), dim3(blocks), dim3(256), 0, st, pa, pb, po, nv, n); break;
+    case EW_RELU_BWD: hipLaunchKernelGGL((k_ew<T, EW_RELU_BWD>), dim3(blocks), dim3(256), 0, st, pa, pb, po, nv, n); break;
     default: return SPCONV_EINVAL;
   }
+  SPC_LAUNCH_CHECK();
+  return SPCONV_OK;
+}
+
+template <typename V>
+int launch_copy_cols(const void* src, int src_ld, int src_off, void* dst, int dst_ld, int dst_off, int cols, long long rows,
+                     hipStream_t st) {
+  const long long total = rows * cols;
+  const unsigned blocks = (unsigned)std::min<long long>((total + 255) / 256, 1 << 16);
+  if (total < (1ll << 31))  // (32-bit index arithmetic: the loop's step stays below 2^24)
+    hipLaunchKernelGGL((k_copy_cols<V, unsigned>), dim3(blocks), dim3(256), 0, st, (const V*)src, src_ld, src_off, (V*)dst,
+                       dst_ld, dst_off, cols, (unsigned)total);
+  else
+    hipLaunchKernelGGL((k_copy_cols<V, unsigned long long>), dim3(blocks), dim3(256), 0, st, (const V*)src, src_ld, src_off,
+                       (V*)dst, dst_ld, dst_off, cols, (unsigned long long)total);
   SPC_LAUNCH_CHECK();
   return SPCONV_OK;
 }
@@ -87,17 +121,19 @@ SPCONV_API int spconv_copy_cols(const void* src, int src_ld, int src_off, void* 
   if (rows == 0 || cols == 0) return SPCONV_OK;
   if (!src || !dst) return SPCONV_EINVAL;
   hipStream_t st = (hipStream_t)stream;
-  const unsigned blocks = (unsigned)std::min<long long>((rows * cols + 255) / 256, 8192);
-  if (dtype == SPCONV_F32)
-    hipLaunchKernelGGL((k_copy_cols<float>), dim3(blocks), dim3(256), 0, st, (const float*)src, src_ld, src_off,
-                       (float*)dst, dst_ld, dst_off, cols, (long long)rows);
-  else if (dtype == SPCONV_F16 || dtype == SPCONV_BF16)
-    hipLaunchKernelGGL((k_copy_cols<unsigned short>), dim3(blocks), dim3(256), 0, st, (const unsigned short*)src,
-                       src_ld, src_off, (unsigned short*)dst, dst_ld, dst_off, cols, (long long)rows);
-  else
-    return SPCONV_EINVAL;
-  SPC_LAUNCH_CHECK();
-  return SPCONV_OK;
+  if (dtype != SPCONV_F32 && dtype != SPCONV_F16 && dtype != SPCONV_BF16) return SPCONV_EINVAL;
+  // the widest unit (16, 8, 4 or 2 bytes) that divides every length, offset and address
+  const int e = dtype == SPCONV_F32 ? 4 : 2;
+  const size_t all = (size_t)(src_ld * e) | (size_t)(src_off * e) | (size_t)(dst_ld * e) | (size_t)(dst_off * e) |
+                     (size_t)(cols * e) | (size_t)src | (size_t)dst;
+  const int u = (all & 15) == 0 ? 16 : (all & 7) == 0 ? 8 : (all & 3) == 0 ? 4 : 2;
+  src_ld = src_ld * e / u, src_off = src_off * e / u, dst_ld = dst_ld * e / u, dst_off = dst_off * e / u, cols = cols * e / u;
+  switch (u) {
+    case 16: return launch_copy_cols<u32x4>(src, src_ld, src_off, dst, dst_ld, dst_off, cols, rows, st);
+    case 8: return launch_copy_cols<unsigned long long>(src, src_ld, src_off, dst, dst_ld, dst_off, cols, rows, st);
+    case 4: return launch_copy_cols<unsigned>(src, src_ld, src_off, dst, dst_ld, dst_off, cols, rows, st);
+  }
+  return launch_copy_cols<unsigned short>(src, src_ld, src_off, dst, dst_ld, dst_off, cols, rows, st);
 }
 
 }  // extern "C"
