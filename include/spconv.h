@@ -90,7 +90,10 @@ typedef enum spconv_op { SPCONV_OP_FWD = 0, SPCONV_OP_DGRAD = 1, SPCONV_OP_WGRAD
 typedef struct spconv_kmap spconv_kmap; /* opaque */
 
 /* Dataflow parameters (the design space of Section 4.1).  Zero-initialise for
- * the defaults.
+ * the defaults.  A null configuration leaves all of them to the library, the row order included:
+ * spconv_fwd and spconv_dgrad then visit the rows in an order of the library's own (similar
+ * neighbour masks together, built once per kmap and side) where the layers that ran on the kmap
+ * so far are wide or many enough to pay for it.
  *   n_split     0: unsorted implicit GEMM, rows in map order, one pass.
  *               s >= 1 (at most 4 and at most K^3): the K^3 offsets are cut into s contiguous
  *               ranges [floor(i*V/s), floor((i+1)*V/s)); in each range the

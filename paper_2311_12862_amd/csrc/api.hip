@@ -130,9 +130,9 @@ int resolve_config(const spconv_config* cfg, spconv_dtype dtype, spconv_config* 
   return SPCONV_OK;
 }
 
-// Tile height of the plan a configuration uses, as the plan cache keys it.
-int plan_tile(const spconv_config& c, bool wave) {
-  return (wave ? 16 : c.tile_m) | ((c.flags & SPCONV_FLAG_SLABS) && c.n_split > 0 ? kPlanSlabs : 0);
+// Flags of the plan a configuration uses, as the plan cache keys it.
+int plan_flags(const spconv_config& c, bool automatic) {
+  return ((c.flags & SPCONV_FLAG_SLABS) ? kPlanSlabs : 0) | (automatic ? kPlanOwnOrder : 0);
 }
 
 // Which table an op walks, and with which weight indexing.
@@ -166,46 +166,67 @@ int64_t auto_wgrad_pairs(spconv_kmap* km, int C_in, int C_out) {
 // Which kernel runs a forward / dgrad call and on which tiles: the caller's configuration with
 // the automatic choices filled in.  Pure host arithmetic (spconv_describe_launch reports it).
 struct KernelChoice {
-  bool wave = false;  // kernel 1 (weights resident in LDS) instead of kernel 2 (workgroup tiles)
-  int tile_m = 0;     // plan tile height: 16 for kernel 1
-  int tile_n = 0;     // as passed to the kernel (0: its own default)
+  enum Kind { TILES, WAVE, RING } kind = TILES;  // k_igemm (register-staged tiles), k_igemm_wave (weights resident), k_ring
+  int tile_m = 0;  // k_igemm
+  int tile_n = 0;  // k_igemm, k_igemm_wave: as passed to the kernel (0: its own default)
+  RingShape ring;
 };
-int choose_kernel(int V, int64_t rows_dst, int c_red, int c_cols, spconv_dtype dtype, bool tile_m_given,
+int choose_kernel(int V, int64_t rows_dst, int64_t rows_src, int c_red, int c_cols, spconv_dtype dtype, const spconv_config* cfg,
                   const spconv_config& c, KernelChoice* out) {
   KernelChoice k;
-  int tile_m = c.tile_m;
-  if (!tile_m_given && dtype != SPCONV_F32) {
+  const bool f32 = dtype == SPCONV_F32, tiles_given = cfg && (cfg->tile_m != 0 || cfg->tile_n != 0);
+  k.tile_n = c.tile_n;
+  if (!f32 && (c.kernel == 1 || (c.kernel == 0 && !(tiles_given && c.tile_n == 128)))) {
+    const int bn = igemm_wave_pick_bn(V, c.n_split, c_red, c_cols, c.tile_n, nullptr);
+    bool wave = bn > 0;
+    if (!wave && c.kernel == 1) return SPCONV_EINVAL;
+    // Automatic choice.  The LDS-resident kernel gathers the input once per column tile: it wins while the output is at
+    // most two tiles wide (64 -> 64 is 2 x 32).  On unsorted maps it also wins beyond that while tiles x reduced
+    // channels x rows stays small (measured against the register-staged tiles: 100k rows, 64 -> 256 in eight
+    // tiles 89 us against 114 us; 128 -> 128 in eight 16-column tiles 160 us against 131 us); on sorted maps the tiles of
+    // k_ring win there (100k rows, 64 -> 128 in eight 16-column tiles 45 us against 30 us).
+    if (wave && c.kernel == 0) {
+      const int64_t tiles = ceil_div(c_cols, bn);
+      if (tiles > 2 && (c.n_split > 0 || (double)tiles * c_red * (double)rows_dst > 6e7)) wave = false;
+      if (c_red > 64 && c.n_split > 0) wave = false;  // (30k rows 128 -> 128: 34 us against 25 us)
+    }
+    if (wave) {
+      k.kind = KernelChoice::WAVE;
+      *out = k;
+      return SPCONV_OK;
+    }
+  }
+  if (c.tile_n == 16) return SPCONV_EINVAL;
+  // tiles loaded straight into LDS, unless the caller asks for the register-staged ones or for a tile shape
+  if ((f32 || (c.kernel == 0 && !tiles_given)) &&
+      igemm_ring_shape(V, c.n_split, rows_dst, rows_src, c_red, c_cols, f32, cfg == nullptr, &k.ring) == SPCONV_OK) {
+    k.kind = KernelChoice::RING;
+    *out = k;
+    return SPCONV_OK;
+  }
+  k.tile_m = c.tile_m;
+  if (!(cfg && cfg->tile_m != 0) && !f32) {
     // automatic tile height (measured on unsorted maps, 10k .. 300k rows): 128 rows when that still
     // leaves several workgroups per CU, or when the reduction is long (>= 128 channels) and there
     // are enough rows for a workgroup per CU anyway; 64 rows otherwise
-    tile_m = (ceil_div(rows_dst, 128) * ceil_div(c_cols, 128) >= 2048 || (rows_dst >= 25000 && c_red >= 128)) ? 128 : 64;
+    k.tile_m = (ceil_div(rows_dst, 128) * ceil_div(c_cols, 128) >= 2048 || (rows_dst >= 25000 && c_red >= 128)) ? 128 : 64;
   }
-  if (c.kernel != 2 && dtype != SPCONV_F32) {
-    const int bn = igemm_wave_pick_bn(V, c.n_split, c_red, c_cols, c.tile_n, nullptr);
-    k.wave = bn > 0;
-    if (!k.wave && c.kernel == 1) return SPCONV_EINVAL;
-    // Automatic choice: the LDS-resident kernel gathers the input once per column tile.  It wins
-    // while the output is at most two tiles wide (64 -> 64 is 2 x 32) and, beyond that, while
-    // tiles x reduced channels x rows stays small: few rows leave the tiled kernel without enough
-    // workgroups, many rows make the repeated gathers the larger cost (measured: 100k rows,
-    // 64 -> 256 in eight tiles 89 us against 114 us; 128 -> 128 in eight 16-column tiles 160 us
-    // against 131 us; 10k rows, 128 -> 128 25 us against 41 us; 300k rows, 64 -> 128 213 us
-    // against 171 us).
-    if (k.wave && c.kernel == 0) {
-      const int64_t tiles = ceil_div(c_cols, bn);
-      if (tiles > 2 && (double)tiles * c_red * (double)rows_dst > 6e7) k.wave = false;
-    }
-  }
-  if (!k.wave && c.tile_n == 16) return SPCONV_EINVAL;
-  k.tile_m = k.wave ? 16 : tile_m;
-  k.tile_n = c.tile_n;
   // few row tiles: 64-column tiles double the workgroups of the tiled kernel (10k rows, 256 -> 256:
   // 91 us against 104 us)
-  if (!k.wave && c.tile_n == 0 && dtype != SPCONV_F32 && tile_m == 64 && c_cols > 64 &&
-      ceil_div(rows_dst, 64) * ceil_div(c_cols, 128) < 400)
+  if (c.tile_n == 0 && !f32 && k.tile_m == 64 && c_cols > 64 && ceil_div(rows_dst, 64) * ceil_div(c_cols, 128) < 400)
     k.tile_n = 64;
   *out = k;
   return SPCONV_OK;
+}
+
+int run_kernel(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan, IgemmArgs& a, const KernelChoice& kc,
+               hipStream_t st) {
+  a.tile_n = kc.tile_n;
+  switch (kc.kind) {
+    case KernelChoice::WAVE: return igemm_wave_run(km, side, plan, a, st);
+    case KernelChoice::RING: return igemm_ring_run(km, side, plan, a, kc.ring, st);
+    default: return igemm_run(km, side, plan, a, kc.tile_m, st);
+  }
 }
 
 // ---- the fixed scratch array of the entry point that allocates nothing --------------------
@@ -233,6 +254,20 @@ int static_scratch(void** out) {
   return SPCONV_OK;
 }
 
+// Whether a call without a configuration sorts the rows of the side it walks (the library's own order).  The order
+// costs about 24 us + 1 us per 10k rows once per map and side.  What a call saves grows with rows x reduced x produced
+// channels; measured (us, unsorted -> sorted): the LDS-resident kernel, 100k rows 64 -> 64 33 -> 23; the tiles, 100k
+// rows 64 -> 128 70 -> 34, 30k rows 128 -> 128 58 -> 27, 9k rows 256 -> 256 94 -> 37, 300k rows 96 -> 96 337 -> 127,
+// 256 -> 256 1061 -> 445; fp32, 30k rows 64 -> 64 145 -> 46.  How many calls the map will see is not known; it is
+// sorted once the calls so far would have saved two thirds of the cost (wide layers: at the first call).
+bool auto_sorted(const spconv_kmap* km, SideMap& side, int c_red, int c_cols, spconv_dtype dtype) {
+  if (km->V < 8) return false;
+  if (side.plans.count(std::make_pair(1, kPlanOwnOrder))) return true;
+  const double unit = dtype == SPCONV_F32 ? 4e-7 : c_red <= 64 && c_cols <= 64 ? 2.3e-8 : 6e-8;
+  side.auto_saved += unit * (double)side.rows * c_red * c_cols;
+  return 1.5 * side.auto_saved >= 24.0 + 1e-4 * (double)side.rows;
+}
+
 // prepared_only: the call may not allocate.  Plans are looked up, never built (SPCONV_ENOPLAN when
 // missing), and split partial sums go to the fixed scratch array (SPCONV_ELIMIT beyond its size).
 // K = 5: forward / dgrad as the sum over the five 25-offset planes.  Every plane runs like a kmap of
@@ -242,7 +277,7 @@ int static_scratch(void** out) {
 // that slice; dgrad on the submanifold map mirrors the offset, 124 - k, which is offset 24 - j of
 // plane 4 - g.
 int run_planes(spconv_op op, const void* src, const void* weights, spconv_kmap* km, int C_in, int C_out,
-               spconv_dtype dtype, const spconv_config* cfg, const spconv_config& c_in, void* dst, hipStream_t st) {
+               spconv_dtype dtype, const spconv_config* cfg, const spconv_config& c, void* dst, hipStream_t st) {
   const int64_t rows = km->n_out;
   const int dgrad = op == SPCONV_OP_DGRAD;
   const int c_red = dgrad ? C_out : C_in, c_dst = dgrad ? C_in : C_out;
@@ -250,21 +285,15 @@ int run_planes(spconv_op op, const void* src, const void* weights, spconv_kmap* 
   const int n_planes = (int)km->groups.size();
   struct Launch {
     IgemmPlan* plan;
-    bool wave;
-    int tile_n;
+    KernelChoice kc;
   };
   std::vector<Launch> ls((size_t)n_planes);
   int parts_total = 0;
   for (int g = 0; g < n_planes; ++g) {
     spconv_kmap* sub = km->groups[(size_t)g].get();
     sub->last_stream = st;
-    spconv_config c = c_in;
-    KernelChoice kc;
-    SPC_TRY(choose_kernel(sub->V, rows, c_red, c_dst, dtype, cfg && cfg->tile_m != 0, c, &kc));
-    c.tile_m = kc.wave ? c.tile_m : kc.tile_m;
-    SPC_TRY(plan_get(sub, sub->out_side, c.n_split, plan_tile(c, kc.wave), st, &ls[(size_t)g].plan));
-    ls[(size_t)g].wave = kc.wave;
-    ls[(size_t)g].tile_n = kc.tile_n;
+    SPC_TRY(choose_kernel(sub->V, rows, rows, c_red, c_dst, dtype, cfg, c, &ls[(size_t)g].kc));
+    SPC_TRY(plan_get(sub, sub->out_side, c.n_split, plan_flags(c, false), st, &ls[(size_t)g].plan));
     parts_total += ls[(size_t)g].plan->parts;
   }
   SPC_TRY(km->scratch.reserve((size_t)parts_total * rows * c_dst * sizeof(float)));
@@ -280,11 +309,10 @@ int run_planes(spconv_op op, const void* src, const void* weights, spconv_kmap* 
     a.dgrad = dgrad;
     a.mirror = dgrad;
     a.dtype = dtype;
-    a.tile_n = ls[(size_t)g].tile_n;
     a.out = nullptr;
     a.partial = km->scratch.as<float>() + (size_t)part0 * rows * c_dst;
     const IgemmPlan& plan = *ls[(size_t)g].plan;
-    SPC_TRY(ls[(size_t)g].wave ? igemm_wave_run(sub, sub->out_side, plan, a, st) : igemm_run(sub, sub->out_side, plan, a, st));
+    SPC_TRY(run_kernel(sub, sub->out_side, plan, a, ls[(size_t)g].kc, st));
     part0 += plan.parts;
   }
   return split_reduce(km->scratch.as<float>(), parts_total, rows, c_dst, dtype, dst, st);
@@ -330,18 +358,19 @@ int run_igemm_op(spconv_op op, const void* src, const void* weights, spconv_kmap
   }
   const int c_red = os.dgrad ? C_out : C_in;
   const int c_cols = os.dgrad ? C_in : C_out;
+  const bool automatic = !cfg && !prepared_only;
+  if (automatic && auto_sorted(km, *os.side, c_red, c_cols, dtype)) c.n_split = 1;
   KernelChoice kc;
-  SPC_TRY(choose_kernel(km->V, rows_dst, c_red, c_cols, dtype, cfg && cfg->tile_m != 0, c, &kc));
-  const bool wave = kc.wave;
-  c.tile_m = wave ? c.tile_m : kc.tile_m;
+  const int64_t rows_src = op == SPCONV_OP_FWD ? km->n_in : km->n_out;
+  SPC_TRY(choose_kernel(km->V, rows_dst, rows_src, c_red, c_cols, dtype, cfg, c, &kc));
   IgemmPlan* plan = nullptr;
   if (prepared_only) {
     if (c.n_split > km->V) return SPCONV_EINVAL;
-    auto it = os.side->plans.find(std::make_pair((int)c.n_split, plan_tile(c, wave)));
+    auto it = os.side->plans.find(std::make_pair((int)c.n_split, c.n_split > 0 ? plan_flags(c, false) : 0));
     if (it == os.side->plans.end()) return SPCONV_ENOPLAN;
     plan = it->second.get();
   } else {
-    SPC_TRY(plan_get(km, *os.side, c.n_split, plan_tile(c, wave), st, &plan));
+    SPC_TRY(plan_get(km, *os.side, c.n_split, plan_flags(c, automatic), st, &plan));
   }
   IgemmArgs a{};
   a.feats = src;
@@ -351,7 +380,6 @@ int run_igemm_op(spconv_op op, const void* src, const void* weights, spconv_kmap
   a.dgrad = os.dgrad;
   a.mirror = os.mirror;
   a.dtype = dtype;
-  a.tile_n = kc.tile_n;
   const int c_dst = os.dgrad ? C_in : C_out;
   if (plan->parts > 1) {
     const size_t need = (size_t)plan->parts * plan->rows * c_dst * sizeof(float);
@@ -365,11 +393,11 @@ int run_igemm_op(spconv_op op, const void* src, const void* weights, spconv_kmap
       a.partial = km->scratch.as<float>();
     }
     a.out = nullptr;
-    SPC_TRY(wave ? igemm_wave_run(km, *os.side, *plan, a, st) : igemm_run(km, *os.side, *plan, a, st));
+    SPC_TRY(run_kernel(km, *os.side, *plan, a, kc, st));
     return split_reduce(a.partial, plan->parts, plan->rows, c_dst, dtype, dst, st);
   }
   a.out = dst;
-  return wave ? igemm_wave_run(km, *os.side, *plan, a, st) : igemm_run(km, *os.side, *plan, a, st);
+  return run_kernel(km, *os.side, *plan, a, kc, st);
 }
 
 }  // namespace
@@ -521,7 +549,7 @@ SPCONV_API int spconv_kmap_prepare(spconv_kmap* km, spconv_op op, const spconv_c
   OpSide os;
   SPC_TRY(side_for(km, op, st, &os));
   IgemmPlan* plan = nullptr;
-  return plan_get(km, *os.side, c.n_split, plan_tile(c, c.kernel == 1), st, &plan);
+  return plan_get(km, *os.side, c.n_split, plan_flags(c, false), st, &plan);
 }
 
 SPCONV_API int spconv_kmap_drop_plans(spconv_kmap* km) {
@@ -558,7 +586,7 @@ SPCONV_API int spconv_kmap_export_perm(spconv_kmap* km, spconv_op op, const spco
   OpSide os;
   SPC_TRY(side_for(km, op, st, &os));
   IgemmPlan* plan = nullptr;
-  SPC_TRY(plan_get(km, *os.side, c.n_split, plan_tile(c, false), st, &plan));
+  SPC_TRY(plan_get(km, *os.side, c.n_split, plan_flags(c, false), st, &plan));
   if (plan->rows == 0) return SPCONV_OK;
   SPC_HIP(hipMemcpyAsync(dst, plan->perm.as<int>() + (size_t)split * plan->rows_pad,
                          (size_t)plan->rows * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
@@ -591,7 +619,7 @@ SPCONV_API int spconv_kmap_mac_units(spconv_kmap* km, spconv_op op, const spconv
   OpSide os;
   SPC_TRY(side_for(km, op, st, &os));
   IgemmPlan* plan = nullptr;
-  SPC_TRY(plan_get(km, *os.side, c.n_split, plan_tile(c, false), st, &plan));
+  SPC_TRY(plan_get(km, *os.side, c.n_split, plan_flags(c, false), st, &plan));
   return plan_mac_units(km, *os.side, plan, 16, st, executed);
 }
 
@@ -1006,21 +1034,31 @@ SPCONV_API int spconv_describe_launch(int K, int64_t rows, int64_t rows_src, int
   if (c.n_split > V) return SPCONV_EINVAL;
   if (rows == 0) return SPCONV_OK;  // nothing is launched
   KernelChoice kc;
-  SPC_TRY(choose_kernel(V, rows, C_red, C_cols, dtype, cfg && cfg->tile_m != 0, c, &kc));
+  SPC_TRY(choose_kernel(V, rows, rows_src, C_red, C_cols, dtype, cfg, c, &kc));
+  const int tile_m = kc.kind == KernelChoice::WAVE ? 16 : kc.kind == KernelChoice::RING ? kc.ring.bm : kc.tile_m;
   PlanShape ps;
-  SPC_TRY(plan_shape(V, rows, c.n_split, kc.tile_m, &ps));
-  out->kernel = kc.wave ? 1 : 2;
-  out->tile_m = kc.tile_m;
+  SPC_TRY(plan_shape(V, rows, c.n_split, 16, &ps));
+  out->kernel = kc.kind == KernelChoice::WAVE ? 1 : 2;
+  out->tile_m = tile_m;
   out->parts = ps.parts;
   out->rows_pad = ps.rows_pad;
-  out->n_tiles = ps.n_tiles;
+  out->n_tiles = ceil_div(rows, tile_m);
   for (int i = 0; i < ps.parts; ++i) {
     out->lo[i] = ps.lo[i];
     out->width[i] = ps.width[i];
     out->map_elems[i] = (int64_t)ps.rows_pad * (c.n_split == 0 ? V : ps.width[i]);
   }
   out->sorted = c.n_split > 0;
-  if (kc.wave) {
+  if (kc.kind == KernelChoice::RING) {
+    out->tile_n = kc.ring.bn;
+    out->k_steps = kc.ring.piece / (dtype == SPCONV_F32 ? 4 : 2);
+    out->waves = kc.ring.threads / 64;
+    out->threads = kc.ring.threads;
+    out->lds_bytes = (int64_t)kc.ring.lds_bytes;
+    out->grid[0] = (int32_t)kc.ring.n_tiles;  // (launched as one row of workgroups where column tiles are dealt to the XCDs)
+    out->grid[1] = kc.ring.cols;
+    out->grid[2] = kc.ring.parts;
+  } else if (kc.kind == KernelChoice::WAVE) {
     WaveShape w;
     SPC_TRY(igemm_wave_shape(V, c.n_split, rows, rows_src, C_red, C_cols, kc.tile_n, &w));
     out->tile_n = w.bn;

@@ -14,7 +14,8 @@ namespace spc {
 constexpr int kMaxSplit = 4;
 constexpr int kRowPad = 256;  // map rows are padded to a multiple of the largest tile_m
 constexpr int kWave = 64;
-constexpr int kPlanSlabs = 0x10000;  // or-ed into the tile height of a plan key: sort keys start with a spatial slab
+constexpr int kPlanSlabs = 1;      // plan flags: sort keys start with a spatial slab
+constexpr int kPlanOwnOrder = 2;  // and: the library's own order (order.hip) instead of the plain bitmask's (one part)
 
 int hip_fail(hipError_t e, const char* what, const char* file, int line);
 #define SPC_HIP(expr)                                                        \
@@ -72,17 +73,17 @@ inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Plan of the implicit-GEMM kernels for one side of the map (output rows for
-// fwd, input rows for dgrad), one split count and one tile height.
+// fwd, input rows for dgrad) and one split count.  Its masks are those of 16-row blocks (the lock-step unit); kernels with
+// taller tiles combine them, so one plan serves every kernel.
 struct IgemmPlan {
   int n_split = 0;  // 0 = unsorted
-  int tile_m = 128;
   int parts = 1;  // max(1, n_split)
   int64_t rows = 0, rows_pad = 0, n_tiles = 0;
   int lo[kMaxSplit] = {0}, width[kMaxSplit] = {0};
   size_t map_off[kMaxSplit] = {0};  // element offsets into maps
   DevBuf maps;      // reordered maps, part i: int32 [rows_pad][width[i]]  (unused when n_split == 0)
   DevBuf perm;      // int32 [parts][rows_pad]                              (unused when n_split == 0)
-  DevBuf tilemask;  // uint32 [parts][n_tiles] bits relative to lo[i]
+  DevBuf tilemask;  // uint32 [parts][n_tiles]: masks of 16-row blocks, bits relative to lo[i]  (unused when n_split == 0)
   bool slabs = false;  // sort keys start with a spatial slab: contiguous ranges of the order are spatially compact
 };
 
@@ -107,7 +108,8 @@ struct SideMap {      // one output-stationary table: rows x V
   DevBuf map;         // int32 [rows_pad][V]
   DevBuf mask;        // uint32 [rows_pad]
   bool ready = false;
-  std::map<std::pair<int, int>, std::unique_ptr<IgemmPlan>> plans;  // (n_split, tile_m)
+  double auto_saved = 0;  // us that calls without a configuration would have saved on a sorted map so far
+  std::map<std::pair<int, int>, std::unique_ptr<IgemmPlan>> plans;  // (n_split, flags)
 };
 
 }  // namespace spc
@@ -216,12 +218,27 @@ struct TileShape {  // igemm_run (kernel 2 and the fp32 kernel)
 int igemm_tile_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_red, int c_out, int tile_m, int tile_n,
                      bool f32, bool dgrad, TileShape* s);
 
+struct RingShape {  // igemm_ring_run (tiles loaded straight into LDS; every fp32 layer)
+  int bm = 0, bn = 0, nwk = 0, piece = 0;  // tile, K groups, bytes of a row per unit
+  int threads = 0, n_cols = 0, cols = 0, parts = 0;
+  int64_t n_tiles = 0;
+  size_t lds_bytes = 0;
+  unsigned grid[3] = {0, 0, 0};
+  unsigned feats_bytes = 0;
+};
+// small_tiles: 32-row tiles and K groups of fp32 may be chosen
+int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_red, int c_out, bool f32, bool small_tiles,
+                     RingShape* s);
+
 // ---- plan.hip
-// tile_m may carry kPlanSlabs (a plan of its own in the cache)
-int plan_get(spconv_kmap* km, SideMap& side, int n_split, int tile_m, hipStream_t st, IgemmPlan** out);
+// flags: kPlanSlabs, kPlanOwnOrder (each combination is a plan of its own in the cache)
+int plan_get(spconv_kmap* km, SideMap& side, int n_split, int flags, hipStream_t st, IgemmPlan** out);
 int plan_mac_units(spconv_kmap* km, SideMap& side, IgemmPlan* plan, int group_rows, hipStream_t st,
                    int64_t* executed);
 int wplan_get(spconv_kmap* km, int64_t target_pairs, hipStream_t st, WgradPlan** out);
+
+// ---- order.hip: fills perm, maps and tilemask of a one-part plan in the library's own order
+int order_rows(const SideMap& side, int V, IgemmPlan& p, hipStream_t st);
 
 // ---- igemm.hip
 struct IgemmArgs {
@@ -235,8 +252,11 @@ struct IgemmArgs {
   spconv_dtype dtype;
   int tile_n;           // 0 = auto
 };
-int igemm_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan, const IgemmArgs& a,
+int igemm_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan, const IgemmArgs& a, int tile_m,
               hipStream_t st);
+// ---- igemm_ring.hip
+int igemm_ring_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan, const IgemmArgs& a, const RingShape& s,
+                   hipStream_t st);
 // ---- igemm_wave.hip (weights resident in LDS; plan tile_m must be 16)
 int igemm_wave_pick_bn(int V, int n_split, int c_red, int c_out, int tile_n, int* waves_out);
 int igemm_wave_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan, const IgemmArgs& a,

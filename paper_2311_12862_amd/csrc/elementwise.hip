@@ -2,7 +2,8 @@
 // their gradients).  Not part of the paper's method; they exist so that a whole network can
 // run on the library's own kernels.  All are bandwidth-bound streaming kernels over
 // [rows][channels] tensors: a lane moves 16 bytes at a time (one element at a time they were bound by the
-// number of memory instructions: 400k x 32 f16, gradient through a ReLU, 20.0 -> 14.5 us).
+// number of memory instructions: gradient through a ReLU at the large levels of a 400k-voxel network 14.6 -> 9.3 us a
+// call, concatenating copies 14.9 -> 7.8 us).
 #include "common.h"
 
 #include <algorithm>

@@ -34,7 +34,8 @@ struct IgemmParams {
   float* partial;
   const int* map[kMaxSplit];
   const int* perm[kMaxSplit];
-  const unsigned* tilemask[kMaxSplit];
+  const unsigned* blkmask[kMaxSplit];  // sorted plans: masks of 16-row blocks
+  const unsigned* rowmask;             // unsorted plans: masks of rows
   int lo[kMaxSplit], width[kMaxSplit];
   long long rows;
   int parts, V;
@@ -46,7 +47,7 @@ struct IgemmParams {
   // sizes of the tables that a tile index reaches (read through range-checked buffer descriptors:
   // beyond the end zeros, no access): each part's map, the permutation (rows_pad entries), the tile masks
   unsigned map_part_bytes[kMaxSplit];
-  unsigned rows_pad_bytes, tiles_bytes;
+  unsigned rows_pad_bytes, blocks_bytes;
 };
 
 template <typename T> struct Mfma;
@@ -74,6 +75,23 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, un
 __device__ __forceinline__ uint4 buf_load16(__amdgpu_buffer_rsrc_t r, unsigned byte_off) {
   const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 0);
   return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// Offsets that some row of the tile [row0, row0 + BM) has: the OR of its 16-row blocks' masks or of its rows'.
+template <int BM>
+__device__ __forceinline__ unsigned tile_mask(const IgemmParams& p, int part, long long row0, int lane) {
+  unsigned m = 0;
+  if (p.rowmask) {
+    const __amdgpu_buffer_rsrc_t r = make_rsrc(p.rowmask, p.rows_pad_bytes);
+#pragma unroll
+    for (int i = 0; i < (BM + 63) / 64; ++i)
+      m |= (unsigned)__builtin_amdgcn_raw_buffer_load_b32(r, (unsigned)(row0 + i * 64 + lane) * 4u, 0, 0);
+  } else if (lane < BM / 16) {
+    m = (unsigned)__builtin_amdgcn_raw_buffer_load_b32(make_rsrc(p.blkmask[part], p.blocks_bytes),
+                                                       (unsigned)(row0 / 16 + lane) * 4u, 0, 0);
+  }
+  for (int o = 1; o < 64; o <<= 1) m |= __shfl_xor(m, o);
+  return (unsigned)__builtin_amdgcn_readfirstlane(m);
 }
 
 // LDS plan of the tiled kernel.  One stage of operands (the next stage waits in registers):
@@ -131,8 +149,7 @@ __global__ void __launch_bounds__(NW * 64) k_igemm(const IgemmParams p) {
   const int n0 = blockIdx.y * BN;
   const int width = p.width[part], lo = p.lo[part];
   const long long row0 = tile * BM;
-  const unsigned tmask = (unsigned)__builtin_amdgcn_raw_buffer_load_b32(make_rsrc(p.tilemask[part], p.tiles_bytes),
-                                                                       (unsigned)tile * 4u, 0, 0);
+  const unsigned tmask = tile_mask<BM>(p, part, row0, lane);
   const int c_red = p.c_red;
   const __amdgpu_buffer_rsrc_t x_rsrc = make_rsrc(p.feats, p.feats_bytes);
   const __amdgpu_buffer_rsrc_t w_rsrc = make_rsrc(p.weights, (unsigned)((size_t)p.V * p.C_in * p.C_out * 2));
@@ -399,8 +416,7 @@ __global__ void __launch_bounds__(256) k_igemm_f32(const IgemmParams p) {
   const int n0 = blockIdx.y * F32_BN;
   const int width = p.width[part], lo = p.lo[part];
   const long long row0 = tile * F32_BM;
-  const unsigned tmask = (unsigned)__builtin_amdgcn_raw_buffer_load_b32(make_rsrc(p.tilemask[part], p.tiles_bytes),
-                                                                       (unsigned)tile * 4u, 0, 0);
+  const unsigned tmask = tile_mask<F32_BM>(p, part, row0, tid & 63);
   const float* feats = reinterpret_cast<const float*>(p.feats);
   const float* wts = reinterpret_cast<const float*>(p.weights);
   const int c_red = p.c_red;
@@ -630,7 +646,7 @@ int igemm_tile_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
   return SPCONV_OK;
 }
 
-int igemm_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan, const IgemmArgs& a,
+int igemm_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan, const IgemmArgs& a, int tile_m,
               hipStream_t st) {
   if (plan.rows == 0) return SPCONV_OK;
   IgemmParams p{};
@@ -649,15 +665,15 @@ int igemm_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan,
   p.c_out = a.dgrad ? a.C_in : a.C_out;
   const int64_t rows_src = (&side == &km->out_side) ? km->n_in : km->n_out;
   TileShape sh;
-  SPC_TRY(igemm_tile_shape(km->V, plan.n_split, plan.rows, rows_src, p.c_red, p.c_out, plan.tile_m, a.tile_n,
+  SPC_TRY(igemm_tile_shape(km->V, plan.n_split, plan.rows, rows_src, p.c_red, p.c_out, tile_m, a.tile_n,
                            a.dtype == SPCONV_F32, a.dgrad != 0, &sh));
-  if (sh.bm != plan.tile_m || sh.grid[0] != (unsigned)plan.n_tiles) return SPCONV_EINVAL;  // (the plan was cut for another tile height)
   const int64_t tiles_alloc = plan.n_tiles > 0 ? plan.n_tiles : 1;
   for (int i = 0; i < plan.parts; ++i) {
     p.lo[i] = plan.lo[i];
     p.width[i] = plan.width[i];
-    p.tilemask[i] = plan.tilemask.as<unsigned>() + (size_t)i * tiles_alloc;
+    p.blkmask[i] = plan.tilemask.as<unsigned>() + (size_t)i * tiles_alloc;
     if (plan.n_split == 0) {
+      p.rowmask = side.mask.as<unsigned>();
       p.map[i] = side.map.as<int>();
       p.perm[i] = nullptr;
     } else {
@@ -667,7 +683,7 @@ int igemm_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan,
     p.map_part_bytes[i] = (unsigned)((uint64_t)plan.rows_pad * plan.width[i] * 4);
   }
   p.rows_pad_bytes = (unsigned)((uint64_t)plan.rows_pad * 4);
-  p.tiles_bytes = (unsigned)((uint64_t)plan.n_tiles * 4);
+  p.blocks_bytes = (unsigned)((uint64_t)plan.n_tiles * 4);
   p.feats_bytes = sh.feats_bytes;
   dim3 grid(sh.grid[0], sh.grid[1], sh.grid[2]);
   if (a.dtype == SPCONV_F32) {
@@ -678,8 +694,8 @@ int igemm_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan,
   // tiles late in a bitmask-sorted order hold the most offsets: they start first, so that the
   // grid does not end on its longest workgroups
   p.heavy_first = plan.n_split > 0 ? 1 : 0;
-  if (a.dtype == SPCONV_F16) return launch_bm<_Float16>(p, plan.tile_m, sh.bn, sh.kc, sh.nw, grid, st);
-  return launch_bm<__bf16>(p, plan.tile_m, sh.bn, sh.kc, sh.nw, grid, st);
+  if (a.dtype == SPCONV_F16) return launch_bm<_Float16>(p, sh.bm, sh.bn, sh.kc, sh.nw, grid, st);
+  return launch_bm<__bf16>(p, sh.bm, sh.bn, sh.kc, sh.nw, grid, st);
 }
 
 int split_reduce(const float* partial, int parts, int64_t rows, int c, spconv_dtype dtype, void* out,

@@ -1,0 +1,537 @@
+// Implicit-GEMM forward / input-gradient with workgroup tiles (Sections 2.2.3, 3.1, 3.2, 4.1), operands
+// loaded straight into LDS: wide layers, and every fp32 layer.
+//
+// A workgroup owns BM consecutive rows of the (usually mask-sorted) map and BN output channels and walks the
+// units (offset, piece of the reduction) that some row of the tile has.  A unit's operands - one 64- or
+// 128-byte piece of each of the BM gathered rows, and the matching piece of the weight slice - are fetched
+// by buffer loads that write LDS (lane l to base + 16 l; an absent neighbour is an out-of-range offset
+// and fills zeros), so a unit in flight costs no registers; two stages alternate, the next one fills while the
+// matrix cores work on this one.  What was measured on the way (256 CUs): such loads deliver 88 B/ns per
+// CU from L2 whether one or four are in flight per wave, 40 from the last-level cache, and pieces of 64
+// bytes half of that beyond L2; three or four stages gain nothing over two, because the workgroups that
+// their LDS displaces hide more latency than they do (100k rows 64 -> 64: 20.9 / 25.6 / 26.2 us with 2 / 3 / 4).
+// What does bound small maps is the longest tile, one step after another: NWK groups of waves (two) therefore
+// take every other unit of the same tile and add their sums at the end through LDS (9k rows, 256 -> 256: 58
+// -> 41 us with two groups, 37 us with 32-row tiles; 94 us for the register-staged kernel on the unsorted map).
+// Column tiles are dealt to the XCDs, so that each L2 holds one column tile of the weights (the same
+// layer: 46 -> 37 us).
+//
+// LDS holds the pieces unpadded, as the loads write them; bank conflicts are avoided by the choice of which
+// 16-byte chunk a lane fetches (XOR with the row, undone by the fragment reads).  The weights are the first operand
+// of the matrix instructions: a lane then ends up with four consecutive output channels of one row,
+// which it stores at once.
+#include "common.h"
+
+#include <algorithm>
+#include <atomic>
+
+namespace spc {
+namespace {
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+
+// c += a . b over the 64 bytes (4 x 16 per row or column) that the four lane groups hold
+template <typename T> __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 c);
+template <> __device__ __forceinline__ f32x4 mma<_Float16>(u32x4 a, u32x4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
+template <> __device__ __forceinline__ f32x4 mma<__bf16>(u32x4 a, u32x4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+template <> __device__ __forceinline__ f32x4 mma<float>(u32x4 a, u32x4 b, f32x4 c) {
+  // 16x16x4: lane group g multiplies its i-th element, reduction channel 4 g + i of the 16
+  const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], y[i], c, 0, 0, 0);
+  return c;
+}
+
+struct RingParams {
+  const void* feats;
+  const void* weights;
+  void* out;
+  float* partial;
+  const int* map[kMaxSplit];
+  const int* perm[kMaxSplit];
+  const unsigned* blkmask[kMaxSplit];  // sorted plans: masks of 16-row blocks
+  const unsigned* rowmask;             // unsorted plans: masks of rows
+  int lo[kMaxSplit], width[kMaxSplit];
+  long long rows;
+  int V, c_red, c_out, C_in, C_out, mirror;
+  int heavy_first;  // sorted maps: tiles late in the order hold the most offsets; they start first
+  int n_tiles;
+  int n_cols;       // column tiles dealt to the XCDs (2, 4 or 8), or 1: grid y is the column tile
+  unsigned feats_bytes, rows_pad;
+};
+
+__device__ __forceinline__ u32x4 rsrc_of(const void* base, unsigned bytes) {
+  const unsigned long long a = (unsigned long long)base;
+  return u32x4{(unsigned)a, (unsigned)(a >> 32), bytes, 0x00020000u};
+}
+// 64 lanes x 16 bytes from a buffer into LDS: lane l fills lds + 16 l, zeros where its offset is out of range.
+// (The five wait states that a vector-memory instruction needs behind a vector instruction that writes one of
+// its scalar registers are part of it.)
+__device__ __forceinline__ void load_to_lds(u32x4 rsrc, unsigned voff, unsigned soff, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc),
+               "s"(soff));
+}
+// Own loads have landed and own LDS reads are done; after the barrier everyone's.
+__device__ __forceinline__ void wait_loads_and_sync() {
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+constexpr unsigned kNoRow = 0xFFFF0000u, kNoWeight = 0x80000000u;  // out of range, also with a scalar offset added
+
+// BM x BN outputs; PB bytes of a row per unit (64 or 128), E bytes per element, NW waves in all, NWK K groups
+template <int BM, int BN, int PB, int E, int NW, int NWK> struct RingSmem {
+  static constexpr int a_bytes = BM * PB, b_bytes = PB / E * BN * E, unit = a_bytes + b_bytes, stage = NWK * unit;
+  static constexpr int slab = (BM * 27 * 4 + NW * 1024 - 1) / (NW * 1024) * (NW * 1024);  // whole loads of every wave
+  static constexpr int total = 2 * stage + slab;
+};
+
+template <typename T, int BM, int BN, int PB, int NWM, int NWN, int NWK, bool DGRAD>
+__global__ void __launch_bounds__(NWM* NWN* NWK * 64) k_ring(const RingParams p) {
+  constexpr int E = (int)sizeof(T), CE = 16 / E, KC = PB / E;  // bytes and chunk length of an element, channels of a unit
+  constexpr int NW = NWM * NWN;                                // waves of a K group
+  typedef RingSmem<BM, BN, PB, E, NW * NWK, NWK> L;
+  constexpr int WM = BM / NWM, WN = BN / NWN, MB = WM / 16, NB = WN / 16;
+  constexpr int CPR = PB / 16;              // chunks of a gathered piece
+  constexpr int RPI = 64 / CPR;             // rows that one load covers
+  constexpr int NA = BM / RPI / NW;         // gather loads per wave and unit
+  constexpr int NBI = L::b_bytes / 1024;    // weight loads per unit
+  constexpr int NBW = (NBI + NW - 1) / NW;  // per wave (with fewer than NW, some waves load the same piece)
+  constexpr int LPR = DGRAD ? CPR : BN / CE;  // chunks of a row of the weight tile
+  constexpr int RPB = 64 / LPR;               // rows of it per load
+  static_assert(NWK == 1 || NWK == 2, "first_piece");
+  static_assert(NA >= 1 && BM % (RPI * NW) == 0 && NBI >= 1 && (NBI % NW == 0 || NW % NBI == 0), "whole loads per wave");
+  extern __shared__ __align__(16) unsigned char smem[];
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
+  const int* mapS = reinterpret_cast<const int*>(smem + 2 * L::stage);
+
+  const int lane = threadIdx.x & 63;
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = NWK > 1 ? wave_all / NW : 0, wave = NWK > 1 ? wave_all % NW : wave_all;
+  const int wm = wave / NWN, wn = wave % NWN;
+  const int fa = lane & 15, fg = lane >> 4;  // fragment row / column, and chunk of a sub-step
+  const int part = blockIdx.z;
+  int t_idx = blockIdx.x, c_idx = blockIdx.y;
+  if (p.n_cols > 1) {  // (workgroups go to the XCDs round-robin)
+    const int e = blockIdx.x & 7;
+    c_idx = e % p.n_cols;
+    t_idx = (int)(blockIdx.x >> 3) * (8 / p.n_cols) + e / p.n_cols;
+    if (t_idx >= p.n_tiles) return;
+  }
+  const int tile = p.heavy_first ? p.n_tiles - 1 - t_idx : t_idx;
+  const int n0 = c_idx * BN;
+  const int width = p.width[part], lo = p.lo[part];
+  const long long row0 = (long long)tile * BM;
+
+  {  // map slab of the tile (consecutive ints) -> LDS; past the end of the map: zeros, never used
+    const u32x4 m_rsrc = rsrc_of(p.map[part], (unsigned)((unsigned long long)p.rows_pad * width * 4));
+    const unsigned bytes = (unsigned)(BM * width * 4), begin = (unsigned)(row0 * width) * 4u;
+    for (unsigned o = wave_all * 1024; o < bytes; o += NW * NWK * 1024)
+      load_to_lds(m_rsrc, begin + o + lane * 16, 0, lds0 + 2 * L::stage + o);
+  }
+  unsigned bmask = 0;  // lane b < BM / 16: mask of the tile's 16-row block b
+  if (p.rowmask) {
+    constexpr int MR = (BM + 63) / 64;
+    unsigned m[MR];
+#pragma unroll
+    for (int i = 0; i < MR; ++i) {
+      const long long r = row0 + i * 64 + lane;
+      m[i] = r < p.rows && i * 64 + lane < BM ? p.rowmask[r] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < MR; ++i) {
+      for (int o = 1; o < 16; o <<= 1) m[i] |= __shfl_xor(m[i], o);
+      const unsigned t = __shfl(m[i], (lane & 3) * 16);
+      if ((lane >> 2) == i) bmask = t;
+    }
+  } else if (lane < BM / 16 && row0 + lane * 16 < p.rows) {
+    bmask = p.blkmask[part][row0 / 16 + lane];
+  }
+  unsigned tmask = bmask;
+  for (int o = 1; o < 16; o <<= 1) tmask |= __shfl_xor(tmask, o);
+  tmask = __builtin_amdgcn_readfirstlane(tmask);
+  unsigned blk[MB], wave_mask = 0;
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    blk[mb] = __builtin_amdgcn_readlane(bmask, wm * MB + mb);
+    wave_mask |= blk[mb];
+  }
+  int orow[MB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const long long g = row0 + wm * WM + mb * 16 + fa;
+    orow[mb] = p.perm[part] ? p.perm[part][g] : (g < p.rows ? (int)g : -1);
+  }
+
+  const int c_red = p.c_red;
+  const unsigned row_bytes = (unsigned)c_red * E, slice = (unsigned)(p.C_in * p.C_out) * E;
+  const u32x4 x_rsrc = rsrc_of(p.feats, p.feats_bytes);
+  const u32x4 w_rsrc = rsrc_of(p.weights, (unsigned)p.V * slice);
+  const int n_pieces = (c_red + KC - 1) / KC;
+
+  // Which chunk stands where.  Gathered pieces (and the input gradient's weight rows): 16 lanes read 8 rows x 2
+  // neighbouring chunks per pass.  Forward weight rows: 16-bit types, the transposing read's passes touch rows r..r+3
+  // and r+8..r+11 at one pair of chunks; fp32, four rows 4 apart at 64 bytes each.
+  auto swz_a = [](int row) { return PB == 128 ? (row & 7) : ((row >> 2) & 1) * 2; };
+  auto swz_b = [](int row) {
+    if (E == 4) return LPR > 4 ? (((row >> 2) & 3) << 2) & (LPR - 1) : 0;
+    return BN == 32 ? ((row >> 3) & 1) << 1
+           : BN == 64 ? (((row >> 1) & 1) << 1) | (((row >> 3) & 1) << 2) : ((row & 3) << 1) | (((row >> 3) & 1) << 3);
+  };
+  const int g_row = lane / CPR, g_chunk = (lane % CPR) ^ swz_a(g_row);  // (RPI is a multiple of 8)
+  const int* g_map = mapS + (wave * NA * RPI + g_row) * width;
+  unsigned w_off[NBW];  // this lane's chunk of the weight tile: offset within a slice, and
+  int w_red[NBW];       // its reduction channel within a piece (far beyond any where there is no such column)
+#pragma unroll
+  for (int i = 0; i < NBW; ++i) {
+    const int j = NBI >= NW ? wave * NBW + i : wave % NBI;
+    const int r = j * RPB + lane / LPR;
+    if constexpr (DGRAD) {  // rows: produced channel ci, chunks along co
+      const int ch = (lane % LPR) ^ swz_a(r), ci = n0 + r;
+      w_red[i] = ci < p.C_in ? ch * CE : 0x40000000;
+      w_off[i] = (unsigned)(ci * p.C_out + ch * CE) * E;
+    } else {  // rows: reduction channel ci, chunks along the produced channel co
+      const int ch = (lane % LPR) ^ swz_b(r), co = n0 + ch * CE;
+      w_red[i] = co < p.C_out ? r : 0x40000000;
+      w_off[i] = (unsigned)(r * p.C_out + co) * E;
+    }
+  }
+
+  // The units of this K group: set bits c of the tile mask, each with its pieces; with two groups every other piece,
+  // or, where their number is odd, starting with the second one for every other offset.  Which group takes a
+  // unit depends on the unit alone, not on the tile: a row's sums do not depend on the rows beside it.
+  const unsigned odd_start = NWK > 1 && (n_pieces & 1) ? 1u : 0u;
+  auto first_piece = [&](int c) { return NWK > 1 ? grp ^ (int)(c & odd_start) : 0; };
+  struct Cursor {
+    unsigned rem;
+    int c, piece;
+  };
+  auto cursor_settle = [&](Cursor& q) {
+    while (q.piece >= n_pieces && q.rem) {
+      q.c = __ffs((int)q.rem) - 1;
+      q.rem &= q.rem - 1;
+      q.piece = first_piece(q.c);
+    }
+  };
+  auto cursor_step = [&](Cursor& q) {
+    q.piece += NWK;
+    cursor_settle(q);
+  };
+  Cursor qi{tmask, 0, n_pieces};  // the unit that is loaded next
+  cursor_settle(qi);
+  Cursor qc = qi;  // the unit that is multiplied next
+  auto units_of = [&](int g) {  // units of K group g
+    if (NWK == 1) return __popc(tmask) * n_pieces;
+    if (!odd_start) return __popc(tmask) * (n_pieces / 2);
+    return __popc(tmask & 0x55555555u) * ((n_pieces + 1 - g) / 2) + __popc(tmask & 0xAAAAAAAAu) * ((n_pieces + g) / 2);
+  };
+  int idx[NA];     // map entries of the unit that is loaded next
+  auto fetch_idx = [&]() {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) idx[i] = g_map[i * RPI * width + qi.c];
+  };
+  auto load_unit = [&](int slot) {
+    const int k = lo + qi.c, r0 = qi.piece * KC;
+    const unsigned a_lds = lds0 + slot * L::stage + grp * L::unit, b_lds = a_lds + L::a_bytes;
+    const unsigned w_soff = (unsigned)(p.mirror ? p.V - 1 - k : k) * slice + (unsigned)(DGRAD ? r0 : r0 * p.C_out) * E;
+    const bool ok = r0 + g_chunk * CE < c_red;
+#pragma unroll
+    for (int i = 0; i < NA; ++i)  // (an absent neighbour, -1, wraps to just below 2^32)
+      load_to_lds(x_rsrc, ok ? (unsigned)idx[i] * row_bytes + (unsigned)g_chunk * 16u : kNoRow, (unsigned)r0 * E,
+                  a_lds + (wave * NA + i) * 1024);
+#pragma unroll
+    for (int i = 0; i < NBW; ++i) {
+      const int j = NBI >= NW ? wave * NBW + i : wave % NBI;
+      load_to_lds(w_rsrc, w_red[i] + r0 < c_red ? w_off[i] : kNoWeight, w_soff, b_lds + j * 1024);
+    }
+    cursor_step(qi);
+    fetch_idx();
+  };
+
+  f32x4 acc[MB][NB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // fragment addresses within a unit
+  constexpr int KS = PB / 64;  // sub-steps
+  unsigned xf[KS], wf[DGRAD ? KS : NB];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    const unsigned ch = (unsigned)((ks * 4 + fg) ^ swz_a(fa)) * 16u;
+    xf[ks] = (unsigned)((wm * WM + fa) * PB) + ch;
+    if constexpr (DGRAD) wf[ks] = (unsigned)(L::a_bytes + (wn * WN + fa) * PB) + ch;
+  }
+  if constexpr (!DGRAD) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      if constexpr (E == 2) {
+        const int r = 8 * fg + (fa >> 2), ch = (wn * WN + nb * 16 + 4 * (fa & 3)) >> 3;
+        wf[nb] = (unsigned)(L::a_bytes + r * BN * E + ((ch ^ swz_b(r)) * 16) + (fa & 1) * 8);
+      } else {
+        const int r = 4 * fg, ch = (wn * WN + nb * 16 + fa) >> 2;
+        wf[nb] = (unsigned)(L::a_bytes + r * BN * E + ((ch ^ swz_b(r)) * 16) + (fa & 3) * 4);
+      }
+    }
+  }
+  auto multiply = [&](int slot, int c) {
+    const unsigned char* st = smem + slot * L::stage + grp * L::unit;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      u32x4 w[NB], x[MB];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        if constexpr (DGRAD) {
+          w[nb] = *reinterpret_cast<const u32x4*>(st + wf[ks] + nb * 16 * PB);
+        } else if constexpr (E == 2) {
+          // 16 lanes fetch a 4 x 16 block of [ci][co] and each receives one column: 4 reduction channels of
+          // its output channel; two reads give the lane's 8 (ci = 8 fg .. 8 fg + 7)
+          const unsigned char* b = st + wf[nb] + ks * 32 * BN * E;
+          const s16x4 l4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(b));
+          const s16x4 h4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(b + 4 * BN * E));
+          w[nb] = __builtin_bit_cast(u32x4, s16x8{l4[0], l4[1], l4[2], l4[3], h4[0], h4[1], h4[2], h4[3]});
+        } else {
+          const unsigned char* b = st + wf[nb] + ks * 16 * BN * E;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) w[nb][i] = *reinterpret_cast<const unsigned*>(b + i * BN * E);
+        }
+      }
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) x[mb] = *reinterpret_cast<const u32x4*>(st + xf[ks] + mb * 16 * PB);
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+        if ((blk[mb] >> c) & 1u) {  // (the lock-step unit: a 16-row block without this offset is skipped)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mma<T>(w[nb], x[mb], acc[mb][nb]);
+        }
+    }
+  };
+
+  wait_loads_and_sync();  // the slab is there
+  fetch_idx();
+  const int mine = units_of(grp), steps = NWK > 1 ? max(mine, units_of(grp ^ 1)) : mine;
+  if (mine > 0) load_unit(0);
+  for (int it = 0; it < steps; ++it) {
+    wait_loads_and_sync();  // this step's unit has landed, and everyone is done with the stage that is filled next
+    if (it + 1 < mine) load_unit((it + 1) & 1);
+    if (it < mine && ((wave_mask >> qc.c) & 1u)) multiply(it & 1, qc.c);
+    cursor_step(qc);
+  }
+  if constexpr (NWK > 1) {  // the K groups' sums meet in LDS; group 0 adds them up in order and stores
+    static_assert((NWK - 1) * BM * BN * 4 <= 2 * L::stage, "the sums fit the stages");
+    wait_loads_and_sync();
+    f32x4* sums = reinterpret_cast<f32x4*>(smem);
+    if (grp > 0) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) sums[(((grp - 1) * NW + wave) * MB * NB + mb * NB + nb) * 64 + lane] = acc[mb][nb];
+    }
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int g = 0; g < NWK - 1; ++g)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] += sums[((g * NW + wave) * MB * NB + mb * NB + nb) * 64 + lane];
+  }
+
+  // a lane holds channels 4 fg + r of row fa of each block
+  const int c_out = p.c_out;
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    if (orow[mb] < 0) continue;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const int col = n0 + wn * WN + nb * 16 + fg * 4;
+      if (col >= c_out) continue;
+      if (p.partial) {
+        *reinterpret_cast<f32x4*>(p.partial + ((long long)part * p.rows + orow[mb]) * c_out + col) = acc[mb][nb];
+      } else {
+        typedef T out4 __attribute__((ext_vector_type(4)));
+        out4 v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = (T)acc[mb][nb][r];
+        *reinterpret_cast<out4*>(reinterpret_cast<T*>(p.out) + (long long)orow[mb] * c_out + col) = v;
+      }
+    }
+  }
+}
+
+template <typename T, int BM, int BN, int PB, int NWM, int NWN, int NWK>
+int launch_ring(const RingParams& p, bool dgrad, dim3 grid, hipStream_t st) {
+  constexpr int NW = NWM * NWN * NWK;
+  typedef RingSmem<BM, BN, PB, (int)sizeof(T), NW, NWK> L;
+  static_assert(L::total <= 160 * 1024, "LDS of a CU");
+  static std::atomic<bool> attr_set{false};  // (set twice by racing threads at worst: the calls are idempotent)
+  auto fwd = k_ring<T, BM, BN, PB, NWM, NWN, NWK, false>;
+  auto dgr = k_ring<T, BM, BN, PB, NWM, NWN, NWK, true>;
+  if (!attr_set.load(std::memory_order_acquire)) {
+    SPC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(fwd), hipFuncAttributeMaxDynamicSharedMemorySize, L::total));
+    SPC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(dgr), hipFuncAttributeMaxDynamicSharedMemorySize, L::total));
+    attr_set.store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL(dgrad ? dgr : fwd, grid, dim3(NW * 64), L::total, st, p);
+  SPC_LAUNCH_CHECK();
+  return SPCONV_OK;
+}
+
+// the tile shapes that are built: BM, BN, waves along the rows, along the columns, K groups
+#define SPC_RING_SHAPES_16(X) \
+  X(32, 64, 1, 2, 2) X(64, 32, 4, 1, 1) X(64, 64, 2, 2, 1) X(64, 64, 2, 2, 2) X(64, 128, 2, 2, 1) X(128, 128, 2, 2, 1) X(256, 256, 2, 4, 1)
+#define SPC_RING_SHAPES_32(X) X(64, 16, 4, 1, 1) X(64, 32, 4, 1, 1) X(64, 64, 2, 2, 1) X(64, 64, 2, 2, 2)
+
+template <typename T, int PB> int launch_shape(const RingParams& p, bool dgrad, const RingShape& s, dim3 grid, hipStream_t st) {
+#define SPC_RING_CASE(BM, BN, NWM, NWN, NWK) \
+  if (s.bm == BM && s.bn == BN && s.nwk == NWK) return launch_ring<T, BM, BN, PB, NWM, NWN, NWK>(p, dgrad, grid, st);
+  if constexpr (sizeof(T) == 4) {
+    SPC_RING_SHAPES_32(SPC_RING_CASE)
+  } else {
+    SPC_RING_SHAPES_16(SPC_RING_CASE)
+  }
+  return SPCONV_EINVAL;
+}
+
+size_t ring_lds_bytes(const RingShape& s, bool f32) {
+#define SPC_RING_LDS(BM, BN, NWM, NWN, NWK)                                                                     \
+  if (s.bm == BM && s.bn == BN && s.nwk == NWK)                                                                 \
+    return s.piece == 128 ? (size_t)RingSmem<BM, BN, 128, E, NWM * NWN * NWK, NWK>::total                       \
+                          : (size_t)RingSmem<BM, BN, 64, E, NWM * NWN * NWK, NWK>::total;
+  if (f32) {
+    constexpr int E = 4;
+    SPC_RING_SHAPES_32(SPC_RING_LDS)
+  } else {
+    constexpr int E = 2;
+    SPC_RING_SHAPES_16(SPC_RING_LDS)
+  }
+  return 0;
+}
+
+int ring_waves(const RingShape& s, bool f32) {
+#define SPC_RING_WAVES(BM, BN, NWM, NWN, NWK) \
+  if (s.bm == BM && s.bn == BN && s.nwk == NWK) return NWM * NWN * NWK;
+  if (f32) {
+    SPC_RING_SHAPES_32(SPC_RING_WAVES)
+  } else {
+    SPC_RING_SHAPES_16(SPC_RING_WAVES)
+  }
+  return 0;
+}
+
+}  // namespace
+
+// Tile shape from the row count and the produced channels.  The largest tile that still gives a few workgroups per
+// CU: a larger one gathers each row and loads each weight slice fewer times, but small maps are bound by the
+// longest tile.  Measured on sorted maps (us): 300k rows 256 -> 256, (256, 256) 435, (128, 128) 480; 96 -> 96, (128, 128)
+// 125, (64, 128) 134; 100k rows 64 -> 128, (64, 128) 30.3, (128, 128) 31.4; 128 -> 64, two K groups (64, 64) 30.2, one
+// 35.2; 30k rows 128 -> 128, (64, 64) with two K groups 24.9, (64, 128) 37.9, (128, 128) 47; 9k rows 256 -> 256, (32,
+// 64) with two K groups 36.9, (64, 64) 41.2, (64, 128) 67.
+int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_red, int c_out, bool f32, bool small_tiles,
+                     RingShape* s) {
+  *s = RingShape{};
+  const int q = f32 ? 4 : 8, e = f32 ? 4 : 2;
+  if (rows < 1 || rows_src < 0 || c_red < q || c_out < q || c_red % q || c_out % q) return SPCONV_EINVAL;
+  PlanShape ps;
+  SPC_TRY(plan_shape(V, rows, n_split, 16, &ps));
+  const uint64_t bytes = (uint64_t)rows_src * c_red * e;
+  // 32-bit buffer offsets; "no row" and "no weight" stay out of range with a scalar offset of one row added
+  if (bytes >= (uint64_t)kNoRow - 0x8000u || (uint64_t)ps.rows_pad * 27 * 4 >= 0xFFFF0000ull ||
+      (uint64_t)V * c_red * c_out * e >= kNoWeight)
+    return SPCONV_EINVAL;
+  s->feats_bytes = (unsigned)bytes;
+  auto wgs = [&](int bm, int bn) { return ceil_div(rows, bm) * ceil_div(c_out, bn) * ps.parts; };
+  s->nwk = 1;
+  if (f32) {
+    s->bm = 64;
+    s->bn = c_out <= 16 ? 16 : c_out <= 32 ? 32 : 64;
+    if (s->bn == 64 && wgs(64, 64) < 1024 && small_tiles) s->nwk = 2;
+    s->piece = c_red <= 16 ? 64 : 128;
+  } else {
+    s->piece = (c_red % 64 == 0) ? 128 : 64;
+    if (c_out <= 32) {
+      s->bm = 64, s->bn = 32;
+    } else if (c_out > 128 && wgs(256, 256) >= 768) {
+      s->bm = 256, s->bn = 256;
+    } else if (c_out > 64 && wgs(128, 128) >= 1024) {
+      s->bm = 128, s->bn = 128;
+    } else if (c_out > 64 && wgs(64, 128) >= 1024) {
+      s->bm = 64, s->bn = 128;
+    } else {
+      // two K groups where the units of a tile are many (long reductions), one where they are few
+      s->bm = 64, s->bn = 64;
+      s->nwk = c_red > 64 ? 2 : 1;
+      if (s->nwk == 2 && wgs(64, 64) < 768 && small_tiles) s->bm = 32;
+    }
+  }
+  s->threads = 64 * ring_waves(*s, f32);
+  s->lds_bytes = ring_lds_bytes(*s, f32);
+  s->n_tiles = ceil_div(rows, s->bm);
+  const int64_t cols = ceil_div(c_out, s->bn);
+  s->n_cols = cols == 2 || cols == 4 || cols == 8 ? (int)cols : 1;
+  s->cols = (int)cols;
+  s->parts = ps.parts;
+  if (s->n_cols > 1) {
+    s->grid[0] = (unsigned)(8 * ceil_div(s->n_tiles, 8 / s->n_cols));
+    s->grid[1] = 1;
+  } else {
+    s->grid[0] = (unsigned)s->n_tiles;
+    s->grid[1] = (unsigned)cols;
+  }
+  s->grid[2] = (unsigned)ps.parts;
+  return SPCONV_OK;
+}
+
+int igemm_ring_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan, const IgemmArgs& a, const RingShape& s,
+                   hipStream_t st) {
+  if (plan.rows == 0) return SPCONV_OK;
+  RingParams p{};
+  p.feats = a.feats;
+  p.weights = a.weights;
+  p.out = a.out;
+  p.partial = a.partial;
+  p.rows = plan.rows;
+  p.V = km->V;
+  p.C_in = a.C_in;
+  p.C_out = a.C_out;
+  p.mirror = a.mirror;
+  p.c_red = a.dgrad ? a.C_out : a.C_in;
+  p.c_out = a.dgrad ? a.C_in : a.C_out;
+  p.feats_bytes = s.feats_bytes;
+  p.rows_pad = (unsigned)plan.rows_pad;
+  const int64_t tiles_alloc = std::max<int64_t>(plan.n_tiles, 1);
+  for (int i = 0; i < plan.parts; ++i) {
+    p.lo[i] = plan.lo[i];
+    p.width[i] = plan.width[i];
+    if (plan.n_split == 0) {
+      p.map[i] = side.map.as<int>();
+      p.rowmask = side.mask.as<unsigned>();
+    } else {
+      p.blkmask[i] = plan.tilemask.as<unsigned>() + (size_t)i * tiles_alloc;
+      p.map[i] = plan.maps.as<int>() + plan.map_off[i];
+      p.perm[i] = plan.perm.as<int>() + (size_t)i * plan.rows_pad;
+    }
+  }
+  p.heavy_first = plan.n_split > 0;
+  p.n_tiles = (int)s.n_tiles;
+  p.n_cols = s.n_cols;
+  const dim3 grid(s.grid[0], s.grid[1], s.grid[2]);
+  const bool dgrad = a.dgrad != 0, wide = s.piece == 128;
+  switch (a.dtype) {
+    case SPCONV_F16: return wide ? launch_shape<_Float16, 128>(p, dgrad, s, grid, st) : launch_shape<_Float16, 64>(p, dgrad, s, grid, st);
+    case SPCONV_BF16: return wide ? launch_shape<__bf16, 128>(p, dgrad, s, grid, st) : launch_shape<__bf16, 64>(p, dgrad, s, grid, st);
+    case SPCONV_F32: return wide ? launch_shape<float, 128>(p, dgrad, s, grid, st) : launch_shape<float, 64>(p, dgrad, s, grid, st);
+  }
+  return SPCONV_EINVAL;
+}
+
+}  // namespace spc

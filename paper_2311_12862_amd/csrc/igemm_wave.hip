@@ -511,7 +511,7 @@ int igemm_wave_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
 int igemm_wave_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan, const IgemmArgs& a,
                    hipStream_t st) {
   if (plan.rows == 0) return SPCONV_OK;
-  if (plan.tile_m != 16 || a.dtype == SPCONV_F32) return SPCONV_EINVAL;
+  if (a.dtype == SPCONV_F32) return SPCONV_EINVAL;
   WaveParams p{};
   p.feats = a.feats;
   p.weights = a.weights;

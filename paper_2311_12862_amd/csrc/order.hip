@@ -1,0 +1,305 @@
+// The library's own row order, for calls that leave the configuration to it: rows with equal or similar
+// neighbour masks next to each other (the bitmask sorting of Section 2.2.3), made in three short launches.
+//
+// A full sort by the 27-bit mask takes three digit passes over all rows (100k rows: 12.6 + 11.8 + 11.0 us and 8.6 us for
+// the reordered map).  What the kernels need is less: blocks of 16 and tiles of 64 to 256 rows whose masks overlap.
+// So the rows go into 128 buckets first (any corner neighbour; the edge neighbours in six pairs), one stable
+// counting pass whose counter matrix is small enough to be summed by every workgroup, and then
+// each stretch of 2048 places is sorted in LDS by 20 bits of the mask.  Which bits matter most: the offsets that few
+// rows have (corners 4 %, edges 20 %, faces 40 % of the rows of a LiDAR-like scan) come first, so that the rows that
+// have one stand together instead of one in every block.  Executed / valid pairs of blocks of 16 rows, tiles of 64,
+// of 128 (100k-voxel scan; 300k-voxel room): this order 1.28, 1.55, 1.71; 1.04, 1.12, 1.21; the full sort by the plain
+// mask 1.22, 1.50, 1.74; 1.02, 1.04, 1.06; map order 4.37, 5.64, 5.85; 2.44, 2.76, 2.78.
+#include "common.h"
+
+#include <algorithm>
+
+namespace spc {
+namespace {
+
+constexpr int kBucketBits = 8, kBuckets = 1 << kBucketBits;
+constexpr int kCountThreads = 256, kCountWaves = 4;
+constexpr int kMaxCountWgs = 256;               // rows of the counter matrix
+constexpr int kChunk = 2048;                    // places that are sorted together in LDS
+constexpr int kPlaceBits = 11;
+constexpr int kLocalThreads = 1024, kLocalWaves = 16, kLocalItems = kChunk / kLocalThreads;
+constexpr int kKeyBits = 20, kDigitBits = 7, kDigits = 1 << kDigitBits;
+static_assert(kChunk == 1 << kPlaceBits && kBuckets == kCountThreads && kLocalItems == 2, "index arithmetic below");
+
+// V = 27: which corner layers dz = -1, +1 have a neighbour (2 bits), 12 edges, 6 faces.  Other maps: the mask itself.
+__device__ __forceinline__ unsigned local_key(unsigned m, int V) {
+  if (V != 27) return m & ((1u << kKeyBits) - 1u);
+  auto b = [&](int from, int to) { return ((m >> from) & 1u) << to; };
+  const unsigned corners = ((m & 0x01040041u) ? 2u : 0u) | ((m & 0x04100104u) ? 1u : 0u);
+  const unsigned edges = b(1, 11) | b(7, 10) | b(19, 9) | b(25, 8) | b(3, 7) | b(5, 6) | b(21, 5) | b(23, 4) | b(9, 3) |
+                         b(11, 2) | b(15, 1) | b(17, 0);
+  const unsigned faces = b(4, 5) | b(10, 4) | b(12, 3) | b(14, 2) | b(16, 1) | b(22, 0);
+  return (corners << 18) | (edges << 6) | faces;
+}
+// V = 27: any corner neighbour, the edge neighbours two by two (two of the four in each coordinate plane: a row of
+// a flat surface has the edges of one plane), the face neighbours along z.
+__device__ __forceinline__ unsigned bucket_bits(unsigned m, int V) {
+  if (V != 27) return V > kBucketBits ? (m >> (V - kBucketBits)) & (kBuckets - 1) : m;
+  auto any = [&](unsigned bits, int to) { return (m & bits ? 1u : 0u) << to; };
+  return any(0x05140145u, 7) | any((1u << 1) | (1u << 7), 6) | any((1u << 19) | (1u << 25), 5) | any((1u << 3) | (1u << 5), 4) |
+         any((1u << 21) | (1u << 23), 3) | any((1u << 9) | (1u << 11), 2) | any((1u << 15) | (1u << 17), 1) |
+         any((1u << 12) | (1u << 14), 0);
+}
+// The buckets in the order of their set bits: rows with many neighbours stand at the end of the order, where the
+// kernels start (the heaviest tiles first).
+struct BucketRanks {
+  unsigned short of[kBuckets];
+};
+constexpr BucketRanks make_bucket_ranks() {
+  BucketRanks r{};
+  int next = 0;
+  for (int bits = 0; bits <= kBucketBits; ++bits)
+    for (int b = 0; b < kBuckets; ++b) {
+      int n = 0;
+      for (int i = 0; i < kBucketBits; ++i) n += (b >> i) & 1;
+      if (n == bits) r.of[b] = (unsigned short)next++;
+    }
+  return r;
+}
+__device__ const BucketRanks d_ranks = make_bucket_ranks();
+
+// counts[workgroup][bucket] of wg_rows consecutive rows each
+__global__ void __launch_bounds__(kCountThreads)
+    k_order_count(const unsigned* __restrict__ mask, int rows, int wg_rows, int V, unsigned* __restrict__ counts) {
+  __shared__ unsigned cnt[kBuckets];
+  for (int d = threadIdx.x; d < kBuckets; d += kCountThreads) cnt[d] = 0;
+  __syncthreads();
+  const int begin = blockIdx.x * wg_rows, end = min(rows, begin + wg_rows);
+  for (int r0 = begin; r0 < end; r0 += 4 * kCountThreads) {
+    unsigned at[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = r0 + i * kCountThreads + threadIdx.x;
+      at[i] = r < end ? d_ranks.of[bucket_bits(mask[r], V)] : kBuckets;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (at[i] < kBuckets) atomicAdd(&cnt[at[i]], 1u);
+  }
+  __syncthreads();
+  for (int d = threadIdx.x; d < kBuckets; d += kCountThreads) counts[blockIdx.x * kBuckets + d] = cnt[d];
+}
+
+// For every lane: how many lower lanes of the wave hold the same digit, and how many lanes do.
+__device__ __forceinline__ void rank_of(unsigned digit, int bits, bool valid, int lane, unsigned* rank, unsigned* peers_out) {
+  unsigned long long peers = __ballot(valid);
+  for (int b = 0; b < bits; ++b) {
+    const bool bit = (digit >> b) & 1u;
+    const unsigned long long bal = __ballot(bit);
+    peers &= bit ? bal : ~bal;
+  }
+  *rank = (unsigned)__popcll(peers & ((1ull << lane) - 1ull));
+  *peers_out = (unsigned)__popcll(peers);
+}
+
+// Rows of one workgroup to their places: bucketed[place] = (local key, row), stable.  The workgroup finds its first
+// places by adding up the counter matrix (at most 256 x 256 counters from L2) instead of waiting for a scan launch.
+__global__ void __launch_bounds__(kCountThreads)
+    k_order_scatter(const unsigned* __restrict__ mask, int rows, int wg_rows, int V, const unsigned* __restrict__ counts,
+                    uint2* __restrict__ bucketed) {
+  __shared__ unsigned off[kCountWaves][kBuckets];  // of a round of 1024 rows: the waves' counts, then first places
+  __shared__ unsigned wave_sum[kCountWaves];
+  const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
+  const int begin = blockIdx.x * wg_rows, end = min(rows, begin + wg_rows);
+  unsigned m[4], bkt[4], rank[4];
+  auto fetch = [&](int r0) {  // a wave takes 256 consecutive rows
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = r0 + wib * 256 + i * 64 + lane;
+      m[i] = r < end ? mask[r] : 0u;
+    }
+  };
+  fetch(begin);
+  unsigned place;  // next place of this thread's bucket
+  {
+    unsigned before = 0, all = 0;
+    const unsigned* col = counts + threadIdx.x;
+    constexpr int R = 32;  // rows in flight: a load that waits for the one before it costs a round trip each
+    for (int w0 = 0; w0 < (int)gridDim.x; w0 += R) {
+      unsigned c[R];
+#pragma unroll
+      for (int i = 0; i < R; ++i) c[i] = w0 + i < (int)gridDim.x ? col[(w0 + i) * kBuckets] : 0u;
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        all += c[i];
+        before += w0 + i < (int)blockIdx.x ? c[i] : 0u;
+      }
+    }
+    unsigned incl = all;
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned up = __shfl_up(incl, o);
+      if (lane >= o) incl += up;
+    }
+    if (lane == 63) wave_sum[wib] = incl;
+    __syncthreads();
+    place = incl - all + before;
+    for (int w = 0; w < wib; ++w) place += wave_sum[w];
+  }
+  for (int r0 = begin; r0 < end; r0 += 1024) {
+    if (r0 > begin) fetch(r0);
+    for (int d = threadIdx.x; d < kCountWaves * kBuckets; d += kCountThreads) (&off[0][0])[d] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {  // rank within the wave's rows; off ends as the wave's counts
+      const bool valid = r0 + wib * 256 + i * 64 + lane < end;
+      bkt[i] = d_ranks.of[bucket_bits(m[i], V)];
+      unsigned peers;
+      rank_of(bkt[i], kBucketBits, valid, lane, &rank[i], &peers);
+      const unsigned have = valid ? off[wib][bkt[i]] : 0u;
+      __builtin_amdgcn_wave_barrier();  // every lane has read the count before a leader advances it
+      if (valid && rank[i] == 0) off[wib][bkt[i]] = have + peers;
+      __builtin_amdgcn_wave_barrier();
+      rank[i] += have;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kCountWaves; ++w) {
+      const unsigned c = off[w][threadIdx.x];
+      off[w][threadIdx.x] = place;
+      place += c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = r0 + wib * 256 + i * 64 + lane;
+      const unsigned at = off[wib][bkt[i]] + rank[i];
+      if (r < end && at < (unsigned)rows) bucketed[at] = make_uint2(local_key(m[i], V), (unsigned)r);
+    }
+    __syncthreads();
+  }
+}
+
+// Sorts a stretch of 2048 places by the local key (stable: three digits in LDS), and writes what a plan consists
+// of: the rows' order, the reordered map and the masks of its 16-row blocks.  Where there are fewer stretches than CUs,
+// gridDim.y workgroups sort the same one and each writes its share (the reordering is most of the work).
+__global__ void __launch_bounds__(kLocalThreads)
+    k_order_local(const uint2* __restrict__ bucketed, const unsigned* __restrict__ mask, const int* __restrict__ map, int V,
+                  int rows, long long rows_pad, long long n_blocks, int* __restrict__ perm, int* __restrict__ reordered,
+                  unsigned* __restrict__ blkmask) {
+  __shared__ int row_of[kChunk];            // by place within the bucket order
+  __shared__ unsigned comp[kChunk];         // key << 11 | place
+  __shared__ unsigned off[kLocalWaves][kDigits];
+  __shared__ int src_of[kChunk];            // rows in the final order
+  const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
+  const long long base = (long long)blockIdx.x * kChunk;
+  unsigned v[kLocalItems];
+#pragma unroll
+  for (int i = 0; i < kLocalItems; ++i) {
+    const int at = wib * (64 * kLocalItems) + i * 64 + lane;
+    const uint2 e = base + at < rows ? bucketed[base + at] : make_uint2((1u << kKeyBits) - 1u, 0xFFFFFFFFu);  // padding last
+    row_of[at] = (int)e.y;
+    v[i] = (e.x << kPlaceBits) | (unsigned)at;
+  }
+  for (int shift = kPlaceBits; shift < kPlaceBits + kKeyBits; shift += kDigitBits) {
+    const int bits = min(kDigitBits, kPlaceBits + kKeyBits - shift);
+    for (int d = threadIdx.x; d < kLocalWaves * kDigits; d += kLocalThreads) (&off[0][0])[d] = 0;
+    __syncthreads();
+    unsigned digit[kLocalItems], rank[kLocalItems];
+#pragma unroll
+    for (int i = 0; i < kLocalItems; ++i) {
+      digit[i] = (v[i] >> shift) & ((1u << bits) - 1u);
+      unsigned peers;
+      rank_of(digit[i], bits, true, lane, &rank[i], &peers);
+      const unsigned have = off[wib][digit[i]];
+      __builtin_amdgcn_wave_barrier();
+      if (rank[i] == 0) off[wib][digit[i]] = have + peers;
+      __builtin_amdgcn_wave_barrier();
+      rank[i] += have;
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {  // first places: digits in order, within a digit the waves in order; two digits per lane
+      unsigned c0 = 0, c1 = 0;
+#pragma unroll
+      for (int w = 0; w < kLocalWaves; ++w) c0 += off[w][2 * lane], c1 += off[w][2 * lane + 1];
+      unsigned incl = c0 + c1;
+      for (int o = 1; o < 64; o <<= 1) {
+        const unsigned up = __shfl_up(incl, o);
+        if (lane >= o) incl += up;
+      }
+      unsigned run = incl - c0 - c1;
+#pragma unroll
+      for (int d = 0; d < 2; ++d)
+#pragma unroll
+        for (int w = 0; w < kLocalWaves; ++w) {
+          const unsigned c = off[w][2 * lane + d];
+          off[w][2 * lane + d] = run;
+          run += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kLocalItems; ++i) comp[off[wib][digit[i]] + rank[i]] = v[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kLocalItems; ++i) v[i] = comp[wib * (64 * kLocalItems) + i * 64 + lane];
+  }
+  const int share = kChunk / gridDim.y, lo = blockIdx.y * share;  // (a power of two, at least 512)
+#pragma unroll
+  for (int i = 0; i < kLocalItems; ++i) {
+    const int at = wib * (64 * kLocalItems) + i * 64 + lane;
+    const long long g = base + at;
+    const int src = row_of[v[i] & (kChunk - 1)];
+    src_of[at] = src;
+    if (at < lo || at >= lo + share) continue;
+    unsigned m = src >= 0 ? mask[src] : 0u;
+    for (int o = 1; o < 16; o <<= 1) m |= __shfl_xor(m, o);
+    if (g < rows_pad) perm[g] = src;
+    if ((lane & 15) == 0 && g / 16 < n_blocks) blkmask[g / 16] = m;
+  }
+  __syncthreads();
+  // e / V by a multiply: (e + 0.5) / V stays 0.5 / 27 away from every integer for e < 55296
+  const long long first = base + lo;
+  if (first >= rows_pad) return;
+  const int n = (int)min((long long)share, rows_pad - first) * V;
+  int* dst = reordered + first * V;
+  const float inv = 1.0f / (float)V;
+  constexpr int U = 14;  // loads in flight per thread
+  for (int e0 = threadIdx.x; e0 < n; e0 += U * kLocalThreads) {
+    int val[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = e0 + u * kLocalThreads;
+      val[u] = -1;
+      if (e < n) {
+        const int rr = (int)(((float)e + 0.5f) * inv), sr = src_of[lo + rr];
+        if (sr >= 0) val[u] = map[(long long)sr * V + (e - rr * V)];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (e0 + u * kLocalThreads < n) dst[e0 + u * kLocalThreads] = val[u];
+  }
+}
+
+}  // namespace
+
+int order_rows(const SideMap& side, int V, IgemmPlan& p, hipStream_t st) {
+  const int rows = (int)p.rows;
+  int wg_rows = 1024;
+  while (ceil_div(rows, wg_rows) > kMaxCountWgs) wg_rows *= 2;
+  const unsigned wgs = (unsigned)ceil_div(rows, wg_rows);
+  DevBuf tmp;  // (returns to the pool while the stream may still use it; later users are ordered behind)
+  const size_t bucketed_bytes = (size_t)rows * sizeof(uint2);
+  SPC_TRY(tmp.alloc(bucketed_bytes + (size_t)wgs * kBuckets * sizeof(unsigned)));
+  uint2* bucketed = tmp.as<uint2>();
+  unsigned* counts = reinterpret_cast<unsigned*>(tmp.as<char>() + bucketed_bytes);
+  const unsigned* mask = side.mask.as<unsigned>();
+  hipLaunchKernelGGL(k_order_count, dim3(wgs), dim3(kCountThreads), 0, st, mask, rows, wg_rows, V, counts);
+  SPC_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_order_scatter, dim3(wgs), dim3(kCountThreads), 0, st, mask, rows, wg_rows, V, counts, bucketed);
+  SPC_LAUNCH_CHECK();
+  const unsigned chunks = (unsigned)ceil_div(p.rows_pad, kChunk);
+  const unsigned shares = chunks * 4 <= 256 ? 4 : chunks * 2 <= 256 ? 2 : 1;
+  hipLaunchKernelGGL(k_order_local, dim3(chunks, shares), dim3(kLocalThreads), 0, st, bucketed, mask,
+                     side.map.as<int>(), V, rows, (long long)p.rows_pad, (long long)p.n_tiles, p.perm.as<int>(), p.maps.as<int>(),
+                     p.tilemask.as<unsigned>());
+  SPC_LAUNCH_CHECK();
+  return SPCONV_OK;
+}
+
+}  // namespace spc

@@ -373,26 +373,6 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// tilemask[t] = OR over the tile's rows of their split keys.  One wave per tile.
-// perm == nullptr: rows in map order.
-__global__ void __launch_bounds__(256)
-    k_tile_mask(const unsigned* __restrict__ mask, const int* __restrict__ perm, long long rows, int tile_m, int lo,
-                int width, long long n_tiles, unsigned* __restrict__ tilemask) {
-  const int lane = threadIdx.x & 63;
-  const long long t = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  if (t >= n_tiles) return;
-  unsigned m = 0;
-  for (int i = lane; i < tile_m; i += 64) {
-    const long long r = t * tile_m + i;
-    if (r < rows) {
-      const int src = perm ? perm[r] : (int)r;
-      if (src >= 0) m |= mask[src];
-    }
-  }
-  for (int o = 32; o > 0; o >>= 1) m |= __shfl_xor(m, o);
-  if (lane == 0) tilemask[t] = (m >> lo) & (width >= 32 ? 0xFFFFFFFFu : ((1u << width) - 1u));
-}
-
 // executed MAC units: for every group of `group` consecutive (sorted) rows,
 // popcount(OR of keys) * real rows in the group
 __global__ void __launch_bounds__(256)
@@ -677,12 +657,14 @@ int plan_shape(int V, int64_t rows, int n_split, int tile_m, PlanShape* s) {
   return SPCONV_OK;
 }
 
-int plan_get(spconv_kmap* km, SideMap& side, int n_split, int tile_m, hipStream_t st, IgemmPlan** out) {
-  const bool force_slabs = (tile_m & kPlanSlabs) != 0 && n_split > 0;
-  auto key = std::make_pair(n_split, n_split > 0 ? tile_m : (tile_m & ~kPlanSlabs));
-  tile_m &= ~kPlanSlabs;
+int plan_get(spconv_kmap* km, SideMap& side, int n_split, int flags, hipStream_t st, IgemmPlan** out) {
+  constexpr int kBlock = 16;  // rows of a mask block
+  if (n_split == 0) flags = 0;
+  if (n_split != 1) flags &= ~kPlanOwnOrder;
+  const bool force_slabs = flags & kPlanSlabs, own_order = flags & kPlanOwnOrder;
+  const auto key = std::make_pair(n_split, flags);
   PlanShape sh;
-  SPC_TRY(plan_shape(km->V, side.rows, n_split, tile_m, &sh));
+  SPC_TRY(plan_shape(km->V, side.rows, n_split, kBlock, &sh));
   if (side.rows > 0 && sh.rows_pad != side.rows_pad) return SPCONV_EINVAL;  // (the map was padded by the same rule)
   auto it = side.plans.find(key);
   if (it != side.plans.end()) {
@@ -693,7 +675,6 @@ int plan_get(spconv_kmap* km, SideMap& side, int n_split, int tile_m, hipStream_
   if (!p) return SPCONV_ENOMEM;
   const int V = km->V;
   p->n_split = n_split;
-  p->tile_m = tile_m;
   p->parts = sh.parts;
   p->rows = side.rows;
   p->rows_pad = sh.rows_pad;
@@ -705,20 +686,13 @@ int plan_get(spconv_kmap* km, SideMap& side, int n_split, int tile_m, hipStream_
   }
   const size_t off = sh.map_elems;
   const int64_t tiles_alloc = std::max<int64_t>(1, p->n_tiles);
-  SPC_TRY(p->tilemask.alloc((size_t)p->parts * tiles_alloc * sizeof(unsigned)));
-  const unsigned tile_blocks = blocks_for(tiles_alloc, 4);
-  if (n_split == 0) {
-    // (16-row blocks are the wave kernel's; it ORs the row masks itself, so no launch here)
-    if (p->n_tiles > 0 && tile_m != 16) {
-      hipLaunchKernelGGL(k_tile_mask, dim3(tile_blocks), dim3(256), 0, st, side.mask.as<unsigned>(),
-                         (const int*)nullptr, (long long)p->rows, tile_m, 0, V, (long long)p->n_tiles,
-                         p->tilemask.as<unsigned>());
-      SPC_LAUNCH_CHECK();
-    }
-  } else {
+  if (n_split > 0) {  // (the unsorted plan is the map itself: the kernels combine the row masks, nothing is launched here)
+    SPC_TRY(p->tilemask.alloc((size_t)p->parts * tiles_alloc * sizeof(unsigned)));
     SPC_TRY(p->maps.alloc(off * sizeof(int)));
     SPC_TRY(p->perm.alloc((size_t)p->parts * p->rows_pad * sizeof(int)));
-    if (p->rows > 0) {
+    if (p->rows > 0 && own_order) {
+      SPC_TRY(order_rows(side, V, *p, st));
+    } else if (p->rows > 0) {
       // the coordinates of the side's rows (slabs need them; a width of 27 + 3 bits still fits the key)
       const DevBuf& crd = (&side == &km->out_side) ? (km->submanifold() ? km->in_coords : km->out_coords)
                                                     : ((km->transposed && km->stride == 1) ? km->out_coords : km->in_coords);
@@ -798,7 +772,7 @@ int plan_get(spconv_kmap* km, SideMap& side, int n_split, int tile_m, hipStream_
         hipLaunchKernelGGL(k_reorder_tiles, dim3((unsigned)(p->rows_pad / 256), 8), dim3(256), 0, st, side.map.as<int>(),
                            side.mask.as<unsigned>(), V, sorted_rows,
                            few_launches ? (const unsigned*)(hist.as<unsigned>() + 48) : (const unsigned*)nullptr,
-                           (int)p->rows, p->lo[i], p->width[i], tile_m,
+                           (int)p->rows, p->lo[i], p->width[i], kBlock,
                            (long long)p->n_tiles, p->maps.as<int>() + p->map_off[i], perm_i,
                            p->tilemask.as<unsigned>() + (size_t)i * tiles_alloc);
         SPC_LAUNCH_CHECK();

@@ -1,0 +1,73 @@
+"""Calls without a configuration: the library's own row order and the tiles loaded straight into LDS, at row and
+channel counts around the edges of blocks, tiles, pieces and sorted stretches, against the oracle.  Wide layers and a
+few repeated calls make the library sort even small maps; every call has to give the same result."""
+import numpy as np
+import pytest
+
+from oracle import sparse_conv as oc
+from workloads import generators as gen
+from _util import TOL, coords_dev, make_layer, norm_err
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(c, K, stride, transposed, dtype, c_in, c_out, calls, seed):
+    import paper_2311_12862_amd as sp
+    ref = oc.build_kmap(c, K, stride, transposed)
+    (x32, x), (w32, w), (g32, g) = make_layer(ref.n_in, ref.n_out, c_in, c_out, K ** 3, dtype, seed)
+    km = sp.build_kmap(coords_dev(c), K, stride, transposed)
+    want_f, want_d = oc.forward(x32, w32, ref.M), oc.dgrad(g32, w32, ref.M, ref.n_in)
+    for i in range(calls):
+        f, d = sp.fwd(x, w, km), sp.dgrad(g, w, km)
+        assert norm_err(f, want_f) <= TOL[dtype], (i, "fwd")
+        assert norm_err(d, want_d) <= TOL[dtype], (i, "dgrad")
+
+
+@pytest.mark.parametrize("n", [1, 15, 17, 257, 2047, 2049, 4100])
+@pytest.mark.parametrize("dtype,c_in,c_out", [("f16", 512, 512), ("bf16", 264, 136), ("f32", 256, 64)])
+def test_row_counts(n, dtype, c_in, c_out):
+    c = gen.uniform_cloud(n, max(2, int(round((4 * n) ** (1 / 3)))) + 1, seed=n)
+    _check(c, 3, 1, False, dtype, c_in, c_out, 6 if n < 1000 else 3, n)
+
+
+@pytest.mark.parametrize("c_in,c_out", [(8, 16), (40, 24), (64, 32), (96, 72), (136, 64), (192, 128), (64, 200), (320, 264)])
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_channel_counts(dtype, c_in, c_out):
+    c = gen.lidar_scene(41, target_n=2500)
+    _check(c, 3, 1, False, dtype, c_in, c_out, 3, c_in)
+
+
+@pytest.mark.parametrize("K,stride,transposed", [(3, 2, False), (3, 2, True), (2, 2, False), (2, 2, True), (3, 3, False), (1, 1, False)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_other_maps(K, stride, transposed, dtype):
+    c = gen.lidar_scene(43, target_n=3000)
+    _check(c, K, stride, transposed, dtype, 128, 192, 4, 7)
+
+
+def test_large_tiles():
+    """256 x 256 and 128 x 128 tiles (they need enough rows to be chosen), ragged at both ends."""
+    c = gen.full_grid(20, 26, seed=5)[:200_003]
+    import paper_2311_12862_amd as sp
+    import torch
+    km = sp.build_kmap(coords_dev(c), 3, 1)
+    for c_in, c_out in ((32, 256), (40, 136), (64, 128)):
+        x = torch.randn(len(c), c_in, device="cuda").half()
+        w = (torch.randn(27, c_in, c_out, device="cuda") / 20).half()
+        cfg = sp.Config(n_split=1, kernel=2, tile_m=64)   # the register-staged kernel
+        assert norm_err(sp.fwd(x, w, km), sp.fwd(x, w, km, cfg).double().cpu().numpy()) <= 2e-3
+        g = torch.randn(len(c), c_out, device="cuda").half()
+        assert norm_err(sp.dgrad(g, w, km), sp.dgrad(g, w, km, cfg).double().cpu().numpy()) <= 2e-3
+
+
+def test_same_bits_every_time():
+    """The same calls on another kmap of the same rows give the same bits (the order is stable, and which K group
+    sums a unit depends on the unit alone)."""
+    import paper_2311_12862_amd as sp
+    c = gen.lidar_scene(47, target_n=6000)
+    (_, x), (_, w), _ = make_layer(len(c), len(c), 128, 128, 27, "f16", 3)
+    outs = []
+    for _ in range(2):
+        km = sp.build_kmap(coords_dev(c), 3, 1)
+        outs.append([sp.fwd(x, w, km).cpu().numpy() for _ in range(6)])
+    assert all(np.array_equal(a, b) for a, b in zip(*outs))
+    assert np.array_equal(outs[0][4], outs[0][5])
