@@ -17,6 +17,7 @@ import torch
 
 OP_FWD, OP_DGRAD, OP_WGRAD = 0, 1, 2
 FLAG_SLABS = 1
+_CUDA = torch.device("cuda")
 _DTYPES = {torch.float32: 0, torch.float16: 1, torch.bfloat16: 2}
 
 
@@ -142,10 +143,21 @@ def _check(status: int, where: str):
         raise SpconvError(status, where)
 
 
+def _current_stream():
+    """Handle of torch's current stream.  torch.cuda.current_stream() builds a Stream object on the way (2.7 us of
+    the 9 us that a call of this module took); the handle itself is a look-up (0.1 us)."""
+    global _current_stream
+    handle = torch.cuda.current_stream().cuda_stream   # (initialises the device if nothing has yet)
+    raw, dev = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is not None and dev is not None and raw(dev()) == handle:
+        _current_stream = lambda: raw(dev())
+    return handle
+
+
 def _stream(stream):
     """None: torch's current stream; a torch stream; or a raw hipStream_t handle as int (0 = null stream)."""
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -205,12 +217,12 @@ class KMap:
         return v.value
 
     def out_coords(self, stream=None):
-        dst = torch.empty((self.n_out, 4), dtype=torch.int32, device="cuda")
+        dst = torch.empty((self.n_out, 4), dtype=torch.int32, device=_CUDA)
         _check(load_library().spconv_kmap_out_coords(self.handle, _ptr(dst), _stream(stream)), "spconv_kmap_out_coords")
         return dst
 
     def in_coords(self, stream=None):
-        dst = torch.empty((self.n_in, 4), dtype=torch.int32, device="cuda")
+        dst = torch.empty((self.n_in, 4), dtype=torch.int32, device=_CUDA)
         _check(load_library().spconv_kmap_in_coords(self.handle, _ptr(dst), _stream(stream)), "spconv_kmap_in_coords")
         return dst
 
@@ -265,7 +277,7 @@ def build_kmap(coords, K: int = 3, stride: int = 1, transposed: bool = False, st
     if coords.ndim != 2 or coords.shape[1] != 4:
         raise ValueError("coords must be [N, 4]")
     h = C.c_void_p()
-    lib = load_library()
+    lib = _LIB or load_library()
     if dilate:
         if stride != 1 or transposed or asynchronous:
             raise ValueError("dilated kmaps are stride 1, not transposed, built synchronously")
@@ -288,6 +300,11 @@ def _out_tensor(out, shape, dtype, like):
 
 
 def _conv_args(a, w_or_b, kmap, rows_a):
+    """The data type's number; what does not fit raises."""
+    dt = _DTYPES.get(a.dtype)
+    if (dt is not None and a.is_cuda and a.is_contiguous() and w_or_b.is_cuda and w_or_b.is_contiguous()
+            and w_or_b.dtype is a.dtype and a.ndim == 2 and a.shape[0] == rows_a):
+        return dt
     _dev_tensor(a)
     if a.dtype not in _DTYPES:
         raise ValueError(f"unsupported dtype {a.dtype}")
@@ -304,10 +321,13 @@ def fwd(feats, weights, kmap: KMap, cfg: Config | None = None, out=None, stream=
     if V != kmap.V or c_in != feats.shape[1]:
         raise SpconvError(-5, "weights shape does not fit")
     if out is None:
-        out = torch.empty((kmap.n_out, c_out), dtype=feats.dtype, device=feats.device)
-    _out_tensor(out, (kmap.n_out, c_out), feats.dtype, feats)
-    _check(load_library().spconv_fwd(_ptr(feats), _ptr(weights), kmap.handle, c_in, c_out, dt, _cfg(cfg),
-                                     _ptr(out), _stream(stream)), "spconv_fwd")
+        out = feats.new_empty((kmap.n_out, c_out))
+    else:
+        _out_tensor(out, (kmap.n_out, c_out), feats.dtype, feats)
+    status = _LIB.spconv_fwd(_ptr(feats), _ptr(weights), kmap.handle, c_in, c_out, dt, _cfg(cfg), _ptr(out),
+                             _stream(stream))
+    if status:
+        _check(status, "spconv_fwd")
     return out
 
 
@@ -330,10 +350,13 @@ def dgrad(dout, weights, kmap: KMap, cfg: Config | None = None, out=None, stream
     if V != kmap.V or c_out != dout.shape[1]:
         raise SpconvError(-5, "weights shape does not fit")
     if out is None:
-        out = torch.empty((kmap.n_in, c_in), dtype=dout.dtype, device=dout.device)
-    _out_tensor(out, (kmap.n_in, c_in), dout.dtype, dout)
-    _check(load_library().spconv_dgrad(_ptr(dout), _ptr(weights), kmap.handle, c_in, c_out, dt, _cfg(cfg),
-                                       _ptr(out), _stream(stream)), "spconv_dgrad")
+        out = dout.new_empty((kmap.n_in, c_in))
+    else:
+        _out_tensor(out, (kmap.n_in, c_in), dout.dtype, dout)
+    status = _LIB.spconv_dgrad(_ptr(dout), _ptr(weights), kmap.handle, c_in, c_out, dt, _cfg(cfg), _ptr(out),
+                               _stream(stream))
+    if status:
+        _check(status, "spconv_dgrad")
     return out
 
 
@@ -344,10 +367,13 @@ def wgrad(feats, dout, kmap: KMap, cfg: Config | None = None, out=None, stream=N
         raise SpconvError(-5, "dout rows do not fit the kmap")
     c_in, c_out = feats.shape[1], dout.shape[1]
     if out is None:
-        out = torch.empty((kmap.V, c_in, c_out), dtype=torch.float32, device=feats.device)
-    _out_tensor(out, (kmap.V, c_in, c_out), torch.float32, feats)
-    _check(load_library().spconv_wgrad(_ptr(feats), _ptr(dout), kmap.handle, c_in, c_out, dt, _cfg(cfg),
-                                       _ptr(out), _stream(stream)), "spconv_wgrad")
+        out = feats.new_empty((kmap.V, c_in, c_out), dtype=torch.float32)
+    else:
+        _out_tensor(out, (kmap.V, c_in, c_out), torch.float32, feats)
+    status = _LIB.spconv_wgrad(_ptr(feats), _ptr(dout), kmap.handle, c_in, c_out, dt, _cfg(cfg), _ptr(out),
+                               _stream(stream))
+    if status:
+        _check(status, "spconv_wgrad")
     return out
 
 
@@ -403,8 +429,9 @@ def ew(op: int, a, b=None, out=None, stream=None):
             raise ValueError("shape mismatch")
     if out is None:
         out = torch.empty_like(a)
-    _check(load_library().spconv_ew(op, _ptr(a), _ptr(b), _ptr(out), a.numel(), _DTYPES[a.dtype], _stream(stream)),
-           "spconv_ew")
+    status = load_library().spconv_ew(op, _ptr(a), _ptr(b), _ptr(out), a.numel(), _DTYPES[a.dtype], _stream(stream))
+    if status:
+        _check(status, "spconv_ew")
     return out
 
 
