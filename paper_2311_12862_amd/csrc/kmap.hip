@@ -14,6 +14,7 @@
 // held as five planes of 25 offsets.
 #include "common.h"
 
+#include <atomic>
 #include <chrono>
 #include <thread>
 
@@ -34,6 +35,7 @@ constexpr int kRetryGeneralSort = 1;  // (internal) build again with the general
 // is spread over 64 cache lines (one atomic per probe workgroup) so that the adds do not queue
 // up on one address.
 constexpr int kPairSlots = 64;
+constexpr int kPlaneSlots = 12;  // K = 5: pair-count slots per plane (5 x 12 <= kPairSlots)
 struct Ctl {
   unsigned long long flags, count, pad[14];
   unsigned long long pairs[kPairSlots * 16];
@@ -49,6 +51,9 @@ struct Ctl {
 // publishes it: bit 63 = written, bits 48..55 = error flags, bits 0..47 = pair count.
 struct HostResult {
   unsigned long long word;
+  // what the other builds hand over (k_publish): written before `ready`
+  unsigned long long flags, count, key_or, key_and, pairs, entries, plane_pairs[5];
+  unsigned long long ready;
 };
 constexpr unsigned long long kHostReady = 1ull << 63;
 
@@ -130,17 +135,6 @@ __device__ __forceinline__ int table_find(const unsigned long long* tab, int log
 __device__ __forceinline__ int floor_div(int a, int s) {
   int q = a / s;
   return (a % s != 0 && a < 0) ? q - 1 : q;
-}
-
-__global__ void k_ctl_init(Ctl* ctl) {
-  if (threadIdx.x == 0) {
-    ctl->flags = 0;
-    ctl->count = 0;
-  }
-  ctl->pairs[threadIdx.x * 16] = 0;  // launched with kPairSlots threads
-  ctl->entries[threadIdx.x * 16] = 0;
-  ctl->key_or[threadIdx.x * 16] = 0;
-  ctl->key_and[threadIdx.x * 16] = ~0ull;
 }
 
 // Insert key(p_j) -> j for every input row; flags range and duplicate errors.
@@ -350,7 +344,6 @@ struct Planes5 {
   int* map[5];
   unsigned* mask[5];
 };
-constexpr int kPlaneSlots = 12;  // pair-count slots per plane (5 x 12 <= kPairSlots)
 __global__ void __launch_bounds__(256)
     k_probe_planes5(const int4* __restrict__ rows, int n_rows, const unsigned long long* __restrict__ tab, int log_cap,
                     Planes5 pl, Ctl* ctl) {
@@ -445,8 +438,8 @@ __global__ void __launch_bounds__(256) k_fill_u32(unsigned* __restrict__ dst, lo
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) dst[i] = v;
 }
 
-// One launch that prepares a submanifold build: fills the table with ones (every key empty,
-// every cell -1) and clears the control block.
+// One launch that prepares a build: fills the table with ones (every key empty, every cell or value -1) and
+// clears the control block.
 __global__ void __launch_bounds__(256) k_build_init(ulonglong2* __restrict__ tab, long long words, Ctl* ctl) {
   const long long stride = (long long)gridDim.x * blockDim.x;
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -455,12 +448,44 @@ __global__ void __launch_bounds__(256) k_build_init(ulonglong2* __restrict__ tab
     if (threadIdx.x == 0) {
       ctl->flags = 0;
       ctl->count = 0;
+      ctl->tick_top = 0;
     }
     if (threadIdx.x < kPairSlots) {
       ctl->pairs[threadIdx.x * 16] = 0;
       ctl->tick[threadIdx.x * 16] = 0;
+      ctl->entries[threadIdx.x * 16] = 0;
+      ctl->key_or[threadIdx.x * 16] = 0;
+      ctl->key_and[threadIdx.x * 16] = ~0ull;
     }
-    if (threadIdx.x == 0) ctl->tick_top = 0;
+  }
+}
+
+// Adds up the control block and writes the figures straight into pinned host memory, where the host polls for them: a
+// copy and a stream synchronisation in its place cost about 20 us of idle GPU per use.  One wave.
+__global__ void __launch_bounds__(64) k_publish(const Ctl* __restrict__ ctl, HostResult* host) {
+  const int lane = threadIdx.x;  // kPairSlots == 64
+  const unsigned long long mine = ctl->pairs[lane * 16] & ((1ull << 40) - 1);  // (above: publish_pairs' arrivals)
+  unsigned long long pairs = mine, entries = ctl->entries[lane * 16], k_or = ctl->key_or[lane * 16], k_and = ctl->key_and[lane * 16];
+  for (int o = 32; o > 0; o >>= 1) {
+    pairs += __shfl_xor(pairs, o);
+    entries += __shfl_xor(entries, o);
+    k_or |= __shfl_xor(k_or, o);
+    k_and &= __shfl_xor(k_and, o);
+  }
+  for (int g = 0; g < 5; ++g) {
+    unsigned long long v = lane / kPlaneSlots == g ? mine : 0ull;
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if (lane == 0) host->plane_pairs[g] = v;
+  }
+  if (lane == 0) {
+    host->flags = ctl->flags;
+    host->count = ctl->count;
+    host->key_or = k_or;
+    host->key_and = k_and;
+    host->pairs = pairs;
+    host->entries = entries;
+    __threadfence_system();
+    __hip_atomic_store(&host->ready, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -759,6 +784,14 @@ int launch_probe(bool transposed, const int4* rows, int64_t n_rows, int stride, 
   return SPCONV_OK;
 }
 
+// Presets of a table in one launch: map entries [0, n_map) = -1 (absent), masks [0, n_mask) = 0.
+__global__ void __launch_bounds__(256) k_fill_side(unsigned* __restrict__ map, long long n_map, unsigned* __restrict__ mask,
+                                                   long long n_mask) {
+  const long long stride = (long long)gridDim.x * blockDim.x, t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  for (long long i = t; i < n_map; i += stride) map[i] = 0xFFFFFFFFu;
+  for (long long i = t; i < n_mask; i += stride) mask[i] = 0u;
+}
+
 int fill_u32(void* dst, int64_t n, unsigned v, hipStream_t st) {
   if (n <= 0) return SPCONV_OK;
   hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)std::min<int64_t>(ceil_div(n, 256), 2048)), dim3(256), 0, st,
@@ -775,8 +808,13 @@ int alloc_side(SideMap& side, int64_t rows, int V, hipStream_t st, bool preset_a
   SPC_TRY(side.map.alloc((size_t)side.rows_pad * V * sizeof(int)));
   SPC_TRY(side.mask.alloc((size_t)side.rows_pad * sizeof(unsigned)));
   const int64_t first = preset_all ? 0 : rows;
-  SPC_TRY(fill_u32(side.map.as<int>() + first * V, (side.rows_pad - first) * V, 0xFFFFFFFFu, st));
-  SPC_TRY(fill_u32(side.mask.as<unsigned>() + first, side.rows_pad - first, 0u, st));
+  if (side.rows_pad > first) {
+    const int64_t n_map = (side.rows_pad - first) * V;
+    hipLaunchKernelGGL(k_fill_side, dim3((unsigned)std::min<int64_t>(ceil_div(n_map, 1024), 2048)), dim3(256), 0, st,
+                       side.map.as<unsigned>() + first * V, (long long)n_map, side.mask.as<unsigned>() + first,
+                       (long long)(side.rows_pad - first));
+    SPC_LAUNCH_CHECK();
+  }
   return SPCONV_OK;
 }
 
@@ -821,8 +859,9 @@ bool host_ctl_ready(const HostCtl* h, double max_seconds) {
   const volatile unsigned long long* w = &h->res.word;
   const auto t0 = std::chrono::steady_clock::now();
   while (!(*w & kHostReady)) {
-    if (std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() > max_seconds) return false;
-    std::this_thread::yield();
+    const double waited = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+    if (waited > max_seconds) return false;
+    if (waited > 2e-4) std::this_thread::yield();
   }
   return true;
 }
@@ -832,37 +871,49 @@ void host_ctl_release(HostCtl* h) {
   g_host_free.push_back(h);
 }
 
-// Reads the control block back through a pinned staging buffer (one per process) and
-// synchronises the stream.
-int read_ctl(const Ctl* ctl, Ctl* host, hipStream_t st) {
-  static std::mutex mu;
-  static Ctl* pinned = nullptr;
-  std::lock_guard<std::mutex> lk(mu);
-  if (!pinned) {
-    void* p = nullptr;
-    if (hipHostMalloc(&p, sizeof(Ctl), hipHostMallocDefault) != hipSuccess) {
-      (void)hipGetLastError();
-      p = nullptr;
+// Launches k_publish behind the work enqueued so far and waits for its figures.
+int read_ctl(const Ctl* ctl, HostResult* res, hipStream_t st) {
+  HostCtl* hc = host_ctl_acquire();
+  if (!hc) return SPCONV_ENOMEM;
+  hc->res.ready = 0;  // (pinned memory: visible to the kernel launched below)
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, st, ctl, hc->dev);
+  int status = SPCONV_OK;
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) {
+    status = hip_fail(e, "k_publish", __FILE__, __LINE__);
+    (void)hipStreamSynchronize(st);
+  } else {
+    const volatile unsigned long long* ready = &hc->res.ready;
+    const auto t0 = std::chrono::steady_clock::now();
+    while (!*ready) {  // polled: the work behind it usually takes well under a millisecond
+      if (std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() > 0.01) {
+        const hipError_t w = hipStreamSynchronize(st);
+        if (w != hipSuccess) status = hip_fail(w, "hipStreamSynchronize", __FILE__, __LINE__);
+        else if (!*ready) status = SPCONV_EHIP;
+        break;
+      }
     }
-    pinned = static_cast<Ctl*>(p);
+    std::atomic_thread_fence(std::memory_order_acquire);
+    if (status == SPCONV_OK) *res = hc->res;
   }
-  Ctl* dst = pinned ? pinned : host;
-  SPC_HIP(hipMemcpyAsync(dst, ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
-  SPC_HIP(hipStreamSynchronize(st));
-  if (pinned) *host = *pinned;
+  host_ctl_release(hc);
+  return status;
+}
+
+int flags_status(unsigned long long flags) {
+  if (flags & FLAG_RANGE) return SPCONV_ERANGE;
+  if (flags & FLAG_DUP) return SPCONV_EDUP;
+  if (flags & FLAG_FULL) return SPCONV_ENOMEM;
   return SPCONV_OK;
 }
 
-int flags_status(const Ctl& h) {
-  if (h.flags & FLAG_RANGE) return SPCONV_ERANGE;
-  if (h.flags & FLAG_DUP) return SPCONV_EDUP;
-  if (h.flags & FLAG_FULL) return SPCONV_ENOMEM;
+
+int build_init(const DevBuf& tab, long long words /*of 16 bytes*/, Ctl* ctl, hipStream_t st) {
+  hipLaunchKernelGGL(k_build_init, dim3((unsigned)std::min<int64_t>(ceil_div(words, 256), 4096)), dim3(256), 0, st,
+                     tab.as<ulonglong2>(), words, ctl);
+  SPC_LAUNCH_CHECK();
   return SPCONV_OK;
 }
-
-}  // namespace
-int kmap_status_impl(spconv_kmap* km, hipStream_t st, bool wait_stream);
-namespace {
 
 // Submanifold 3x3x3 build: init, insert, probe (whose last workgroup publishes the result to
 // pinned host memory).
@@ -879,11 +930,7 @@ int build_submanifold3(spconv_kmap* km, const int4* rows, int64_t N, bool async,
   side.rows_pad = round_up(N, kRowPad);
   SPC_TRY(side.map.alloc((size_t)side.rows_pad * V * sizeof(int)));
   SPC_TRY(side.mask.alloc((size_t)side.rows_pad * sizeof(unsigned)));
-  const long long words = 2ll << lc;  // 16-byte words of the table, all set to ones
-  const unsigned init_blocks = (unsigned)std::min<int64_t>(ceil_div(words, 256), 4096);
-  hipLaunchKernelGGL(k_build_init, dim3(init_blocks), dim3(256), 0, st, tab.as<ulonglong2>(), words,
-                     ctl);
-  SPC_LAUNCH_CHECK();
+  SPC_TRY(build_init(tab, 2ll << lc, ctl, st));
   hipLaunchKernelGGL(k_insert_runs, dim3(blocks_for(N, 256)), dim3(256), 0, st, rows, (int)N, tab.as<RunSlot>(), lc,
                      ctl, own_rows.as<int4>());
   SPC_LAUNCH_CHECK();
@@ -906,7 +953,19 @@ int build_submanifold3(spconv_kmap* km, const int4* rows, int64_t N, bool async,
   km->pending = true;
   km->n_pairs = -1;
   // (ctl_buf returns to the pool here; reuse is ordered behind the probe on this stream)
-  if (!async) SPC_TRY(kmap_status_impl(km, st, true));
+  if (!async) {
+    // A kernel of its own reports the end: once it runs, the probe's stores are visible to every stream.
+    HostResult h{};
+    const int rc = read_ctl(ctl, &h, st);
+    km->pending = false;
+    km->pending_host = nullptr;
+    if (rc != SPCONV_OK) (void)hipStreamSynchronize(st);  // (the probe still writes to hc)
+    host_ctl_release(hc);
+    SPC_TRY(rc);
+    km->n_pairs = (int64_t)h.pairs;
+    km->build_status = flags_status(h.flags);
+    SPC_TRY(km->build_status);
+  }
   std::swap(km->in_coords.p, own_rows.p);  // P_out == P_in: out_coords stays empty
   std::swap(km->in_coords.bytes, own_rows.bytes);
   return SPCONV_OK;
@@ -919,11 +978,9 @@ int build_submanifold5(spconv_kmap* km, const int4* rows, int64_t N, hipStream_t
   DevBuf ctl_buf, tab, own_rows;
   SPC_TRY(ctl_buf.alloc(sizeof(Ctl)));
   Ctl* ctl = ctl_buf.as<Ctl>();
-  hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(kPairSlots), 0, st, ctl);
-  SPC_LAUNCH_CHECK();
   const int lc = log2_capacity(N);
   SPC_TRY(tab.alloc((size_t)16 << lc));
-  SPC_TRY(fill_u32(tab.p, (int64_t)4 << lc, 0xFFFFFFFFu, st));
+  SPC_TRY(build_init(tab, 1ll << lc, ctl, st));
   SPC_TRY(own_rows.alloc((size_t)N * 16));
   hipLaunchKernelGGL(k_insert_rows, dim3(blocks_for(N, 256)), dim3(256), 0, st, rows, (int)N,
                      tab.as<unsigned long long>(), lc, ctl, own_rows.as<int4>());
@@ -946,19 +1003,17 @@ int build_submanifold5(spconv_kmap* km, const int4* rows, int64_t N, hipStream_t
   hipLaunchKernelGGL(k_probe_planes5, dim3(blocks_for(ceil_div(N, 2), 4), 5), dim3(256), 0, st, rows, (int)N,
                      tab.as<unsigned long long>(), lc, pl, ctl);
   SPC_LAUNCH_CHECK();
-  Ctl h{};
+  HostResult h{};
   SPC_TRY(read_ctl(ctl, &h, st));
   std::swap(km->in_coords.p, own_rows.p);  // P_out == P_in: out_coords stays empty
   std::swap(km->in_coords.bytes, own_rows.bytes);
   km->n_in = km->n_out = N;
   km->n_pairs = 0;
   for (int g = 0; g < 5; ++g) {
-    int64_t n = 0;
-    for (int i = 0; i < kPlaneSlots; ++i) n += (int64_t)h.pairs[(g * kPlaneSlots + i) * 16];
-    km->groups[g]->n_pairs = n;
-    km->n_pairs += n;
+    km->groups[g]->n_pairs = (int64_t)h.plane_pairs[g];
+    km->n_pairs += (int64_t)h.plane_pairs[g];
   }
-  km->build_status = flags_status(h);
+  km->build_status = flags_status(h.flags);
   return km->build_status;
 }
 
@@ -973,14 +1028,10 @@ struct HostCtlHandle {
   }
 };
 
-// wait_stream: wait for the whole stream (the synchronous build: everything on it is the build);
-// otherwise only for the probe's result word.
-int kmap_status_impl(spconv_kmap* km, hipStream_t st, bool wait_stream) {
+int kmap_status(spconv_kmap* km, hipStream_t) {
   if (!km->pending) return km->build_status;
   HostCtl* hc = static_cast<HostCtl*>(km->pending_host);
-  if (wait_stream) {
-    SPC_HIP(hipStreamSynchronize(st));
-  } else if (!host_ctl_ready(hc, 0.002)) {
+  if (!host_ctl_ready(hc, 0.002)) {
     // not there yet: wait for the stream the build runs on instead of spinning
     SPC_HIP(hipStreamSynchronize(km->build_stream));
   }
@@ -993,9 +1044,7 @@ int kmap_status_impl(spconv_kmap* km, hipStream_t st, bool wait_stream) {
     return SPCONV_EHIP;
   }
   const unsigned long long word = hc->res.word;
-  Ctl h{};
-  h.flags = (unsigned)((word >> 48) & 0xFFu);
-  const int status = flags_status(h);
+  const int status = flags_status((word >> 48) & 0xFFu);
   km->n_pairs = (int64_t)(word & 0xFFFFFFFFFFFFull);
   km->pending = false;
   km->pending_host = nullptr;
@@ -1003,8 +1052,6 @@ int kmap_status_impl(spconv_kmap* km, hipStream_t st, bool wait_stream) {
   km->build_status = status;  // kept: whoever resolved the build (a pair count, a tuner), spconv_kmap_status still reports it
   return status;
 }
-
-int kmap_status(spconv_kmap* km, hipStream_t st) { return kmap_status_impl(km, st, false); }
 
 namespace {
 int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int transposed, bool async, hipStream_t st,
@@ -1059,8 +1106,6 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
   DevBuf ctl_buf, tab_fine, tab_coarse, ukeys_a, ukeys_b, hist;
   SPC_TRY(ctl_buf.alloc(sizeof(Ctl)));
   Ctl* ctl = ctl_buf.as<Ctl>();
-  hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(kPairSlots), 0, st, ctl);
-  SPC_LAUNCH_CHECK();
 
   // Stride-2 3x3x3 maps are built from the input side and need no table of the fine points.  (Only
   // stride 2: there every input row meets the output floor(p/2), so every row writes at least one
@@ -1073,19 +1118,22 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
   SPC_TRY(own_rows.alloc((size_t)N * 16));
   if (!from_inputs) {
     SPC_TRY(tab_fine.alloc((size_t)16 << lc_fine));
-    SPC_TRY(fill_u32(tab_fine.p, (int64_t)4 << lc_fine, 0xFFFFFFFFu, st));
+    SPC_TRY(build_init(tab_fine, 1ll << lc_fine, ctl, st));
     hipLaunchKernelGGL(k_insert_rows, dim3(blocks_for(N, 256)), dim3(256), 0, st, rows, (int)N,
                        tab_fine.as<unsigned long long>(), lc_fine, ctl, own_rows.as<int4>());
     SPC_LAUNCH_CHECK();
   }
 
-  Ctl h{};
+  HostResult h{};
   int64_t U = 0;
   DevBuf coarse_rows;
   const int lc_coarse = dilate ? log2_capacity(cand) : lc_fine;
   if (needs_coarse) {
     SPC_TRY(tab_coarse.alloc((size_t)16 << lc_coarse));
-    SPC_TRY(fill_u32(tab_coarse.p, (int64_t)4 << lc_coarse, 0xFFFFFFFFu, st));
+    if (from_inputs)
+      SPC_TRY(build_init(tab_coarse, 1ll << lc_coarse, ctl, st));
+    else
+      SPC_TRY(fill_u32(tab_coarse.p, (int64_t)4 << lc_coarse, 0xFFFFFFFFu, st));
     SPC_TRY(ukeys_a.alloc((size_t)cand * 8));
     SPC_TRY(ukeys_b.alloc((size_t)cand * 8));
     if (dilate) {
@@ -1106,18 +1154,13 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
   if (needs_coarse) {
     // the one synchronisation of a strided build: error flags, U, varying key bits
     SPC_TRY(read_ctl(ctl, &h, st));
-    SPC_TRY(flags_status(h));
+    SPC_TRY(flags_status(h.flags));
     U = (int64_t)h.count;
     SPC_TRY(hist.alloc(sort_hist_elems(U) * sizeof(uint32_t)));
     int in_b = 0;
-    unsigned long long key_or = 0, key_and = ~0ull;
-    for (int i = 0; i < kPairSlots; ++i) {
-      key_or |= h.key_or[i * 16];
-      key_and &= h.key_and[i * 16];
-    }
-    const unsigned long long varying = key_or ^ key_and;
+    const unsigned long long varying = h.key_or ^ h.key_and;
     BitRuns runs{};
-    runs.base = key_and & ~varying;
+    runs.base = h.key_and & ~varying;
     for (int f = 0; f < 4; ++f) {
       const unsigned v = (unsigned)((varying >> (16 * f)) & 0xFFFFu);
       if (!v) continue;
@@ -1212,13 +1255,11 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
 
   if (!needs_coarse || from_inputs) {  // (from_inputs: duplicate rows only show up in the scatter)
     SPC_TRY(read_ctl(ctl, &h, st));
-    int64_t pairs = 0, entries = 0;  // the probe ran before this synchronisation: its pair count is final
-    for (int i = 0; i < kPairSlots; ++i) pairs += (int64_t)h.pairs[i * 16];
-    for (int i = 0; i < kPairSlots; ++i) entries += (int64_t)h.entries[i * 16];
-    if (from_inputs && entries != pairs) h.flags |= FLAG_DUP;  // two rows wrote one entry
+    // (the probe ran before this synchronisation: its pair count is final)
+    if (from_inputs && h.entries != h.pairs) h.flags |= FLAG_DUP;  // two rows wrote one entry
     if (h.flags & FLAG_SORT) return kRetryGeneralSort;
-    SPC_TRY(flags_status(h));
-    km->n_pairs = pairs;
+    SPC_TRY(flags_status(h.flags));
+    km->n_pairs = (int64_t)h.pairs;
   }
 
   // coordinate sets kept for the export calls and for the next layer of a network
@@ -1250,9 +1291,8 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
 int kmap_build_in_side(spconv_kmap* km, hipStream_t st) {
   if (km->in_side.ready) return SPCONV_OK;
   const int V = km->V;
-  SPC_TRY(alloc_side(km->in_side, km->n_in, V, st));
+  SPC_TRY(alloc_side(km->in_side, km->n_in, V, st, true));
   if (km->n_in > 0) {
-    SPC_TRY(fill_u32(km->in_side.map.p, km->in_side.rows_pad * V, 0xFFFFFFFFu, st));
     const long long entries = (long long)km->n_out * V;
     if (entries > 0) {
       hipLaunchKernelGGL(k_scatter_in_side, dim3(blocks_for(entries, 256)), dim3(256), 0, st,
