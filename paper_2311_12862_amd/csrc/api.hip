@@ -155,14 +155,6 @@ int side_for(spconv_kmap* km, spconv_op op, hipStream_t st, OpSide* o) {
   return SPCONV_OK;
 }
 
-int64_t auto_wgrad_pairs(spconv_kmap* km, int C_in, int C_out) {
-  const int tile = (C_in > 64 || C_out > 64) ? 128 : 64;
-  const int64_t tiles = ceil_div(C_in, tile) * ceil_div(C_out, tile);
-  const int64_t want_items = std::max<int64_t>(32, 1536 / tiles);
-  const int64_t pairs = km->n_pairs > 0 ? km->n_pairs : km->n_out * 4;  // unknown while a build is pending
-  return std::max<int64_t>(1024, ceil_div(pairs, want_items));
-}
-
 // Which kernel runs a forward / dgrad call and on which tiles: the caller's configuration with
 // the automatic choices filled in.  Pure host arithmetic (spconv_describe_launch reports it).
 struct KernelChoice {
@@ -337,8 +329,8 @@ int run_igemm_op(spconv_op op, const void* src, const void* weights, spconv_kmap
     if (prepared_only) return SPCONV_EINVAL;
     const int dgrad = op == SPCONV_OP_DGRAD;
     if (!fod_supported(km, dgrad, C_in, C_out, dtype)) return SPCONV_EINVAL;
-    WgradPlan* wp = nullptr;
-    SPC_TRY(wplan_get(km, c.tile_m, st, &wp));
+    ItemPlan* wp = nullptr;
+    SPC_TRY(item_plan_get(km, c.tile_m, st, &wp));
     IgemmArgs a{};
     a.feats = src;
     a.weights = weights;
@@ -539,12 +531,12 @@ SPCONV_API int spconv_kmap_prepare(spconv_kmap* km, spconv_op op, const spconv_c
   SPC_TRY(resolve_config(cfg, SPCONV_F16, &c));
   if (op == SPCONV_OP_WGRAD) {
     if (c.wgrad_pairs == 0) return SPCONV_EINVAL;  // the automatic choice needs the channel counts
-    WgradPlan* wp = nullptr;
-    return wplan_get(km, c.wgrad_pairs, st, &wp);
+    PairList* pl = nullptr;
+    return pair_list_get(km, st, &pl);
   }
   if (c.kernel == 3) {
-    WgradPlan* wp = nullptr;
-    return wplan_get(km, c.tile_m, st, &wp);
+    ItemPlan* wp = nullptr;
+    return item_plan_get(km, c.tile_m, st, &wp);
   }
   OpSide os;
   SPC_TRY(side_for(km, op, st, &os));
@@ -563,10 +555,12 @@ SPCONV_API int spconv_kmap_drop_plans(spconv_kmap* km) {
     km->in_side.mask.release();
     km->in_side.ready = false;
   }
-  km->wplans.clear();
+  km->pair_list.reset();
+  km->item_plans.clear();
   for (auto& sub : km->groups) {
     sub->out_side.plans.clear();
-    sub->wplans.clear();
+    sub->pair_list.reset();
+    sub->item_plans.clear();
   }
   return SPCONV_OK;
 }
@@ -664,10 +658,9 @@ SPCONV_API int spconv_wgrad(const void* feats, const void* dout, spconv_kmap* km
     return SPCONV_OK;
   }
   if (km->n_pairs < 0 && !km->pending) SPC_TRY(kmap_count_pairs(km, st, nullptr));
-  const int64_t target = c.wgrad_pairs > 0 ? c.wgrad_pairs : auto_wgrad_pairs(km, C_in, C_out);
-  WgradPlan* wp = nullptr;
-  SPC_TRY(wplan_get(km, target, st, &wp));
-  return wgrad_run(km, *wp, feats, dout, C_in, C_out, dtype, dweights, st);
+  PairList* pl = nullptr;
+  SPC_TRY(pair_list_get(km, st, &pl));
+  return wgrad_run(km, *pl, c.wgrad_pairs, feats, dout, C_in, C_out, dtype, dweights, st);
 }
 
 SPCONV_API int spconv_tune(spconv_kmap* km, int C_in, int C_out, spconv_dtype dtype, spconv_op op, int layers_sharing_kmap,
@@ -702,10 +695,10 @@ SPCONV_API int spconv_tune(spconv_kmap* km, int C_in, int C_out, spconv_dtype dt
   std::vector<spconv_config> cands;
   if (op == SPCONV_OP_WGRAD) {
     if (km->n_pairs < 0) SPC_TRY(kmap_count_pairs(km, st, nullptr));
-    const int64_t base = auto_wgrad_pairs(km, C_in, C_out);
+    const int64_t base = wgrad_auto_pairs(km, C_in, C_out, dtype);
     for (int64_t f : {1, 2, 4}) {
       spconv_config c{};
-      c.wgrad_pairs = (int32_t)std::min<int64_t>(base * f / 2 + 512, 0x7FFFFFFF);
+      c.wgrad_pairs = (int32_t)std::min<int64_t>(std::max<int64_t>(base * f / 2, 512), 1 << 30);
       cands.push_back(c);
     }
   } else {
@@ -760,8 +753,8 @@ SPCONV_API int spconv_tune(spconv_kmap* km, int C_in, int C_out, spconv_dtype dt
       (void)spconv_kmap_drop_plans(km);
       (void)hipEventRecord(e0, st);
       if (op == SPCONV_OP_WGRAD) {
-        WgradPlan* wp = nullptr;
-        status = wplan_get(km, c.wgrad_pairs, st, &wp);
+        PairList* pl = nullptr;
+        status = pair_list_get(km, st, &pl);
       } else {
         status = spconv_kmap_prepare(km, op, &c, st);
       }
@@ -837,8 +830,8 @@ struct GroupTimer {
       SPC_TRY(spconv_kmap_drop_plans(km));
       (void)hipEventRecord(e0, st);
       if (op == SPCONV_OP_WGRAD) {
-        WgradPlan* wp = nullptr;
-        SPC_TRY(wplan_get(km, c.wgrad_pairs, st, &wp));
+        PairList* pl = nullptr;
+        SPC_TRY(pair_list_get(km, st, &pl));
       } else {
         SPC_TRY(spconv_kmap_prepare(km, op, &c, st));
       }

@@ -87,19 +87,23 @@ struct IgemmPlan {
   bool slabs = false;  // sort keys start with a spatial slab: contiguous ranges of the order are spatially compact
 };
 
-struct WgradItem {
-  int32_t k, pair_begin, pair_end, pad;  // pairs [pair_begin, pair_end) of offset k; item i writes partial tile i
+// Weight-stationary view of the map: the present pairs of each offset, compacted in row order (the M_delta of Section
+// 2.2.1).  Made once per kmap, by the first wgrad or fetch-on-demand call.
+struct PairList {
+  DevBuf pairs;           // int2 [cap]: (output row n, input row j), offset-major
+  int64_t cap = 0;        // n_pairs, or the bound n_out * V while an asynchronous build is pending
+  DevBuf seg;             // int32 [V+1]: pairs of offset k are seg[k]..seg[k+1]
 };
 
-// Weight-stationary view of the map for wgrad: the present pairs of each offset, compacted
-// in row order (the M_delta of Section 2.2.1), cut into work items of about target_pairs.
-struct WgradPlan {
-  int64_t target_pairs = 0;
-  int max_items = 0;  // launch bound: V + ceil(n_pairs / target_pairs)
-  DevBuf pairs;       // int2 [pairs_cap]: (output row n, input row j), offset-major
-  int64_t pairs_cap = 0;  // n_pairs, or the bound n_out * V while an asynchronous build is pending
-  DevBuf seg;         // int32 [V+1]: pairs of offset k are seg[k]..seg[k+1]
-  DevBuf items;       // WgradItem [max_items]
+struct PairItem {
+  int32_t k, pair_begin, pair_end, pad;  // pairs [pair_begin, pair_end) of offset k
+};
+
+// The pair list cut into work items of about `target` pairs of one offset each (fetch-on-demand).
+struct ItemPlan {
+  int64_t target = 0;
+  int max_items = 0;  // launch bound: V + ceil(pairs / target)
+  DevBuf items;       // PairItem [max_items]
   DevBuf item_seg;    // int32 [V+2]: items of offset k are item_seg[k]..item_seg[k+1]; [V+1] = n_items
 };
 
@@ -140,7 +144,8 @@ struct spconv_kmap {
         in_side(*in_ref) {}
   spconv_kmap(const spconv_kmap&) = delete;
   spconv_kmap& operator=(const spconv_kmap&) = delete;
-  std::map<int64_t, std::unique_ptr<spc::WgradPlan>> wplans;  // by target_pairs
+  std::unique_ptr<spc::PairList> pair_list;
+  std::map<int64_t, std::unique_ptr<spc::ItemPlan>> item_plans;  // by target
   // K = 5 (125 offsets): the kmap is held as its five x-planes, each a submanifold map of 25 offsets
   // (dx = g - 2) over the same rows, so that masks, sort keys and tile masks stay 32-bit words and
   // every kernel runs on a plane as it runs on a 27-offset map; the planes' results are summed like
@@ -235,7 +240,8 @@ int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
 int plan_get(spconv_kmap* km, SideMap& side, int n_split, int flags, hipStream_t st, IgemmPlan** out);
 int plan_mac_units(spconv_kmap* km, SideMap& side, IgemmPlan* plan, int group_rows, hipStream_t st,
                    int64_t* executed);
-int wplan_get(spconv_kmap* km, int64_t target_pairs, hipStream_t st, WgradPlan** out);
+int pair_list_get(spconv_kmap* km, hipStream_t st, PairList** out);
+int item_plan_get(spconv_kmap* km, int64_t target, hipStream_t st, ItemPlan** out);
 
 // ---- order.hip: fills perm, maps and tilemask of a one-part plan in the library's own order
 int order_rows(const SideMap& side, int V, IgemmPlan& p, hipStream_t st);
@@ -266,10 +272,11 @@ int split_reduce(const float* partial, int parts, int64_t rows, int c, spconv_dt
 
 // ---- fod.hip (fetch-on-demand dataflow; wp must have been cut into items of tile_m pairs)
 bool fod_supported(const spconv_kmap* km, int dgrad, int C_in, int C_out, spconv_dtype dtype);
-int fod_run(spconv_kmap* km, const WgradPlan& wp, const IgemmArgs& a, int tile_m, void* dst, hipStream_t st);
+int fod_run(spconv_kmap* km, const ItemPlan& wp, const IgemmArgs& a, int tile_m, void* dst, hipStream_t st);
 
 // ---- wgrad.hip
-int wgrad_run(spconv_kmap* km, const WgradPlan& wp, const void* feats, const void* dout, int C_in,
-              int C_out, spconv_dtype dtype, float* dweights, hipStream_t st);
+int64_t wgrad_auto_pairs(const spconv_kmap* km, int C_in, int C_out, spconv_dtype dtype);
+int wgrad_run(spconv_kmap* km, const PairList& pl, int64_t piece_pairs, const void* feats, const void* dout, int C_in, int C_out,
+              spconv_dtype dtype, float* dweights, hipStream_t st);
 
 }  // namespace spc

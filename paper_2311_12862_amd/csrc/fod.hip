@@ -35,7 +35,7 @@ struct FodParams {
   const void* weights;   // [V][C_in][C_out]
   float* acc;            // [rows_dst][c_out] fp32, zero before the launch
   const int2* pairs;     // (output row n, input row j), offset-major
-  const WgradItem* items;
+  const PairItem* items;
   const int* item_seg;   // [V] = number of items
   unsigned feats_bytes, pairs_bytes, acc_bytes;
   int V, C_in, C_out;
@@ -104,7 +104,7 @@ __global__ void __launch_bounds__(256) k_fod(const FodParams p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wave_m = wave >> 1, wave_n = wave & 1;
   const int n0 = blockIdx.y * BN;
-  const WgradItem item = p.items[item_id];
+  const PairItem item = p.items[item_id];
   int cnt = item.pair_end - item.pair_begin;
   if (cnt > BM) cnt = BM;  // items are cut to at most BM pairs by the plan
   const int c_red = p.c_red;
@@ -262,7 +262,7 @@ __global__ void __launch_bounds__(256) k_fod_f32(const FodParams p) {
   if (item_id >= p.item_seg[p.V]) return;  // the grid is sized by a bound on the item count
   const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
   const int n0 = blockIdx.y * FF_BN;
-  const WgradItem item = p.items[item_id];
+  const PairItem item = p.items[item_id];
   int cnt = item.pair_end - item.pair_begin;
   if (cnt > FF_BM) cnt = FF_BM;  // items are cut to at most 64 pairs by the plan
   const __amdgpu_buffer_rsrc_t x_rsrc = make_rsrc(p.feats, p.feats_bytes);
@@ -391,11 +391,10 @@ bool fod_supported(const spconv_kmap* km, int dgrad, int C_in, int C_out, spconv
          (uint64_t)km->n_out * km->V * 8 < 0xFFFFC000ull;
 }
 
-int fod_run(spconv_kmap* km, const WgradPlan& wp, const IgemmArgs& a, int tile_m, void* dst, hipStream_t st) {
+int fod_run(spconv_kmap* km, const ItemPlan& wp, const IgemmArgs& a, int tile_m, void* dst, hipStream_t st) {
   if (tile_m != 64 && tile_m != 128) return SPCONV_EINVAL;
   if (a.dtype == SPCONV_F32 && tile_m != FF_BM) return SPCONV_EINVAL;  // the fp32 kernel has one tile shape
-  if (wp.target_pairs != tile_m) return SPCONV_EINVAL;  // one work item is one tile of pairs
-  if (wp.max_items >= (1 << 20)) return SPCONV_EINVAL;  // the plan's item table is capped there
+  if (!km->pair_list || wp.target != tile_m) return SPCONV_EINVAL;  // one work item is one tile of pairs
   if (!fod_supported(km, a.dgrad, a.C_in, a.C_out, a.dtype)) return SPCONV_EINVAL;
   const int64_t rows_src = a.dgrad ? km->n_out : km->n_in, rows_dst = a.dgrad ? km->n_in : km->n_out;
   if (rows_dst == 0) return SPCONV_OK;
@@ -410,15 +409,16 @@ int fod_run(spconv_kmap* km, const WgradPlan& wp, const IgemmArgs& a, int tile_m
     hipLaunchKernelGGL(k_zero_f4, dim3(blocks), dim3(256), 0, st, km->scratch.as<float4>(), n4);
     SPC_LAUNCH_CHECK();
   }
-  if (wp.pairs_cap > 0 && rows_src > 0) {
+  const PairList& pl = *km->pair_list;
+  if (pl.cap > 0 && rows_src > 0) {
     p.feats = a.feats;
     p.weights = a.weights;
     p.acc = km->scratch.as<float>();
-    p.pairs = wp.pairs.as<int2>();
-    p.items = wp.items.as<WgradItem>();
+    p.pairs = pl.pairs.as<int2>();
+    p.items = wp.items.as<PairItem>();
     p.item_seg = wp.item_seg.as<int>();
     p.feats_bytes = (unsigned)((uint64_t)rows_src * p.c_red * (a.dtype == SPCONV_F32 ? 4 : 2));
-    p.pairs_bytes = (unsigned)((uint64_t)wp.pairs_cap * 8);
+    p.pairs_bytes = (unsigned)((uint64_t)pl.cap * 8);
     p.acc_bytes = (unsigned)acc_bytes;
     p.V = km->V;
     p.C_in = a.C_in;

@@ -434,54 +434,6 @@ __global__ void __launch_bounds__(256)
   if (w == 0 && threadIdx.x == 63) counts[(long long)V * n_chunks] = 0;  // the slot that will receive the total
 }
 
-// Cuts every offset's pair range into ceil(count / target) nearly equal work items.  Called by a
-// whole workgroup; begin_of(k) returns the scanned pair offset of offset k (k = V: the total).
-template <typename BeginOf>
-__device__ __forceinline__ void make_items(BeginOf begin_of, int V, unsigned target, int max_items, int* seg,
-                                           WgradItem* items, int* item_seg) {
-  __shared__ unsigned s_begin[33], s_cnt[33], s_first[34];
-  const int lane = threadIdx.x;
-  if (lane < 64) {  // the first wave works out the per-offset figures
-    const unsigned begin = lane <= V ? begin_of(lane) : 0u;
-    const unsigned next = __shfl_down(begin, 1);
-    const unsigned cnt = lane < V ? next - begin : 0u;
-    if (lane <= V) seg[lane] = (int)begin;
-    const unsigned pieces = cnt ? (cnt + target - 1) / target : 0u;
-    unsigned incl = pieces;
-    for (int o = 1; o < 64; o <<= 1) {
-      const unsigned up = __shfl_up(incl, o);
-      if (lane >= o) incl += up;
-    }
-    unsigned first = incl - pieces;
-    if (first > (unsigned)max_items) first = (unsigned)max_items;
-    if (lane <= V) {
-      s_begin[lane] = begin;
-      s_cnt[lane] = cnt;
-      s_first[lane] = first;
-      item_seg[lane] = (int)first;
-    }
-    if (lane == V) {
-      s_first[V + 1] = first;
-      item_seg[V + 1] = (int)first;
-    }
-  }
-  __syncthreads();
-  const unsigned n_items = s_first[V];
-  for (unsigned i = lane; i < n_items; i += blockDim.x) {
-    int k = 0;
-    while (k + 1 < V && s_first[k + 1] <= i) ++k;
-    const unsigned c = s_cnt[k], pc = s_first[k + 1] - s_first[k], q = i - s_first[k];
-    // c * q / pc with c = a * pc + r
-    const unsigned a = c / pc, r = c - a * pc;
-    WgradItem w;
-    w.k = k;
-    w.pair_begin = (int)(s_begin[k] + a * q + (unsigned)(((unsigned long long)r * q) / pc));
-    w.pair_end = (int)(s_begin[k] + a * (q + 1) + (unsigned)(((unsigned long long)r * (q + 1)) / pc));
-    w.pad = 0;
-    items[i] = w;
-  }
-}
-
 // Most chunks for which the fill kernel adds up the per-chunk counts by itself: 64 lanes x steps.
 constexpr int kSelfScanSteps = 10;
 constexpr int kSelfScanChunks = 64 * kSelfScanSteps;
@@ -494,14 +446,13 @@ constexpr int kSelfScanChunks = 64 * kSelfScanSteps;
 // Where the chunk's range starts: with SELF_SCAN the workgroup adds up the raw per-chunk counts
 // itself (every offset's total, and the part of it that the chunks before this one hold; 27 x
 // chunks counters, read from L2 by every workgroup, which is cheaper than a scan launch in between
-// while there are a few hundred chunks), and workgroup 0 also cuts the work items; otherwise
-// `counts` was scanned before the launch and the items are made elsewhere.
+// while there are a few hundred chunks), and workgroup 0 also writes the offsets' ranges; otherwise
+// `counts` was scanned before the launch.
 template <int V, bool SELF_SCAN>
 __global__ void __launch_bounds__(256)
     k_pair_fill(const int* __restrict__ map, const unsigned* __restrict__ mask, long long rows, int n_chunks,
                 int wave_rows, const unsigned* __restrict__ counts, int2* __restrict__ pairs, long long pairs_cap,
-                unsigned target, int max_items, int* __restrict__ seg, WgradItem* __restrict__ items,
-                int* __restrict__ item_seg) {
+                int* __restrict__ seg) {
   __shared__ int slab[4][64 * V];
   __shared__ unsigned part[4][32];
   __shared__ unsigned s_before[32], s_total[32], s_seg[34];
@@ -566,8 +517,11 @@ __global__ void __launch_bounds__(256)
       base = counts[(long long)lane * n_chunks + w];
     for (int i = 0; i < wib; ++i) base += part[i][lane];
   }
-  if constexpr (SELF_SCAN) {
-    if (w == 0) make_items([&](int k) { return s_seg[k]; }, V, target, max_items, seg, items, item_seg);
+  if (w == 0 && wib == 0 && lane <= V) {
+    if constexpr (SELF_SCAN)
+      seg[lane] = (int)s_seg[lane];
+    else
+      seg[lane] = (int)counts[(long long)lane * n_chunks];
   }
   const unsigned long long lt = (1ull << lane) - 1ull;
   int* ms = slab[wib];
@@ -595,10 +549,49 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-__global__ void __launch_bounds__(256)
-    k_make_items(const unsigned* __restrict__ scanned, int V, int n_waves, unsigned target, int max_items,
-                 int* __restrict__ seg, WgradItem* __restrict__ items, int* __restrict__ item_seg) {
-  make_items([&](int k) { return scanned[(long long)k * n_waves]; }, V, target, max_items, seg, items, item_seg);
+// Cuts every offset's pair range into ceil(count / target) nearly equal work items.  One workgroup.
+__global__ void __launch_bounds__(256) k_make_items(const int* __restrict__ seg, int V, unsigned target, int max_items,
+                                                    PairItem* __restrict__ items, int* __restrict__ item_seg) {
+  __shared__ unsigned s_begin[33], s_cnt[33], s_first[34];
+  const int lane = threadIdx.x;
+  if (lane < 64) {  // the first wave works out the per-offset figures
+    const unsigned begin = lane <= V ? (unsigned)seg[lane] : 0u;
+    const unsigned next = __shfl_down(begin, 1);
+    const unsigned cnt = lane < V ? next - begin : 0u;
+    const unsigned pieces = cnt ? (cnt + target - 1) / target : 0u;
+    unsigned incl = pieces;
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned up = __shfl_up(incl, o);
+      if (lane >= o) incl += up;
+    }
+    unsigned first = incl - pieces;
+    if (first > (unsigned)max_items) first = (unsigned)max_items;
+    if (lane <= V) {
+      s_begin[lane] = begin;
+      s_cnt[lane] = cnt;
+      s_first[lane] = first;
+      item_seg[lane] = (int)first;
+    }
+    if (lane == V) {
+      s_first[V + 1] = first;
+      item_seg[V + 1] = (int)first;
+    }
+  }
+  __syncthreads();
+  const unsigned n_items = s_first[V];
+  for (unsigned i = lane; i < n_items; i += blockDim.x) {
+    int k = 0;
+    while (k + 1 < V && s_first[k + 1] <= i) ++k;
+    const unsigned c = s_cnt[k], pc = s_first[k + 1] - s_first[k], q = i - s_first[k];
+    // c * q / pc with c = a * pc + r
+    const unsigned a = c / pc, r = c - a * pc;
+    PairItem w;
+    w.k = k;
+    w.pair_begin = (int)(s_begin[k] + a * q + (unsigned)(((unsigned long long)r * q) / pc));
+    w.pair_end = (int)(s_begin[k] + a * (q + 1) + (unsigned)(((unsigned long long)r * (q + 1)) / pc));
+    w.pad = 0;
+    items[i] = w;
+  }
 }
 
 }  // namespace
@@ -809,28 +802,20 @@ int plan_mac_units(spconv_kmap* km, SideMap& side, IgemmPlan* plan, int group_ro
   return SPCONV_OK;
 }
 
-int wplan_get(spconv_kmap* km, int64_t target_pairs, hipStream_t st, WgradPlan** out) {
-  const int64_t requested = target_pairs;  // (the cache key; the item size may be raised below)
-  auto it = km->wplans.find(target_pairs);
-  if (it != km->wplans.end()) {
-    *out = it->second.get();
+int pair_list_get(spconv_kmap* km, hipStream_t st, PairList** out) {
+  if (km->pair_list) {
+    *out = km->pair_list.get();
     return SPCONV_OK;
   }
   // The pair count is known after a synchronous submanifold build.  While an asynchronous build is
-  // pending, sizes come from the bound n_out * V (surplus workgroups exit at once); maps built with
-  // stride > 1 count their pairs here (one synchronisation).
+  // pending, sizes come from the bound n_out * V; maps built with stride > 1 count their pairs here
+  // (one synchronisation).
   if (km->n_pairs < 0 && !km->pending) SPC_TRY(kmap_count_pairs(km, st, nullptr));
-  std::unique_ptr<WgradPlan> p(new (std::nothrow) WgradPlan);
+  std::unique_ptr<PairList> p(new (std::nothrow) PairList);
   if (!p) return SPCONV_ENOMEM;
   const int V = km->V;
   const SideMap& side = km->out_side;
-  p->pairs_cap = km->n_pairs >= 0 ? km->n_pairs : km->n_out * V;
-  // At most 2^20 work items: a smaller request is raised to the item size that covers every pair
-  // (the item cutter gives later offsets no item once the list is full, which would drop pairs).
-  constexpr int64_t kMaxItems = 1 << 20;
-  if (V + ceil_div(p->pairs_cap, target_pairs) > kMaxItems) target_pairs = ceil_div(p->pairs_cap, kMaxItems - V);
-  p->target_pairs = target_pairs;
-  p->max_items = (int)(V + ceil_div(p->pairs_cap, target_pairs));
+  p->cap = km->n_pairs >= 0 ? km->n_pairs : km->n_out * V;
   // rows per chunk (one workgroup, a quarter per wave): 256, or the next power of two up to 2048
   // that lets the fill kernel add up the counters itself
   int wave_rows = 256;
@@ -840,10 +825,8 @@ int wplan_get(spconv_kmap* km, int64_t target_pairs, hipStream_t st, WgradPlan**
   const size_t n_sums = scan_sums_elems((int64_t)n_counts);
   DevBuf counts;
   SPC_TRY(counts.alloc((n_counts + n_sums) * sizeof(unsigned)));
-  SPC_TRY(p->pairs.alloc(std::max<size_t>(1, (size_t)p->pairs_cap) * sizeof(int2)));
+  SPC_TRY(p->pairs.alloc(std::max<size_t>(2, (size_t)round_up(p->cap, 2)) * sizeof(int2)));  // (read two pairs at a time)
   SPC_TRY(p->seg.alloc((size_t)(V + 1) * sizeof(int)));
-  SPC_TRY(p->items.alloc((size_t)p->max_items * sizeof(WgradItem)));
-  SPC_TRY(p->item_seg.alloc((size_t)(V + 2) * sizeof(int)));
   const unsigned blocks = (unsigned)n_waves;  // one workgroup per chunk
   hipLaunchKernelGGL(k_pair_count, dim3(blocks), dim3(256), 0, st, side.mask.as<unsigned>(), (long long)km->n_out, V,
                      n_waves, wave_rows, counts.as<unsigned>());
@@ -853,18 +836,13 @@ int wplan_get(spconv_kmap* km, int64_t target_pairs, hipStream_t st, WgradPlan**
   const bool self_scan = n_waves <= kSelfScanChunks;
   if (!self_scan) {
     SPC_TRY(scan_u32_inplace(counts.as<uint32_t>(), (int64_t)n_counts, counts.as<uint32_t>() + n_counts, st));
-    hipLaunchKernelGGL(k_make_items, dim3(1), dim3(256), 0, st, counts.as<unsigned>(), V, n_waves,
-                       (unsigned)target_pairs, p->max_items, p->seg.as<int>(), p->items.as<WgradItem>(),
-                       p->item_seg.as<int>());
-    SPC_LAUNCH_CHECK();
   }
   const int* mp = side.map.as<int>();
   const unsigned* mk = side.mask.as<unsigned>();
-  const long long cap = (long long)std::max<int64_t>(1, p->pairs_cap);  // elements the pair buffer holds
+  const long long cap = (long long)std::max<int64_t>(1, p->cap);  // elements the pair buffer holds
 #define SPC_FILL(VV, SELF)                                                                                       \
   hipLaunchKernelGGL((k_pair_fill<VV, SELF>), dim3(blocks), dim3(256), 0, st, mp, mk, (long long)km->n_out,       \
-                     n_waves, wave_rows, counts.as<unsigned>(), p->pairs.as<int2>(), cap, (unsigned)target_pairs, \
-                     p->max_items, p->seg.as<int>(), p->items.as<WgradItem>(), p->item_seg.as<int>())
+                     n_waves, wave_rows, counts.as<unsigned>(), p->pairs.as<int2>(), cap, p->seg.as<int>())
   if (V == 27) {
     if (self_scan) SPC_FILL(27, true); else SPC_FILL(27, false);
   } else if (V == 25) {  // a plane of a K = 5 map
@@ -877,7 +855,33 @@ int wplan_get(spconv_kmap* km, int64_t target_pairs, hipStream_t st, WgradPlan**
 #undef SPC_FILL
   SPC_LAUNCH_CHECK();
   *out = p.get();
-  km->wplans[requested] = std::move(p);
+  km->pair_list = std::move(p);
+  return SPCONV_OK;
+}
+
+int item_plan_get(spconv_kmap* km, int64_t target, hipStream_t st, ItemPlan** out) {
+  auto it = km->item_plans.find(target);
+  if (it != km->item_plans.end()) {
+    *out = it->second.get();
+    return SPCONV_OK;
+  }
+  PairList* pl = nullptr;
+  SPC_TRY(pair_list_get(km, st, &pl));
+  std::unique_ptr<ItemPlan> p(new (std::nothrow) ItemPlan);
+  if (!p) return SPCONV_ENOMEM;
+  const int V = km->V;
+  // At most 2^20 work items (the item cutter gives later offsets no item once the list is full).
+  constexpr int64_t kMaxItems = 1 << 20;
+  if (V + ceil_div(pl->cap, target) > kMaxItems) return SPCONV_EINVAL;
+  p->target = target;
+  p->max_items = (int)(V + ceil_div(pl->cap, target));
+  SPC_TRY(p->items.alloc((size_t)p->max_items * sizeof(PairItem)));
+  SPC_TRY(p->item_seg.alloc((size_t)(V + 2) * sizeof(int)));
+  hipLaunchKernelGGL(k_make_items, dim3(1), dim3(256), 0, st, pl->seg.as<int>(), V, (unsigned)target, p->max_items,
+                     p->items.as<PairItem>(), p->item_seg.as<int>());
+  SPC_LAUNCH_CHECK();
+  *out = p.get();
+  km->item_plans[target] = std::move(p);
   return SPCONV_OK;
 }
 

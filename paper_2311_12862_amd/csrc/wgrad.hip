@@ -4,209 +4,350 @@
 // The reduction runs over output rows, the long inner loop the paper singles
 // out.  Here it walks the compacted pair list of one offset (the
 // weight-stationary view of the map, Section 2.2.1), so no multiply is spent
-// on absent neighbours and the row order of the map does not matter.  A
-// workgroup owns a 64 x 64 tile of dW[k] and a range of pairs.  Per batch of 64
-// pairs it gathers 64 rows of x and of dy (16-byte segments, out-of-range
-// buffer loads for the ragged tail), one batch ahead of the matrix cores, and
-// stores them row-major in LDS; the MFMA operands need the reduction index
-// (the pair) contiguous per lane, which the CDNA4 transposing LDS read
-// (ds_read_b64_tr_b16) delivers without a software transpose.  Each work item
-// writes an fp32 partial tile; a second kernel adds the tiles of each offset
-// in item order, so results are bit-reproducible.
+// on absent neighbours and the row order of the map does not matter.
+//
+// Work split.  Each offset's pairs are cut into pieces of nearly equal length, one per workgroup.  A piece leaves an fp32
+// partial tile; a second kernel adds the tiles of each offset in order, so results are bit-reproducible.  The number
+// of pieces weighs the time that a piece takes against the tiles that are written and read back
+// (split_length), and at most as many run as the GPU holds at once.
+//
+// What bounds it is the gather: every pair's two rows cross the cache hierarchy once per column or row of tiles,
+// so the tile is as wide as the layer up to 256 x 256.  Rows go straight into LDS (batches of 32 pairs, two to three of them
+// in flight ahead of the one that is multiplied, each load waited for by count); the matrix instructions need the
+// pair index contiguous per lane, which the transposing LDS read (ds_read_b64_tr_b16) delivers.  Fragments of
+// the next batch are read while the matrix cores work on this one.  Narrow layers (one wave's tile) give every
+// wave batches of its own: no barrier, and the waves' sums meet in LDS at the end of a segment.
 #include "common.h"
+#include "lds_tiles.h"
 
+#include <algorithm>
 #include <atomic>
+#include <cmath>
 
 namespace spc {
 namespace {
 
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
-template <typename T> struct Mfma;
-template <> struct Mfma<_Float16> {
-  static __device__ __forceinline__ f32x4 run(s16x8 a, s16x8 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0,
-                                                  0);
-  }
-};
-template <> struct Mfma<__bf16> {
-  static __device__ __forceinline__ f32x4 run(s16x8 a, s16x8 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
-                                                   0, 0);
-  }
+struct Split {
+  int pieces;    // at most so many (grid, partial tiles)
+  int length;    // pairs of a piece as asked for, or 0: chosen by
+  float weight;  // sqrt(time of a pair in a piece / time of a partial tile), and at least
+  int unit;      // so many
 };
 
 struct WgradParams {
   const void* feats;   // [n_in][C_in]
   const void* dout;    // [n_out][C_out]
   const int2* pairs;   // (n, j), offset-major
-  const WgradItem* items;
-  const int* item_seg; // [V+2], [V] = number of items
-  float* partial;      // [max_items][C_in][C_out]
+  const int* seg;      // [V+1]
+  float* partial;      // [piece][C_in][C_out]
   unsigned feats_bytes, dout_bytes, pairs_bytes;
   int C_in, C_out, V;
+  Split split;
 };
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
-}
-__device__ __forceinline__ uint4 buf_load16(__amdgpu_buffer_rsrc_t r, unsigned byte_off) {
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 0);
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ int2 buf_load8(__amdgpu_buffer_rsrc_t r, unsigned byte_off) {
-  const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, byte_off, 0, 0);
-  return make_int2((int)v.x, (int)v.y);
-}
+constexpr unsigned kNoRow = 0xFFFFC000u;  // beyond every buffer
 
-constexpr int WG_BK = 64;   // pairs per batch
-
-// Transposing read: the 16 lanes of a group together fetch a 4 (rows) x 16 (columns) block,
-// lane a pointing at row a/4, columns 4*(a%4)..+3; lane a receives column a of the block,
-// i.e. four consecutive rows of one channel.  Two reads give the 8 reduction steps of a lane.
-template <int LD>
-__device__ __forceinline__ s16x8 read_frag(const unsigned short* tile, int row0, int col0, int lane) {
-  const int a = lane & 15, g = lane >> 4;
-  const unsigned short* p = tile + (row0 + 8 * g + (a >> 2)) * LD + col0 + 4 * (a & 3);
-  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) s16x4*)(p));
-  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) s16x4*)(p + 4 * LD));
-  return s16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+// Pairs per piece; computed by every workgroup, as the pair count may only be known on the device.
+// g pieces take time ~ pairs / g (a workgroup's serial part) + g * (a tile written and read): least at g ~ sqrt(pairs).
+__device__ __forceinline__ int split_length(const Split& s, int pairs, int V) {
+  if (s.length > 0) return s.length;
+  const int g = min(s.pieces - V, (int)(s.weight * sqrtf((float)pairs)) + 1);
+  return max(s.unit, (pairs + g - 1) / g);
+}
+// Lane k < V of a wave: the pieces of the offsets before k, and of k.
+struct Pieces {
+  int before, count;
+};
+__device__ __forceinline__ Pieces pieces_of(const Split& s, int bound, int V, int lane) {  // bound: lane k <= V holds seg[k]
+  const int length = split_length(s, __builtin_amdgcn_readlane(bound, V), V);
+  const int pairs = __shfl_down(bound, 1) - bound;
+  const int count = lane < V ? (pairs + length - 1) / length : 0;
+  int incl = count;
+  for (int o = 1; o < 32; o <<= 1) {
+    const int up = __shfl_up(incl, o);
+    if (lane >= o) incl += up;
+  }
+  return {incl - count, count};
 }
 
-// TILE x TILE outputs of dW[k] per workgroup (32, 64 or 128); each of the four waves owns a
-// TILE/2 x TILE/2 quadrant as QB x QB MFMA blocks.  A larger tile gathers every pair's rows
-// fewer times when the layer has more than 64 channels.
-template <typename T, int TILE>
-__global__ void __launch_bounds__(256) k_wgrad(const WgradParams p) {
-  constexpr int QB = TILE / 32;        // 16 x 16 blocks per quadrant side
-  constexpr int LD = TILE + 16;        // LDS row pitch in 2-byte elements: 8 words mod 32, so that the
-                                       // four rows a transposing read touches fall on disjoint banks
-  constexpr int SEGS = TILE / 8;       // 16-byte segments per staged row
-  constexpr int PASSES = WG_BK * SEGS / 256;
-  constexpr int RPP = 256 / SEGS;      // pair rows covered per pass
-  extern __shared__ __align__(16) unsigned char smem_w[];
-  unsigned short* Xs = reinterpret_cast<unsigned short*>(smem_w);  // [2][pair][ci]
-  unsigned short* Ds = Xs + 2 * WG_BK * LD;                        // [2][pair][co]
+template <int N> __device__ __forceinline__ void wait_loads() {  // all but the N youngest; own LDS reads are done as well
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"i"(N) : "memory");
+}
 
-  const int n_items = p.item_seg[p.V];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int ci0 = blockIdx.y * TILE, co0 = blockIdx.z * TILE;
-  // the grid is bounded; a workgroup takes items blockIdx.x, blockIdx.x + gridDim.x, ...
-  for (int item_id = blockIdx.x; item_id < n_items; item_id += gridDim.x) {
-  const WgradItem item = p.items[item_id];
-  const __amdgpu_buffer_rsrc_t x_rsrc = make_rsrc(p.feats, p.feats_bytes);
-  const __amdgpu_buffer_rsrc_t d_rsrc = make_rsrc(p.dout, p.dout_bytes);
-  const __amdgpu_buffer_rsrc_t p_rsrc = make_rsrc(p.pairs, p.pairs_bytes);
-  const unsigned x_row = (unsigned)p.C_in * 2u, d_row = (unsigned)p.C_out * 2u;
+// TI x TO (channels of x, of dy) per workgroup; NWI x NWO waves share a batch, or (NWK > 1) each wave has its own.
+// S stages.
+template <typename T, int TI, int TO, int NWI, int NWO, int NWK, int S> struct WgradShape {
+  static constexpr int E = (int)sizeof(T), CE = 16 / E;  // bytes and chunk length of an element
+  static constexpr int BP = E == 2 ? 32 : 16;            // pairs of a batch
+  static constexpr int NW = NWI * NWO;
+  static constexpr int WI = TI / NWI, WO = TO / NWO, IB = WI / 16, OB = WO / 16;
+  static constexpr int x_bytes = BP * TI * E, d_bytes = BP * TO * E, stage = x_bytes + d_bytes;
+  static constexpr int LX = x_bytes / 1024, LD = d_bytes / 1024;  // loads of a stage
+  static constexpr int L = (LX + LD) / NW;                        // per wave
+  static constexpr int idx_bytes = BP * 8;
+  static constexpr int R = 2 * S;                        // index ring
+  static constexpr int group = S * stage + R * idx_bytes;  // LDS of a wave group
+  static constexpr int sums = NWK > 1 ? TI * TO * 4 : 0;
+  static constexpr int total = NWK * (group > sums ? group : sums);
+  static constexpr int threads = NW * NWK * 64;
+  static_assert(NW == 1 || NWK == 1, "");
+  static_assert((LX + LD) % NW == 0 && x_bytes % 1024 == 0 && d_bytes % 1024 == 0, "whole loads");
+  static_assert(L * (S - 2) + S - 2 < 64, "vmcnt");
+};
 
-  const int wci = (wave >> 1) * (TILE / 2), wco = (wave & 1) * (TILE / 2);
-  f32x4 acc[QB][QB];
+// Where chunk c (16 bytes) of row r of a staged batch stands.  16-bit types: the transposing read of 32 lanes takes rows
+// r..r+3 and r+8..r+11 at one 32-byte block each; fp32: four rows at one 64-byte block.  Eight (four) blocks span
+// the LDS banks, so the block number is XORed (six blocks: rotated) by the row.
+template <int E, int CPR> __device__ __forceinline__ int chunk_block_shift(int r) {
+  if constexpr (E == 4) return CPR >= 16 ? (r & 3) : (r >> 1) & 1;
+  else if constexpr (CPR == 4) return (r >> 3) & 1;
+  else if constexpr (CPR == 8) return ((r >> 1) & 1) | (((r >> 3) & 1) << 1);
+  else if constexpr (CPR == 12) return (r >> 3) & 1;
+  else return (r & 3) | (((r >> 3) & 1) << 2);
+}
+// block b of row r stands at block place_of(b), and place q holds block block_at(q)
+template <int E, int CPR> __device__ __forceinline__ int place_of(int b, int r) {
+  if constexpr (E == 2 && CPR == 12) {
+    const int q = b + chunk_block_shift<E, CPR>(r);
+    return q >= 6 ? q - 6 : q;
+  } else {
+    return b ^ chunk_block_shift<E, CPR>(r);
+  }
+}
+template <int E, int CPR> __device__ __forceinline__ int block_at(int q, int r) {
+  if constexpr (E == 2 && CPR == 12) {
+    const int b = q - chunk_block_shift<E, CPR>(r);
+    return b < 0 ? b + 6 : b;
+  } else {
+    return q ^ chunk_block_shift<E, CPR>(r);
+  }
+}
+
+template <typename T, int TI, int TO, int NWI, int NWO, int NWK, int S>
+__global__ void __launch_bounds__(NWI* NWO* NWK * 64) k_wgrad(const WgradParams p) {
+  typedef WgradShape<T, TI, TO, NWI, NWO, NWK, S> W;
+  constexpr int E = W::E, CE = W::CE, BP = W::BP, NW = W::NW, IB = W::IB, OB = W::OB, L = W::L, R = W::R;
+  constexpr int CX = TI / CE, CD = TO / CE;     // chunks of a staged row
+  constexpr int BC = E == 2 ? 2 : 4;            // chunks of a block (16 channels)
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & 63;
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = NWK > 1 ? wave_all : 0, wave = NWK > 1 ? 0 : wave_all;
+  const int wi = wave / NWO, wo = wave % NWO;
+  const int fa = lane & 15, fg = lane >> 4;
+  const int ci0 = blockIdx.y * TI, co0 = blockIdx.z * TO;
+  unsigned char* const my = smem + grp * W::group;   // stages, then the index ring
+  const unsigned lds = (unsigned)(size_t)(__attribute__((address_space(3))) void*)my;
+  constexpr int kIdx = S * W::stage;
+
+  const int bound = lane <= p.V ? p.seg[lane] : 0x7FFFFFFF;  // lane k: where offset k's pairs begin
+  int k, begin, end;
+  {
+    const Pieces pc = pieces_of(p.split, bound, p.V, lane);
+    k = __popcll(__ballot(lane < p.V && pc.before + pc.count <= (int)blockIdx.x));
+    if (k >= p.V) return;
+    const int q = (int)blockIdx.x - __builtin_amdgcn_readlane(pc.before, k);
+    const int first = __builtin_amdgcn_readlane(bound, k), all = __builtin_amdgcn_readlane(bound, k + 1) - first;
+    const int count = __builtin_amdgcn_readlane(pc.count, k), length = (all + count - 1) / count;
+    begin = first + q * length;
+    end = max(begin, min(first + all, begin + length));  // (may be empty: the tile is then zero)
+  }
+
+  const u32x4 x_rsrc = rsrc_of(p.feats, p.feats_bytes), d_rsrc = rsrc_of(p.dout, p.dout_bytes);
+  const u32x4 p_rsrc = rsrc_of(p.pairs, p.pairs_bytes);
+  const unsigned x_row = (unsigned)p.C_in * E, d_row = (unsigned)p.C_out * E;
+
+  // this wave's loads of a stage: lane -> row of the batch, byte offset within the row (kNoRow: no such channel)
+  int l_row[L];
+  unsigned l_off[L];
 #pragma unroll
-  for (int i = 0; i < QB; ++i)
+  for (int i = 0; i < L; ++i) {
+    const int j = wave * L + i;
+    if (j < W::LX) {
+      const int q = j * 64 + lane, r = q / CX, c = q % CX;
+      const int ch = (block_at<E, CX>(c / BC, r) * BC + c % BC) * CE + ci0;
+      l_row[i] = r;
+      l_off[i] = ch < p.C_in ? (unsigned)ch * E : kNoRow;
+    } else {
+      const int q = (j - W::LX) * 64 + lane, r = q / CD, c = q % CD;
+      const int ch = (block_at<E, CD>(c / BC, r) * BC + c % BC) * CE + co0;
+      l_row[i] = r;
+      l_off[i] = ch < p.C_out ? (unsigned)ch * E : kNoRow;
+    }
+  }
+  // fragment addresses within a stage
+  unsigned xa[IB], da[OB];
+  {
+    const int r = E == 2 ? 8 * fg + (fa >> 2) : fg;
+    const int in = E == 2 ? (fa & 3) * 8 : fa * 4;
 #pragma unroll
-    for (int j = 0; j < QB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // staging: thread (q, seg) moves segment seg (8 channels) of pair rows q, q + RPP, ...
-  const int seg = tid % SEGS, q0 = tid / SEGS;
-  const bool x_ok = ci0 + seg * 8 < p.C_in, d_ok = co0 + seg * 8 < p.C_out;
-  const int n_batches = (item.pair_end - item.pair_begin + WG_BK - 1) / WG_BK;
-
-  int2 pr[PASSES];            // pair indices of the batch after next
-  uint4 rx[PASSES], rd[PASSES];  // rows of the next batch
-  auto load_pairs = [&](int batch) {
+    for (int i = 0; i < IB; ++i) xa[i] = (unsigned)(r * TI * E + place_of<E, CX>(wi * IB + i, r) * BC * 16 + in);
 #pragma unroll
-    for (int h = 0; h < PASSES; ++h) {
-      const int e = item.pair_begin + batch * WG_BK + q0 + RPP * h;
-      pr[h] = buf_load8(p_rsrc, (batch < n_batches && e < item.pair_end) ? (unsigned)e * 8u : 0xFFFFFFFFu);
+    for (int i = 0; i < OB; ++i) da[i] = (unsigned)(W::x_bytes + r * TO * E + place_of<E, CD>(wo * OB + i, r) * BC * 16 + in);
+  }
+  auto frag = [&](const unsigned char* at, int pitch) -> u32x4 {
+    if constexpr (E == 2) {
+      // 16 lanes fetch a 4 x 16 block of [pair][channel] and each receives one column; two reads give the lane's
+      // 8 pairs (8 fg .. 8 fg + 7) of its channel
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(at));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(at + 4 * pitch));
+      return __builtin_bit_cast(u32x4, s16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+    } else {  // pairs fg, 4 + fg, 8 + fg, 12 + fg
+      u32x4 v;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] = *reinterpret_cast<const unsigned*>(at + t * 4 * pitch);
+      return v;
     }
   };
-  auto load_rows = [&](int batch) {
+
+  const int first = begin & ~1;  // (index loads are 16 bytes: two pairs)
+  const int batches = max(end - first + BP - 1, 0) / BP;
+  const int mine = NWK > 1 ? (batches - grp + NWK - 1) / NWK : batches;  // batches grp, grp + NWK, ...
+
+  auto batch_pair = [&](int b) { return first + (NWK > 1 ? b * NWK + grp : b) * BP; };
+  auto load_idx = [&](int b) {  // pair indices of own batch b into the ring; every wave of a group loads the same bytes
+    if (lane < BP / 2)
+      load_to_lds(p_rsrc, (unsigned)(batch_pair(b) + lane * 2) * 8u, 0, lds + kIdx + (unsigned)(b % R) * W::idx_bytes);
+  };
+  unsigned src[L];
+  auto read_idx = [&](int b) {  // row offsets of own batch b
+    const int e0 = batch_pair(b);
+    const unsigned char* ring = my + kIdx + (b % R) * W::idx_bytes;
+    unsigned row[L];
 #pragma unroll
-    for (int h = 0; h < PASSES; ++h) {
-      const int e = item.pair_begin + batch * WG_BK + q0 + RPP * h;
-      const bool live = batch < n_batches && e < item.pair_end;
-      rx[h] = buf_load16(x_rsrc, (live && x_ok) ? (unsigned)pr[h].y * x_row + (unsigned)(ci0 + seg * 8) * 2u
-                                                 : 0xFFFFFFFFu);
-      rd[h] = buf_load16(d_rsrc, (live && d_ok) ? (unsigned)pr[h].x * d_row + (unsigned)(co0 + seg * 8) * 2u
-                                                 : 0xFFFFFFFFu);
+    for (int i = 0; i < L; ++i)
+      row[i] = *reinterpret_cast<const unsigned*>(ring + l_row[i] * 8 + ((NW == 1 ? i < W::LX : wave * L + i < W::LX) ? 4 : 0));
+#pragma unroll
+    for (int i = 0; i < L; ++i) asm volatile("" : "+v"(row[i]));  // (else every read becomes a branch of its own)
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      const bool is_x = NW == 1 ? i < W::LX : wave * L + i < W::LX;
+      const bool live = (unsigned)(e0 + l_row[i] - begin) < (unsigned)(end - begin);
+      const unsigned at = row[i] * (is_x ? x_row : d_row) + l_off[i];
+      src[i] = live && l_off[i] != kNoRow ? at : kNoRow;
     }
   };
-  auto store_rows = [&](int buf) {
+  auto load_stage = [&](int slot) {
 #pragma unroll
-    for (int h = 0; h < PASSES; ++h) {
-      *reinterpret_cast<uint4*>(Xs + (buf * WG_BK + q0 + RPP * h) * LD + seg * 8) = rx[h];
-      *reinterpret_cast<uint4*>(Ds + (buf * WG_BK + q0 + RPP * h) * LD + seg * 8) = rd[h];
+    for (int i = 0; i < L; ++i) {
+      const int j = wave * L + i;
+      const bool is_x = NW == 1 ? i < W::LX : j < W::LX;
+      load_to_lds(is_x ? x_rsrc : d_rsrc, src[i], 0, lds + slot * W::stage + j * 1024);
     }
+  };
+  auto sync = [&]() {
+    if constexpr (NW > 1) asm volatile("s_barrier" ::: "memory");
   };
 
-  load_pairs(0);
-  load_rows(0);
-  load_pairs(1);
-  store_rows(0);
-  __syncthreads();
-  for (int b = 0; b < n_batches; ++b) {
-    load_rows(b + 1);   // out-of-range (zero, no traffic) past the last batch
-    load_pairs(b + 2);
-    const unsigned short* xs = Xs + (b & 1) * WG_BK * LD;
-    const unsigned short* ds = Ds + (b & 1) * WG_BK * LD;
+  f32x4 acc[OB][IB];
 #pragma unroll
-    for (int ks = 0; ks < WG_BK / 32; ++ks) {
-      s16x8 af[QB], bf[QB];
+  for (int o = 0; o < OB; ++o)
 #pragma unroll
-      for (int i = 0; i < QB; ++i) af[i] = read_frag<LD>(xs, ks * 32, wci + i * 16, lane);
+    for (int i = 0; i < IB; ++i) acc[o][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // indices of the first 2 S batches, stages of the first S
 #pragma unroll
-      for (int j = 0; j < QB; ++j) bf[j] = read_frag<LD>(ds, ks * 32, wco + j * 16, lane);
+  for (int b = 0; b < R; ++b) load_idx(b);
+  wait_loads<0>();
+  sync();
 #pragma unroll
-      for (int i = 0; i < QB; ++i)
+  for (int b = 0; b < S; ++b) {
+    read_idx(b);
+    load_stage(b);
+  }
+  read_idx(S);
+  wait_loads<(S - 1) * L>();
+  sync();
+  u32x4 x[IB], d[OB];
 #pragma unroll
-        for (int j = 0; j < QB; ++j) acc[i][j] = Mfma<T>::run(af[i], bf[j], acc[i][j]);
+  for (int o = 0; o < OB; ++o) d[o] = frag(my + da[o], TO * E);
+#pragma unroll
+  for (int i = 0; i < IB; ++i) x[i] = frag(my + xa[i], TI * E);
+
+  int slot = 0;
+  for (int b = 0; b < mine; ++b) {
+    // batch b + 1 has landed (and the indices of b + S + 1), and everyone holds batch b in registers
+    if (b < S - 2) wait_loads<(S - 2) * L>();
+    else wait_loads<(S - 2) * (L + 1)>();
+    sync();
+    load_stage(slot);  // batch b + S
+    load_idx(b + 2 * S);
+    slot = slot + 1 == S ? 0 : slot + 1;
+    read_idx(b + S + 1);
+    const unsigned char* next = my + slot * W::stage;
+    u32x4 xn[IB];
+#pragma unroll
+    for (int i = 0; i < IB; ++i) xn[i] = frag(next + xa[i], TI * E);
+#pragma unroll
+    for (int o = 0; o < OB; ++o) {
+#pragma unroll
+      for (int i = 0; i < IB; ++i) acc[o][i] = mma<T>(d[o], x[i], acc[o][i]);
+      d[o] = frag(next + da[o], TO * E);
     }
-    store_rows((b + 1) & 1);
+#pragma unroll
+    for (int i = 0; i < IB; ++i) x[i] = xn[i];
+  }
+  wait_loads<0>();  // (nothing may land in LDS that is used for something else next)
+
+  // a lane holds channels co = 4 fg .. + 3 of row ci = fa of each block
+  float* dst = p.partial + (long long)blockIdx.x * p.C_in * p.C_out;
+  auto store = [&](int ci, int co, f32x4 v) {
+    if (ci < p.C_in && co < p.C_out) *reinterpret_cast<f32x4*>(dst + (long long)ci * p.C_out + co) = v;
+  };
+  if constexpr (NWK > 1) {
     __syncthreads();
-  }
-
-  float* dst = p.partial + (long long)item_id * p.C_in * p.C_out;
+    f32x4* sums = reinterpret_cast<f32x4*>(smem);  // [group][block][lane]
 #pragma unroll
-  for (int i = 0; i < QB; ++i)
+    for (int o = 0; o < OB; ++o)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int ci = ci0 + wci + i * 16 + (lane >> 4) * 4 + r;
-      if (ci >= p.C_in) continue;
+      for (int i = 0; i < IB; ++i) sums[(grp * OB * IB + o * IB + i) * 64 + lane] = acc[o][i];
+    __syncthreads();
+    constexpr int Q = OB * IB / NWK;  // blocks that each group adds up
+    static_assert(NWK == 1 || OB * IB % NWK == 0, "");
 #pragma unroll
-      for (int j = 0; j < QB; ++j) {
-        const int co = co0 + wco + j * 16 + (lane & 15);
-        if (co < p.C_out) dst[(long long)ci * p.C_out + co] = acc[i][j][r];
-      }
+    for (int u = 0; u < Q; ++u) {
+      const int blk = grp * Q + u, o = blk / IB, i = blk % IB;
+      f32x4 v = sums[blk * 64 + lane];
+#pragma unroll
+      for (int g = 1; g < NWK; ++g) v += sums[(g * OB * IB + blk) * 64 + lane];
+      store(ci0 + i * 16 + fa, co0 + o * 16 + fg * 4, v);
     }
-  __syncthreads();  // the LDS tiles are reused by the next item
+  } else {
+#pragma unroll
+    for (int o = 0; o < OB; ++o)
+#pragma unroll
+      for (int i = 0; i < IB; ++i)
+        store(ci0 + wi * W::WI + i * 16 + fa, co0 + wo * W::WO + o * 16 + fg * 4, acc[o][i]);
   }
 }
 
-// fp32 path: plain FMA arithmetic, 16 pairs at a time.
+// fp32 with more than 32 bits of byte offsets: plain FMA arithmetic, 16 pairs at a time.
 __global__ void __launch_bounds__(256) k_wgrad_f32(const WgradParams p) {
   __shared__ float Xs[16][64 + 4];
   __shared__ float Ds[16][64 + 4];
-  if ((int)blockIdx.x >= p.item_seg[p.V]) return;
   const int tid = threadIdx.x;
-  const WgradItem item = p.items[blockIdx.x];
+  int begin, end;
+  {
+    const int lane = tid & 63, bound = lane <= p.V ? p.seg[lane] : 0x7FFFFFFF;
+    const Pieces pc = pieces_of(p.split, bound, p.V, lane);
+    const int k = __popcll(__ballot(lane < p.V && pc.before + pc.count <= (int)blockIdx.x));
+    if (k >= p.V) return;
+    const int q = (int)blockIdx.x - __builtin_amdgcn_readlane(pc.before, k);
+    const int first = __builtin_amdgcn_readlane(bound, k), all = __builtin_amdgcn_readlane(bound, k + 1) - first;
+    const int count = __builtin_amdgcn_readlane(pc.count, k), length = (all + count - 1) / count;
+    begin = first + q * length;
+    end = max(begin, min(first + all, begin + length));
+  }
   const int ci0 = blockIdx.y * 64, co0 = blockIdx.z * 64;
   const float* feats = reinterpret_cast<const float*>(p.feats);
   const float* dout = reinterpret_cast<const float*>(p.dout);
   const int ty = tid / 16, tx = tid % 16;
   const int q = tid / 16, seg4 = (tid % 16) * 4;
   float acc[4][4] = {};
-  for (int base = item.pair_begin; base < item.pair_end; base += 16) {
+  for (int base = begin; base < end; base += 16) {
     const int e = base + q;
     float4 vx = make_float4(0.f, 0.f, 0.f, 0.f), vd = vx;
-    if (e < item.pair_end) {
+    if (e < end) {
       const int2 pr = p.pairs[e];
       if (ci0 + seg4 < p.C_in) vx = *reinterpret_cast<const float4*>(feats + (long long)pr.y * p.C_in + ci0 + seg4);
       if (co0 + seg4 < p.C_out) vd = *reinterpret_cast<const float4*>(dout + (long long)pr.x * p.C_out + co0 + seg4);
@@ -240,16 +381,17 @@ __global__ void __launch_bounds__(256) k_wgrad_f32(const WgradParams p) {
 }
 
 // dW[k][e] = sum of the partial tiles of offset k.  A workgroup covers 64 float4 columns; its four
-// waves take the items of the offset round-robin (four loads in flight each) and their sums are
+// waves take the tiles of the offset round-robin (four loads in flight each) and their sums are
 // added in wave order, so the order of additions is fixed and results are bit-reproducible.
 __global__ void __launch_bounds__(256) k_wgrad_reduce(const float* __restrict__ partial,
-                                                      const int* __restrict__ item_seg, int elems,
+                                                      const int* __restrict__ seg, int V, Split split, int elems,
                                                       float* __restrict__ dw) {
   __shared__ float4 part[4][64];
   const int col = threadIdx.x & 63, stripe = threadIdx.x >> 6;
   const int e4 = (blockIdx.x * 64 + col) * 4;
   const int k = blockIdx.y;
-  const int first = item_seg[k], last = item_seg[k + 1];
+  const Pieces pc = pieces_of(split, col <= V ? seg[col] : 0x7FFFFFFF, V, col);
+  const int first = __builtin_amdgcn_readlane(pc.before, k), last = first + __builtin_amdgcn_readlane(pc.count, k);
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   if (e4 < elems) {
     int it = first + stripe;
@@ -290,22 +432,82 @@ __global__ void __launch_bounds__(256) k_wgrad_reduce(const float* __restrict__ 
 
 }  // namespace
 
-int wgrad_run(spconv_kmap* km, const WgradPlan& wp, const void* feats, const void* dout, int C_in, int C_out,
+// Tiles by channels: as wide as the layer, so that a pair's rows are gathered once, as long as there are pairs enough to
+// give every workgroup a long window (a window costs a partial tile of 4 bytes per weight, written and read back).
+#define SPC_WGRAD_16(X) X(32, 32, 1, 1, 4, 4) X(64, 64, 1, 1, 4, 3) X(96, 96, 2, 2, 1, 3) X(128, 128, 2, 2, 1, 3) X(256, 256, 2, 4, 1, 4)
+#define SPC_WGRAD_32(X) X(32, 32, 1, 1, 4, 3) X(64, 64, 1, 1, 4, 2)
+
+namespace {
+struct TilePick {
+  int tile, per_cu;
+  float weight;
+};
+TilePick pick_tile(int C_in, int C_out, bool f32, int64_t pairs) {
+  const int c = std::max(C_in, C_out);
+  if (f32) return c <= 32 ? TilePick{32, 2, 1.1f} : TilePick{64, 2, 0.9f};
+  if (c <= 32) return {32, 2, 1.1f};
+  if (c <= 64) return {64, 1, 0.75f};
+  if (c <= 96) return {96, 3, 0.65f};
+  if (c <= 128 || pairs < (1 << 19)) return {128, 3, 0.6f};
+  return {256, 1, 0.4f};
+}
+Split split_for(const TilePick& t, int64_t tiles, int V, int64_t pairs) {
+  Split s{};
+  s.weight = t.weight / sqrtf((float)tiles);
+  s.unit = 64;
+  const int64_t g = std::max<int64_t>(1, std::min<int64_t>({256 * t.per_cu / tiles - V, (int64_t)(s.weight * sqrt((double)pairs)) + 2, ceil_div(pairs, s.unit)}));
+  s.pieces = (int)g + V;
+  return s;
+}
+template <typename T, int TI, int TO, int NWI, int NWO, int NWK, int S>
+int launch_wgrad(const WgradParams& p, dim3 grid, hipStream_t st) {
+  typedef WgradShape<T, TI, TO, NWI, NWO, NWK, S> W;
+  static_assert(W::total <= 160 * 1024, "LDS of a CU");
+  auto kernel = k_wgrad<T, TI, TO, NWI, NWO, NWK, S>;
+  static std::atomic<bool> attr_set{false};  // (set twice by racing threads at worst: the calls are idempotent)
+  if (!attr_set.load(std::memory_order_acquire)) {
+    SPC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, W::total));
+    attr_set.store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL(kernel, grid, dim3(W::threads), W::total, st, p);
+  SPC_LAUNCH_CHECK();
+  return SPCONV_OK;
+}
+}  // namespace
+
+// Pairs of a piece that calls without a configuration get.
+int64_t wgrad_auto_pairs(const spconv_kmap* km, int C_in, int C_out, spconv_dtype dtype) {
+  const int64_t pairs = std::max<int64_t>(km->n_pairs, 1);
+  const TilePick t = pick_tile(C_in, C_out, dtype == SPCONV_F32, pairs);
+  const Split s = split_for(t, ceil_div(C_in, t.tile) * ceil_div(C_out, t.tile), km->V, pairs);
+  return std::max<int64_t>(s.unit, ceil_div(pairs, s.pieces - km->V));
+}
+
+// piece_pairs: pairs of a piece, 0: chosen here.
+int wgrad_run(spconv_kmap* km, const PairList& pl, int64_t piece_pairs, const void* feats, const void* dout, int C_in, int C_out,
               spconv_dtype dtype, float* dweights, hipStream_t st) {
   const int V = km->V;
   const int elems = C_in * C_out;
   const size_t e = dtype == SPCONV_F32 ? 4 : 2;
   const uint64_t feats_bytes = (uint64_t)km->n_in * C_in * e, dout_bytes = (uint64_t)km->n_out * C_out * e;
-  const uint64_t pairs_bytes = (uint64_t)std::max<int64_t>(wp.pairs_cap, 0) * 8;
-  if (dtype != SPCONV_F32 && (feats_bytes >= 0xFFFFC000ull || dout_bytes >= 0xFFFFC000ull || pairs_bytes >= 0xFFFFC000ull))
-    return SPCONV_EINVAL;  // buffer descriptors address 32 bits
-  SPC_TRY(km->scratch.reserve((size_t)wp.max_items * elems * sizeof(float)));
+  const uint64_t pairs_bytes = (uint64_t)round_up(std::max<int64_t>(pl.cap, 0), 2) * 8;
+  const bool fits = feats_bytes < kNoRow && dout_bytes < kNoRow && pairs_bytes < kNoRow;  // buffer descriptors address 32 bits
+  if (dtype != SPCONV_F32 && !fits) return SPCONV_EINVAL;
   WgradParams p{};
+  const TilePick t = pick_tile(C_in, C_out, dtype == SPCONV_F32, pl.cap);
+  const int tile = dtype == SPCONV_F32 && !fits ? 64 : t.tile;
+  if (piece_pairs > 0) {  // about 2^20 pieces at most: a smaller request is raised
+    constexpr int64_t kMaxPieces = 1 << 20;
+    p.split.length = (int)std::min<int64_t>(std::max<int64_t>(piece_pairs, ceil_div(pl.cap, kMaxPieces)), 1 << 30);
+    p.split.pieces = (int)ceil_div(pl.cap, p.split.length) + V;
+  } else {
+    p.split = split_for(t, ceil_div(C_in, tile) * ceil_div(C_out, tile), V, pl.cap);
+  }
+  SPC_TRY(km->scratch.reserve((size_t)p.split.pieces * elems * sizeof(float)));
   p.feats = feats;
   p.dout = dout;
-  p.pairs = wp.pairs.as<int2>();
-  p.items = wp.items.as<WgradItem>();
-  p.item_seg = wp.item_seg.as<int>();
+  p.pairs = pl.pairs.as<int2>();
+  p.seg = pl.seg.as<int>();
   p.partial = km->scratch.as<float>();
   p.feats_bytes = (unsigned)feats_bytes;
   p.dout_bytes = (unsigned)dout_bytes;
@@ -313,41 +515,32 @@ int wgrad_run(spconv_kmap* km, const WgradPlan& wp, const void* feats, const voi
   p.C_in = C_in;
   p.C_out = C_out;
   p.V = V;
-  if (wp.pairs_cap > 0) {
-    if (dtype == SPCONV_F32) {
-      dim3 grid((unsigned)wp.max_items, (unsigned)ceil_div(C_in, 64), (unsigned)ceil_div(C_out, 64));
+  if (pl.cap > 0) {
+    const dim3 grid((unsigned)p.split.pieces, (unsigned)ceil_div(C_in, tile), (unsigned)ceil_div(C_out, tile));
+    if (dtype == SPCONV_F32 && !fits) {
       hipLaunchKernelGGL(k_wgrad_f32, grid, dim3(256), 0, st, p);
+      SPC_LAUNCH_CHECK();
     } else {
-      // 128 x 128 tiles as soon as a 64 x 64 tile would gather every pair's rows more than once
-      // (and 32 x 32 tiles for layers of at most 32 channels, whose rows would otherwise be half padding)
-      const int tile = (C_in > 64 || C_out > 64) ? 128 : ((C_in > 32 || C_out > 32) ? 64 : 32);
-      const unsigned tiles = (unsigned)(ceil_div(C_in, tile) * ceil_div(C_out, tile));
-      const unsigned gx = (unsigned)std::min<int64_t>(wp.max_items, std::max<unsigned>(64u, 512u / tiles));
-      dim3 grid(gx, (unsigned)ceil_div(C_in, tile), (unsigned)ceil_div(C_out, tile));
-      const size_t smem = (size_t)2 * 2 * WG_BK * (tile + 16) * 2;
-      static std::atomic<bool> attr_set{false};  // (set twice by racing threads at worst: the calls are idempotent)
-      if (!attr_set.load(std::memory_order_acquire)) {
-        SPC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_wgrad<_Float16, 128>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)((size_t)8 * WG_BK * 144)));
-        SPC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_wgrad<__bf16, 128>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)((size_t)8 * WG_BK * 144)));
-        attr_set.store(true, std::memory_order_release);
-      }
+      int status = SPCONV_EINVAL;
+#define SPC_WGRAD_F16(TI, TO, NWI, NWO, NWK, S) \
+  if (tile == TI) status = launch_wgrad<_Float16, TI, TO, NWI, NWO, NWK, S>(p, grid, st);
+#define SPC_WGRAD_BF16(TI, TO, NWI, NWO, NWK, S) \
+  if (tile == TI) status = launch_wgrad<__bf16, TI, TO, NWI, NWO, NWK, S>(p, grid, st);
+#define SPC_WGRAD_F32(TI, TO, NWI, NWO, NWK, S) \
+  if (tile == TI) status = launch_wgrad<float, TI, TO, NWI, NWO, NWK, S>(p, grid, st);
       if (dtype == SPCONV_F16) {
-        if (tile == 32) hipLaunchKernelGGL((k_wgrad<_Float16, 32>), grid, dim3(256), smem, st, p);
-        else if (tile == 64) hipLaunchKernelGGL((k_wgrad<_Float16, 64>), grid, dim3(256), smem, st, p);
-        else hipLaunchKernelGGL((k_wgrad<_Float16, 128>), grid, dim3(256), smem, st, p);
+        SPC_WGRAD_16(SPC_WGRAD_F16)
+      } else if (dtype == SPCONV_BF16) {
+        SPC_WGRAD_16(SPC_WGRAD_BF16)
       } else {
-        if (tile == 32) hipLaunchKernelGGL((k_wgrad<__bf16, 32>), grid, dim3(256), smem, st, p);
-        else if (tile == 64) hipLaunchKernelGGL((k_wgrad<__bf16, 64>), grid, dim3(256), smem, st, p);
-        else hipLaunchKernelGGL((k_wgrad<__bf16, 128>), grid, dim3(256), smem, st, p);
+        SPC_WGRAD_32(SPC_WGRAD_F32)
       }
+      SPC_TRY(status);
     }
-    SPC_LAUNCH_CHECK();
   }
   dim3 rgrid((unsigned)ceil_div(elems / 4, 64), (unsigned)V);
-  hipLaunchKernelGGL(k_wgrad_reduce, rgrid, dim3(256), 0, st, km->scratch.as<float>(), wp.item_seg.as<int>(), elems,
-                     dweights);
+  hipLaunchKernelGGL(k_wgrad_reduce, rgrid, dim3(256), 0, st, km->scratch.as<float>(), pl.seg.as<int>(), V, p.split,
+                     elems, dweights);
   SPC_LAUNCH_CHECK();
   return SPCONV_OK;
 }

@@ -1,0 +1,39 @@
+"""Weight gradients at the channel counts around the tiles' edges and at piece lengths around the batches' edges (one
+pair, a batch, an odd first pair, several offsets with no pair at all), against the oracle."""
+import pytest
+
+from oracle import sparse_conv as oc
+from workloads import generators as gen
+from _util import coords_dev, make_layer, norm_err
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(c, dtype, c_in, c_out, pieces, seed):
+    import paper_2311_12862_amd as sp
+    ref = oc.build_kmap(c, 3, 1)
+    (x32, x), _, (g32, g) = make_layer(ref.n_in, ref.n_out, c_in, c_out, 27, dtype, seed)
+    want = oc.wgrad(x32, g32, ref.M)
+    km = sp.build_kmap(coords_dev(c), 3, 1)
+    for n in pieces:
+        cfg = sp.Config(wgrad_pairs=n) if n else None
+        dw = sp.wgrad(x, g, km, cfg)
+        assert norm_err(dw, want) <= 1e-4, n
+        assert (dw == sp.wgrad(x, g, km, cfg)).all(), n
+
+
+@pytest.mark.parametrize("c_in,c_out", [(8, 16), (32, 32), (40, 64), (64, 24), (72, 96), (104, 40), (128, 136), (264, 16)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_channels(dtype, c_in, c_out):
+    _check(gen.lidar_scene(51, target_n=1200), dtype, c_in, c_out, (0, 1, 31, 33, 129, 4000), c_in)
+
+
+@pytest.mark.parametrize("n", [1, 2, 33, 700])
+@pytest.mark.parametrize("dtype,ch", [("f16", 32), ("bf16", 64), ("f16", 96), ("f16", 160), ("f32", 64)])
+def test_few_pairs(dtype, ch, n):
+    _check(gen.uniform_cloud(n, max(2, int(round((3 * n) ** (1 / 3)))) + 1, seed=n), dtype, ch, ch, (0, 7), n)
+
+
+def test_wide_tile():
+    """The 256 x 256 tile (it needs half a million pairs to be chosen), ragged in both directions."""
+    _check(gen.full_grid(29, 1, seed=6), "bf16", 136, 200, (0,), 3)
