@@ -485,3 +485,14 @@ def test_k5_refusals(sp):
         km.transpose()
     assert e.value.status == -1
     km.destroy()
+
+
+@pytest.mark.parametrize("n,grid,lo", [(1, 1, 0), (12, 3, -32768), (13, 3, 32765), (49, 4, -3), (2401, 14, -32768)])
+def test_k5_map_at_the_edges(sp, n, grid, lo):
+    """Row counts around the probe's twelve rows per wave, runs of four cells cut by either end of the range."""
+    c = gen.uniform_cloud(n, grid, seed=900 + n, lo=lo)
+    ref = oc.build_kmap(c, 5, 1)
+    km = sp.build_kmap(coords_dev(c), 5, 1)
+    np.testing.assert_array_equal(km.export().cpu().numpy(), ref.M)
+    np.testing.assert_array_equal(km.export_mask().cpu().numpy().view(np.uint32), _mask_words(oc.bitmask(ref.M), 4))
+    assert km.n_pairs() == int((ref.M >= 0).sum())
