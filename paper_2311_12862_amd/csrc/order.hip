@@ -3,7 +3,7 @@
 //
 // A full sort by the 27-bit mask takes three digit passes over all rows (100k rows: 12.6 + 11.8 + 11.0 us and 8.6 us for
 // the reordered map).  What the kernels need is less: blocks of 16 and tiles of 64 to 256 rows whose masks overlap.
-// So the rows go into 128 buckets first (any corner neighbour; the edge neighbours in six pairs), one stable
+// So the rows go into 256 buckets first (any corner neighbour; the edge neighbours in six pairs; faces along z), one stable
 // counting pass whose counter matrix is small enough to be summed by every workgroup, and then
 // each stretch of 2048 places is sorted in LDS by 20 bits of the mask.  Which bits matter most: the offsets that few
 // rows have (corners 4 %, edges 20 %, faces 40 % of the rows of a LiDAR-like scan) come first, so that the rows that
