@@ -709,21 +709,35 @@ __global__ void __launch_bounds__(256) k_scatter_in_side(const int* __restrict__
   }
 }
 
-template <int V>
+// Masks of finished map rows.  One load covers two rows of 27 entries; on large maps a wave has eight in flight and
+// stores their 16 masks together (200k -> 127k rows and back: 9.5 -> 6.9 us), on small ones the
+// waves are few and one load each is quicker (10k to 30k rows: 3.4 us against 5.0).
+template <int V, int LOADS> struct MaskRows {
+  static constexpr int per_load = 64 / V, loads = LOADS, per_wave = per_load * loads;
+  static_assert(per_wave <= 64, "a lane stores the mask of at most one row");
+};
+template <int V, int LOADS>
 __global__ void __launch_bounds__(256) k_mask_from_map(const int* __restrict__ map, int n_rows,
                                                        unsigned* __restrict__ mask, Ctl* ctl) {
   __shared__ unsigned wave_cnt[4];
-  constexpr int RPW = 64 / V;
+  typedef MaskRows<V, LOADS> R;
   const int lane = threadIdx.x & 63;
-  const long long wave = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int sub = lane / V, k = lane - sub * V;
-  const long long row = wave * RPW + sub;
-  const bool active = (sub < RPW) && (row < n_rows);
-  const bool hit = active && map[row * V + k] >= 0;
-  const unsigned long long bal = __ballot(hit);
-  if (active && k == 0) mask[row] = (unsigned)((bal >> (sub * V)) & ((1ull << V) - 1ull));
+  const long long row0 = (((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * R::per_wave;
+  const long long left = n_rows - row0;  // rows of this wave (may be <= 0)
+  int v[R::loads];
+#pragma unroll
+  for (int u = 0; u < R::loads; ++u)
+    v[u] = lane < R::per_load * V && u * R::per_load + lane / V < left ? map[(row0 + u * R::per_load) * V + lane] : -1;
+  unsigned mine = 0, found = 0;
+#pragma unroll
+  for (int u = 0; u < R::loads; ++u) {
+    const unsigned long long bal = __ballot(v[u] >= 0);
+    found += (unsigned)__popcll(bal);
+    if (lane / R::per_load == u) mine = (unsigned)((bal >> (lane % R::per_load * V)) & ((1ull << V) - 1ull));
+  }
+  if (lane < R::per_wave && lane < left) mask[row0 + lane] = mine;
   if (!ctl) return;  // (uniform) otherwise count the present entries, one atomic per workgroup
-  if (lane == 0) wave_cnt[threadIdx.x >> 6] = (unsigned)__popcll(bal);
+  if (lane == 0) wave_cnt[threadIdx.x >> 6] = found;
   __syncthreads();
   if (threadIdx.x == 0) {
     const unsigned n = wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3];
@@ -927,6 +941,17 @@ int read_ctl(const Ctl* ctl, HostResult* res, hipStream_t st) {
   }
   host_ctl_release(hc);
   return status;
+}
+
+template <int V> int masks_from_map(const int* map, int64_t rows, unsigned* mask, Ctl* ctl, hipStream_t st) {
+  constexpr int kMany = V == 27 ? 8 : 1;
+  auto blocks = [&](int per_wave) { return dim3(blocks_for(ceil_div(rows, per_wave), 4)); };
+  if (rows >= 65536)
+    hipLaunchKernelGGL((k_mask_from_map<V, kMany>), blocks(MaskRows<V, kMany>::per_wave), dim3(256), 0, st, map, (int)rows, mask, ctl);
+  else
+    hipLaunchKernelGGL((k_mask_from_map<V, 1>), blocks(MaskRows<V, 1>::per_wave), dim3(256), 0, st, map, (int)rows, mask, ctl);
+  SPC_LAUNCH_CHECK();
+  return SPCONV_OK;
 }
 
 int flags_status(unsigned long long flags) {
@@ -1250,9 +1275,7 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
     hipLaunchKernelGGL(k_scatter_down3, dim3(blocks_for(ceil_div(N, 8), 4)), dim3(256), 0, st, rows, (int)N, stride,
                        tab_coarse.as<unsigned long long>(), lc_coarse, km->out_side.map.as<int>(), ctl);
     SPC_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_mask_from_map<27>), dim3(blocks_for(ceil_div(U, 2), 4)), dim3(256), 0, st,
-                       km->out_side.map.as<int>(), (int)U, km->out_side.mask.as<unsigned>(), ctl);
-    SPC_LAUNCH_CHECK();
+    SPC_TRY(masks_from_map<27>(km->out_side.map.as<int>(), U, km->out_side.mask.as<unsigned>(), ctl, st));
   } else if (!transposed) {
     km->n_in = N;
     km->n_out = needs_coarse ? U : N;
@@ -1328,17 +1351,11 @@ int kmap_build_in_side(spconv_kmap* km, hipStream_t st) {
                          km->out_side.map.as<int>(), entries, V, km->in_side.map.as<int>());
       SPC_LAUNCH_CHECK();
     }
-    const int64_t rpw = 64 / V;
-    const unsigned blocks = blocks_for(ceil_div(km->n_in, rpw), 4);
     const int* tm = km->in_side.map.as<int>();
     unsigned* tk = km->in_side.mask.as<unsigned>();
-    if (V == 27)
-      hipLaunchKernelGGL((k_mask_from_map<27>), dim3(blocks), dim3(256), 0, st, tm, (int)km->n_in, tk, (Ctl*)nullptr);
-    else if (V == 8)
-      hipLaunchKernelGGL((k_mask_from_map<8>), dim3(blocks), dim3(256), 0, st, tm, (int)km->n_in, tk, (Ctl*)nullptr);
-    else
-      hipLaunchKernelGGL((k_mask_from_map<1>), dim3(blocks), dim3(256), 0, st, tm, (int)km->n_in, tk, (Ctl*)nullptr);
-    SPC_LAUNCH_CHECK();
+    SPC_TRY(V == 27  ? masks_from_map<27>(tm, km->n_in, tk, nullptr, st)
+            : V == 8 ? masks_from_map<8>(tm, km->n_in, tk, nullptr, st)
+                     : masks_from_map<1>(tm, km->n_in, tk, nullptr, st));
   }
   km->in_side.ready = true;
   return SPCONV_OK;

@@ -5,7 +5,7 @@ import torch
 
 from oracle import sparse_conv as oc
 from workloads import generators as gen
-from _util import coords_dev
+from _util import coords_dev, make_layer, norm_err
 
 pytestmark = pytest.mark.gpu
 
@@ -496,3 +496,16 @@ def test_k5_map_at_the_edges(sp, n, grid, lo):
     np.testing.assert_array_equal(km.export().cpu().numpy(), ref.M)
     np.testing.assert_array_equal(km.export_mask().cpu().numpy().view(np.uint32), _mask_words(oc.bitmask(ref.M), 4))
     assert km.n_pairs() == int((ref.M >= 0).sum())
+
+
+@pytest.mark.parametrize("K,n_coarse", [(2, 1), (2, 9), (2, 1025), (3, 1), (3, 3), (3, 1025), (3, 65535), (3, 65545)])
+def test_stride2_masks_by_rows_of_a_wave(sp, K, n_coarse):
+    """Masks that are derived from finished map rows: whole and broken waves, on both sides of the 65,536 rows from
+    which a wave of a 3x3x3 map takes 16 rows instead of two."""
+    c = np.zeros((2 * n_coarse - 1, 4), np.int32)
+    i = np.arange(2 * n_coarse - 1)
+    c[:, 1], c[:, 3] = 4 * (i // 4000), i % 4000  # lines: their coarse points are n_coarse
+    ref = _check_kmap(sp, c, K, 2, False)
+    km = sp.build_kmap(coords_dev(c), K, 2)
+    (x32, x), (w32, w), (g32, g) = make_layer(ref.n_in, ref.n_out, 16, 16, K ** 3, "f16", n_coarse)
+    assert norm_err(sp.dgrad(g, w, km), oc.dgrad(g32, w32, ref.M, ref.n_in)) <= 2e-2  # (walks the input side and its masks)
