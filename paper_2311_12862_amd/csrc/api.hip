@@ -131,9 +131,7 @@ int resolve_config(const spconv_config* cfg, spconv_dtype dtype, spconv_config* 
 }
 
 // Flags of the plan a configuration uses, as the plan cache keys it.
-int plan_flags(const spconv_config& c, bool automatic) {
-  return ((c.flags & SPCONV_FLAG_SLABS) ? kPlanSlabs : 0) | (automatic ? kPlanOwnOrder : 0);
-}
+int plan_flags(const spconv_config& c) { return (c.flags & SPCONV_FLAG_SLABS) ? kPlanSlabs : 0; }
 
 // Which table an op walks, and with which weight indexing.
 struct OpSide {
@@ -246,18 +244,41 @@ int static_scratch(void** out) {
   return SPCONV_OK;
 }
 
-// Whether a call without a configuration sorts the rows of the side it walks (the library's own order).  The order
-// costs about 24 us + 1 us per 10k rows once per map and side.  What a call saves grows with rows x reduced x produced
+// Whether a call without a configuration sorts the rows of the side it walks (the library's own order): where `kCalls`
+// calls of this layer would save what the order costs, about 24 us + 1 us per 10k rows once per map and side.  What a
+// call saves grows with rows x reduced x produced
 // channels; measured (us, unsorted -> sorted): the LDS-resident kernel, 100k rows 64 -> 64 33 -> 23; the tiles, 100k
 // rows 64 -> 128 70 -> 34, 30k rows 128 -> 128 58 -> 27, 9k rows 256 -> 256 94 -> 37, 300k rows 96 -> 96 337 -> 127,
-// 256 -> 256 1061 -> 445; fp32, 30k rows 64 -> 64 145 -> 46.  How many calls the map will see is not known; it is
-// sorted once the calls so far would have saved two thirds of the cost (wide layers: at the first call).
-bool auto_sorted(const spconv_kmap* km, SideMap& side, int c_red, int c_cols, spconv_dtype dtype) {
-  if (km->V < 8) return false;
-  if (side.plans.count(std::make_pair(1, kPlanOwnOrder))) return true;
+// 256 -> 256 1061 -> 445; fp32, 30k rows 64 -> 64 145 -> 46.  How many calls a map will see is not known; the answer
+// depends on the map's size and the layer alone, not on what ran before, so that a call has the same kernel, the same
+// bits and the same plans whenever it is made, and one call is enough to warm a layer up.
+bool auto_sorted(int V, int64_t rows, int c_red, int c_cols, spconv_dtype dtype) {
+  if (V < 8) return false;
+  constexpr double kCalls = 3.0;
   const double unit = dtype == SPCONV_F32 ? 4e-7 : c_red <= 64 && c_cols <= 64 ? 2.3e-8 : 6e-8;
-  side.auto_saved += unit * (double)side.rows * c_red * c_cols;
-  return 1.5 * side.auto_saved >= 24.0 + 1e-4 * (double)side.rows;
+  return kCalls * unit * (double)rows * c_red * c_cols >= 24.0 + 1e-4 * (double)rows;
+}
+
+// While a stream is being captured nothing may be allocated, and what is launched runs at the replays, not now.
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) != hipSuccess) {  // (the null stream beside another stream's capture)
+    (void)hipGetLastError();
+    return true;
+  }
+  return status != hipStreamCaptureStatusNone;
+}
+
+// The plan of a call without a configuration.  sorted: the layer runs in the library's own order (auto_sorted).  Where that
+// order is not there and cannot be made - under capture, without memory - the layer runs in map order: the
+// kernel was chosen for the layer, and its sums do not depend on the rows beside a row, so the result is the same.
+int auto_plan_get(spconv_kmap* km, SideMap& side, bool sorted, hipStream_t st, IgemmPlan** out) {
+  SPC_TRY(plan_get(km, side, 0, 0, st, out));  // (the map itself: nothing is allocated or launched)
+  if (!sorted || (!side.plans.count(std::make_pair(1, kPlanOwnOrder)) && capturing(st))) return SPCONV_OK;
+  IgemmPlan* own = nullptr;
+  const int status = plan_get(km, side, 1, kPlanOwnOrder, st, &own);
+  if (status == SPCONV_OK) *out = own;
+  return status == SPCONV_ENOMEM ? SPCONV_OK : status;
 }
 
 // prepared_only: the call may not allocate.  Plans are looked up, never built (SPCONV_ENOPLAN when
@@ -285,7 +306,7 @@ int run_planes(spconv_op op, const void* src, const void* weights, spconv_kmap* 
     spconv_kmap* sub = km->groups[(size_t)g].get();
     sub->last_stream = st;
     SPC_TRY(choose_kernel(sub->V, rows, rows, c_red, c_dst, dtype, cfg, c, &ls[(size_t)g].kc));
-    SPC_TRY(plan_get(sub, sub->out_side, c.n_split, plan_flags(c, false), st, &ls[(size_t)g].plan));
+    SPC_TRY(plan_get(sub, sub->out_side, c.n_split, plan_flags(c), st, &ls[(size_t)g].plan));
     parts_total += ls[(size_t)g].plan->parts;
   }
   SPC_TRY(km->scratch.reserve((size_t)parts_total * rows * c_dst * sizeof(float)));
@@ -350,19 +371,19 @@ int run_igemm_op(spconv_op op, const void* src, const void* weights, spconv_kmap
   }
   const int c_red = os.dgrad ? C_out : C_in;
   const int c_cols = os.dgrad ? C_in : C_out;
-  const bool automatic = !cfg && !prepared_only;
-  if (automatic && auto_sorted(km, *os.side, c_red, c_cols, dtype)) c.n_split = 1;
+  const bool own_order = !cfg && auto_sorted(km->V, rows_dst, c_red, c_cols, dtype);
+  if (own_order) c.n_split = 1;
   KernelChoice kc;
   const int64_t rows_src = op == SPCONV_OP_FWD ? km->n_in : km->n_out;
   SPC_TRY(choose_kernel(km->V, rows_dst, rows_src, c_red, c_cols, dtype, cfg, c, &kc));
   IgemmPlan* plan = nullptr;
   if (prepared_only) {
     if (c.n_split > km->V) return SPCONV_EINVAL;
-    auto it = os.side->plans.find(std::make_pair((int)c.n_split, c.n_split > 0 ? plan_flags(c, false) : 0));
+    auto it = os.side->plans.find(std::make_pair((int)c.n_split, c.n_split > 0 ? plan_flags(c) : 0));
     if (it == os.side->plans.end()) return SPCONV_ENOPLAN;
     plan = it->second.get();
   } else {
-    SPC_TRY(plan_get(km, *os.side, c.n_split, plan_flags(c, automatic), st, &plan));
+    SPC_TRY(cfg ? plan_get(km, *os.side, c.n_split, plan_flags(c), st, &plan) : auto_plan_get(km, *os.side, own_order, st, &plan));
   }
   IgemmArgs a{};
   a.feats = src;
@@ -541,7 +562,7 @@ SPCONV_API int spconv_kmap_prepare(spconv_kmap* km, spconv_op op, const spconv_c
   OpSide os;
   SPC_TRY(side_for(km, op, st, &os));
   IgemmPlan* plan = nullptr;
-  return plan_get(km, *os.side, c.n_split, plan_flags(c, false), st, &plan);
+  return plan_get(km, *os.side, c.n_split, plan_flags(c), st, &plan);
 }
 
 SPCONV_API int spconv_kmap_drop_plans(spconv_kmap* km) {
@@ -580,7 +601,7 @@ SPCONV_API int spconv_kmap_export_perm(spconv_kmap* km, spconv_op op, const spco
   OpSide os;
   SPC_TRY(side_for(km, op, st, &os));
   IgemmPlan* plan = nullptr;
-  SPC_TRY(plan_get(km, *os.side, c.n_split, plan_flags(c, false), st, &plan));
+  SPC_TRY(plan_get(km, *os.side, c.n_split, plan_flags(c), st, &plan));
   if (plan->rows == 0) return SPCONV_OK;
   SPC_HIP(hipMemcpyAsync(dst, plan->perm.as<int>() + (size_t)split * plan->rows_pad,
                          (size_t)plan->rows * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
@@ -613,7 +634,7 @@ SPCONV_API int spconv_kmap_mac_units(spconv_kmap* km, spconv_op op, const spconv
   OpSide os;
   SPC_TRY(side_for(km, op, st, &os));
   IgemmPlan* plan = nullptr;
-  SPC_TRY(plan_get(km, *os.side, c.n_split, plan_flags(c, false), st, &plan));
+  SPC_TRY(plan_get(km, *os.side, c.n_split, plan_flags(c), st, &plan));
   return plan_mac_units(km, *os.side, plan, 16, st, executed);
 }
 

@@ -112,7 +112,6 @@ struct SideMap {      // one output-stationary table: rows x V
   DevBuf map;         // int32 [rows_pad][V]
   DevBuf mask;        // uint32 [rows_pad]
   bool ready = false;
-  double auto_saved = 0;  // us that calls without a configuration would have saved on a sorted map so far
   std::map<std::pair<int, int>, std::unique_ptr<IgemmPlan>> plans;  // (n_split, flags)
 };
 
