@@ -83,15 +83,15 @@ def test_bits_do_not_depend_on_what_ran_before(dtype, c_in, c_out):
     """The first call of a layer on a fresh kmap and its calls after many others, some of which sorted the rows, agree
     to the bit: neither the kernel nor the order of additions depends on the kmap's history."""
     import paper_2311_12862_amd as sp
+    import torch
     c = gen.lidar_scene(48, target_n=4000)
     km = sp.build_kmap(coords_dev(c), 3, 1)
     x, w, g = _layer_on(sp, km, c_in, c_out, dtype, 3)
-    first = sp.fwd(x, w, km).cpu().numpy(), sp.dgrad(g, w, km).cpu().numpy()
+    first = sp.fwd(x, w, km), sp.dgrad(g, w, km)
     xw, ww, gw = _layer_on(sp, km, 512, 512, "f16", 4)
     for i in range(8):
         sp.fwd(xw, ww, km)
-        again = sp.fwd(x, w, km).cpu().numpy(), sp.dgrad(g, w, km).cpu().numpy()
-        assert np.array_equal(first[0], again[0]) and np.array_equal(first[1], again[1]), i
+        assert torch.equal(first[0], sp.fwd(x, w, km)) and torch.equal(first[1], sp.dgrad(g, w, km)), i
 
 
 def test_nothing_is_sorted_under_capture():
