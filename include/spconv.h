@@ -242,7 +242,8 @@ SPCONV_API int spconv_kmap_export_mask(const spconv_kmap* km, uint32_t* dst, voi
  * masks (Sections 2.2.3, 3.2, 4.1), the offset-major map and work list of
  * wgrad.  The compute calls do this themselves on first use; calling it
  * explicitly lets the mapping cost be timed apart from the kernels
- * (Section 6.1 separates them the same way).  May synchronise the stream. */
+ * (Section 6.1 separates them the same way).  A null configuration (fwd, dgrad) prepares both orders that a call without one
+ * may choose, so that no layer's first call builds anything.  May synchronise the stream. */
 SPCONV_API int spconv_kmap_prepare(spconv_kmap* km, spconv_op op, const spconv_config* cfg_or_null, void* stream);
 
 /* Drops every cached plan (not the map itself), so that mapping can be timed again: the sorted

@@ -379,7 +379,12 @@ int run_igemm_op(spconv_op op, const void* src, const void* weights, spconv_kmap
   IgemmPlan* plan = nullptr;
   if (prepared_only) {
     if (c.n_split > km->V) return SPCONV_EINVAL;
-    auto it = os.side->plans.find(std::make_pair((int)c.n_split, c.n_split > 0 ? plan_flags(c) : 0));
+    auto it = os.side->plans.end();
+    if (own_order) it = os.side->plans.find(std::make_pair(1, kPlanOwnOrder));
+    if (it == os.side->plans.end()) {  // (without a configuration: map order where the library's own was not prepared)
+      const int n_split = cfg ? c.n_split : 0;
+      it = os.side->plans.find(std::make_pair(n_split, n_split > 0 ? plan_flags(c) : 0));
+    }
     if (it == os.side->plans.end()) return SPCONV_ENOPLAN;
     plan = it->second.get();
   } else {
@@ -545,7 +550,8 @@ SPCONV_API int spconv_kmap_prepare(spconv_kmap* km, spconv_op op, const spconv_c
   hipStream_t st = (hipStream_t)stream;
   km->last_stream = st;
   if (!km->groups.empty()) {
-    for (auto& sub : km->groups) SPC_TRY(spconv_kmap_prepare(sub.get(), op, cfg, stream));
+    const spconv_config defaults{};  // (planes run in map order unless the caller sorts them)
+    for (auto& sub : km->groups) SPC_TRY(spconv_kmap_prepare(sub.get(), op, cfg ? cfg : &defaults, stream));
     return SPCONV_OK;
   }
   spconv_config c;
@@ -562,6 +568,8 @@ SPCONV_API int spconv_kmap_prepare(spconv_kmap* km, spconv_op op, const spconv_c
   OpSide os;
   SPC_TRY(side_for(km, op, st, &os));
   IgemmPlan* plan = nullptr;
+  // without a configuration the layer decides between map order and the library's own: both are made
+  if (!cfg) return auto_plan_get(km, *os.side, km->V >= 8, st, &plan);
   return plan_get(km, *os.side, c.n_split, plan_flags(c), st, &plan);
 }
 

@@ -95,3 +95,49 @@ def test_partial_sums_beyond_the_fixed_array_are_refused():
     assert _raw_noalloc(x, w, km, 64, 64, cfg, out) == 0
     torch.cuda.synchronize()
     assert (out == 0).all()
+
+
+@pytest.mark.parametrize("c_in,c_out", [(256, 192), (32, 32)])   # sorted rows, map order
+@pytest.mark.parametrize("how", ["prepare", "fwd", "another layer"])
+def test_without_a_configuration(c_in, c_out, how):
+    other = _case(37, 3000, c_in, c_out)
+    sp.fwd(other[3], other[5], other[1])  # (loads the kernels)
+    ref, km, x32, x, w32, w = _case(35, 3000, c_in, c_out)
+    out = torch.full((km.n_out, c_out), float("nan"), dtype=torch.float16, device="cuda")
+    with pytest.raises(sp.SpconvError) as e:
+        sp.fwd_noalloc(x, w, km, out)
+    assert e.value.status == -7 and torch.isnan(out).all()
+    if how == "prepare":
+        km.prepare(sp.OP_FWD)
+    elif how == "fwd":
+        sp.fwd(x, w, km)
+    else:  # a narrow layer has made map order only: a wide one runs in it
+        sp.fwd(torch.zeros((km.n_in, 16), dtype=torch.float16, device="cuda"),
+               torch.zeros((27, 16, 16), dtype=torch.float16, device="cuda"), km)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    sp.fwd_noalloc(x, w, km, out)
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] == free
+    assert torch.equal(out, sp.fwd(x, w, km))
+    assert norm_err(out, oc.forward(x32, w32, ref.M)) <= TOL["f16"]
+
+
+def test_prepare_without_a_configuration_makes_both_orders():
+    """Once prepared, neither a wide nor a narrow layer's first call allocates device memory."""
+    ref, km, _, x, _, w = _case(36, 40000, 256, 256)
+    xn, wn = x[:, :16].contiguous(), w[:, :16, :16].contiguous()
+    out, outn = torch.empty((km.n_out, 256), dtype=torch.float16, device="cuda"), torch.empty_like(xn)
+
+    def layers(km):
+        sp.fwd(x, w, km, out=out), sp.dgrad(x, w, km, out=out)
+        sp.fwd(xn, wn, km, out=outn), sp.dgrad(xn, wn, km, out=outn)
+        torch.cuda.synchronize()
+    other = sp.build_kmap(km.out_coords(), 3, 1)
+    layers(other)  # (loads the kernels)
+    for op in (sp.OP_FWD, sp.OP_DGRAD):
+        km.prepare(op)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    layers(km)
+    assert torch.cuda.mem_get_info()[0] == free
