@@ -245,18 +245,20 @@ int static_scratch(void** out) {
 }
 
 // Whether a call without a configuration sorts the rows of the side it walks (the library's own order): where `kCalls`
-// calls of this layer would save what the order costs, about 24 us + 1 us per 10k rows once per map and side.  What a
-// call saves grows with rows x reduced x produced
-// channels; measured (us, unsorted -> sorted): the LDS-resident kernel, 100k rows 64 -> 64 33 -> 23; the tiles, 100k
-// rows 64 -> 128 70 -> 34, 30k rows 128 -> 128 58 -> 27, 9k rows 256 -> 256 94 -> 37, 300k rows 96 -> 96 337 -> 127,
-// 256 -> 256 1061 -> 445; fp32, 30k rows 64 -> 64 145 -> 46.  How many calls a map will see is not known; the answer
-// depends on the map's size and the layer alone, not on what ran before, so that a call has the same kernel, the same
-// bits and the same plans whenever it is made, and one call is enough to warm a layer up.
+// calls of this layer would save what the order costs.  How many calls a map will see is not known; the answer depends
+// on the map's size and the layer alone, not on what ran before, so that a call has the same kernel, the same bits and
+// the same plans whenever it is made, and one call is enough to warm a layer up.  Measured (us; 10k, 30k, 100k, 200k and
+// 400k rows of LiDAR-like scans, 4.2 pairs a row; a dense room with 9 saves up to twice as much):
+//   the order, first use  24, 26, 35, 51, 73
+//   unsorted -> sorted    f16 64 -> 64 13.4 -> 10.7, 16.0 -> 12.2, 30 -> 22, 52 -> 36, 98 -> 63; 64 -> 128 13.7 -> 17.3,
+//                         21.5 -> 20.9, 50 -> 34, 94 -> 51, 205 -> 89; 128 -> 128 26 -> 19, 57 -> 28, 133 -> 51, 197 -> 77,
+//                         356 -> 138; fp32 64 -> 64 47 -> 38, 68 -> 43, 166 -> 71, 312 -> 113, 599 -> 213
+// 32 -> 32 saves 0 to 3 us at every size.
 bool auto_sorted(int V, int64_t rows, int c_red, int c_cols, spconv_dtype dtype) {
   if (V < 8) return false;
   constexpr double kCalls = 3.0;
-  const double unit = dtype == SPCONV_F32 ? 4e-7 : c_red <= 64 && c_cols <= 64 ? 2.3e-8 : 6e-8;
-  return kCalls * unit * (double)rows * c_red * c_cols >= 24.0 + 1e-4 * (double)rows;
+  const double unit = dtype == SPCONV_F32 ? 2.3e-7 : c_red <= 64 ? 2e-8 : 5e-8;  // us saved per row and channel pair
+  return kCalls * unit * (double)rows * c_red * c_cols >= 23.0 + 1.3e-4 * (double)rows;
 }
 
 // While a stream is being captured nothing may be allocated, and what is launched runs at the replays, not now.
