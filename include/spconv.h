@@ -378,6 +378,8 @@ SPCONV_API int spconv_set_allocator(void* (*alloc)(size_t bytes, void* stream, v
  *   rows_src rows of the tensor that is gathered from
  *   C_red    reduced channels (C_in for forward, C_out for dgrad), C_cols the produced ones
  *   dgrad    0 / 1 (the tiled kernel's LDS layout differs)
+ * A null configuration describes what a call without one launches, the row order that it chooses included (under
+ * stream capture a call that finds its order not made yet launches the same kernel on the map's own order).
  * Returns SPCONV_EINVAL for every shape or configuration the compute calls refuse, SPCONV_OK with
  * an all-zero structure for rows = 0 (nothing is launched). */
 typedef struct spconv_launch_info {

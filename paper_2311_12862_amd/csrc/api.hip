@@ -1057,6 +1057,7 @@ SPCONV_API int spconv_describe_launch(int K, int64_t rows, int64_t rows_src, int
   const int V = K == 5 ? 25 : K * K * K;  // K = 5 launches once per 25-offset plane: the launch of one plane
   if (c.n_split > V) return SPCONV_EINVAL;
   if (rows == 0) return SPCONV_OK;  // nothing is launched
+  if (!cfg && K != 5 && auto_sorted(V, rows, C_red, C_cols, dtype)) c.n_split = 1;
   KernelChoice kc;
   SPC_TRY(choose_kernel(V, rows, rows_src, C_red, C_cols, dtype, cfg, c, &kc));
   const int tile_m = kc.kind == KernelChoice::WAVE ? 16 : kc.kind == KernelChoice::RING ? kc.ring.bm : kc.tile_m;
@@ -1079,9 +1080,7 @@ SPCONV_API int spconv_describe_launch(int K, int64_t rows, int64_t rows_src, int
     out->waves = kc.ring.threads / 64;
     out->threads = kc.ring.threads;
     out->lds_bytes = (int64_t)kc.ring.lds_bytes;
-    out->grid[0] = (int32_t)kc.ring.n_tiles;  // (launched as one row of workgroups where column tiles are dealt to the XCDs)
-    out->grid[1] = kc.ring.cols;
-    out->grid[2] = kc.ring.parts;
+    for (int i = 0; i < 3; ++i) out->grid[i] = (int32_t)kc.ring.grid[i];
   } else if (kc.kind == KernelChoice::WAVE) {
     WaveShape w;
     SPC_TRY(igemm_wave_shape(V, c.n_split, rows, rows_src, C_red, C_cols, kc.tile_n, &w));
@@ -1093,7 +1092,7 @@ SPCONV_API int spconv_describe_launch(int K, int64_t rows, int64_t rows_src, int
     out->slab_bytes = w.slab_bytes;
     out->slab_map_bytes = w.map_bytes;
     for (int i = 0; i < 3; ++i) out->grid[i] = (int32_t)w.grid[i];
-    out->xcd_ranges = ((c.flags & SPCONV_FLAG_SLABS) || rows >= (1 << 20)) && c.n_split > 0 && w.grid[0] % 8 == 0;
+    out->xcd_ranges = ((c.flags & SPCONV_FLAG_SLABS) || (cfg && rows >= (1 << 20))) && c.n_split > 0 && w.grid[0] % 8 == 0;
   } else {
     TileShape t;
     SPC_TRY(igemm_tile_shape(V, c.n_split, rows, rows_src, C_red, C_cols, kc.tile_m, kc.tile_n, dtype == SPCONV_F32,

@@ -224,7 +224,7 @@ int igemm_tile_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
 
 struct RingShape {  // igemm_ring_run (tiles loaded straight into LDS; every fp32 layer)
   int bm = 0, bn = 0, nwk = 0, piece = 0;  // tile, K groups, bytes of a row per unit
-  int threads = 0, n_cols = 0, cols = 0, parts = 0;
+  int threads = 0, n_cols = 0;
   int64_t n_tiles = 0;
   size_t lds_bytes = 0;
   unsigned grid[3] = {0, 0, 0};

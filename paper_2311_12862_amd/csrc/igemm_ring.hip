@@ -43,7 +43,7 @@ struct RingParams {
   int V, c_red, c_out, C_in, C_out, mirror;
   int heavy_first;  // sorted maps: tiles late in the order hold the most offsets; they start first
   int n_tiles;
-  int n_cols;       // column tiles dealt to the XCDs (2, 4 or 8), or 1: grid y is the column tile
+  int n_cols;       // column tiles where they are dealt to the XCDs (2, 4 or 8), or 1: grid y is the column tile
   unsigned feats_bytes, rows_pad;
 };
 
@@ -82,11 +82,10 @@ __global__ void __launch_bounds__(NWM* NWN* NWK * 64) k_ring(const RingParams p)
   const int fa = lane & 15, fg = lane >> 4;  // fragment row / column, and chunk of a sub-step
   const int part = blockIdx.z;
   int t_idx = blockIdx.x, c_idx = blockIdx.y;
-  if (p.n_cols > 1) {  // (workgroups go to the XCDs round-robin)
-    const int e = blockIdx.x & 7;
-    c_idx = e % p.n_cols;
-    t_idx = (int)(blockIdx.x >> 3) * (8 / p.n_cols) + e / p.n_cols;
-    if (t_idx >= p.n_tiles) return;
+  if (p.n_cols > 1) {  // (workgroups go to the XCDs round-robin by their linear index)
+    const unsigned at = blockIdx.y * gridDim.x + blockIdx.x, e = at & 7;
+    c_idx = (int)e % p.n_cols;
+    t_idx = (int)(at >> 3) * (8 / p.n_cols) + (int)e / p.n_cols;  // (every (tile, column) once, also in a last row that is not full)
   }
   const int tile = p.heavy_first ? p.n_tiles - 1 - t_idx : t_idx;
   const int n0 = c_idx * BN;
@@ -440,15 +439,8 @@ int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
   s->n_tiles = ceil_div(rows, s->bm);
   const int64_t cols = ceil_div(c_out, s->bn);
   s->n_cols = cols == 2 || cols == 4 || cols == 8 ? (int)cols : 1;
-  s->cols = (int)cols;
-  s->parts = ps.parts;
-  if (s->n_cols > 1) {
-    s->grid[0] = (unsigned)(8 * ceil_div(s->n_tiles, 8 / s->n_cols));
-    s->grid[1] = 1;
-  } else {
-    s->grid[0] = (unsigned)s->n_tiles;
-    s->grid[1] = (unsigned)cols;
-  }
+  s->grid[0] = (unsigned)s->n_tiles;
+  s->grid[1] = (unsigned)cols;
   s->grid[2] = (unsigned)ps.parts;
   return SPCONV_OK;
 }

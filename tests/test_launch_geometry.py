@@ -137,3 +137,29 @@ def test_degenerate_shapes_are_refused():
     assert lib.spconv_describe_launch(4, 10, 10, 64, 64, 1, None, 0, out) == -1
     assert lib.spconv_describe_launch(3, -1, 10, 64, 64, 1, None, 0, out) == -1
     assert lib.spconv_describe_launch(3, 10, 10, 64, 64, 1, None, 0, None) == -1
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+def test_calls_without_a_configuration(dtype):
+    """The launch that such a call makes: the row order that it chooses, 32-row tiles and K groups (which only these
+    calls get), and grids whose column tiles are dealt to the XCDs.  Every (tile, column) belongs to one workgroup."""
+    seen_tile_m, seen_cols, seen_sorted = set(), set(), set()
+    for rows, c_red, c_cols in itertools.product(ROWS + [300_001], CHANNELS + [264, 512], CHANNELS + [512, 1024]):
+        info = sp.describe_launch(3, rows, rows, c_red, c_cols, dtype)
+        seen_sorted.add(info.sorted)
+        if info.kernel == 1:
+            _check_kernel1(info, 27, rows, c_red, c_cols, info.sorted)
+            continue
+        assert info.tile_m in (32, 64, 128, 256) and info.threads == 64 * info.waves <= 512
+        assert 0 < info.lds_bytes <= LDS_PER_CU and info.n_tiles * info.tile_m <= info.rows_pad
+        gx, cols = info.grid[0], info.grid[1]
+        assert gx == info.n_tiles == -(-rows // info.tile_m) and cols == -(-c_cols // info.tile_n) and info.grid[2] == 1
+        seen_tile_m.add(info.tile_m)
+        seen_cols.add(cols)
+        if cols in (2, 4, 8) and gx < 2000:  # (the kernel's arithmetic, from the linear index)
+            at = [(i >> 3) * (8 // cols) + (i & 7) // cols for i in range(gx * cols)]
+            assert sorted((t, (i & 7) % cols) for i, t in enumerate(at)) == list(itertools.product(range(gx), range(cols)))
+    assert seen_sorted == {0, 1} and {2, 4, 8} <= seen_cols
+    assert seen_tile_m == ({32, 64, 128, 256} if dtype == torch.float16 else {64})
+    assert not sp.describe_launch(5, 300_000, 300_000, 256, 256, dtype).sorted   # (planes run in map order)
+    assert not sp.describe_launch(1, 300_000, 300_000, 256, 256, dtype).sorted
