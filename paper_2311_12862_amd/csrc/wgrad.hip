@@ -439,7 +439,8 @@ __global__ void __launch_bounds__(256) k_wgrad_reduce(const float* __restrict__ 
 
 // Tiles by channels: as wide as the layer, so that a pair's rows are gathered once.  Beyond 128 channels only
 // where there are pairs enough: a 256 x 256 tile is one workgroup per CU, with a partial tile of 256 KB each (85k pairs,
-// 256 -> 256: 128 x 128 tiles 37 us, of which 6 for the reduction).  weight: sqrt(time of a pair / time of a partial tile), from
+// 256 -> 256: 128 x 128 tiles 37 us, of which 6 for the reduction), or tiles so many that they fill the GPU anyway (421k
+// pairs 768 -> 768: 717 us, 128 x 128 tiles 1005 us; 38k pairs: 132, 129).  weight: sqrt(time of a pair / time of a partial tile), from
 // sweeps of the piece length (60k-row scan 128 -> 128, 512 / 1024 / 2048 pairs: 40 / 35 / 36 us; 100k rows
 // 64 -> 64, 1024 / 2048 / 4096: 27 / 22 / 23 us).
 #define SPC_WGRAD_16(X) X(32, 32, 1, 1, 4, 4) X(64, 64, 1, 1, 4, 3) X(96, 96, 2, 2, 1, 3) X(128, 128, 2, 2, 1, 3) X(256, 256, 2, 4, 1, 4)
@@ -456,14 +457,21 @@ TilePick pick_tile(int C_in, int C_out, bool f32, int64_t pairs) {
   if (c <= 32) return {32, 2, 1.1f};
   if (c <= 64) return {64, 1, 0.75f};
   if (c <= 96) return {96, 3, 0.65f};
-  if (c <= 128 || pairs < (1 << 19)) return {128, 3, 0.6f};
+  if (c <= 128 || (c <= 384 && pairs < (1 << 19))) return {128, 3, 0.6f};
   return {256, 1, 0.4f};
 }
+// As many pieces as the GPU holds at once, where that leaves each offset a few: wide layers have so many tiles that every
+// piece comes in several rounds anyway, and one piece per offset would wait for the longest one (421k pairs, of
+// which a quarter at the centre offset: fp32 256 -> 256 1650 us at one piece per offset, 548 us at 2,900 pairs a piece;
+// f16 640 -> 640 1528 and 635 us).
 Split split_for(const TilePick& t, int64_t tiles, int V, int64_t pairs) {
   Split s{};
   s.weight = t.weight / sqrtf((float)tiles);
   s.unit = 64;
-  const int64_t g = std::max<int64_t>(1, std::min<int64_t>({256 * t.per_cu / tiles - V, (int64_t)(s.weight * sqrt((double)pairs)) + 2, ceil_div(pairs, s.unit)}));
+  const int64_t at_once = 256 * t.per_cu / tiles;
+  int64_t g = std::min<int64_t>((int64_t)(s.weight * sqrt((double)pairs)) + 2, ceil_div(pairs, s.unit));
+  if (at_once >= 3 * V) g = std::min<int64_t>(g, at_once - V);
+  g = std::max<int64_t>(g, 1);
   s.pieces = (int)g + V;
   return s;
 }

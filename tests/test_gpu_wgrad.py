@@ -37,3 +37,33 @@ def test_few_pairs(dtype, ch, n):
 def test_wide_tile():
     """The 256 x 256 tile (it needs half a million pairs to be chosen), ragged in both directions."""
     _check(gen.full_grid(29, 1, seed=6), "bf16", 136, 200, (0,), 3)
+
+
+@pytest.mark.parametrize("dtype,c_in,c_out", [("f16", 640, 512), ("bf16", 400, 776), ("f32", 320, 256)])
+def test_very_wide_layers(dtype, c_in, c_out):
+    _check(gen.lidar_scene(52, target_n=1500), dtype, c_in, c_out, (0, 777), c_in)
+
+
+@pytest.mark.parametrize("dtype,ch", [("f16", 768), ("f32", 256)])
+def test_very_wide_layers_keep_their_pieces_short(dtype, ch):
+    """However many tiles a layer has, its longest offset (a quarter of all pairs here) is not left to one workgroup per
+    tile: that took two to three times as long as pieces of 4,096 pairs."""
+    import torch
+    import paper_2311_12862_amd as sp
+    from _util import TORCH_DT
+    c = gen.lidar_scene(53, target_n=100_000)
+    km = sp.build_kmap(coords_dev(c), 3, 1)
+    x, g = (torch.randn(len(c), ch, device="cuda").to(TORCH_DT[dtype]) for _ in range(2))
+    dw = torch.empty(27, ch, ch, device="cuda")
+
+    def ms(cfg):
+        best = 1e9
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            sp.wgrad(x, g, km, cfg, out=dw)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+    assert ms(None) <= 1.4 * ms(sp.Config(wgrad_pairs=4096))
