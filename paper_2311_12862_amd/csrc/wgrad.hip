@@ -457,7 +457,9 @@ TilePick pick_tile(int C_in, int C_out, bool f32, int64_t pairs) {
   if (c <= 32) return {32, 2, 1.1f};
   if (c <= 64) return {64, 1, 0.75f};
   if (c <= 96) return {96, 3, 0.65f};
-  if (c <= 128 || (c <= 384 && pairs < (1 << 19))) return {128, 3, 0.6f};
+  // (a 256-wide tile of a layer with one narrow side multiplies mostly padding: 2.7M pairs 16 -> 256 367 us, with 128 x
+  // 128 tiles 280; 64 -> 256 381 and 304; 96 -> 256 373 and 386)
+  if (c <= 128 || std::min(C_in, C_out) <= 64 || (c <= 384 && pairs < (1 << 19))) return {128, 3, 0.6f};
   return {256, 1, 0.4f};
 }
 // As many pieces as the GPU holds at once, where that leaves each offset a few: wide layers have so many tiles that every

@@ -39,6 +39,12 @@ def test_wide_tile():
     _check(gen.full_grid(29, 1, seed=6), "bf16", 136, 200, (0,), 3)
 
 
+@pytest.mark.parametrize("c_in,c_out", [(24, 200), (136, 64), (400, 16), (72, 136)])
+def test_uneven_channels_with_many_pairs(c_in, c_out):
+    """One narrow side, at the pair counts of the 256 x 256 tile."""
+    _check(gen.full_grid(29, 1, seed=7), "f16", c_in, c_out, (0,), c_in)
+
+
 @pytest.mark.parametrize("dtype,c_in,c_out", [("f16", 640, 512), ("bf16", 400, 776), ("f32", 320, 256)])
 def test_very_wide_layers(dtype, c_in, c_out):
     _check(gen.lidar_scene(52, target_n=1500), dtype, c_in, c_out, (0, 777), c_in)
