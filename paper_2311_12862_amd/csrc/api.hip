@@ -694,6 +694,47 @@ SPCONV_API int spconv_wgrad(const void* feats, const void* dout, spconv_kmap* km
   return wgrad_run(km, *pl, c.wgrad_pairs, feats, dout, C_in, C_out, dtype, dweights, st);
 }
 
+}  // extern "C"
+
+namespace {
+// What the tuners try for fwd / dgrad on one map structure (n_split, or fetch-on-demand): every kernel and tile, and
+// the configuration that names neither, where that is a kernel of its own (tiles loaded straight into LDS).
+std::vector<spconv_config> gemm_candidates(spconv_kmap* km, spconv_op op, int C_in, int C_out, spconv_dtype dtype, int n_split,
+                                           bool fod) {
+  const bool f32 = dtype == SPCONV_F32;
+  const int c_red = op == SPCONV_OP_DGRAD ? C_out : C_in, c_dst = op == SPCONV_OP_DGRAD ? C_in : C_out;
+  std::vector<spconv_config> cands;
+  for (int tm : {64, 128, 256}) {
+    if (fod ? (tm == 256 || (f32 && tm != 64)) : (f32 && tm != 64)) continue;
+    spconv_config c{};
+    c.n_split = fod ? 0 : n_split;
+    c.tile_m = tm;
+    c.kernel = fod ? 3 : 2;
+    cands.push_back(c);
+  }
+  if (f32 || fod) return cands;
+  for (int tn : {64, 32, 16}) {
+    if (tn >= 2 * c_dst && tn > 16) continue;
+    if (igemm_wave_pick_bn(km->V, n_split, c_red, c_dst, tn, nullptr) == 0) continue;
+    spconv_config c{};
+    c.n_split = n_split;
+    c.kernel = 1;
+    c.tile_n = tn;
+    cands.push_back(c);
+  }
+  spconv_config any{}, c;
+  any.n_split = n_split;
+  const int64_t rows_out = op == SPCONV_OP_DGRAD ? km->n_in : km->n_out, rows_src = op == SPCONV_OP_DGRAD ? km->n_out : km->n_in;
+  KernelChoice kc;
+  if (resolve_config(&any, dtype, &c) == SPCONV_OK && choose_kernel(km->V, rows_out, rows_src, c_red, c_dst, dtype, &any, c, &kc) == SPCONV_OK &&
+      kc.kind == KernelChoice::RING)
+    cands.push_back(any);
+  return cands;
+}
+}  // namespace
+
+extern "C" {
+
 SPCONV_API int spconv_tune(spconv_kmap* km, int C_in, int C_out, spconv_dtype dtype, spconv_op op, int layers_sharing_kmap,
                 spconv_config* best, float* best_us, void* stream) {
   StreamScope scope((hipStream_t)stream);
@@ -733,34 +774,11 @@ SPCONV_API int spconv_tune(spconv_kmap* km, int C_in, int C_out, spconv_dtype dt
       cands.push_back(c);
     }
   } else {
-    const int tiles[3] = {64, 128, 256};
-    const int c_red = op == SPCONV_OP_DGRAD ? C_out : C_in, c_dst = op == SPCONV_OP_DGRAD ? C_in : C_out;
-    if (fod_supported(km, op == SPCONV_OP_DGRAD, C_in, C_out, dtype))
-      for (int tm : {64, 128}) {  // the fetch-on-demand dataflow (its mapping: the pair lists)
-        if (dtype == SPCONV_F32 && tm != 64) continue;
-        spconv_config c{};
-        c.kernel = 3;
-        c.tile_m = tm;
-        cands.push_back(c);
-      }
-    for (int s = 0; s <= kMaxSplit && s <= km->V; ++s) {  // (a part needs at least one offset)
-      for (int t = 0; t < (dtype == SPCONV_F32 ? 1 : 3); ++t) {
-        spconv_config c{};
-        c.n_split = s;
-        c.tile_m = tiles[t];
-        c.kernel = 2;
-        cands.push_back(c);
-      }
-      if (dtype == SPCONV_F32) continue;
-      for (int tn : {64, 32, 16}) {
-        if (tn >= 2 * c_dst && tn > 16) continue;
-        if (igemm_wave_pick_bn(km->V, s, c_red, c_dst, tn, nullptr) == 0) continue;
-        spconv_config c{};
-        c.n_split = s;
-        c.kernel = 1;
-        c.tile_n = tn;
-        cands.push_back(c);
-      }
+    if (fod_supported(km, op == SPCONV_OP_DGRAD, C_in, C_out, dtype))  // (its mapping: the pair lists)
+      cands = gemm_candidates(km, op, C_in, C_out, dtype, 0, true);
+    for (int n = 0; n <= kMaxSplit && n <= km->V; ++n) {  // (a part needs at least one offset)
+      const auto more = gemm_candidates(km, op, C_in, C_out, dtype, n, false);
+      cands.insert(cands.end(), more.begin(), more.end());
     }
   }
   int status = SPCONV_OK;
@@ -854,17 +872,19 @@ struct GroupTimer {
     *us = best * 1000.f;
     return SPCONV_OK;
   }
-  // time to build the plan of c from scratch, in microseconds (best of two)
-  int mapping_us(spconv_op op, const spconv_config& c, float* us) {
+  // time to build the plans of cfgs from scratch, in microseconds (best of two)
+  int mapping_us(spconv_op op, const std::vector<spconv_config>& cfgs, float* us) {
     float best = 1e30f;
     for (int rep = 0; rep < 2; ++rep) {
       SPC_TRY(spconv_kmap_drop_plans(km));
       (void)hipEventRecord(e0, st);
-      if (op == SPCONV_OP_WGRAD) {
-        PairList* pl = nullptr;
-        SPC_TRY(pair_list_get(km, st, &pl));
-      } else {
-        SPC_TRY(spconv_kmap_prepare(km, op, &c, st));
+      for (const spconv_config& c : cfgs) {
+        if (op == SPCONV_OP_WGRAD) {
+          PairList* pl = nullptr;
+          SPC_TRY(pair_list_get(km, st, &pl));
+        } else {
+          SPC_TRY(spconv_kmap_prepare(km, op, &c, st));
+        }
       }
       best = std::min(best, elapsed_ms());
     }
@@ -925,7 +945,8 @@ SPCONV_API int spconv_tune_group(spconv_kmap* km, const spconv_layer_shape* laye
   // splits (choices 0..max_split), or the fetch-on-demand dataflow on the pair lists (the last choice).
   const int n_choices = max_split + 2, fod_choice = max_split + 1;
   // fwd / dgrad: for every map structure, the fastest kernel and tile of each layer shape, plus the
-  // mapping time of every plan (structure, tile height) those choices need, paid once per group
+  // mapping time of what those choices need, paid once per group: implicit GEMM walks one plan per
+  // structure whatever the kernel, fetch-on-demand one list of work items per tile height
   auto tune_op = [&](spconv_op op, std::vector<SplitChoice>* out) -> int {
     out->assign(n_choices, SplitChoice{});
     for (int s = 0; s < n_choices; ++s) {
@@ -938,29 +959,10 @@ SPCONV_API int spconv_tune_group(spconv_kmap* km, const spconv_layer_shape* laye
       SplitChoice& ch = (*out)[s];
       ch.cfg.resize(shapes.size());
       float total = 0.f;
-      std::vector<int> plan_keys;  // tile heights whose plans are used (16 = kernel 1)
+      std::vector<spconv_config> plans;
       for (size_t j = 0; j < shapes.size(); ++j) {
         const int ci = shapes[j].first, co = shapes[j].second;
-        const int c_red = op == SPCONV_OP_DGRAD ? co : ci, c_dst = op == SPCONV_OP_DGRAD ? ci : co;
-        std::vector<spconv_config> cands;
-        for (int tm : {64, 128, 256}) {
-          if (fod ? (tm == 256 || (dtype == SPCONV_F32 && tm != 64)) : (dtype == SPCONV_F32 && tm != 64)) continue;
-          spconv_config c{};
-          c.n_split = fod ? 0 : s;
-          c.tile_m = tm;
-          c.kernel = fod ? 3 : 2;
-          cands.push_back(c);
-        }
-        if (dtype != SPCONV_F32 && !fod)
-          for (int tn : {64, 32, 16}) {
-            if (tn >= 2 * c_dst && tn > 16) continue;
-            if (igemm_wave_pick_bn(km->V, s, c_red, c_dst, tn, nullptr) == 0) continue;
-            spconv_config c{};
-            c.n_split = s;
-            c.kernel = 1;
-            c.tile_n = tn;
-            cands.push_back(c);
-          }
+        const auto cands = gemm_candidates(km, op, ci, co, dtype, s, fod);
         float best = 1e30f;
         for (const auto& c : cands) {
           float us = 0.f;
@@ -971,18 +973,13 @@ SPCONV_API int spconv_tune_group(spconv_kmap* km, const spconv_layer_shape* laye
           }
         }
         total += best * (float)count[j];
-        const int key = ch.cfg[j].kernel == 1 ? 16 : ch.cfg[j].tile_m;
-        if (std::find(plan_keys.begin(), plan_keys.end(), key) == plan_keys.end()) plan_keys.push_back(key);
+        const spconv_config& picked = ch.cfg[j];
+        if (std::none_of(plans.begin(), plans.end(), [&](const spconv_config& c) { return !fod || c.tile_m == picked.tile_m; }))
+          plans.push_back(picked);
       }
-      for (int key : plan_keys) {
-        spconv_config c{};
-        c.n_split = fod ? 0 : s;
-        c.kernel = fod ? 3 : (key == 16 ? 1 : 2);
-        c.tile_m = key == 16 ? 0 : key;
-        float us = 0.f;
-        SPC_TRY(t.mapping_us(op, c, &us));
-        total += us;
-      }
+      float us = 0.f;
+      SPC_TRY(t.mapping_us(op, plans, &us));
+      total += us;
       ch.us = total;
     }
     return SPCONV_OK;
@@ -1024,7 +1021,7 @@ SPCONV_API int spconv_tune_group(spconv_kmap* km, const spconv_layer_shape* laye
       spconv_config c{};
       c.wgrad_pairs = pairs;
       float sum = 0.f, us = 0.f;
-      SPC_TRY(t.mapping_us(SPCONV_OP_WGRAD, c, &us));
+      SPC_TRY(t.mapping_us(SPCONV_OP_WGRAD, {c}, &us));
       sum += us;
       for (size_t j = 0; j < shapes.size(); ++j) {
         SPC_TRY(t.kernel_us(SPCONV_OP_WGRAD, shapes[j].first, shapes[j].second, c, &us));

@@ -333,6 +333,35 @@ def test_tune_returns_a_valid_config(sp, cloud):
     assert norm_err(sp.fwd(x, w, km, best), oc.forward(x32, w32, ref.M)) <= TOL["f16"]
 
 
+def test_tuners_offer_the_default_kernel_of_wide_layers(sp):
+    """A wide layer's tuned configuration is not slower than the ones that name neither a kernel nor a tile (tiles
+    loaded straight into LDS, about twice as fast here as every kernel that the tuners name), and computes the layer."""
+    c = gen.lidar_scene(79, target_n=20000)
+    km = sp.build_kmap(coords_dev(c), 3, 1)
+    x, w = torch.randn(len(c), 256, device="cuda").half(), (torch.randn(27, 256, 256, device="cuda") / 40).half()
+    out = torch.empty_like(x)
+
+    def ms(cfg):
+        sp.fwd(x, w, km, cfg, out=out)
+        best = 1e9
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                sp.fwd(x, w, km, cfg, out=out)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+    best, _ = sp.tune(km, 256, 256, torch.float16, sp.OP_FWD, 1000)
+    f, _, _, _ = sp.tune_group(km, [(256, 256)] * 50, torch.float16)
+    plain = min(ms(_cfg(sp, s)) for s in range(5))
+    want = sp.fwd(x, w, km, _cfg(sp, 1)).double().cpu().numpy()
+    for cfg in (best, f[0]):
+        assert ms(cfg) <= 1.25 * plain, repr(cfg)
+        assert norm_err(sp.fwd(x, w, km, cfg), want) <= 2e-3
+
+
 def test_layer_on_a_pending_asynchronous_kmap(sp, cloud):
     """fwd / dgrad / wgrad may run before the build's status has been read (wgrad then sizes its
     work list from the bound n_out * 27)."""
