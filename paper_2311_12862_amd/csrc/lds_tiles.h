@@ -35,10 +35,12 @@ __device__ __forceinline__ u32x4 rsrc_of(const void* base, unsigned bytes) {
 }
 // 64 lanes x 16 bytes from a buffer into LDS: lane l fills lds + 16 l, zeros where its offset is out of range.
 // (The five wait states that a vector-memory instruction needs behind a vector instruction that writes one of
-// its scalar registers are part of it.)
+// its scalar registers are part of it.  m0 is a reserved register, which clobber lists do not take; no instruction that
+// is generated for these kernels uses it: LDS accesses need it up to gfx8 only.)
 __device__ __forceinline__ void load_to_lds(u32x4 rsrc, unsigned voff, unsigned soff, unsigned lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc),
-               "s"(soff));
+               "s"(soff)
+               : "memory");
 }
 // Own loads have landed and own LDS reads are done; after the barrier everyone's.
 __device__ __forceinline__ void wait_loads_and_sync() {
