@@ -92,17 +92,21 @@ typedef struct spconv_kmap spconv_kmap; /* opaque */
 /* Dataflow parameters (the design space of Section 4.1).  Zero-initialise for
  * the defaults.  A null configuration leaves all of them to the library, the row order included:
  * spconv_fwd and spconv_dgrad then visit the rows in an order of the library's own (similar
- * neighbour masks together, built once per kmap and side) where the layers that ran on the kmap
- * so far are wide or many enough to pay for it.
+ * neighbour masks together, built once per kmap and side by the first such call) where the layer is wide
+ * enough for the map's size that a few calls of it pay for the order.  That, and the kernel, depend
+ * on the map's size and the layer alone, never on earlier calls: the same call gives the same bits
+ * whenever it is made.  Under stream capture the order is used where it exists and never made; the
+ * result is the same without it.
  *   n_split     0: unsorted implicit GEMM, rows in map order, one pass.
  *               s >= 1 (at most 4 and at most K^3): the K^3 offsets are cut into s contiguous
  *               ranges [floor(i*V/s), floor((i+1)*V/s)); in each range the
  *               rows are visited in ascending order of that range's bitmask
  *               bits (stable), and for s > 1 the fp32 partial sums of the
  *               ranges are added by a reduction kernel.
- *   kernel      which fwd / dgrad kernel runs (F32 has one implicit-GEMM kernel,
- *               which runs for 0, 1 and 2, and one fetch-on-demand kernel with
- *               tiles of 64 pairs x 64 channels for 3):
+ *   kernel      which fwd / dgrad kernel runs (F32 has one implicit-GEMM kernel for
+ *               0, 1 and 2 - workgroup tiles loaded straight into LDS, or plain
+ *               64 x 64 tiles where a tensor exceeds 32-bit byte offsets - and one
+ *               fetch-on-demand kernel with tiles of 64 pairs x 64 channels for 3):
  *               1: weights of a split resident in LDS, one wave per 16-row
  *                  block (needs reduced channels <= 128 and the split's
  *                  weight slices for tile_n channels to fit in LDS, else
@@ -116,11 +120,16 @@ typedef struct spconv_kmap spconv_kmap; /* opaque */
  *                  spent on absent neighbours; results are the same up to
  *                  the order of the fp32 additions (which varies from call to
  *                  call).  Needs n_split = 0, else SPCONV_EINVAL;
- *               0: never 3; 1 where it fits and either the output is at most two
- *                  column tiles wide or (column tiles x reduced channels x
- *                  rows) is small, else 2.
+ *               0: never 3; 1 where it fits and the output is at most two column
+ *                  tiles wide (sorted maps: and at most 64 channels are reduced), or
+ *                  on unsorted maps (column tiles x reduced channels x rows) is
+ *                  small; else workgroup tiles: those of 2 where tile_m or tile_n is
+ *                  given, else tiles whose operands are loaded straight into LDS and
+ *                  whose shape the library picks.
  *   tile_m      output rows per workgroup of kernel 2: 64, 128 or 256 (0 = 64 or
- *               128, from the row count and the channel counts);
+ *               128, from the row count and the channel counts; F32: 64).  A kernel
+ *               that picks its own shape has 64, 128 or 256 as well, and 32 only
+ *               in calls without a configuration;
  *               pairs per workgroup of kernel 3: 64 or 128 (0 = 64; F32: 64 only).
  *   tile_n      output channels per workgroup: 16, 32, 64 (kernel 1) or 32, 64,
  *               128 (kernels 2 and 3); 0 = chosen from the channel counts (and,
@@ -133,7 +142,7 @@ typedef struct spconv_kmap spconv_kmap; /* opaque */
  *               chip's eight L2 domains a contiguous range of that order, so that its gathers
  *               stay within about one eighth of the input.  Any visiting order gives the same
  *               result; this one trades some lock-step redundancy for less traffic beyond
- *               L2.  Without the flag the library uses slabs from 2^20 rows on.
+ *               L2.  Without the flag a configuration's sorted maps have slabs from 2^20 rows on.
  */
 typedef struct spconv_config {
   int32_t n_split;
@@ -254,14 +263,15 @@ SPCONV_API int spconv_kmap_drop_plans(spconv_kmap* km);
 
 /* Permutation of split `split` of the cached plan of (op, cfg): int32
  * [n_rows] with row r of the sorted order = original row perm[r] (identity
- * for n_split = 0).  For tests of the sort invariants. */
+ * for n_split = 0, which a null configuration stands for here).  For tests of the sort invariants. */
 SPCONV_API int spconv_kmap_export_perm(spconv_kmap* km, spconv_op op, const spconv_config* cfg_or_null,
                             int split, int32_t* dst, void* stream);
 
 /* Executed and effective MAC units (units of C_in*C_out MACs) of op under cfg
  * in this library's lock-step model: a block of 16 consecutive rows of the
  * visiting order (one MFMA block) pays for offset k whenever one of them has
- * neighbour k (the quantity plotted in Section 4.1).  Synchronises the stream. */
+ * neighbour k (the quantity plotted in Section 4.1).  A null configuration counts the map's own
+ * order (n_split = 0).  Synchronises the stream. */
 SPCONV_API int spconv_kmap_mac_units(spconv_kmap* km, spconv_op op, const spconv_config* cfg_or_null,
                           int64_t* executed, int64_t* effective, void* stream);
 
@@ -281,7 +291,9 @@ SPCONV_API int spconv_fwd(const void* feats, const void* weights, spconv_kmap* k
  * spconv_fwd, but the call makes no allocation of any kind (no hipMalloc / hipFree, no allocator
  * callback, no pool):
  *   - the plan of cfg must exist already, made by spconv_kmap_prepare(km, SPCONV_OP_FWD, cfg) or by
- *     an earlier spconv_fwd with the same cfg; otherwise SPCONV_ENOPLAN.  kernel = 3 (fetch on
+ *     an earlier spconv_fwd with the same cfg; otherwise SPCONV_ENOPLAN.  (cfg null: by any
+ *     earlier call without a configuration; where only another layer's made the plans, this
+ *     layer's kernel may run in map order, with the same result.)  kernel = 3 (fetch on
  *     demand) is refused with SPCONV_EINVAL;
  *   - the fp32 partial sums of n_split >= 2 (n_split * n_out * C_out * 4 bytes) go to a fixed
  *     array of SPCONV_NOALLOC_SCRATCH_BYTES that every GPU the library runs on holds until the
@@ -313,7 +325,8 @@ SPCONV_API int spconv_wgrad(const void* feats, const void* dout, spconv_kmap* km
  * / layers_sharing_kmap (layers that use the same maps form a group and share
  * the mapping cost, Section 4.2).  Blocking: allocates scratch tensors, runs
  * and times every candidate on `stream`.  best receives the winner;
- * best_us (may be NULL) its time in microseconds. */
+ * best_us (may be NULL) its time in microseconds.  (Candidates are configurations: the library's own
+ * row order, which only calls without one use, is not among them.) */
 SPCONV_API int spconv_tune(spconv_kmap* km, int C_in, int C_out, spconv_dtype dtype, spconv_op op,
                 int layers_sharing_kmap, spconv_config* best, float* best_us, void* stream);
 
@@ -387,7 +400,8 @@ typedef struct spconv_launch_info {
   int32_t parts;          /* max(1, n_split) */
   int32_t sorted;         /* n_split >= 1: rows are visited through a permutation */
   int32_t tile_m, tile_n; /* rows per block / tile, output channels per workgroup */
-  int32_t k_steps;        /* kernel 1: 32-channel steps per offset; kernel 2: channels per LDS stage */
+  int32_t k_steps;        /* kernel 1: 32-channel steps per offset; kernel 2: channels per LDS stage (tiles loaded
+                             straight into LDS: the channels of a gathered piece) */
   int32_t waves, threads; /* per workgroup */
   int32_t grid[3];        /* kernel 1: workgroups per slice, column tiles, parts; kernel 2: tiles, column tiles, parts */
   int32_t xcd_ranges;     /* kernel 1: blocks are dealt to the XCDs as eight contiguous ranges */

@@ -262,7 +262,7 @@ int igemm_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan,
 // ---- igemm_ring.hip
 int igemm_ring_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan, const IgemmArgs& a, const RingShape& s,
                    hipStream_t st);
-// ---- igemm_wave.hip (weights resident in LDS; plan tile_m must be 16)
+// ---- igemm_wave.hip (weights resident in LDS)
 int igemm_wave_pick_bn(int V, int n_split, int c_red, int c_out, int tile_n, int* waves_out);
 int igemm_wave_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan, const IgemmArgs& a,
                    hipStream_t st);
