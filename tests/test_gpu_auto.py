@@ -130,3 +130,41 @@ def test_nothing_is_sorted_under_capture():
         torch.cuda.synchronize()
         assert torch.equal(y, want[0]) and torch.equal(d, want[1]), i
         assert torch.equal(sp.fwd(x, w, km), want[0]), i
+
+
+def test_without_memory_for_the_order():
+    """Where the order cannot be allocated the layer runs in map order, with the same bits, and sorts later."""
+    import gc
+    import paper_2311_12862_amd as sp
+    import torch
+    gc.collect()
+    held, refuse = {}, []
+
+    def alloc(n, stream):
+        if refuse:
+            refuse.append(n)
+            return 0
+        t = torch.empty(max(n, 1), dtype=torch.uint8, device="cuda")
+        held[t.data_ptr()] = t
+        return t.data_ptr()
+
+    sp.set_allocator(alloc, lambda ptr, stream: held.pop(ptr, None))
+    try:
+        c = gen.lidar_scene(50, target_n=5000)
+        km = sp.build_kmap(coords_dev(c), 3, 1)
+        x, w, g = _layer_on(sp, km, 256, 256, "f16", 7)
+        refuse.append("start")
+        y, d = sp.fwd(x, w, km), sp.dgrad(g, w, km)
+        assert len(refuse) > 1
+        refuse.clear()
+        have = len(held)
+        assert torch.equal(y, sp.fwd(x, w, km)) and torch.equal(d, sp.dgrad(g, w, km))
+        assert len(held) > have
+        torch.cuda.synchronize()
+        km.destroy()
+        assert not held
+    finally:
+        refuse.clear()
+        gc.collect()
+        torch.cuda.synchronize()
+        sp.set_allocator(None, None)
