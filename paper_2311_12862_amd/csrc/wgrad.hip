@@ -37,6 +37,7 @@ struct Split {
   int length;    // pairs of a piece as asked for, or 0: chosen by
   float weight;  // sqrt(time of a pair in a piece / time of a partial tile), and at least
   int unit;      // so many
+  int per_round;  // pieces that make one workgroup per CU
 };
 
 struct WgradParams {
@@ -54,9 +55,17 @@ constexpr unsigned kNoRow = 0xFFFFC000u;  // beyond every buffer
 
 // Pairs per piece; computed by every workgroup, as the pair count may only be known on the device.
 // g pieces take time ~ pairs / g (a workgroup's serial part) + g * (a tile written and read): least at g ~ sqrt(pairs).
+// Long pieces then go down to whole rounds of one workgroup per CU, each offset's last piece counted: two workgroups of a CU
+// gather at half the rate each, and the launch waits for the CUs that have one more (421k pairs 128 -> 128, 410 pieces 47.2 us,
+// 249 pieces 40.9; 256 -> 128, 604 workgroups 80.0, 510 69.1).  Not where that takes too many of them (271k pairs 256 ->
+// 128, 496 workgroups 47.9 us, 256 57.1), nor where pieces are short, so that their start is what counts (127k pairs 256
+// -> 128: 32.9 us, in one round 35.3).
 __device__ __forceinline__ int split_length(const Split& s, int pairs, int V) {
   if (s.length > 0) return s.length;
-  const int g = min(s.pieces - V, (int)(s.weight * sqrtf((float)pairs)) + 1);
+  int g = min(s.pieces - V, (int)(s.weight * sqrtf((float)pairs)) + 1);
+  const int whole = (g + V) / s.per_round * s.per_round - V;
+  const int least = s.per_round == 256 ? g / 2 : g - g / 4;  // (a single column of tiles: rounds are finer)
+  if (whole >= least && pairs / g >= 900) g = whole;
   return max(s.unit, (pairs + g - 1) / g);
 }
 // Lane k < V of a wave: the pieces of the offsets before k, and of k.
@@ -442,7 +451,8 @@ __global__ void __launch_bounds__(256) k_wgrad_reduce(const float* __restrict__ 
 // 256 -> 256: 128 x 128 tiles 37 us, of which 6 for the reduction), or tiles so many that they fill the GPU anyway (421k
 // pairs 768 -> 768: 717 us, 128 x 128 tiles 1005 us; 38k pairs: 132, 129).  weight: sqrt(time of a pair / time of a partial tile), from
 // sweeps of the piece length (60k-row scan 128 -> 128, 512 / 1024 / 2048 pairs: 40 / 35 / 36 us; 100k rows
-// 64 -> 64, 1024 / 2048 / 4096: 27 / 22 / 23 us).
+// 64 -> 64, 1024 / 2048 / 4096: 27 / 22 / 23 us).  32-wide tiles stay within one round (2.7M pairs 32 -> 32: 75 us, in two
+// rounds 78; 271k pairs: 10.8, 12.3).
 #define SPC_WGRAD_16(X) X(32, 32, 1, 1, 4, 4) X(64, 64, 1, 1, 4, 3) X(96, 96, 2, 2, 1, 3) X(128, 128, 2, 2, 1, 3) X(256, 256, 2, 4, 1, 4)
 #define SPC_WGRAD_32(X) X(32, 32, 1, 1, 4, 3) X(64, 64, 1, 1, 4, 2)
 
@@ -454,7 +464,7 @@ struct TilePick {
 TilePick pick_tile(int C_in, int C_out, bool f32, int64_t pairs) {
   const int c = std::max(C_in, C_out);
   if (f32) return c <= 32 ? TilePick{32, 2, 1.1f} : TilePick{64, 2, 0.9f};
-  if (c <= 32) return {32, 2, 1.1f};
+  if (c <= 32) return {32, 1, 1.1f};
   if (c <= 64) return {64, 1, 0.75f};
   if (c <= 96) return {96, 3, 0.65f};
   // (a 256-wide tile of a layer with one narrow side multiplies mostly padding: 2.7M pairs 16 -> 256 367 us, with 128 x
@@ -470,6 +480,7 @@ Split split_for(const TilePick& t, int64_t tiles, int V, int64_t pairs) {
   Split s{};
   s.weight = t.weight / sqrtf((float)tiles);
   s.unit = 64;
+  s.per_round = (int)std::max<int64_t>(1, 256 / tiles);
   const int64_t at_once = 256 * t.per_cu / tiles;
   int64_t g = std::min<int64_t>((int64_t)(s.weight * sqrt((double)pairs)) + 2, ceil_div(pairs, s.unit));
   if (at_once >= 3 * V) g = std::min<int64_t>(g, at_once - V);

@@ -45,6 +45,20 @@ def test_uneven_channels_with_many_pairs(c_in, c_out):
     _check(gen.full_grid(29, 1, seed=7), "f16", c_in, c_out, (0,), c_in)
 
 
+@pytest.mark.parametrize("c_in,c_out", [(128, 104), (96, 40), (256, 128)])
+def test_whole_rounds(c_in, c_out):
+    """Pair counts at which the number of pieces goes down to whole rounds of one workgroup per CU, on a build that is
+    waited for and on one whose pair count only the device knows."""
+    import paper_2311_12862_amd as sp
+    c = gen.full_grid(26, 1, seed=8)
+    _check(c, "f16", c_in, c_out, (0,), c_in)
+    (_, x), _, (_, g) = make_layer(len(c), len(c), c_in, c_out, 27, "f16", c_in)
+    known, pending = sp.build_kmap(coords_dev(c), 3, 1), sp.build_kmap(coords_dev(c), 3, 1, asynchronous=True)
+    want = sp.wgrad(x, g, known).double().cpu().numpy()
+    assert norm_err(sp.wgrad(x, g, pending), want) <= 1e-5
+    pending.status()
+
+
 @pytest.mark.parametrize("dtype,c_in,c_out", [("f16", 640, 512), ("bf16", 400, 776), ("f32", 320, 256)])
 def test_very_wide_layers(dtype, c_in, c_out):
     _check(gen.lidar_scene(52, target_n=1500), dtype, c_in, c_out, (0, 777), c_in)
