@@ -92,11 +92,11 @@ typedef struct spconv_kmap spconv_kmap; /* opaque */
 /* Dataflow parameters (the design space of Section 4.1).  Zero-initialise for
  * the defaults.  A null configuration leaves all of them to the library, the row order included:
  * spconv_fwd and spconv_dgrad then visit the rows in an order of the library's own (similar
- * neighbour masks together, built once per kmap and side by the first such call) where the layer is wide
- * enough for the map's size that a few calls of it pay for the order.  That, and the kernel, depend
- * on the map's size and the layer alone, never on earlier calls: the same call gives the same bits
- * whenever it is made.  Under stream capture the order is used where it exists and never made; the
- * result is the same without it.
+ * neighbour masks together, built once per kmap and side) where it exists; a call makes it if the layer is
+ * wide enough for the map's size that a few calls of it pay for the order.  That, and the kernel, depend
+ * on the map's size and the layer alone, never on earlier calls, and a row's sums do not depend on the
+ * order of the rows: with finite weights the same call gives the same bits whenever it is made.
+ * Under stream capture the order is never made.
  *   n_split     0: unsorted implicit GEMM, rows in map order, one pass.
  *               s >= 1 (at most 4 and at most K^3): the K^3 offsets are cut into s contiguous
  *               ranges [floor(i*V/s), floor((i+1)*V/s)); in each range the
@@ -292,8 +292,8 @@ SPCONV_API int spconv_fwd(const void* feats, const void* weights, spconv_kmap* k
  * callback, no pool):
  *   - the plan of cfg must exist already, made by spconv_kmap_prepare(km, SPCONV_OP_FWD, cfg) or by
  *     an earlier spconv_fwd with the same cfg; otherwise SPCONV_ENOPLAN.  (cfg null: by any
- *     earlier call without a configuration; where only another layer's made the plans, this
- *     layer's kernel may run in map order, with the same result.)  kernel = 3 (fetch on
+ *     earlier call without a configuration; the layer's kernel then runs in the library's own
+ *     order or in map order, whichever there is, with the same result.)  kernel = 3 (fetch on
  *     demand) is refused with SPCONV_EINVAL;
  *   - the fp32 partial sums of n_split >= 2 (n_split * n_out * C_out * 4 bytes) go to a fixed
  *     array of SPCONV_NOALLOC_SCRATCH_BYTES that every GPU the library runs on holds until the
@@ -391,8 +391,8 @@ SPCONV_API int spconv_set_allocator(void* (*alloc)(size_t bytes, void* stream, v
  *   rows_src rows of the tensor that is gathered from
  *   C_red    reduced channels (C_in for forward, C_out for dgrad), C_cols the produced ones
  *   dgrad    0 / 1 (the tiled kernel's LDS layout differs)
- * A null configuration describes what a call without one launches, the row order that it chooses included (under
- * stream capture a call that finds its order not made yet launches the same kernel on the map's own order).
+ * A null configuration describes what a call without one launches on a kmap that no call has used yet, the row
+ * order included.
  * Returns SPCONV_EINVAL for every shape or configuration the compute calls refuse, SPCONV_OK with
  * an all-zero structure for rows = 0 (nothing is launched). */
 typedef struct spconv_launch_info {

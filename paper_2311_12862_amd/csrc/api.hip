@@ -244,21 +244,30 @@ int static_scratch(void** out) {
   return SPCONV_OK;
 }
 
-// Whether a call without a configuration sorts the rows of the side it walks (the library's own order): where `kCalls`
-// calls of this layer would save what the order costs.  How many calls a map will see is not known; the answer depends
-// on the map's size and the layer alone, not on what ran before, so that a call has the same kernel, the same bits and
-// the same plans whenever it is made, and one call is enough to warm a layer up.  Measured (us; 10k, 30k, 100k, 200k and
-// 400k rows of LiDAR-like scans, 4.2 pairs a row; a dense room with 9 saves up to twice as much):
+// Whether a call without a configuration makes the library's own order of the side it walks, and with it which kernel it
+// runs: where the calls that the side may expect would save what the order costs.  The answer depends on the map's size and the layer
+// alone, not on what ran before, so that a call has the same kernel and the same bits whenever it is made, and one call is
+// enough to warm a layer up.  Measured (us; 10k, 30k, 100k, 200k and 400k rows of LiDAR-like scans, 4.2 pairs a row; a dense
+// room with 9 saves up to twice as much):
 //   the order, first use  24, 26, 35, 51, 73
 //   unsorted -> sorted    f16 64 -> 64 13.4 -> 10.7, 16.0 -> 12.2, 30 -> 22, 52 -> 36, 98 -> 63; 64 -> 128 13.7 -> 17.3,
 //                         21.5 -> 20.9, 50 -> 34, 94 -> 51, 205 -> 89; 128 -> 128 26 -> 19, 57 -> 28, 133 -> 51, 197 -> 77,
 //                         356 -> 138; fp32 64 -> 64 47 -> 38, 68 -> 43, 166 -> 71, 312 -> 113, 599 -> 213
-// 32 -> 32 saves 0 to 3 us at every size.
-bool auto_sorted(int V, int64_t rows, int c_red, int c_cols, spconv_dtype dtype) {
+// 32 -> 32 saves 0 to 3 us at every size.  96 -> 32 is faster on the unsorted map with resident weights than sorted with
+// tiles (100k rows 34, 41).  2x2x2 maps have few offsets to skip (up to 100k rows 128 -> 64 27 -> 15, 256 -> 256 131 -> 44).
+bool auto_sorted(int V, int64_t rows, int64_t rows_src, int c_red, int c_cols, spconv_dtype dtype) {
   if (V < 8) return false;
-  constexpr double kCalls = 3.0;
-  const double unit = dtype == SPCONV_F32 ? 2.3e-7 : c_red <= 64 ? 2e-8 : 5e-8;  // us saved per row and channel pair
-  return kCalls * unit * (double)rows * c_red * c_cols >= 23.0 + 1.3e-4 * (double)rows;
+  const bool f32 = dtype == SPCONV_F32;
+  if (!f32 && c_red > 64 && c_red <= 128 && c_cols <= 32) return false;
+  if (f32) {  // (its time goes by whole pieces and column tiles: 22k rows 44 -> 44 saves what 64 -> 64 does, 17 us)
+    c_red = (int)round_up(c_red, c_red <= 16 ? 16 : 32);
+    c_cols = (int)round_up(c_cols, c_cols <= 32 ? 16 : 64);
+  }
+  // us saved per row and channel pair
+  const double unit = V == 8 ? (f32 ? 1e-7 : 1.5e-8) : f32 ? 2e-7 : c_red <= 64 ? 2e-8 : 4.5e-8;
+  // a submanifold map (as many rows on both sides) serves the layers of a stage, a strided one its layer and a gradient
+  const double calls = rows == rows_src ? 2.5 : 2.0;
+  return calls * unit * (double)rows * c_red * c_cols >= 23.0 + 1.3e-4 * (double)rows;
 }
 
 // While a stream is being captured nothing may be allocated, and what is launched runs at the replays, not now.
@@ -271,12 +280,13 @@ bool capturing(hipStream_t st) {
   return status != hipStreamCaptureStatusNone;
 }
 
-// The plan of a call without a configuration.  sorted: the layer runs in the library's own order (auto_sorted).  Where that
-// order is not there and cannot be made - under capture, without memory - the layer runs in map order: the
-// kernel was chosen for the layer, and its sums do not depend on the rows beside a row, so the result is the same.
-int auto_plan_get(spconv_kmap* km, SideMap& side, bool sorted, hipStream_t st, IgemmPlan** out) {
+// The plan of a call without a configuration: the library's own order where it exists; where it does not, the order is made
+// if `make` says so.  Else - also under capture, and where there is no memory for the order - the layer runs in map order:
+// its kernel was chosen for the layer, and a row's sums do not depend on the rows beside it, so the result is the same.
+int auto_plan_get(spconv_kmap* km, SideMap& side, bool make, hipStream_t st, IgemmPlan** out) {
   SPC_TRY(plan_get(km, side, 0, 0, st, out));  // (the map itself: nothing is allocated or launched)
-  if (!sorted || (!side.plans.count(std::make_pair(1, kPlanOwnOrder)) && capturing(st))) return SPCONV_OK;
+  const bool exists = side.plans.count(std::make_pair(1, kPlanOwnOrder)) > 0;
+  if (!exists && (!make || capturing(st))) return SPCONV_OK;
   IgemmPlan* own = nullptr;
   const int status = plan_get(km, side, 1, kPlanOwnOrder, st, &own);
   if (status == SPCONV_OK) *out = own;
@@ -373,17 +383,17 @@ int run_igemm_op(spconv_op op, const void* src, const void* weights, spconv_kmap
   }
   const int c_red = os.dgrad ? C_out : C_in;
   const int c_cols = os.dgrad ? C_in : C_out;
-  const bool own_order = !cfg && auto_sorted(km->V, rows_dst, c_red, c_cols, dtype);
+  const int64_t rows_src = op == SPCONV_OP_FWD ? km->n_in : km->n_out;
+  const bool own_order = !cfg && auto_sorted(km->V, rows_dst, rows_src, c_red, c_cols, dtype);
   if (own_order) c.n_split = 1;
   KernelChoice kc;
-  const int64_t rows_src = op == SPCONV_OP_FWD ? km->n_in : km->n_out;
   SPC_TRY(choose_kernel(km->V, rows_dst, rows_src, c_red, c_cols, dtype, cfg, c, &kc));
   IgemmPlan* plan = nullptr;
   if (prepared_only) {
     if (c.n_split > km->V) return SPCONV_EINVAL;
     auto it = os.side->plans.end();
-    if (own_order) it = os.side->plans.find(std::make_pair(1, kPlanOwnOrder));
-    if (it == os.side->plans.end()) {  // (without a configuration: map order where the library's own was not prepared)
+    if (!cfg) it = os.side->plans.find(std::make_pair(1, kPlanOwnOrder));
+    if (it == os.side->plans.end()) {  // (without a configuration: map order where the library's own does not exist)
       const int n_split = cfg ? c.n_split : 0;
       it = os.side->plans.find(std::make_pair(n_split, n_split > 0 ? plan_flags(c) : 0));
     }
@@ -1054,7 +1064,7 @@ SPCONV_API int spconv_describe_launch(int K, int64_t rows, int64_t rows_src, int
   const int V = K == 5 ? 25 : K * K * K;  // K = 5 launches once per 25-offset plane: the launch of one plane
   if (c.n_split > V) return SPCONV_EINVAL;
   if (rows == 0) return SPCONV_OK;  // nothing is launched
-  if (!cfg && K != 5 && auto_sorted(V, rows, C_red, C_cols, dtype)) c.n_split = 1;
+  if (!cfg && K != 5 && auto_sorted(V, rows, rows_src, C_red, C_cols, dtype)) c.n_split = 1;
   KernelChoice kc;
   SPC_TRY(choose_kernel(V, rows, rows_src, C_red, C_cols, dtype, cfg, c, &kc));
   const int tile_m = kc.kind == KernelChoice::WAVE ? 16 : kc.kind == KernelChoice::RING ? kc.ring.bm : kc.tile_m;

@@ -97,7 +97,7 @@ def test_partial_sums_beyond_the_fixed_array_are_refused():
     assert (out == 0).all()
 
 
-@pytest.mark.parametrize("c_in,c_out", [(256, 192), (32, 32)])   # sorted rows, map order
+@pytest.mark.parametrize("c_in,c_out", [(320, 256), (32, 32)])   # sorted rows, map order
 @pytest.mark.parametrize("how", ["prepare", "fwd", "another layer"])
 def test_without_a_configuration(c_in, c_out, how):
     other = _case(37, 3000, c_in, c_out)
