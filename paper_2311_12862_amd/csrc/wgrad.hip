@@ -8,11 +8,12 @@
 //
 // Work split.  Each offset's pairs are cut into pieces of nearly equal length, one per workgroup.  A piece leaves an fp32
 // partial tile; a second kernel adds the tiles of each offset in order, so results are bit-reproducible.  The number
-// of pieces weighs the time that a piece takes against the tiles that are written and read back
-// (split_length), and at most as many run as the GPU holds at once.
+// of pieces weighs the time that a piece takes against the tiles that are written and read back, and goes down to whole
+// rounds of one workgroup per CU (split_length); at most as many run as the GPU holds at once, unless a layer's tiles alone
+// fill it (split_for).
 //
 // What bounds it is the gather: every pair's two rows cross the cache hierarchy once per column or row of tiles,
-// so the tile is as wide as the layer up to 256 x 256.  Rows go straight into LDS (batches of 32 pairs, two to three of them
+// so the tile is as wide as the layer up to 256 x 256 (pick_tile).  Rows go straight into LDS (batches of 32 pairs, two to three of them
 // in flight ahead of the one that is multiplied, each load waited for by count); the matrix instructions need the
 // pair index contiguous per lane, which the transposing LDS read (ds_read_b64_tr_b16) delivers.  Fragments of
 // the next batch are read while the matrix cores work on this one.  Narrow layers (one wave's tile) give every
