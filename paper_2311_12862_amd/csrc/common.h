@@ -223,14 +223,14 @@ int igemm_tile_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
                      bool f32, bool dgrad, TileShape* s);
 
 struct RingShape {  // igemm_ring_run (tiles loaded straight into LDS; every fp32 layer)
-  int bm = 0, bn = 0, nwk = 0, piece = 0;  // tile, K groups, bytes of a row per unit
+  int bm = 0, bn = 0, nwk = 0, nwr = 0, piece = 0;  // rows and columns of a workgroup, K groups, tiles (one below the other), bytes of a row per unit
   int threads = 0, n_cols = 0;
   int64_t n_tiles = 0;
   size_t lds_bytes = 0;
   unsigned grid[3] = {0, 0, 0};
   unsigned feats_bytes = 0;
 };
-// small_tiles: 32-row tiles and K groups of fp32 may be chosen
+// small_tiles: 32-row tiles, and column tiles of fp32 that the layer's width does not ask for, may be chosen
 int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_red, int c_out, bool f32, bool small_tiles,
                      RingShape* s);
 

@@ -49,18 +49,19 @@ struct RingParams {
 
 constexpr unsigned kNoRow = 0xFFFF0000u, kNoWeight = 0x80000000u;  // out of range, also with a scalar offset added
 
-// BM x BN outputs; PB bytes of a row per unit (64 or 128), E bytes per element, NW waves in all, NWK K groups
-template <int BM, int BN, int PB, int E, int NW, int NWK> struct RingSmem {
-  static constexpr int a_bytes = BM * PB, b_bytes = PB / E * BN * E, unit = a_bytes + b_bytes, stage = NWK * unit;
-  static constexpr int slab = (BM * 27 * 4 + NW * 1024 - 1) / (NW * 1024) * (NW * 1024);  // whole loads of every wave
+// BM x BN outputs; PB bytes of a row per unit (64 or 128), E bytes per element, NW waves in all, NWK K groups for each of
+// NWR such tiles, one below the other
+template <int BM, int BN, int PB, int E, int NW, int NWK, int NWR> struct RingSmem {
+  static constexpr int a_bytes = BM * PB, b_bytes = PB / E * BN * E, unit = a_bytes + b_bytes, stage = NWR * NWK * unit;
+  static constexpr int slab = (NWR * BM * 27 * 4 + NW * 1024 - 1) / (NW * 1024) * (NW * 1024);  // whole loads of every wave
   static constexpr int total = 2 * stage + slab;
 };
 
-template <typename T, int BM, int BN, int PB, int NWM, int NWN, int NWK, bool DGRAD>
-__global__ void __launch_bounds__(NWM* NWN* NWK * 64) k_ring(const RingParams p) {
+template <typename T, int BM, int BN, int PB, int NWM, int NWN, int NWK, int NWR, bool DGRAD>
+__global__ void __launch_bounds__(NWM* NWN* NWK* NWR * 64) k_ring(const RingParams p) {
   constexpr int E = (int)sizeof(T), CE = 16 / E, KC = PB / E;  // bytes and chunk length of an element, channels of a unit
   constexpr int NW = NWM * NWN;                                // waves of a K group
-  typedef RingSmem<BM, BN, PB, E, NW * NWK, NWK> L;
+  typedef RingSmem<BM, BN, PB, E, NW * NWK * NWR, NWK, NWR> L;
   constexpr int WM = BM / NWM, WN = BN / NWN, MB = WM / 16, NB = WN / 16;
   constexpr int CPR = PB / 16;              // chunks of a gathered piece
   constexpr int RPI = 64 / CPR;             // rows that one load covers
@@ -69,7 +70,7 @@ __global__ void __launch_bounds__(NWM* NWN* NWK * 64) k_ring(const RingParams p)
   constexpr int NBW = (NBI + NW - 1) / NW;  // per wave (with fewer than NW, some waves load the same piece)
   constexpr int LPR = DGRAD ? CPR : BN / CE;  // chunks of a row of the weight tile
   constexpr int RPB = 64 / LPR;               // rows of it per load
-  static_assert(NWK == 1 || NWK == 2, "first_piece");
+  static_assert((NWK == 1 || NWK == 2) && (NWR == 1 || NWR == 2), "first_piece, tmask_other");
   static_assert(NA >= 1 && BM % (RPI * NW) == 0 && NBI >= 1 && (NBI % NW == 0 || NW % NBI == 0), "whole loads per wave");
   extern __shared__ __align__(16) unsigned char smem[];
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
@@ -77,7 +78,8 @@ __global__ void __launch_bounds__(NWM* NWN* NWK * 64) k_ring(const RingParams p)
 
   const int lane = threadIdx.x & 63;
   const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int grp = NWK > 1 ? wave_all / NW : 0, wave = NWK > 1 ? wave_all % NW : wave_all;
+  const int wave = wave_all % NW, unit = wave_all / NW;                 // within its tile and K group, and which of these
+  const int grp = NWK > 1 ? unit % NWK : 0, half = NWR > 1 ? unit / NWK : 0;  // K group, tile of the workgroup
   const int wm = wave / NWN, wn = wave % NWN;
   const int fa = lane & 15, fg = lane >> 4;  // fragment row / column, and chunk of a sub-step
   const int part = blockIdx.z;
@@ -90,22 +92,22 @@ __global__ void __launch_bounds__(NWM* NWN* NWK * 64) k_ring(const RingParams p)
   const int tile = p.heavy_first ? p.n_tiles - 1 - t_idx : t_idx;
   const int n0 = c_idx * BN;
   const int width = p.width[part], lo = p.lo[part];
-  const long long row0 = (long long)tile * BM;
+  const long long row0 = (long long)tile * (BM * NWR);
 
   {  // map slab of the tile (consecutive ints) -> LDS; past the end of the map: zeros, never used
     const u32x4 m_rsrc = rsrc_of(p.map[part], (unsigned)((unsigned long long)p.rows_pad * width * 4));
-    const unsigned bytes = (unsigned)(BM * width * 4), begin = (unsigned)(row0 * width) * 4u;
-    for (unsigned o = wave_all * 1024; o < bytes; o += NW * NWK * 1024)
+    const unsigned bytes = (unsigned)(NWR * BM * width * 4), begin = (unsigned)(row0 * width) * 4u;
+    for (unsigned o = wave_all * 1024; o < bytes; o += NW * NWK * NWR * 1024)
       load_to_lds(m_rsrc, begin + o + lane * 16, 0, lds0 + 2 * L::stage + o);
   }
-  unsigned bmask = 0;  // lane b < BM / 16: mask of the tile's 16-row block b
+  unsigned bmask = 0;  // lane b < NWR * BM / 16: mask of the 16-row block b
   if (p.rowmask) {
-    constexpr int MR = (BM + 63) / 64;
+    constexpr int MR = (NWR * BM + 63) / 64;
     unsigned m[MR];
 #pragma unroll
     for (int i = 0; i < MR; ++i) {
       const long long r = row0 + i * 64 + lane;
-      m[i] = r < p.rows && i * 64 + lane < BM ? p.rowmask[r] : 0u;
+      m[i] = r < p.rows && i * 64 + lane < NWR * BM ? p.rowmask[r] : 0u;
     }
 #pragma unroll
     for (int i = 0; i < MR; ++i) {
@@ -113,22 +115,24 @@ __global__ void __launch_bounds__(NWM* NWN* NWK * 64) k_ring(const RingParams p)
       const unsigned t = __shfl(m[i], (lane & 3) * 16);
       if ((lane >> 2) == i) bmask = t;
     }
-  } else if (lane < BM / 16 && row0 + lane * 16 < p.rows) {
+  } else if (lane < NWR * BM / 16 && row0 + lane * 16 < p.rows) {
     bmask = p.blkmask[part][row0 / 16 + lane];
   }
-  unsigned tmask = bmask;
-  for (int o = 1; o < 16; o <<= 1) tmask |= __shfl_xor(tmask, o);
-  tmask = __builtin_amdgcn_readfirstlane(tmask);
+  static_assert(NWR * BM <= 256, "blocks of a workgroup: 16 lanes");
+  unsigned tmask = bmask;  // of the tile, and of the workgroup's other one
+  for (int o = 1; o < BM / 16; o <<= 1) tmask |= __shfl_xor(tmask, o);
+  const unsigned tmask_other = NWR > 1 ? __builtin_amdgcn_readlane(tmask, (half ^ 1) * (BM / 16)) : 0u;
+  tmask = __builtin_amdgcn_readlane(tmask, half * (BM / 16));
   unsigned blk[MB], wave_mask = 0;
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
-    blk[mb] = __builtin_amdgcn_readlane(bmask, wm * MB + mb);
+    blk[mb] = __builtin_amdgcn_readlane(bmask, (half * NWM + wm) * MB + mb);
     wave_mask |= blk[mb];
   }
   int orow[MB];
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
-    const long long g = row0 + wm * WM + mb * 16 + fa;
+    const long long g = row0 + half * BM + wm * WM + mb * 16 + fa;
     orow[mb] = p.perm[part] ? p.perm[part][g] : (g < p.rows ? (int)g : -1);
   }
 
@@ -148,7 +152,7 @@ __global__ void __launch_bounds__(NWM* NWN* NWK * 64) k_ring(const RingParams p)
            : BN == 64 ? (((row >> 1) & 1) << 1) | (((row >> 3) & 1) << 2) : ((row & 3) << 1) | (((row >> 3) & 1) << 3);
   };
   const int g_row = lane / CPR, g_chunk = (lane % CPR) ^ swz_a(g_row);  // (RPI is a multiple of 8)
-  const int* g_map = mapS + (wave * NA * RPI + g_row) * width;
+  const int* g_map = mapS + (half * BM + wave * NA * RPI + g_row) * width;
   unsigned w_off[NBW];  // this lane's chunk of the weight tile: offset within a slice, and
   int w_red[NBW];       // its reduction channel within a piece (far beyond any where there is no such column)
 #pragma unroll
@@ -189,10 +193,10 @@ __global__ void __launch_bounds__(NWM* NWN* NWK * 64) k_ring(const RingParams p)
   Cursor qi{tmask, 0, n_pieces};  // the unit that is loaded next
   cursor_settle(qi);
   Cursor qc = qi;  // the unit that is multiplied next
-  auto units_of = [&](int g) {  // units of K group g
-    if (NWK == 1) return __popc(tmask) * n_pieces;
-    if (!odd_start) return __popc(tmask) * (n_pieces / 2);
-    return __popc(tmask & 0x55555555u) * ((n_pieces + 1 - g) / 2) + __popc(tmask & 0xAAAAAAAAu) * ((n_pieces + g) / 2);
+  auto units_of = [&](unsigned of, int g) {  // units of K group g of a tile with this mask
+    if (NWK == 1) return __popc(of) * n_pieces;
+    if (!odd_start) return __popc(of) * (n_pieces / 2);
+    return __popc(of & 0x55555555u) * ((n_pieces + 1 - g) / 2) + __popc(of & 0xAAAAAAAAu) * ((n_pieces + g) / 2);
   };
   int idx[NA];     // map entries of the unit that is loaded next
   auto fetch_idx = [&]() {
@@ -201,7 +205,7 @@ __global__ void __launch_bounds__(NWM* NWN* NWK * 64) k_ring(const RingParams p)
   };
   auto load_unit = [&](int slot) {
     const int k = lo + qi.c, r0 = qi.piece * KC;
-    const unsigned a_lds = lds0 + slot * L::stage + grp * L::unit, b_lds = a_lds + L::a_bytes;
+    const unsigned a_lds = lds0 + slot * L::stage + unit * L::unit, b_lds = a_lds + L::a_bytes;
     const unsigned w_soff = (unsigned)(p.mirror ? p.V - 1 - k : k) * slice + (unsigned)(DGRAD ? r0 : r0 * p.C_out) * E;
     const bool ok = r0 + g_chunk * CE < c_red;
 #pragma unroll
@@ -245,7 +249,7 @@ __global__ void __launch_bounds__(NWM* NWN* NWK * 64) k_ring(const RingParams p)
     }
   }
   auto multiply = [&](int slot, int c) {
-    const unsigned char* st = smem + slot * L::stage + grp * L::unit;
+    const unsigned char* st = smem + slot * L::stage + unit * L::unit;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       u32x4 w[NB], x[MB];
@@ -279,7 +283,10 @@ __global__ void __launch_bounds__(NWM* NWN* NWK * 64) k_ring(const RingParams p)
 
   wait_loads_and_sync();  // the slab is there
   fetch_idx();
-  const int mine = units_of(grp), steps = NWK > 1 ? max(mine, units_of(grp ^ 1)) : mine;
+  const int mine = units_of(tmask, grp);
+  int steps = mine;  // every wave passes as many barriers
+  if (NWK > 1) steps = max(steps, units_of(tmask, grp ^ 1));
+  if (NWR > 1) steps = max(steps, max(units_of(tmask_other, 0), NWK > 1 ? units_of(tmask_other, 1) : 0));
   if (mine > 0) load_unit(0);
   for (int it = 0; it < steps; ++it) {
     wait_loads_and_sync();  // this step's unit has landed, and everyone is done with the stage that is filled next
@@ -288,14 +295,14 @@ __global__ void __launch_bounds__(NWM* NWN* NWK * 64) k_ring(const RingParams p)
     cursor_step(qc);
   }
   if constexpr (NWK > 1) {  // the K groups' sums meet in LDS; group 0 adds them up in order and stores
-    static_assert((NWK - 1) * BM * BN * 4 <= 2 * L::stage, "the sums fit the stages");
+    static_assert(NWR * (NWK - 1) * BM * BN * 4 <= 2 * L::stage, "the sums fit the stages");
     wait_loads_and_sync();
     f32x4* sums = reinterpret_cast<f32x4*>(smem);
     if (grp > 0) {
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) sums[(((grp - 1) * NW + wave) * MB * NB + mb * NB + nb) * 64 + lane] = acc[mb][nb];
+        for (int nb = 0; nb < NB; ++nb) sums[(((half * (NWK - 1) + grp - 1) * NW + wave) * MB * NB + mb * NB + nb) * 64 + lane] = acc[mb][nb];
     }
     __syncthreads();
     if (grp > 0) return;
@@ -304,7 +311,7 @@ __global__ void __launch_bounds__(NWM* NWN* NWK * 64) k_ring(const RingParams p)
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] += sums[((g * NW + wave) * MB * NB + mb * NB + nb) * 64 + lane];
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] += sums[(((half * (NWK - 1) + g) * NW + wave) * MB * NB + mb * NB + nb) * 64 + lane];
   }
 
   // a lane holds channels 4 fg + r of row fa of each block
@@ -329,14 +336,14 @@ __global__ void __launch_bounds__(NWM* NWN* NWK * 64) k_ring(const RingParams p)
   }
 }
 
-template <typename T, int BM, int BN, int PB, int NWM, int NWN, int NWK>
+template <typename T, int BM, int BN, int PB, int NWM, int NWN, int NWK, int NWR>
 int launch_ring(const RingParams& p, bool dgrad, dim3 grid, hipStream_t st) {
-  constexpr int NW = NWM * NWN * NWK;
-  typedef RingSmem<BM, BN, PB, (int)sizeof(T), NW, NWK> L;
+  constexpr int NW = NWM * NWN * NWK * NWR;
+  typedef RingSmem<BM, BN, PB, (int)sizeof(T), NW, NWK, NWR> L;
   static_assert(L::total <= 160 * 1024, "LDS of a CU");
   static std::atomic<bool> attr_set{false};  // (set twice by racing threads at worst: the calls are idempotent)
-  auto fwd = k_ring<T, BM, BN, PB, NWM, NWN, NWK, false>;
-  auto dgr = k_ring<T, BM, BN, PB, NWM, NWN, NWK, true>;
+  auto fwd = k_ring<T, BM, BN, PB, NWM, NWN, NWK, NWR, false>;
+  auto dgr = k_ring<T, BM, BN, PB, NWM, NWN, NWK, NWR, true>;
   if (!attr_set.load(std::memory_order_acquire)) {
     SPC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(fwd), hipFuncAttributeMaxDynamicSharedMemorySize, L::total));
     SPC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(dgr), hipFuncAttributeMaxDynamicSharedMemorySize, L::total));
@@ -347,14 +354,16 @@ int launch_ring(const RingParams& p, bool dgrad, dim3 grid, hipStream_t st) {
   return SPCONV_OK;
 }
 
-// the tile shapes that are built: BM, BN, waves along the rows, along the columns, K groups
+// the tile shapes that are built: BM, BN, waves along the rows, along the columns, K groups, tiles of a workgroup
 #define SPC_RING_SHAPES_16(X) \
-  X(32, 64, 1, 2, 2) X(64, 32, 4, 1, 1) X(64, 64, 2, 2, 1) X(64, 64, 2, 2, 2) X(64, 128, 2, 2, 1) X(128, 128, 2, 2, 1) X(256, 256, 2, 4, 1)
-#define SPC_RING_SHAPES_32(X) X(64, 16, 4, 1, 1) X(64, 32, 4, 1, 1) X(64, 64, 2, 2, 1) X(64, 64, 2, 2, 2)
+  X(32, 64, 1, 2, 2, 1) X(64, 32, 4, 1, 1, 1) X(64, 64, 2, 2, 1, 1) X(64, 64, 2, 2, 2, 1) X(64, 128, 2, 2, 1, 1) \
+  X(128, 128, 2, 2, 1, 1) X(256, 256, 2, 4, 1, 1)
+#define SPC_RING_SHAPES_32(X) \
+  X(32, 16, 2, 1, 2, 2) X(32, 32, 1, 2, 2, 2) X(64, 16, 4, 1, 1, 1) X(64, 32, 4, 1, 1, 1) X(64, 64, 2, 2, 1, 1)
 
 template <typename T, int PB> int launch_shape(const RingParams& p, bool dgrad, const RingShape& s, dim3 grid, hipStream_t st) {
-#define SPC_RING_CASE(BM, BN, NWM, NWN, NWK) \
-  if (s.bm == BM && s.bn == BN && s.nwk == NWK) return launch_ring<T, BM, BN, PB, NWM, NWN, NWK>(p, dgrad, grid, st);
+#define SPC_RING_CASE(BM, BN, NWM, NWN, NWK, NWR) \
+  if (s.bm == BM * NWR && s.bn == BN && s.nwk == NWK && s.nwr == NWR) return launch_ring<T, BM, BN, PB, NWM, NWN, NWK, NWR>(p, dgrad, grid, st);
   if constexpr (sizeof(T) == 4) {
     SPC_RING_SHAPES_32(SPC_RING_CASE)
   } else {
@@ -364,10 +373,10 @@ template <typename T, int PB> int launch_shape(const RingParams& p, bool dgrad, 
 }
 
 size_t ring_lds_bytes(const RingShape& s, bool f32) {
-#define SPC_RING_LDS(BM, BN, NWM, NWN, NWK)                                                                     \
-  if (s.bm == BM && s.bn == BN && s.nwk == NWK)                                                                 \
-    return s.piece == 128 ? (size_t)RingSmem<BM, BN, 128, E, NWM * NWN * NWK, NWK>::total                       \
-                          : (size_t)RingSmem<BM, BN, 64, E, NWM * NWN * NWK, NWK>::total;
+#define SPC_RING_LDS(BM, BN, NWM, NWN, NWK, NWR)                                                                     \
+  if (s.bm == BM * NWR && s.bn == BN && s.nwk == NWK && s.nwr == NWR)                                                                 \
+    return s.piece == 128 ? (size_t)RingSmem<BM, BN, 128, E, NWM * NWN * NWK * NWR, NWK, NWR>::total                       \
+                          : (size_t)RingSmem<BM, BN, 64, E, NWM * NWN * NWK * NWR, NWK, NWR>::total;
   if (f32) {
     constexpr int E = 4;
     SPC_RING_SHAPES_32(SPC_RING_LDS)
@@ -379,8 +388,8 @@ size_t ring_lds_bytes(const RingShape& s, bool f32) {
 }
 
 int ring_waves(const RingShape& s, bool f32) {
-#define SPC_RING_WAVES(BM, BN, NWM, NWN, NWK) \
-  if (s.bm == BM && s.bn == BN && s.nwk == NWK) return NWM * NWN * NWK;
+#define SPC_RING_WAVES(BM, BN, NWM, NWN, NWK, NWR) \
+  if (s.bm == BM * NWR && s.bn == BN && s.nwk == NWK && s.nwr == NWR) return NWM * NWN * NWK * NWR;
   if (f32) {
     SPC_RING_SHAPES_32(SPC_RING_WAVES)
   } else {
@@ -411,11 +420,20 @@ int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
     return SPCONV_EINVAL;
   s->feats_bytes = (unsigned)bytes;
   auto wgs = [&](int bm, int bn) { return ceil_div(rows, bm) * ceil_div(c_out, bn) * ps.parts; };
-  s->nwk = 1;
+  s->nwk = s->nwr = 1;
   if (f32) {
+    // The matrix cores' fp32 rate makes a tile with all 27 offsets last: 64 x 64 outputs of 64 channels 23 us of a CU
+    // on its own.  So a workgroup takes two tiles of 32 x 32 outputs, each with two K groups, unless there are workgroups
+    // enough for the longest not to matter.  Measured on sorted maps (us; 64 x 64 with two K groups, two 32 x 32, 64 x 32):
+    // 2k rows 16 -> 16 8.8 (64 x 16), two 32 x 16 6.6; 5k 64 -> 64 37, 26; 20k 256 -> 256 230, 173; 30k 64 -> 64 44, 29.5; 60k
+    // 64 -> 64 48, 42; and where the line lies: 30k 96 -> 96 66, 62; 50k of a dense room 64 -> 64 57, 62; 60k 96 -> 96 103 (one K
+    // group), 96; 100k 128 -> 128 165 (one), 178.
     s->bm = 64;
-    s->bn = c_out <= 16 ? 16 : c_out <= 32 ? 32 : 64;
-    if (s->bn == 64 && wgs(64, 64) < 1024 && small_tiles) s->nwk = 2;
+    s->bn = c_out <= 16 ? 16 : 32;
+    if (small_tiles && wgs(64, s->bn) < (c_red <= 32 ? 1500 : 2000))
+      s->nwk = s->nwr = 2;
+    else if (c_out > 32)
+      s->bn = 64;
     s->piece = c_red <= 16 ? 64 : 128;
   } else {
     s->piece = (c_red % 64 == 0) ? 128 : 64;

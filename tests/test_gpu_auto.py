@@ -168,3 +168,16 @@ def test_without_memory_for_the_order():
         gc.collect()
         torch.cuda.synchronize()
         sp.set_allocator(None, None)
+
+
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 64, 65, 97, 2049])
+@pytest.mark.parametrize("c_in,c_out", [(4, 16), (12, 20), (16, 64), (36, 36), (68, 100)])
+def test_fp32_tiles_in_pairs(n, c_in, c_out):
+    """fp32 layers of small maps: a workgroup holds two 32-row tiles, whose masks, units and sums are their own; row counts
+    around their edges (a last workgroup with an empty or a partial second tile), odd and even numbers of pieces."""
+    import torch
+    import paper_2311_12862_amd as sp
+    info = sp.describe_launch(3, n, n, c_in, c_out, torch.float32)
+    assert info.tile_m == 64 and info.waves == 8 and info.tile_n == (16 if c_out <= 16 else 32)
+    c = gen.uniform_cloud(n, max(2, int(round((4 * n) ** (1 / 3)))) + 1, seed=n)
+    _check(c, 3, 1, False, "f32", c_in, c_out, 1, n)
