@@ -30,8 +30,9 @@
  *     (stride 1, not transposed, synchronous build): the library holds such
  *     a map as five planes of 25 offsets (dx = g - 2; offset k is offset
  *     k % 25 of plane k / 25), runs forward and dgrad plane by plane and sums
- *     the planes like the parts of a split, and sorts each plane by its own
- *     25-bit mask.  spconv_kmap_export_perm then counts parts over the
+ *     the planes like the parts of a split (16-bit layers that reduce over
+ *     at most 16 channels, unless the configuration says otherwise: all
+ *     planes in one launch), and sorts each plane by its own 25-bit mask.  spconv_kmap_export_perm then counts parts over the
  *     planes (split = plane * n_split + part); the tuners, the paired
  *     transposed kmap, fetch-on-demand and spconv_fwd_noalloc refuse a K = 5
  *     kmap with SPCONV_EINVAL;
@@ -391,6 +392,7 @@ SPCONV_API int spconv_set_allocator(void* (*alloc)(size_t bytes, void* stream, v
  *   rows_src rows of the tensor that is gathered from
  *   C_red    reduced channels (C_in for forward, C_out for dgrad), C_cols the produced ones
  *   dgrad    0 / 1 (the tiled kernel's LDS layout differs)
+ * K = 5: the launch of one plane, or the one launch that narrow layers make.
  * A null configuration describes what a call without one launches on a kmap that no call has used yet, the row
  * order included.
  * Returns SPCONV_EINVAL for every shape or configuration the compute calls refuse, SPCONV_OK with

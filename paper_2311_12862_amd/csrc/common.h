@@ -204,14 +204,16 @@ struct PlanShape {  // plan_get: parts of the offset range, padded rows, tiles
 int plan_shape(int V, int64_t rows, int n_split, int tile_m, PlanShape* s);
 
 struct WaveShape {  // igemm_wave_run (kernel 1)
-  int bn = 0, waves = 0, ks = 0, max_width = 0, threads = 0;
-  int slab_bytes = 0, map_bytes = 0;
+  int bn = 0, waves = 0, ks = 0, pack = 1, max_width = 0, threads = 0;  // pack: offsets that share a matrix instruction
+  int slab_bytes = 0, map_bytes = 0, weight_bytes = 0;
   size_t lds_bytes = 0;
   unsigned grid[3] = {0, 0, 0};
   unsigned feats_bytes = 0;
 };
 int igemm_wave_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_red, int c_out, int tile_n,
                      WaveShape* s);
+
+int igemm_wave_planes_shape(int64_t rows, int64_t rows_src, int c_red, int c_out, WaveShape* s);  // K = 5 in one launch
 
 struct TileShape {  // igemm_run (kernel 2 and the fp32 kernel)
   int bm = 0, bn = 0, kc = 0, nw = 0, threads = 0;
@@ -266,6 +268,7 @@ int igemm_ring_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& 
 int igemm_wave_pick_bn(int V, int n_split, int c_red, int c_out, int tile_n, int* waves_out);
 int igemm_wave_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan, const IgemmArgs& a,
                    hipStream_t st);
+int igemm_wave_planes_run(const spconv_kmap* km, const IgemmArgs& a, hipStream_t st);  // km: K = 5, map order
 int split_reduce(const float* partial, int parts, int64_t rows, int c, spconv_dtype dtype, void* out,
                  hipStream_t st);
 

@@ -18,12 +18,22 @@
 //   * the block's map rows are staged in a per-wave LDS slab (the hoisted
 //     addressing of Section 3.2), and output rows leave through the same slab
 //     as whole 16-byte segments.
+//
+// Narrow reductions (PACK).  A matrix instruction reduces over 32 channels; with 8 channels four consecutive offsets
+// share one, each group of lanes gathering the row of its own offset, so that a 27-offset block takes at most 7 steps and no
+// lane fetches padding.  The offsets that share an instruction are fixed (k / PACK), not those that happen to be present, so a
+// row's sums still do not depend on the rows beside it.  8 -> 32 in map order, us: 100k rows 12.3 -> 11.3, 200k 20.9 -> 17.7 (what
+// remains is launch, weights and the map).
+//
+// K = 5 (PLANES): with at most 16 channels (pairs of offsets) the weights of all 125 offsets fit in LDS, and a block walks the five
+// planes one after the other into the same accumulators: one launch, no partial sums and no reduction of them.  60k
+// rows 8 -> 32: 63 -> 27 us, 16 -> 16 54 -> 29, of which 8 are the 30 MB of map at the rate of a copy; 10k 16 -> 64 43 -> 26.
 #include "common.h"
 
 #include <atomic>
 
 #include <algorithm>
-#include <cstdlib>
+#include <type_traits>
 
 namespace spc {
 namespace {
@@ -46,6 +56,8 @@ template <> struct MfmaW<__bf16> {
   }
 };
 
+constexpr int kPlanes = 5;  // of a K = 5 map
+
 struct WaveParams {
   const void* feats;
   const void* weights;
@@ -63,6 +75,7 @@ struct WaveParams {
   int dgrad, mirror;
   int slab_bytes;  // per-wave LDS slab: map rows, then the output staging tile
   int map_bytes;   // size of the map part of the slab
+  int weight_bytes;  // LDS in front of the slabs
   unsigned feats_bytes;  // size of the gathered tensor, < 2^32 - 16 KiB
   unsigned map_part_bytes[kMaxSplit];  // sizes of the tables a plan index reaches: each part's map,
   unsigned rows_pad_bytes;             //   the permutation and the row masks (rows_pad entries),
@@ -70,9 +83,14 @@ struct WaveParams {
   int quad;     // gathers issued by quads of lanes per row and permuted to the operand layout
   int xcd_ranges;  // blocks are dealt to the 8 XCDs as contiguous ranges (gridDim.x is a multiple of 8)
 };
+struct PlaneParams : WaveParams {  // K = 5, map order: the planes' maps and row masks
+  const int* plane_map[kPlanes];
+  const unsigned* plane_mask[kPlanes];
+};
 
 // physical 16-byte chunk of logical chunk q in weight row n (row pitch = 4*KS chunks)
-template <int KS> __device__ __forceinline__ int swz(int q, int n) {
+template <int KS, int PACK = 1> __device__ __forceinline__ int swz(int q, int n) {
+  if (PACK > 1) return q;  // (rows of one or two chunks: 16 lanes read 256 or 512 consecutive bytes)
   if ((4 * KS) % 8 == 0) return (q & ~7) | ((q ^ n) & 7);
   return (q & ~3) | ((q ^ (n >> 1)) & 3);
 }
@@ -96,11 +114,13 @@ constexpr int kMapVecs = 7;  // ceil(16 rows * 27 offsets / 64 lanes)
 
 // DEPTH = offsets whose A-fragments are in flight per wave.  DEPTH 8 needs more than the 128
 // registers a 16-wave workgroup leaves per lane, so it runs with 8 waves.
-template <typename T, int KS, int NB, int DEPTH, bool QUAD>
-__global__ void __launch_bounds__(DEPTH > 4 ? 512 : 1024) k_igemm_wave(const WaveParams p) {
+// PACK = offsets that share a matrix instruction, PLANES = planes of the map (see the head of the file).
+template <typename T, int KS, int NB, int DEPTH, bool QUAD, int PACK, int PLANES>
+__global__ void __launch_bounds__(DEPTH > 4 && PACK == 1 ? 512 : 1024) k_igemm_wave(const std::conditional_t<(PLANES > 1), PlaneParams, WaveParams> p) {
+  static_assert(PACK == 1 || (KS == 1 && !QUAD), "");
   constexpr int BN = NB * 16;
-  constexpr int ROW_CHUNKS = 4 * KS;        // 16-byte chunks per weight row
-  constexpr int ROW_HALFS = 32 * KS;
+  constexpr int ROW_CHUNKS = 4 * KS / PACK;  // 16-byte chunks per weight row
+  constexpr int ROW_HALFS = 32 * KS / PACK;
   extern __shared__ __align__(16) unsigned char smem[];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -112,8 +132,9 @@ __global__ void __launch_bounds__(DEPTH > 4 ? 512 : 1024) k_igemm_wave(const Wav
   const int width = p.width[part], lo = p.lo[part];
   const int c_red = p.c_red, c_out = p.c_out;
 
-  unsigned short* Ws = reinterpret_cast<unsigned short*>(smem);  // [width][BN][ROW_HALFS] swizzled
-  unsigned char* slab = smem + (size_t)width * BN * ROW_HALFS * 2 + (size_t)wave * p.slab_bytes;
+  const int pitch = PACK > 1 ? (width + PACK - 1) / PACK * PACK : width;  // offsets per plane in LDS: whole groups
+  unsigned short* Ws = reinterpret_cast<unsigned short*>(smem);  // [plane][pitch][BN][ROW_HALFS] swizzled; PACK > 1: and a slice of zeros
+  unsigned char* slab = smem + p.weight_bytes + (size_t)wave * p.slab_bytes;
   int* mapW = reinterpret_cast<int*>(slab);
 
   const __amdgpu_buffer_rsrc_t w_rsrc = make_rsrc(p.weights, (unsigned)((size_t)p.V * p.C_in * p.C_out * 2));
@@ -138,7 +159,7 @@ __global__ void __launch_bounds__(DEPTH > 4 ? 512 : 1024) k_igemm_wave(const Wav
   const bool has_work = wave < nj;
   if (tid == 0) next_ticket = (unsigned)n_waves;
   const unsigned row_bytes = (unsigned)c_red * 2u;
-  const int map_len = 16 * width;
+  const int map_len = 16 * pitch;
   const int* map_part = p.map[part];
   const int* pm = p.perm[part];
   const unsigned* bmask = p.blkmask[part];
@@ -154,34 +175,56 @@ __global__ void __launch_bounds__(DEPTH > 4 ? 512 : 1024) k_igemm_wave(const Wav
   // maps, whose blocks hold few absent rows, and cost more than they save on unsorted ones).
   constexpr unsigned kAbsent = 0xFFFF0000u;  // byte offset that is out of range with any lane offset added
   const int grow = QUAD ? lane >> 2 : arow, gq = QUAD ? lane & 3 : aq;  // gather role: block row, chunk of a k-step
-  const unsigned lane_map = (unsigned)(grow * width) * 4u;  // this lane's map row in the slab
+  const int my_off = aq / ROW_CHUNKS;  // PACK > 1: which of the group's offsets this lane multiplies
+  const unsigned lane_map = (unsigned)(grow * pitch + (PACK > 1 ? my_off : 0)) * 4u;  // this lane's map row in the slab
   const int frag_src = (4 * arow + aq) * 4;  // (byte address of) the lane that gathered this lane's MFMA fragment
   unsigned lane_col[KS];  // the 8 channels this lane gathers of a row (bytes), or out of range
   unsigned lane_b[KS];    // this lane's weight chunk within an offset's slice (bytes, first 16 columns)
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
-    const unsigned col = (unsigned)(ks * 4 + gq) * 8u;
+    const unsigned col = (unsigned)(PACK > 1 ? gq % ROW_CHUNKS : ks * 4 + gq) * 8u;
     lane_col[ks] = col < (unsigned)c_red ? col * 2u : 0x80000000u;
-    lane_b[ks] = (unsigned)(arow * ROW_HALFS + swz<KS>(ks * 4 + aq, arow) * 8) * 2u;
+    lane_b[ks] = PACK > 1 ? (unsigned)(arow * ROW_HALFS + (aq % ROW_CHUNKS) * 8) * 2u
+                          : (unsigned)(arow * ROW_HALFS + swz<KS>(ks * 4 + aq, arow) * 8) * 2u;
   }
 
+  // PACK > 1: a row's entries stand at a pitch of whole groups in the slab, the surplus ones absent
+  unsigned msrc[PACK > 1 ? kMapVecs : 1];
+  if constexpr (PACK > 1) {
+#pragma unroll
+    for (int i = 0; i < kMapVecs; ++i) {
+      const int e = lane + 64 * i, r = e / pitch, c = e - r * pitch;
+      msrc[i] = r < 16 && c < width ? (unsigned)(r * width + c) * 4u : 0xFFFFFFFFu;
+    }
+  }
   // registers holding the next block's map rows, mask and output rows
   int mreg[kMapVecs];
   unsigned bm_next = 0;
   int orow_next = -1;
   // Every table that a block index reaches is read through a range-checked buffer descriptor
   // (beyond the end: zeros, no access), like the gathered rows: a wrong index cannot fault.
-  auto prefetch_block = [&](long long b) {
-    const __amdgpu_buffer_rsrc_t m_rsrc = make_rsrc(map_part, p.map_part_bytes[part]);
-    const unsigned mbase = (unsigned)(b * map_len) * 4u;
+  auto prefetch_block = [&](long long b, int plane) {
+    const int* from = map_part;
+    const unsigned* rowmask = p.rowmask;
+    if constexpr (PLANES > 1) {
+      from = p.plane_map[plane];
+      rowmask = p.plane_mask[plane];
+    }
+    const __amdgpu_buffer_rsrc_t m_rsrc = make_rsrc(from, p.map_part_bytes[part]);
+    const unsigned mbase = (unsigned)(b * 16 * width) * 4u;
 #pragma unroll
     for (int i = 0; i < kMapVecs; ++i) {
       const int e = lane + 64 * i;
-      mreg[i] = __builtin_amdgcn_raw_buffer_load_b32(m_rsrc, e < map_len ? mbase + (unsigned)e * 4u : 0xFFFFFFFFu, 0, 0);
+      if constexpr (PACK > 1) {
+        const int v = __builtin_amdgcn_raw_buffer_load_b32(m_rsrc, msrc[i] != 0xFFFFFFFFu ? mbase + msrc[i] : 0xFFFFFFFFu, 0, 0);
+        mreg[i] = msrc[i] != 0xFFFFFFFFu ? v : -1;
+      } else {
+        mreg[i] = __builtin_amdgcn_raw_buffer_load_b32(m_rsrc, e < map_len ? mbase + (unsigned)e * 4u : 0xFFFFFFFFu, 0, 0);
+      }
     }
     const unsigned g4 = (unsigned)(b * 16 + arow) * 4u;
-    if (p.rowmask)  // OR-reduced when the block starts
-      bm_next = (unsigned)__builtin_amdgcn_raw_buffer_load_b32(make_rsrc(p.rowmask, p.rows_pad_bytes), g4, 0, 0);
+    if (rowmask)  // OR-reduced when the block starts
+      bm_next = (unsigned)__builtin_amdgcn_raw_buffer_load_b32(make_rsrc(rowmask, p.rows_pad_bytes), g4, 0, 0);
     else
       bm_next = (unsigned)__builtin_amdgcn_raw_buffer_load_b32(make_rsrc(bmask, p.blocks_bytes), (unsigned)b * 4u, 0, 0);
     const long long g = b * 16 + arow;
@@ -193,11 +236,11 @@ __global__ void __launch_bounds__(DEPTH > 4 ? 512 : 1024) k_igemm_wave(const Wav
 
   uint4 fr[DEPTH][KS];
   int cc[DEPTH];
-  unsigned m = 0;
+  unsigned m = 0, present = 0;  // steps of the block that are still to be issued; PACK > 1: its offsets
   // Always issues KS loads: with no offset left they are out-of-range loads (zeros, no traffic).
   // The slab holds byte offsets of the gathered rows (kAbsent for a missing neighbour).
   auto issue = [&](int s) {
-    const int c = m ? __ffs((int)m) - 1 : -1;
+    const int c = m ? __ffs((int)m) - 1 : -1;  // (PACK > 1: the first offset of a group)
     m &= m - 1;  // 0 stays 0
     cc[s] = c;
     unsigned rowb = kAbsent;
@@ -208,31 +251,37 @@ __global__ void __launch_bounds__(DEPTH > 4 ? 512 : 1024) k_igemm_wave(const Wav
   // Publishes the prefetched block in the wave's slab, takes the ticket of the block after it and
   // starts that block's prefetch, then puts the first DEPTH offsets in flight.
   int t_next = 0;
-  auto start_block = [&]() {
+  auto start_block = [&](int t_cur, int plane) {
 #pragma unroll
     for (int i = 0; i < kMapVecs; ++i) {
       const int e = lane + 64 * i;
       if (e < map_len) mapW[e] = mreg[i] < 0 ? (int)kAbsent : (int)((unsigned)mreg[i] * row_bytes);
     }
     unsigned bm = bm_next;
-    if (p.rowmask) {  // lanes 0..15 (and their three copies) hold the rows' masks
+    if (PLANES > 1 || p.rowmask) {  // lanes 0..15 (and their three copies) hold the rows' masks
       bm |= __shfl_xor(bm, 1);
       bm |= __shfl_xor(bm, 2);
       bm |= __shfl_xor(bm, 4);
       bm |= __shfl_xor(bm, 8);
     }
-    m = __builtin_amdgcn_readfirstlane(bm);
-    unsigned t = 0;
-    if (lane == 0) t = atomicAdd(&next_ticket, 1u);
-    t_next = (int)__builtin_amdgcn_readfirstlane(t);
-    prefetch_block(block_of(t_next < nj ? t_next : nj - 1));
+    m = present = __builtin_amdgcn_readfirstlane(bm);
+    if constexpr (PACK == 4) m = (m | m >> 1 | m >> 2 | m >> 3) & 0x11111111u;
+    if constexpr (PACK == 2) m = (m | m >> 1) & 0x55555555u;
+    if (plane + 1 < PLANES) {
+      prefetch_block(block_of(t_cur), plane + 1);
+    } else {
+      unsigned t = 0;
+      if (lane == 0) t = atomicAdd(&next_ticket, 1u);
+      t_next = (int)__builtin_amdgcn_readfirstlane(t);
+      prefetch_block(block_of(t_next < nj ? t_next : nj - 1), 0);
+    }
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int s = 0; s < DEPTH; ++s) issue(s);
   };
 
   // the first block's map rows travel while the weights are being staged
-  if (has_work) prefetch_block(block_of(wave));
+  if (has_work) prefetch_block(block_of(wave), 0);
 
   // ---- weights of this part -> LDS (once per workgroup), kFill loads in flight per thread
   constexpr int kFill = 8;
@@ -240,16 +289,17 @@ __global__ void __launch_bounds__(DEPTH > 4 ? 512 : 1024) k_igemm_wave(const Wav
     const unsigned slice = (unsigned)(p.C_in * p.C_out * 2);
     if (p.dgrad) {
       // B[kk = co][n = ci] = W[k][ci][co]: rows of W are already reduction-contiguous
-      const int chunks = width * BN * ROW_CHUNKS;
+      const int chunks = (PLANES * pitch + (PACK > 1 ? 1 : 0)) * BN * ROW_CHUNKS;
       for (int e0 = tid; e0 < chunks; e0 += kFill * blockDim.x) {
         uint4 v[kFill];
 #pragma unroll
         for (int u = 0; u < kFill; ++u) {
           const int e = e0 + u * blockDim.x;
-          const int q = e % ROW_CHUNKS, n = (e / ROW_CHUNKS) % BN, c = e / (ROW_CHUNKS * BN);
-          const int k = lo + c;
+          const int q = e % ROW_CHUNKS, n = (e / ROW_CHUNKS) % BN, cp = e / (ROW_CHUNKS * BN);
+          const int plane = PLANES > 1 ? cp / pitch : PACK > 1 && cp >= pitch, c = cp - plane * pitch;
+          const int k = lo + plane * width + c;
           const int ci = n0 + n, co = q * 8;
-          const bool ok = e < chunks && ci < p.C_in && co < p.C_out;
+          const bool ok = e < chunks && (PACK == 1 || (c < width && plane < PLANES)) && ci < p.C_in && co < p.C_out;
           const unsigned off = (unsigned)(p.mirror ? p.V - 1 - k : k) * slice + (unsigned)(ci * p.C_out + co) * 2u;
           v[u] = buf_load16(w_rsrc, ok ? off : 0xFFFFFFFFu);
         }
@@ -258,7 +308,7 @@ __global__ void __launch_bounds__(DEPTH > 4 ? 512 : 1024) k_igemm_wave(const Wav
           const int e = e0 + u * blockDim.x;
           const int q = e % ROW_CHUNKS, n = (e / ROW_CHUNKS) % BN, c = e / (ROW_CHUNKS * BN);
           if (e < chunks)
-            *reinterpret_cast<uint4*>(Ws + ((size_t)(c * BN + n) * ROW_CHUNKS + swz<KS>(q, n)) * 8) = v[u];
+            *reinterpret_cast<uint4*>(Ws + ((size_t)(c * BN + n) * ROW_CHUNKS + swz<KS, PACK>(q, n)) * 8) = v[u];
         }
       }
     } else {
@@ -267,20 +317,21 @@ __global__ void __launch_bounds__(DEPTH > 4 ? 512 : 1024) k_igemm_wave(const Wav
       // each output channel's four reduction steps with one 8-byte store (2-byte stores made this
       // fill 1.7 us slower than the input gradient's, whose rows are copied as they are).
       constexpr int kQuad = kFill / 4;  // 4-row groups in flight per thread
-      const int groups = width * (ROW_HALFS / 4) * (BN / 8);
+      const int groups = (PLANES * pitch + (PACK > 1 ? 1 : 0)) * (ROW_HALFS / 4) * (BN / 8);
       for (int e0 = tid; e0 < groups; e0 += kQuad * blockDim.x) {
         uint4 v[kQuad][4];
 #pragma unroll
         for (int u = 0; u < kQuad; ++u) {
           const int e = e0 + u * blockDim.x;
-          const int ng = e % (BN / 8), k4 = (e / (BN / 8)) % (ROW_HALFS / 4), c = e / ((BN / 8) * (ROW_HALFS / 4));
-          const int k = lo + c;
+          const int ng = e % (BN / 8), k4 = (e / (BN / 8)) % (ROW_HALFS / 4), cp = e / ((BN / 8) * (ROW_HALFS / 4));
+          const int plane = PLANES > 1 ? cp / pitch : PACK > 1 && cp >= pitch, c = cp - plane * pitch;
+          const int k = lo + plane * width + c;
           const int co = n0 + ng * 8;
           const unsigned base = (unsigned)(p.mirror ? p.V - 1 - k : k) * slice;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int ci = k4 * 4 + r;
-            const bool ok = e < groups && ci < p.C_in && co < p.C_out;
+            const bool ok = e < groups && (PACK == 1 || (c < width && plane < PLANES)) && ci < p.C_in && co < p.C_out;
             v[u][r] = buf_load16(w_rsrc, ok ? base + (unsigned)(ci * p.C_out + co) * 2u : 0xFFFFFFFFu);
           }
         }
@@ -300,7 +351,7 @@ __global__ void __launch_bounds__(DEPTH > 4 ? 512 : 1024) k_igemm_wave(const Wav
             const int sh = (i & 1) * 16;
             const unsigned h0 = (w[0][i >> 1] >> sh) & 0xFFFFu, h1 = (w[1][i >> 1] >> sh) & 0xFFFFu;
             const unsigned h2 = (w[2][i >> 1] >> sh) & 0xFFFFu, h3 = (w[3][i >> 1] >> sh) & 0xFFFFu;
-            *reinterpret_cast<uint2*>(Ws + ((size_t)(c * BN + n) * ROW_CHUNKS + swz<KS>(kk >> 3, n)) * 8 + (kk & 7)) =
+            *reinterpret_cast<uint2*>(Ws + ((size_t)(c * BN + n) * ROW_CHUNKS + swz<KS, PACK>(kk >> 3, n)) * 8 + (kk & 7)) =
                 make_uint2(h0 | (h1 << 16), h2 | (h3 << 16));
           }
         }
@@ -312,13 +363,18 @@ __global__ void __launch_bounds__(DEPTH > 4 ? 512 : 1024) k_igemm_wave(const Wav
 
   for (int t_cur = wave; t_cur < nj; t_cur = t_next) {
     const int orow_cur = orow_next;
-    start_block();
     f32x4 acc[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    int plane = 0;
     auto consume = [&](int s) {
-      const unsigned char* wk = smem + (unsigned)cc[s] * (unsigned)(BN * ROW_HALFS * 2);
+      int slice = cc[s];
+      if constexpr (PACK > 1) {  // an offset that no row of the block has meets zeros, as if it were skipped
+        slice += my_off;
+        slice = (present >> slice) & 1u ? plane * pitch + slice : PLANES * pitch;
+      }
+      const unsigned char* wk = smem + (unsigned)slice * (unsigned)(BN * ROW_HALFS * 2);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         uint4 af = fr[s][ks];
@@ -338,6 +394,8 @@ __global__ void __launch_bounds__(DEPTH > 4 ? 512 : 1024) k_igemm_wave(const Wav
 
     // The exits leave the loop directly (not through its latch), so that the wait-count
     // bookkeeping at the loop head sees only the steady state: DEPTH - 1 slots in flight.
+  next_plane:
+    start_block(t_cur, plane);
     for (;;) {
 #pragma unroll
       for (int rep = 0; rep < kLoopUnroll; ++rep) {
@@ -350,6 +408,7 @@ __global__ void __launch_bounds__(DEPTH > 4 ? 512 : 1024) k_igemm_wave(const Wav
       }
     }
   offsets_done:
+    if (PLANES > 1 && ++plane < PLANES) goto next_plane;
 
     // ---- output rows
     if (p.partial) {
@@ -388,10 +447,10 @@ __global__ void __launch_bounds__(DEPTH > 4 ? 512 : 1024) k_igemm_wave(const Wav
   }
 }
 
-template <typename T, int KS, int NB, int DEPTH, bool QUAD>
-int launch_wave_q(const WaveParams& p, dim3 grid, int threads, size_t smem, hipStream_t st) {
+template <typename T, int KS, int NB, int DEPTH, bool QUAD, int PACK = 1, int PLANES = 1>
+int launch_wave_q(const std::conditional_t<(PLANES > 1), PlaneParams, WaveParams>& p, dim3 grid, int threads, size_t smem, hipStream_t st) {
   static std::atomic<size_t> attr_bytes{0};  // largest dynamic LDS size announced for this instance so far
-  auto fn = k_igemm_wave<T, KS, NB, DEPTH, QUAD>;
+  auto fn = k_igemm_wave<T, KS, NB, DEPTH, QUAD, PACK, PLANES>;
   if (smem > attr_bytes.load(std::memory_order_acquire)) {
     SPC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)smem));
@@ -437,12 +496,28 @@ int launch_wave_ks(int ks, int nb, const WaveParams& p, dim3 grid, int threads, 
   return SPCONV_EINVAL;
 }
 
+// narrow reductions: eight offsets in flight are eight registers a lane, so that most blocks have all of theirs on the way
+template <typename T, int PACK, int PLANES>
+int launch_wave_packed(int nb, const std::conditional_t<(PLANES > 1), PlaneParams, WaveParams>& p, dim3 grid, int threads, size_t smem, hipStream_t st) {
+  switch (nb) {
+    case 1: return launch_wave_q<T, 1, 1, 8, false, PACK, PLANES>(p, grid, threads, smem, st);
+    case 2: return launch_wave_q<T, 1, 2, 8, false, PACK, PLANES>(p, grid, threads, smem, st);
+    case 4: return launch_wave_q<T, 1, 4, 8, false, PACK, PLANES>(p, grid, threads, smem, st);
+  }
+  return SPCONV_EINVAL;
+}
+
 constexpr size_t kLdsBudget = 160 * 1024 - 64;  // (64 bytes for the static ticket counter)
 
-size_t map_bytes_for(int max_width) { return (size_t)round_up((int64_t)16 * max_width * 4, 16); }
+// Offsets that share a matrix instruction.  Reductions over 9 to 16 channels only pair offsets where that makes their weights fit
+// (PLANES): pairs of consecutive offsets are both absent too rarely (100k rows 16 -> 16: 14 pairs a block against 18 offsets,
+// 11.9 us against 11.6).  A 1x1x1 map has nothing to share.
+int pack_for(int c_red, int width, bool planes = false) { return width < 2 || c_red > 16 ? 1 : c_red <= 8 ? 4 : planes ? 2 : 1; }
 
-size_t slab_bytes_for(int max_width, int bn, int parts) {
-  return map_bytes_for(max_width) + (parts == 1 ? (size_t)16 * bn * 2 : 0);
+size_t map_bytes_for(int max_width, int pack) { return (size_t)round_up(16 * round_up(max_width, pack) * 4, 16); }
+
+size_t slab_bytes_for(int max_width, int pack, int bn, int parts) {
+  return map_bytes_for(max_width, pack) + (parts == 1 ? (size_t)16 * bn * 2 : 0);
 }
 
 }  // namespace
@@ -462,7 +537,7 @@ int igemm_wave_pick_bn(int V, int n_split, int c_red, int c_out, int tile_n, int
     // unsorted maps: two 32-column tiles beat one of 64 (100k voxels, 32 -> 64: 24.3 us against 26.7 us)
     if (tile_n == 0 && bn == 64 && n_split == 0) continue;
     const size_t w = (size_t)max_width * bn * ks * 64;
-    const size_t slab = slab_bytes_for(max_width, bn, parts);
+    const size_t slab = slab_bytes_for(max_width, pack_for(c_red, max_width), bn, parts);
     for (int waves : {16, 8}) {
       if (w + (size_t)waves * slab <= kLdsBudget) {
         if (waves_out) *waves_out = waves;
@@ -493,9 +568,11 @@ int igemm_wave_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
   for (int i = 0; i < ps.parts; ++i) s->max_width = std::max(s->max_width, ps.width[i]);
   // the map, the permutation and the masks are read through 32-bit buffer offsets as well
   if ((uint64_t)ps.rows_pad * s->max_width * 4 >= 0xFFFF0000ull) return SPCONV_EINVAL;
-  s->slab_bytes = (int)slab_bytes_for(s->max_width, s->bn, ps.parts);
-  s->map_bytes = (int)map_bytes_for(s->max_width);
-  s->lds_bytes = (size_t)s->max_width * s->bn * s->ks * 64 + (size_t)waves * s->slab_bytes;
+  s->pack = pack_for(c_red, s->max_width);
+  s->slab_bytes = (int)slab_bytes_for(s->max_width, s->pack, s->bn, ps.parts);
+  s->map_bytes = (int)map_bytes_for(s->max_width, s->pack);
+  s->weight_bytes = s->max_width * s->bn * s->ks * 64;  // (more than packed weights need)
+  s->lds_bytes = (size_t)s->weight_bytes + (size_t)waves * s->slab_bytes;
   if (s->lds_bytes > kLdsBudget) return SPCONV_EINVAL;
   const int n_tiles_n = (int)ceil_div(c_out, s->bn);
   // persistent workgroups: about one per CU over all (n-tile, part) slices, each wave gets >= 1 block
@@ -506,6 +583,80 @@ int igemm_wave_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
   s->grid[1] = (unsigned)n_tiles_n;
   s->grid[2] = (unsigned)ps.parts;
   return SPCONV_OK;
+}
+
+// All planes of a K = 5 map in one launch: 16-bit layers that reduce over at most 16 channels, in map order.  Wider ones
+// run a launch per plane: their 125 weight slices do not fit.
+int igemm_wave_planes_shape(int64_t rows, int64_t rows_src, int c_red, int c_out, WaveShape* s) {
+  constexpr int kWidth = 25;
+  *s = WaveShape{};
+  if (c_red > 16) return SPCONV_EINVAL;
+  WaveShape one;
+  SPC_TRY(igemm_wave_shape(kWidth, 0, rows, rows_src, c_red, c_out, 0, &one));
+  one.pack = pack_for(c_red, kWidth, true);
+  one.map_bytes = (int)map_bytes_for(kWidth, one.pack);
+  for (int bn : {32, 16}) {
+    for (int waves : {16, 8}) {
+      if (bn > 16 && bn >= 2 * c_out) continue;
+      *s = one;
+      s->bn = bn;
+      s->waves = waves;
+      s->threads = waves * 64;
+      s->slab_bytes = (int)slab_bytes_for(kWidth, s->pack, bn, 1);
+      s->weight_bytes = (kPlanes * (int)round_up(kWidth, s->pack) + 1) * bn * 64 / s->pack;
+      s->lds_bytes = (size_t)s->weight_bytes + (size_t)waves * s->slab_bytes;
+      if (s->lds_bytes > kLdsBudget) continue;
+      const int n_tiles_n = (int)ceil_div(c_out, bn);
+      int64_t wgs = std::max<int64_t>(1, 256 / n_tiles_n);
+      wgs = std::min<int64_t>(wgs, ceil_div(ceil_div(rows, 16), waves));
+      if (wgs > 8) wgs = wgs / 8 * 8;
+      s->grid[0] = (unsigned)wgs;
+      s->grid[1] = (unsigned)n_tiles_n;
+      s->grid[2] = 1;
+      return SPCONV_OK;
+    }
+  }
+  return SPCONV_EINVAL;
+}
+
+int igemm_wave_planes_run(const spconv_kmap* km, const IgemmArgs& a, hipStream_t st) {
+  const int64_t rows = km->n_out;
+  if (rows == 0) return SPCONV_OK;
+  PlaneParams p{};
+  p.feats = a.feats;
+  p.weights = a.weights;
+  p.out = a.out;
+  p.rows = rows;
+  p.n_blocks = ceil_div(rows, 16);
+  p.parts = 1;
+  p.V = km->V;
+  p.C_in = a.C_in;
+  p.C_out = a.C_out;
+  p.dgrad = a.dgrad;
+  p.mirror = a.mirror;
+  p.c_red = a.dgrad ? a.C_out : a.C_in;
+  p.c_out = a.dgrad ? a.C_in : a.C_out;
+  WaveShape sh;
+  SPC_TRY(igemm_wave_planes_shape(rows, km->n_in, p.c_red, p.c_out, &sh));
+  p.feats_bytes = sh.feats_bytes;
+  for (int g = 0; g < kPlanes; ++g) {
+    p.plane_map[g] = km->groups[(size_t)g]->out_side.map.as<int>();
+    p.plane_mask[g] = km->groups[(size_t)g]->out_side.mask.as<unsigned>();
+  }
+  const uint64_t rows_pad = (uint64_t)km->groups[0]->out_side.rows_pad;
+  p.width[0] = km->groups[0]->V;
+  p.map_part_bytes[0] = (unsigned)(rows_pad * p.width[0] * 4);
+  p.rows_pad_bytes = (unsigned)(rows_pad * 4);
+  p.slab_bytes = sh.slab_bytes;
+  p.map_bytes = sh.map_bytes;
+  p.weight_bytes = sh.weight_bytes;
+  const dim3 grid(sh.grid[0], sh.grid[1], sh.grid[2]);
+  const int nb = sh.bn / 16;
+  if (a.dtype == SPCONV_F16)
+    return sh.pack == 4 ? launch_wave_packed<_Float16, 4, kPlanes>(nb, p, grid, sh.threads, sh.lds_bytes, st)
+                        : launch_wave_packed<_Float16, 2, kPlanes>(nb, p, grid, sh.threads, sh.lds_bytes, st);
+  return sh.pack == 4 ? launch_wave_packed<__bf16, 4, kPlanes>(nb, p, grid, sh.threads, sh.lds_bytes, st)
+                      : launch_wave_packed<__bf16, 2, kPlanes>(nb, p, grid, sh.threads, sh.lds_bytes, st);
 }
 
 int igemm_wave_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& plan, const IgemmArgs& a,
@@ -550,9 +701,15 @@ int igemm_wave_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& 
   p.blocks_bytes = (unsigned)((uint64_t)plan.n_tiles * 4);
   p.slab_bytes = sh.slab_bytes;
   p.map_bytes = sh.map_bytes;
+  p.weight_bytes = sh.weight_bytes;
   p.xcd_ranges = plan.slabs && sh.grid[0] % 8 == 0;  // (contiguous ranges of a purely bitmask-sorted order are unequal work)
-  p.quad = plan.n_split > 0;
+  p.quad = plan.n_split > 0 && sh.pack == 1;
   dim3 grid(sh.grid[0], sh.grid[1], sh.grid[2]);
+  if (sh.pack > 1) {
+    const int nb = sh.bn / 16;
+    if (a.dtype == SPCONV_F16) return launch_wave_packed<_Float16, 4, 1>(nb, p, grid, sh.threads, sh.lds_bytes, st);
+    return launch_wave_packed<__bf16, 4, 1>(nb, p, grid, sh.threads, sh.lds_bytes, st);
+  }
   if (a.dtype == SPCONV_F16) return launch_wave_ks<_Float16>(sh.ks, sh.bn / 16, p, grid, sh.threads, sh.lds_bytes, st);
   return launch_wave_ks<__bf16>(sh.ks, sh.bn / 16, p, grid, sh.threads, sh.lds_bytes, st);
 }

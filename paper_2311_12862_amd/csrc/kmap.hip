@@ -642,7 +642,7 @@ struct Planes5 {
   unsigned* mask[5];
 };
 __global__ void __launch_bounds__(256)
-    k_probe_planes5(const int4* __restrict__ rows, int n_rows, const RunSlot* __restrict__ tab, int log_cap,
+    k_probe_planes5(const int4* __restrict__ rows, int n_rows, long long rows_pad, const RunSlot* __restrict__ tab, int log_cap,
                     Planes5 pl, Ctl* ctl) {
   __shared__ unsigned wave_pairs[4];
   constexpr int VP = 25, LPR = 5, RPW = 12;
@@ -651,9 +651,9 @@ __global__ void __launch_bounds__(256)
   const long long wave = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int sub = lane / LPR, col = lane - sub * LPR;
   const long long row = wave * RPW + sub;
-  const bool active = (sub < RPW) && (row < n_rows);
+  const bool active = (sub < RPW) && (row < rows_pad);
   int nb[5] = {-1, -1, -1, -1, -1};
-  if (active) {
+  if (active && row < n_rows) {
     const int4 c = rows[row];
     const int tx = c.y + g - 2, ty = c.z + col - 2;
     if (coord_ok(c.x, c.y, c.z, c.w) && coord_ok(c.x, tx, ty, c.w)) {  // (run indices and cells beside the range: as above)
@@ -674,6 +674,8 @@ __global__ void __launch_bounds__(256)
       // a row that does not find itself at its own place shares it with another row
       if (g == 2 && col == 2 && nb[2] != (int)row) atomicOr(&ctl->flags, FLAG_DUP);
     }
+  }
+  if (active) {
     int* dst = pl.map[g] + row * VP + LPR * col;
 #pragma unroll
     for (int d = 0; d < 5; ++d) dst[d] = nb[d];
@@ -1048,14 +1050,17 @@ int build_submanifold5(spconv_kmap* km, const int4* rows, int64_t N, hipStream_t
     sub->V = VP;
     sub->n_in = sub->n_out = N;
     sub->build_stream = sub->last_stream = st;
-    SPC_TRY(alloc_side(sub->out_side, N, VP, st));
+    sub->out_side.rows = N;
+    sub->out_side.rows_pad = round_up(N, kRowPad);
+    SPC_TRY(sub->out_side.map.alloc((size_t)sub->out_side.rows_pad * VP * sizeof(int)));  // (padding rows are the probe's)
+    SPC_TRY(sub->out_side.mask.alloc((size_t)sub->out_side.rows_pad * sizeof(unsigned)));
     sub->out_side.ready = true;
     pl.map[g] = sub->out_side.map.as<int>();
     pl.mask[g] = sub->out_side.mask.as<unsigned>();
     km->groups.push_back(std::move(sub));
   }
-  hipLaunchKernelGGL(k_probe_planes5, dim3(blocks_for(ceil_div(N, 12), 4), 5), dim3(256), 0, st, rows, (int)N,
-                     tab.as<RunSlot>(), lc, pl, ctl);
+  hipLaunchKernelGGL(k_probe_planes5, dim3(blocks_for(ceil_div(round_up(N, kRowPad), 12), 4), 5), dim3(256), 0, st, rows, (int)N,
+                     (long long)round_up(N, kRowPad), tab.as<RunSlot>(), lc, pl, ctl);
   SPC_LAUNCH_CHECK();
   HostResult h{};
   SPC_TRY(read_ctl(ctl, &h, st));
