@@ -10,8 +10,8 @@
 // slot per key (64-bit packed coordinate + row index) in an open-addressing
 // table at load factor <= 0.5 and one probe lane per (output row, offset), so
 // that map writes are contiguous per wave and the bitmask comes from a wave
-// ballot; stride-2 3x3x3 maps are filled from the input side; K = 5 maps are
-// held as five planes of 25 offsets.
+// ballot; stride-2 maps are built over a bit per cell of the coarse points'
+// box; K = 5 maps are held as five planes of 25 offsets.
 #include "common.h"
 
 #include <atomic>
@@ -28,8 +28,10 @@ namespace {
 
 constexpr unsigned long long kEmpty = ~0ull;
 
-enum : unsigned long long { FLAG_RANGE = 1, FLAG_DUP = 2, FLAG_FULL = 4, FLAG_SORT = 8 };  // SORT: a sort's bounded wait ran out
+// SORT: a sort's bounded wait ran out; BOX: the coarse points' bounding box is too large for a bit per cell
+enum : unsigned long long { FLAG_RANGE = 1, FLAG_DUP = 2, FLAG_FULL = 4, FLAG_SORT = 8, FLAG_BOX = 16 };
 constexpr int kRetryGeneralSort = 1;  // (internal) build again with the general sort
+constexpr int kRetryTable = 2;        // (internal) build again with a hash table of the coarse points
 
 // Control block read back by the host at the build's synchronisation point.  The pair counter
 // is spread over 64 cache lines (one atomic per probe workgroup) so that the adds do not queue
@@ -387,6 +389,296 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// ---- stride-2 builds over a bit per cell ----
+// The coarse points floor(p / 2) of a scan fill a box of a few hundred cells per row.  One bit per cell, set by the rows, is the
+// de-duplication, the lexicographic sort (the order of the bits) and the look-up table (a point's row is the number of set
+// bits before its own: a prefix per 64-bit word and a population count) at once; nothing is hashed, sorted or probed, and the
+// host waits once, at the end.  Launches: the box, clearing, marking, counting, prefixes (and the presets of
+// the map), the map from the input side (and the coordinates), masks.  Against de-duplication through a hash table, a radix sort and table
+// look-ups, whole builds in us: LiDAR-like scans of 2k rows 71 -> 36, 10k 80 -> 40, 30k 89 -> 46, 100k 109 -> 64, 200k (127k
+// outputs) 178 -> 79, 400k 227 -> 124; a room of 300k 135 -> 96.  What is left is launches of 4 to 5 us and the marks: an atomic
+// per row, which the memory side takes at 10 per ns (200k rows: 20 us of the 69 of kernels).
+// A box of more than kCellsPerRow cells a row (a scan of 5 cm voxels has about 450) is left to the table; the kernels behind
+// the first two then find nothing to do, which costs such a build 25 us (20k points spread over 60,000 cells an axis: 190 -> 215).
+constexpr int kBoxBlocks = 256;
+constexpr int kCellsPerRow = 2048;
+constexpr int kChunkWords = 2048;  // 64-bit words per workgroup and step
+constexpr int64_t kMaxBoxWords = 1ll << 25;
+
+struct Box {
+  int lo[4];         // of (b, x, y, z)
+  unsigned span[4];  // (up to 65536 each)
+  unsigned words;    // 64-bit words of the bitmap; 0: nothing to do
+  unsigned flags;
+};
+
+__device__ __forceinline__ unsigned cell_of(const Box& box, int b, int x, int y, int z) {  // (in the box: below 2^31)
+  return (((unsigned)(b - box.lo[0]) * box.span[1] + (unsigned)(x - box.lo[1])) * box.span[2] + (unsigned)(y - box.lo[2])) * box.span[3] +
+         (unsigned)(z - box.lo[3]);
+}
+
+// partial[block] = {least, largest of (b, floor(x / 2), ..), flags} over the rows that the block visits
+__global__ void __launch_bounds__(256)
+    k_box_bounds(const int4* __restrict__ coords, int n, int4* __restrict__ keep, int* __restrict__ partial) {
+  __shared__ int red[4][9];
+  int v[9] = {0x7FFFFFFF, 0x7FFFFFFF, 0x7FFFFFFF, 0x7FFFFFFF, (int)0x80000000, (int)0x80000000, (int)0x80000000, (int)0x80000000, 0};
+  constexpr int U = 4;
+  const int step = gridDim.x * 256;
+  for (int r0 = blockIdx.x * 256 + threadIdx.x; r0 < n; r0 += U * step) {
+    int4 c[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) c[u] = (long long)r0 + (long long)u * step < n ? coords[r0 + u * step] : make_int4(-1, 0, 0, 0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if ((long long)r0 + (long long)u * step >= n) continue;
+      keep[r0 + u * step] = c[u];
+      if (!coord_ok(c[u].x, c[u].y, c[u].z, c[u].w)) {
+        v[8] = (int)FLAG_RANGE;
+        continue;
+      }
+      const int q[4] = {c[u].x, c[u].y >> 1, c[u].z >> 1, c[u].w >> 1};
+#pragma unroll
+      for (int a = 0; a < 4; ++a) v[a] = min(v[a], q[a]), v[4 + a] = max(v[4 + a], q[a]);
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < 9; ++a)
+    for (int o = 32; o > 0; o >>= 1) {
+      const int w = __shfl_xor(v[a], o);
+      v[a] = a < 4 ? min(v[a], w) : a < 8 ? max(v[a], w) : v[a] | w;
+    }
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int a = 0; a < 9; ++a) red[threadIdx.x >> 6][a] = v[a];
+  __syncthreads();
+  if (threadIdx.x < 9) {
+    const int a = threadIdx.x;
+    int w = red[0][a];
+    for (int i = 1; i < 4; ++i) w = a < 4 ? min(w, red[i][a]) : a < 8 ? max(w, red[i][a]) : w | red[i][a];
+    partial[blockIdx.x * 9 + a] = w;
+  }
+}
+
+// Every workgroup works out the box; the bitmap is cleared as far as it reaches; the first one clears the control block and
+// leaves the box for the launches behind.
+__global__ void __launch_bounds__(256)
+    k_box_clear(const int* __restrict__ partial, int n_partial, long long max_words, ulonglong2* __restrict__ bits, Box* box_out, Ctl* ctl) {
+  __shared__ int red[4][9];
+  __shared__ Box s_box;
+  const int t = threadIdx.x;
+  int v[9];  // (kBoxBlocks == 256 partials at most: one per thread)
+#pragma unroll
+  for (int a = 0; a < 9; ++a)
+    v[a] = t < n_partial ? partial[t * 9 + a] : a < 4 ? 0x7FFFFFFF : a < 8 ? (int)0x80000000 : 0;
+#pragma unroll
+  for (int a = 0; a < 9; ++a)
+    for (int o = 32; o > 0; o >>= 1) {
+      const int w = __shfl_xor(v[a], o);
+      v[a] = a < 4 ? min(v[a], w) : a < 8 ? max(v[a], w) : v[a] | w;
+    }
+  if ((t & 63) == 0)
+#pragma unroll
+    for (int a = 0; a < 9; ++a) red[t >> 6][a] = v[a];
+  __syncthreads();
+  if (t == 0) {
+    Box b;
+    unsigned long long cells = 1;
+    b.flags = 0;
+    for (int i = 0; i < 4; ++i) b.flags |= (unsigned)red[i][8];
+    for (int a = 0; a < 4; ++a) {
+      int lo = red[0][a], hi = red[0][4 + a];
+      for (int i = 1; i < 4; ++i) lo = min(lo, red[i][a]), hi = max(hi, red[i][4 + a]);
+      b.lo[a] = lo;
+      b.span[a] = lo <= hi ? (unsigned)(hi - lo) + 1u : 0u;  // (no valid row: an empty box)
+      cells = cells > (1ull << 40) ? cells : cells * b.span[a];
+    }
+    const unsigned long long words = (cells + 63) / 64;
+    if (words > (unsigned long long)max_words) b.flags |= (unsigned)FLAG_BOX;
+    b.words = words > (unsigned long long)max_words ? 0u : (unsigned)words;
+    s_box = b;
+    if (blockIdx.x == 0) *box_out = b;
+  }
+  __syncthreads();
+  const long long pairs_of_words = ((long long)s_box.words + 1) / 2;  // (the buffer holds an even number)
+  for (long long i = (long long)blockIdx.x * 256 + t; i < pairs_of_words; i += (long long)gridDim.x * 256)
+    bits[i] = make_ulonglong2(0ull, 0ull);
+  if (blockIdx.x == 0) {
+    if (t == 0) {
+      ctl->flags = s_box.flags;
+      ctl->count = 0;
+      ctl->tick_top = 0;
+    }
+    if (t < kPairSlots) {
+      ctl->pairs[t * 16] = 0;
+      ctl->tick[t * 16] = 0;
+      ctl->entries[t * 16] = 0;
+      ctl->key_or[t * 16] = 0;
+      ctl->key_and[t * 16] = ~0ull;
+    }
+  }
+}
+
+__global__ void __launch_bounds__(256)
+    k_box_mark(const int4* __restrict__ coords, int n, const Box* __restrict__ box_in, unsigned* __restrict__ bits) {
+  const Box box = *box_in;
+  const int j = blockIdx.x * 256 + threadIdx.x;
+  if (j >= n || !box.words) return;
+  const int4 c = coords[j];
+  if (!coord_ok(c.x, c.y, c.z, c.w)) return;
+  const unsigned cell = cell_of(box, c.x, c.y >> 1, c.z >> 1, c.w >> 1);
+  atomicOr(&bits[cell >> 5], 1u << (cell & 31));
+}
+
+// totals[chunk] = set bits of kChunkWords words
+__global__ void __launch_bounds__(256)
+    k_box_count(const Box* __restrict__ box_in, const unsigned long long* __restrict__ bits, unsigned* __restrict__ totals) {
+  __shared__ unsigned red[4];
+  const unsigned words = box_in->words, chunks = (words + kChunkWords - 1) / kChunkWords;
+  for (unsigned c = blockIdx.x; c < chunks; c += gridDim.x) {
+    unsigned long long w[kChunkWords / 256];
+#pragma unroll
+    for (int i = 0; i < kChunkWords / 256; ++i) {
+      const unsigned at = c * kChunkWords + i * 256 + threadIdx.x;
+      w[i] = at < words ? bits[at] : 0ull;
+    }
+    unsigned sum = 0;
+#pragma unroll
+    for (int i = 0; i < kChunkWords / 256; ++i) sum += (unsigned)__popcll(w[i]);
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) totals[c] = red[0] + red[1] + red[2] + red[3];
+    __syncthreads();
+  }
+}
+
+// The prefix of every word, and the presets of the map (rows up to the padding) and of the padding's masks.  A workgroup
+// takes consecutive chunks; it adds up the totals before them itself.
+__global__ void __launch_bounds__(256)
+    k_box_prefix(const Box* __restrict__ box_in, const unsigned long long* __restrict__ bits, const unsigned* __restrict__ totals,
+               unsigned* __restrict__ prefix, int V, uint4* __restrict__ map, unsigned* __restrict__ mask, Ctl* ctl) {
+  __shared__ unsigned s_before[4], s_all[4], s_wave[4];
+  const unsigned words = box_in->words, chunks = (words + kChunkWords - 1) / kChunkWords;
+  const unsigned per = (chunks + gridDim.x - 1) / gridDim.x, c0 = blockIdx.x * per, c1 = min(chunks, c0 + per);
+  const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
+  unsigned before = 0, all = 0;
+  for (unsigned i0 = 0; i0 < chunks; i0 += 8 * 256) {
+    unsigned v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const unsigned i = i0 + u * 256 + threadIdx.x;
+      v[u] = i < chunks ? totals[i] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      all += v[u];
+      if (i0 + u * 256 + threadIdx.x < c0) before += v[u];
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    before += __shfl_xor(before, o);
+    all += __shfl_xor(all, o);
+  }
+  if (lane == 0) s_before[wib] = before, s_all[wib] = all;
+  __syncthreads();
+  unsigned base = s_before[0] + s_before[1] + s_before[2] + s_before[3];
+  const unsigned total = s_all[0] + s_all[1] + s_all[2] + s_all[3];
+  if (blockIdx.x == 0 && threadIdx.x == 0) ctl->count = total;
+  constexpr int W = kChunkWords / 256;  // words per lane: a wave owns 64 * W consecutive ones
+  for (unsigned c = c0; c < c1; ++c) {
+    const unsigned first = c * kChunkWords + wib * (64 * W);
+    unsigned long long w[W];
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      const unsigned at = first + i * 64 + lane;
+      w[i] = at < words ? bits[at] : 0ull;
+    }
+    unsigned mine[W], run = 0;  // set bits of the wave before this lane's word
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      const unsigned cnt = (unsigned)__popcll(w[i]);
+      unsigned incl = cnt;
+      for (int o = 1; o < 64; o <<= 1) {
+        const unsigned up = __shfl_up(incl, o);
+        if (lane >= o) incl += up;
+      }
+      mine[i] = run + incl - cnt;
+      run += __shfl(incl, 63);
+    }
+    __syncthreads();
+    if (lane == 0) s_wave[wib] = run;
+    __syncthreads();
+    unsigned at0 = base;
+    for (int i = 0; i < wib; ++i) at0 += s_wave[i];
+    base += s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      const unsigned at = first + i * 64 + lane;
+      if (at < words) prefix[at] = at0 + mine[i];
+    }
+  }
+  const unsigned rows_pad = (total + kRowPad - 1) / kRowPad * kRowPad;
+  const long long vecs = (long long)rows_pad * V / 4;
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < vecs; i += (long long)gridDim.x * 256)
+    map[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+  if (blockIdx.x == 0 && total + threadIdx.x < rows_pad) mask[total + threadIdx.x] = 0u;
+}
+
+// Row of a coarse point, or -1.
+__device__ __forceinline__ int box_find(const Box& box, const unsigned long long* bits, const unsigned* prefix, int b, int x, int y, int z) {
+  if ((unsigned)(x - box.lo[1]) >= box.span[1] || (unsigned)(y - box.lo[2]) >= box.span[2] || (unsigned)(z - box.lo[3]) >= box.span[3]) return -1;
+  const unsigned cell = cell_of(box, b, x, y, z);
+  const unsigned long long w = bits[cell >> 6];
+  const unsigned before = prefix[cell >> 6];
+  const unsigned long long bit = 1ull << (cell & 63);
+  return w & bit ? (int)(before + (unsigned)__popcll(w & (bit - 1))) : -1;
+}
+
+// The map from the input side (see k_scatter_down3), and the coarse points: every input meets the output floor(p / 2) (K = 2:
+// only that one) and writes its coordinates; inputs of one output write the same (expanding the bits instead took 35 us where
+// many stand in one word).
+template <int K>
+__global__ void __launch_bounds__(256)
+    k_box_scatter(const int4* __restrict__ rows, int n_rows, const Box* __restrict__ box_in, const unsigned long long* __restrict__ bits,
+                  const unsigned* __restrict__ prefix, int* __restrict__ map, int4* __restrict__ coarse, Ctl* ctl) {
+  __shared__ unsigned wave_pairs[4];
+  constexpr int LPR = K == 3 ? 8 : 1, V = K * K * K;
+  const Box box = *box_in;
+  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+  const long long row = t / LPR;
+  const int cand = K == 3 ? (int)(t & 7) : 0;
+  bool found = false;
+  if (row < n_rows && box.words) {
+    const int4 c = rows[row];
+    const int pc[3] = {c.y, c.z, c.w};
+    int q[3], k = 0;
+    bool ok = coord_ok(c.x, c.y, c.z, c.w);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int up = (cand >> (2 - a)) & 1;
+      q[a] = (pc[a] >> 1) + up;
+      const int d = pc[a] - 2 * q[a];
+      ok = ok && d >= -1;  // (d <= 1 always)
+      k = k * K + (K == 3 ? d + 1 : d);
+    }
+    if (ok) {
+      const int n = box_find(box, bits, prefix, c.x, q[0], q[1], q[2]);
+      if (n >= 0) {
+        map[(long long)n * V + k] = (int)row;
+        if (cand == 0) coarse[n] = make_int4(c.x, q[0], q[1], q[2]);
+        found = true;
+      }
+    }
+  }
+  const unsigned long long bal = __ballot(found);
+  if ((threadIdx.x & 63) == 0) wave_pairs[threadIdx.x >> 6] = (unsigned)__popcll(bal);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned n = wave_pairs[0] + wave_pairs[1] + wave_pairs[2] + wave_pairs[3];
+    if (n) atomicAdd(&ctl->pairs[(blockIdx.x % kPairSlots) * 16], (unsigned long long)n);
+  }
+}
+
 // Plain fills (in place of memset calls, which must stay out of anything a caller may capture).
 // The K = 1 map of a row set: row r meets itself; rows of the padding meet nothing.
 __global__ void __launch_bounds__(256) k_identity_map(int* __restrict__ map, unsigned* __restrict__ mask,
@@ -720,7 +1012,8 @@ template <int V, int LOADS> struct MaskRows {
 };
 template <int V, int LOADS>
 __global__ void __launch_bounds__(256) k_mask_from_map(const int* __restrict__ map, int n_rows,
-                                                       unsigned* __restrict__ mask, Ctl* ctl) {
+                                                       unsigned* __restrict__ mask, Ctl* ctl, bool counted) {
+  if (counted) n_rows = min(n_rows, (int)ctl->count);  // (the launch covers the most rows that there can be)
   __shared__ unsigned wave_cnt[4];
   typedef MaskRows<V, LOADS> R;
   const int lane = threadIdx.x & 63;
@@ -945,13 +1238,14 @@ int read_ctl(const Ctl* ctl, HostResult* res, hipStream_t st) {
   return status;
 }
 
-template <int V> int masks_from_map(const int* map, int64_t rows, unsigned* mask, Ctl* ctl, hipStream_t st) {
+// counted: ctl->count rows, at most `rows`
+template <int V> int masks_from_map(const int* map, int64_t rows, unsigned* mask, Ctl* ctl, hipStream_t st, bool counted = false) {
   constexpr int kMany = V == 27 ? 8 : 1;
   auto blocks = [&](int per_wave) { return dim3(blocks_for(ceil_div(rows, per_wave), 4)); };
   if (rows >= 65536)
-    hipLaunchKernelGGL((k_mask_from_map<V, kMany>), blocks(MaskRows<V, kMany>::per_wave), dim3(256), 0, st, map, (int)rows, mask, ctl);
+    hipLaunchKernelGGL((k_mask_from_map<V, kMany>), blocks(MaskRows<V, kMany>::per_wave), dim3(256), 0, st, map, (int)rows, mask, ctl, counted);
   else
-    hipLaunchKernelGGL((k_mask_from_map<V, 1>), blocks(MaskRows<V, 1>::per_wave), dim3(256), 0, st, map, (int)rows, mask, ctl);
+    hipLaunchKernelGGL((k_mask_from_map<V, 1>), blocks(MaskRows<V, 1>::per_wave), dim3(256), 0, st, map, (int)rows, mask, ctl, counted);
   SPC_LAUNCH_CHECK();
   return SPCONV_OK;
 }
@@ -1076,6 +1370,70 @@ int build_submanifold5(spconv_kmap* km, const int4* rows, int64_t N, hipStream_t
   return km->build_status;
 }
 
+// Stride-2 builds (K = 2, 3) over a bit per cell of the coarse points' box; kRetryTable where the box is too large.
+int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t st) {
+  const int V = K * K * K;
+  const int64_t max_words = std::min<int64_t>(std::max<int64_t>(N * (kCellsPerRow / 64), 1 << 14), kMaxBoxWords);
+  const int64_t max_chunks = ceil_div(max_words, kChunkWords);
+  DevBuf ctl_buf, own_rows, coarse_rows, small, bits, prefix;
+  SPC_TRY(ctl_buf.alloc(sizeof(Ctl)));
+  Ctl* ctl = ctl_buf.as<Ctl>();
+  SPC_TRY(own_rows.alloc((size_t)N * 16));
+  SPC_TRY(coarse_rows.alloc((size_t)N * 16));
+  const size_t partial_bytes = (size_t)kBoxBlocks * 9 * sizeof(int);
+  SPC_TRY(small.alloc(sizeof(Box) + partial_bytes + (size_t)max_chunks * sizeof(unsigned)));
+  Box* box = small.as<Box>();
+  int* partial = reinterpret_cast<int*>(box + 1);
+  unsigned* totals = reinterpret_cast<unsigned*>(small.as<char>() + sizeof(Box) + partial_bytes);
+  if (bits.alloc((size_t)(max_words + 1) * 8) != SPCONV_OK || prefix.alloc((size_t)max_words * 4) != SPCONV_OK)
+    return kRetryTable;  // (the table is smaller)
+  // sized for as many outputs as inputs: their number is read at the end
+  SideMap& side = km->out_side;
+  const int64_t most = round_up(N, kRowPad);
+  SPC_TRY(side.map.alloc((size_t)most * V * sizeof(int)));
+  SPC_TRY(side.mask.alloc((size_t)most * sizeof(unsigned)));
+  int* map = side.map.as<int>();
+  const unsigned n_partial = (unsigned)std::min<int64_t>(ceil_div(N, 1024), kBoxBlocks);
+  hipLaunchKernelGGL(k_box_bounds, dim3(n_partial), dim3(256), 0, st, rows, (int)N, own_rows.as<int4>(), partial);
+  SPC_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_box_clear, dim3((unsigned)std::min<int64_t>(ceil_div(max_words, 2048), 1024)), dim3(256), 0, st, partial,
+                     (int)n_partial, (long long)max_words, bits.as<ulonglong2>(), box, ctl);
+  SPC_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_box_mark, dim3(blocks_for(N, 256)), dim3(256), 0, st, rows, (int)N, box, bits.as<unsigned>());
+  SPC_LAUNCH_CHECK();
+  const dim3 chunk_grid((unsigned)std::min<int64_t>(max_chunks, 1024));
+  hipLaunchKernelGGL(k_box_count, chunk_grid, dim3(256), 0, st, box, bits.as<unsigned long long>(), totals);
+  SPC_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_box_prefix, chunk_grid, dim3(256), 0, st, box, bits.as<unsigned long long>(), totals, prefix.as<unsigned>(),
+                     V, side.map.as<uint4>(), side.mask.as<unsigned>(), ctl);
+  SPC_LAUNCH_CHECK();
+  const dim3 scatter_grid(blocks_for(K == 3 ? N * 8 : N, 256));
+  if (K == 3)
+    hipLaunchKernelGGL(k_box_scatter<3>, scatter_grid, dim3(256), 0, st, rows, (int)N, box, bits.as<unsigned long long>(),
+                       prefix.as<unsigned>(), map, coarse_rows.as<int4>(), ctl);
+  else
+    hipLaunchKernelGGL(k_box_scatter<2>, scatter_grid, dim3(256), 0, st, rows, (int)N, box, bits.as<unsigned long long>(),
+                       prefix.as<unsigned>(), map, coarse_rows.as<int4>(), ctl);
+  SPC_LAUNCH_CHECK();
+  SPC_TRY(K == 3 ? masks_from_map<27>(map, N, side.mask.as<unsigned>(), ctl, st, true)
+                 : masks_from_map<8>(map, N, side.mask.as<unsigned>(), ctl, st, true));
+  HostResult h{};
+  SPC_TRY(read_ctl(ctl, &h, st));
+  if (h.entries != h.pairs) h.flags |= FLAG_DUP;  // two rows wrote one entry
+  SPC_TRY(flags_status(h.flags));
+  if (h.flags & FLAG_BOX) return kRetryTable;
+  km->n_in = N;
+  km->n_out = side.rows = (int64_t)h.count;
+  side.rows_pad = round_up(side.rows, kRowPad);
+  side.ready = true;
+  km->n_pairs = (int64_t)h.pairs;
+  std::swap(km->in_coords.p, own_rows.p);
+  std::swap(km->in_coords.bytes, own_rows.bytes);
+  std::swap(km->out_coords.p, coarse_rows.p);
+  std::swap(km->out_coords.bytes, coarse_rows.bytes);
+  return SPCONV_OK;
+}
+
 }  // namespace
 
 struct HostCtlHandle {
@@ -1114,17 +1472,18 @@ int kmap_status(spconv_kmap* km, hipStream_t) {
 
 namespace {
 int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int transposed, bool async, hipStream_t st,
-                    spconv_kmap** out, bool dilate, bool few_launch_sort);
+                    spconv_kmap** out, bool dilate, bool bit_per_cell, bool few_launch_sort);
 }
 int kmap_build(const int32_t* coords, int64_t N, int K, int stride, int transposed, bool async, hipStream_t st,
                spconv_kmap** out, bool dilate) {
-  const int status = kmap_build_impl(coords, N, K, stride, transposed, async, st, out, dilate, true);
-  if (status != kRetryGeneralSort) return status;
-  return kmap_build_impl(coords, N, K, stride, transposed, async, st, out, dilate, false);
+  int status = kmap_build_impl(coords, N, K, stride, transposed, async, st, out, dilate, true, true);
+  if (status == kRetryTable) status = kmap_build_impl(coords, N, K, stride, transposed, async, st, out, dilate, false, true);
+  if (status == kRetryGeneralSort) status = kmap_build_impl(coords, N, K, stride, transposed, async, st, out, dilate, false, false);
+  return status;
 }
 namespace {
 int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int transposed, bool async, hipStream_t st,
-                    spconv_kmap** out, bool dilate, bool few_launch_sort) {
+                    spconv_kmap** out, bool dilate, bool bit_per_cell, bool few_launch_sort) {
   std::unique_ptr<spconv_kmap> km(new (std::nothrow) spconv_kmap);
   if (!km) return SPCONV_ENOMEM;
   km->K = K;
@@ -1159,6 +1518,11 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
   }
   if (K == 3 && stride == 1 && !transposed && !dilate) {
     SPC_TRY(build_submanifold3(km.get(), rows, N, async, st));
+    *out = km.release();
+    return SPCONV_OK;
+  }
+  if (stride == 2 && (K == 2 || K == 3) && !transposed && bit_per_cell) {
+    SPC_TRY(build_down2(km.get(), rows, N, K, st));
     *out = km.release();
     return SPCONV_OK;
   }

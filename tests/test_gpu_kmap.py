@@ -509,3 +509,25 @@ def test_stride2_masks_by_rows_of_a_wave(sp, K, n_coarse):
     km = sp.build_kmap(coords_dev(c), K, 2)
     (x32, x), (w32, w), (g32, g) = make_layer(ref.n_in, ref.n_out, 16, 16, K ** 3, "f16", n_coarse)
     assert norm_err(sp.dgrad(g, w, km), oc.dgrad(g32, w32, ref.M, ref.n_in)) <= 2e-2  # (walks the input side and its masks)
+
+
+@pytest.mark.parametrize("K", [2, 3])
+@pytest.mark.parametrize("n,span,lo", [
+    (1, (1, 1, 1), 0), (3, (2, 1, 3), -5), (64, (1, 1, 64), -1), (65, (1, 1, 130), 7), (900, (40, 1, 33), -21),
+    (5000, (256, 64, 8), 1),           # exactly one chunk of 2048 words, and a part of another
+    (5000, (258, 66, 10), -3),
+    (80_000, (1016, 1010, 1160), 0),   # more chunks than workgroups: several per workgroup
+    (40, (60_000, 60_000, 60_000), -30_000), (2000, (1, 65_000, 64_000), -32_768)])  # boxes that are left to the table
+def test_stride2_boxes(sp, K, n, span, lo):
+    """Stride-2 builds keep one bit per cell of the coarse points' box: boxes around word, chunk and workgroup limits, flat
+    and long ones, negative and odd corners, several batches, and boxes too large for it."""
+    rng = np.random.default_rng(n + K)
+    corners = np.array([[0] * 3, [s - 1 for s in span]])[:min(n, 2)]
+    c = np.concatenate([corners, rng.integers(0, span, size=(2 * n, 3))])
+    c = np.unique(np.concatenate([rng.integers(0, 3 if n < 1000 else 1, size=(len(c), 1)) * 2, c + lo], 1), axis=0)
+    c = c[rng.permutation(len(c))][:n].astype(np.int32)
+    _check_kmap(sp, c, K, 2, False)
+    dup = np.concatenate([c, c[:1]])
+    with pytest.raises(sp.SpconvError) as e:
+        sp.build_kmap(coords_dev(dup), K, 2)
+    assert e.value.status == -3
