@@ -531,3 +531,29 @@ def test_stride2_boxes(sp, K, n, span, lo):
     with pytest.raises(sp.SpconvError) as e:
         sp.build_kmap(coords_dev(dup), K, 2)
     assert e.value.status == -3
+
+
+@pytest.mark.parametrize("K,n", [(3, 79_999), (3, 80_000), (3, 80_321), (5, 49_999), (5, 50_007)])
+def test_submanifold_builds_on_both_sides_of_the_filter(sp, K, n):
+    """From 80,000 (5x5x5: 50,000) rows on the probe keeps a filter of the existing runs: half of the rows in a dense slab,
+    half scattered, two batches, negative coordinates; and duplicates are still found."""
+    rng = np.random.default_rng(n)
+    c = np.concatenate([rng.integers(0, (300, 300, 3), size=(n, 3)), rng.integers(-9000, 9000, size=(n, 3))])
+    c = np.unique(np.concatenate([rng.integers(0, 2, size=(2 * n, 1)), c], 1), axis=0)
+    c = c[rng.permutation(len(c))][:n].astype(np.int32)
+    _check_kmap(sp, c, K, 1, False) if K == 3 else _check_k5(sp, c)
+    dup = np.concatenate([c[:-1], c[5:6]])
+    with pytest.raises(sp.SpconvError) as e:
+        sp.build_kmap(coords_dev(dup), K, 1)
+    assert e.value.status == -3
+
+
+def _check_k5(sp, c):
+    ref = oc.build_kmap(c, 5, 1)
+    km = sp.build_kmap(coords_dev(c), 5, 1)
+    np.testing.assert_array_equal(km.export().cpu().numpy(), ref.M)
+    assert km.n_pairs() == int((ref.M >= 0).sum())
+    words = km.export_mask().cpu().numpy().view(np.uint32).reshape(-1, 4)
+    present = ref.M >= 0
+    for k in range(125):
+        np.testing.assert_array_equal((words[:, k // 32] >> (k % 32)) & 1, present[:, k])
