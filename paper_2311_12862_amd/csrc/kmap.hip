@@ -742,6 +742,7 @@ __global__ void __launch_bounds__(64) k_publish(const Ctl* __restrict__ ctl, Hos
     host->key_and = k_and;
     host->pairs = pairs;
     host->entries = entries;
+    host->word = kHostReady | ((ctl->flags & 0xFFu) << 48) | (pairs & 0xFFFFFFFFFFFFull);  // (what an unwaited build is asked for)
     __threadfence_system();
     __hip_atomic_store(&host->ready, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
@@ -1016,6 +1017,143 @@ __global__ void __launch_bounds__(FILTER ? kProbeThreads : 256)
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) sum += wave_pairs[w];
   publish_pairs(sum, ctl, host);
+}
+
+// ---- small submanifold 3x3x3 builds in one launch ----
+// Up to kSmallRows rows every workgroup hashes all of them into a table of its own in LDS and looks its share of the rows up
+// there: nothing is cleared beforehand, no atomic leaves the CU, and no launch waits for another.  A slot holds the row and 19
+// bits of its hash, so that a lookup compares keys only where it has most likely found its row.  Whole builds, us: 500 rows 37
+// -> 21, 2k 36 -> 23, 5k 32 -> 27; at 7k 34 and 32, at 9k 32 and 43: every workgroup inserts all rows, one after the other per
+// thread.
+constexpr int kSmallRows = 5120, kSmallThreads = 1024, kSmallWgs = kPairSlots;
+constexpr int kSmallRowBits = 13;
+constexpr unsigned kSmallEmpty = ~0u;
+static_assert(kSmallRows < (1 << kSmallRowBits) - 1, "a slot is never mistaken for an empty one");
+__host__ __device__ constexpr int small_slots(int n) {
+  int c = 1024;
+  while (c < 2 * n) c *= 2;
+  return c;
+}
+__global__ void __launch_bounds__(kSmallThreads)
+    k_build_small3(const int4* __restrict__ rows, int n, int rows_pad, int4* __restrict__ keep, int* __restrict__ map,
+                   unsigned* __restrict__ mask, Ctl* ctl) {
+  constexpr int V = 27, RPW = 2, kWaves = kSmallThreads / 64;
+  extern __shared__ __align__(16) unsigned long long keys[];  // [n], then the slots
+  __shared__ unsigned flags, wave_pairs[kWaves];
+  const int slots = small_slots(n);
+  unsigned* const slot = reinterpret_cast<unsigned*>(keys + (n + 1) / 2 * 2);  // (16-byte aligned)
+  const int t = threadIdx.x, lane = t & 63, wib = t >> 6;
+  const int share = (rows_pad + gridDim.x - 1) / gridDim.x, first = blockIdx.x * share, last = min(rows_pad, first + share);
+  // The upper bits of a hash choose a bucket of four slots, which fill in order and are read at once (single slots: chains of a
+  // dozen steps for the slowest lane of a wave, 30 us for 5k rows against 27); the lower 19 stand in the slot.
+  const int shift = __clz(slots) + 3, buckets = slots / 4;
+  auto place = [&](unsigned h) { return (int)(h >> shift); };
+  auto entry = [&](unsigned h, int row) { return (h << kSmallRowBits) | (unsigned)row; };
+  if (t == 0) flags = 0;
+  for (int i = t; i < slots; i += kSmallThreads) slot[i] = kSmallEmpty;
+  constexpr int U = kSmallRows / kSmallThreads;
+  unsigned long long mine[U];
+  unsigned bad = 0;
+  {
+    int4 c[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) c[u] = u * kSmallThreads + t < n ? rows[u * kSmallThreads + t] : make_int4(-1, 0, 0, 0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = u * kSmallThreads + t;
+      if (j >= n) {
+        mine[u] = kEmpty;
+        continue;
+      }
+      const bool ok = coord_ok(c[u].x, c[u].y, c[u].z, c[u].w);
+      mine[u] = ok ? pack_key(c[u].x, c[u].y, c[u].z, c[u].w) : kEmpty;
+      if (!ok) bad |= (unsigned)FLAG_RANGE;
+      keys[j] = mine[u];
+      if (j >= first && j < last) keep[j] = c[u];  // the kmap's own copy of the caller's rows
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (mine[u] == kEmpty) continue;
+    const unsigned h = hash_run(mine[u]), e = entry(h, u * kSmallThreads + t);
+    int at = place(h);
+    bool done = false;
+    for (int it = 0; it < buckets && !done; ++it) {
+      const uint4 v4 = *reinterpret_cast<const uint4*>(slot + 4 * at);
+      const unsigned v[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (done) continue;
+        unsigned old = v[i];
+        if (old == kSmallEmpty) old = atomicCAS(&slot[4 * at + i], kSmallEmpty, e);
+        done = old == kSmallEmpty;
+        if (!done && ((old ^ e) >> kSmallRowBits) == 0 && keys[old & ((1u << kSmallRowBits) - 1u)] == mine[u]) {
+          bad |= (unsigned)FLAG_DUP;
+          done = true;
+        }
+      }
+      at = at + 1 == buckets ? 0 : at + 1;
+    }
+  }
+  if (bad) atomicOr(&flags, bad);
+  __syncthreads();
+  // two rows per wave, a lane per offset
+  const int sub = lane / V, k = lane - sub * V;
+  const int dx = k / 9 - 1, dy = k / 3 % 3 - 1, dz = k % 3 - 1;
+  unsigned pairs = 0;
+  for (int r0 = first + wib * RPW; r0 < last; r0 += kWaves * RPW) {
+    const int row = r0 + sub;
+    const bool active = sub < RPW && row < last;
+    int found = -1;
+    if (active && row < n && keys[row] != kEmpty) {
+      const unsigned long long own = keys[row];
+      const int b = (int)(own >> 48), x = (int)((own >> 32) & 0xFFFF) - 32768 + dx, y = (int)((own >> 16) & 0xFFFF) - 32768 + dy,
+                z = (int)(own & 0xFFFF) - 32768 + dz;
+      if (coord_ok(b, x, y, z)) {
+        const unsigned long long key = pack_key(b, x, y, z);
+        const unsigned h = hash_run(key), e = entry(h, 0);
+        int at = place(h);
+        bool done = false;
+        for (int it = 0; it < buckets && !done; ++it) {
+          const uint4 v4 = *reinterpret_cast<const uint4*>(slot + 4 * at);
+          const unsigned v[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int j = (int)(v[i] & ((1u << kSmallRowBits) - 1u));
+            done = done || v[i] == kSmallEmpty;
+            if (!done && ((v[i] ^ e) >> kSmallRowBits) == 0 && keys[j] == key) {
+              found = j;
+              done = true;
+            }
+          }
+          at = at + 1 == buckets ? 0 : at + 1;
+        }
+      }
+    }
+    if (active) map[row * V + k] = found;  // (rows of the padding: no neighbours)
+    const unsigned long long bal = __ballot(found >= 0);
+    if (active && k == 0) mask[row] = (unsigned)((bal >> (sub * V)) & ((1ull << V) - 1ull));
+    pairs += (unsigned)__popcll(bal);
+  }
+  if (lane == 0) wave_pairs[wib] = pairs;
+  __syncthreads();
+  if (t == 0) {
+    unsigned sum = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) sum += wave_pairs[w];
+    ctl->pairs[blockIdx.x * 16] = sum;
+  }
+  if (blockIdx.x == 0 && t < kPairSlots) {  // the rest of what k_publish reads (every workgroup has seen every row)
+    if (t >= (int)gridDim.x) ctl->pairs[t * 16] = 0;
+    ctl->entries[t * 16] = 0;
+    ctl->key_or[t * 16] = 0;
+    ctl->key_and[t * 16] = 0;
+    if (t == 0) {
+      ctl->flags = flags;
+      ctl->count = 0;
+    }
+  }
 }
 
 // K = 5, submanifold: the 125 offsets as five x-planes of 25 (dx = g - 2; offset j of a plane is
@@ -1383,41 +1521,48 @@ int build_runs(const int4* rows, int64_t N, bool filter, Ctl* ctl, int4* keep, R
   SPC_LAUNCH_CHECK();
   return SPCONV_OK;
 }
-template <typename F> int allow_filter_lds(F kernel, std::atomic<bool>& done) {  // (set twice by racing threads at worst)
+template <typename F> int allow_lds(F kernel, int bytes, std::atomic<bool>& done) {  // (set twice by racing threads at worst)
   if (done.load(std::memory_order_acquire)) return SPCONV_OK;
-  SPC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kFilterWords * 4));
+  SPC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
   done.store(true, std::memory_order_release);
   return SPCONV_OK;
 }
 
 // Submanifold 3x3x3 build: init, insert, probe (whose last workgroup publishes the result to
-// pinned host memory).
+// pinned host memory); small maps: one launch, and k_publish.
 int build_submanifold3(spconv_kmap* km, const int4* rows, int64_t N, bool async, hipStream_t st) {
   const int V = 27;
   DevBuf ctl_buf, own_rows;
   RunTable tab;
   SPC_TRY(ctl_buf.alloc(sizeof(Ctl)));
   Ctl* ctl = ctl_buf.as<Ctl>();
-  const bool filter = N >= kFilterRows3;
-  static std::atomic<bool> lds_allowed{false};
-  if (filter) SPC_TRY(allow_filter_lds(k_probe_runs3<true>, lds_allowed));
+  const bool small = N <= kSmallRows, filter = N >= kFilterRows3;
+  const int small_lds = (int)round_up(N, 2) * 8 + small_slots((int)std::min<int64_t>(N, kSmallRows)) * 4;
+  static std::atomic<bool> filter_lds{false}, small_lds_set{false};
+  if (small) SPC_TRY(allow_lds(k_build_small3, kSmallRows * 8 + small_slots(kSmallRows) * 4, small_lds_set));
+  if (filter) SPC_TRY(allow_lds(k_probe_runs3<true>, kFilterWords * 4, filter_lds));
   SPC_TRY(own_rows.alloc((size_t)N * 16));
   SideMap& side = km->out_side;
   side.rows = N;
   side.rows_pad = round_up(N, kRowPad);
   SPC_TRY(side.map.alloc((size_t)side.rows_pad * V * sizeof(int)));
   SPC_TRY(side.mask.alloc((size_t)side.rows_pad * sizeof(unsigned)));
-  SPC_TRY(build_runs(rows, N, filter, ctl, own_rows.as<int4>(), &tab, st));
+  if (!small) SPC_TRY(build_runs(rows, N, filter, ctl, own_rows.as<int4>(), &tab, st));
   HostCtl* hc = host_ctl_acquire();
   if (!hc) return SPCONV_ENOMEM;
   hc->res.word = 0;  // (pinned memory: visible to the kernel launched below)
-  if (filter)
+  if (small)
+    hipLaunchKernelGGL(k_build_small3, dim3((unsigned)std::min<int64_t>(ceil_div(side.rows_pad, 32), kSmallWgs)), dim3(kSmallThreads),
+                       small_lds, st, rows, (int)N, (int)side.rows_pad, own_rows.as<int4>(), side.map.as<int>(),
+                       side.mask.as<unsigned>(), ctl);
+  else if (filter)
     hipLaunchKernelGGL(k_probe_runs3<true>, dim3(256), dim3(kProbeThreads), kFilterWords * 4, st, rows, (int)N, (long long)side.rows_pad,
                        tab.buf.as<RunSlot>(), tab.log_cap, tab.bits, side.map.as<int>(), side.mask.as<unsigned>(), ctl, hc->dev);
   else
     hipLaunchKernelGGL(k_probe_runs3<false>, dim3(blocks_for(ceil_div(side.rows_pad, 7), 4)), dim3(256), 0, st, rows, (int)N,
                        (long long)side.rows_pad, tab.buf.as<RunSlot>(), tab.log_cap, (const unsigned*)nullptr, side.map.as<int>(),
                        side.mask.as<unsigned>(), ctl, hc->dev);
+  if (small && async) hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, st, ctl, hc->dev);
   const bool ok = hipGetLastError() == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
@@ -1459,7 +1604,7 @@ int build_submanifold5(spconv_kmap* km, const int4* rows, int64_t N, hipStream_t
   Ctl* ctl = ctl_buf.as<Ctl>();
   const bool filter = N >= kFilterRows5;
   static std::atomic<bool> lds_allowed{false};
-  if (filter) SPC_TRY(allow_filter_lds(k_probe_planes5<true>, lds_allowed));
+  if (filter) SPC_TRY(allow_lds(k_probe_planes5<true>, kFilterWords * 4, lds_allowed));
   SPC_TRY(own_rows.alloc((size_t)N * 16));
   SPC_TRY(build_runs(rows, N, filter, ctl, own_rows.as<int4>(), &tab, st));
   Planes5 pl{};

@@ -557,3 +557,30 @@ def _check_k5(sp, c):
     present = ref.M >= 0
     for k in range(125):
         np.testing.assert_array_equal((words[:, k // 32] >> (k % 32)) & 1, present[:, k])
+
+
+@pytest.mark.parametrize("n", [1, 2, 31, 1023, 1025, 2048, 2049, 4095, 5119, 5120, 5121, 9001])
+@pytest.mark.parametrize("asynchronous", [False, True])
+def test_small_submanifold_builds(sp, n, asynchronous):
+    """Up to 5,120 rows a submanifold map is built in one launch: dense and scattered rows, corners of the coordinate range,
+    and, waited for or not, duplicate rows and rows beside the range."""
+    rng = np.random.default_rng(n)
+    c = np.concatenate([rng.integers(0, (40, 40, 9), size=(n, 3)), rng.integers(-32768, 32768, size=(n, 3)),
+                        [[-32768] * 3, [-32768, -32768, -32767], [32767] * 3, [32767, 32766, 32767]]])
+    c = np.unique(np.concatenate([rng.integers(0, 2, size=(len(c), 1)) * 65534, c], 1), axis=0)
+    c = c[rng.permutation(len(c))][:n].astype(np.int32)
+    ref = oc.build_kmap(c, 3, 1)
+    km = sp.build_kmap(coords_dev(c), 3, 1, asynchronous=asynchronous)
+    if asynchronous:
+        km.status()
+    np.testing.assert_array_equal(km.export().cpu().numpy(), ref.M)
+    np.testing.assert_array_equal(km.in_coords().cpu().numpy(), ref.in_coords)
+    np.testing.assert_array_equal(km.export_mask().cpu().numpy().view(np.uint32), oc.bitmask(ref.M))
+    assert km.n_pairs() == int((ref.M >= 0).sum())
+    for row, status in ((c[0], -3), ([0, 0, 40_000, 0], -2)):
+        bad = np.concatenate([c, [row]]).astype(np.int32)
+        with pytest.raises(sp.SpconvError) as e:
+            km = sp.build_kmap(coords_dev(bad), 3, 1, asynchronous=asynchronous)
+            if asynchronous:
+                km.status()
+        assert e.value.status == status
