@@ -278,6 +278,8 @@ int fod_run(spconv_kmap* km, const ItemPlan& wp, const IgemmArgs& a, int tile_m,
 
 // ---- wgrad.hip
 int64_t wgrad_auto_pairs(const spconv_kmap* km, int C_in, int C_out, spconv_dtype dtype);
+bool wgrad_from_map(const spconv_kmap* km, int C_in, int C_out, spconv_dtype dtype);
+int wgrad_map_run(spconv_kmap* km, const void* feats, const void* dout, int C_in, int C_out, spconv_dtype dtype, float* dweights, hipStream_t st);
 int wgrad_run(spconv_kmap* km, const PairList& pl, int64_t piece_pairs, const void* feats, const void* dout, int C_in, int C_out,
               spconv_dtype dtype, float* dweights, hipStream_t st);
 

@@ -29,6 +29,8 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <type_traits>
+#include <utility>
 
 namespace spc {
 namespace {
@@ -445,6 +447,257 @@ __global__ void __launch_bounds__(256) k_wgrad_reduce(const float* __restrict__ 
   }
 }
 
+// ---- narrow layers on dense maps: straight from the map ----
+// A layer of up to 32 channels on either side has a gradient so small that a wave's registers hold it for J offsets.  Such a wave walks
+// batches of 32 map rows, keeps the batch's rows of dy in registers for all of its offsets and gathers their rows of x
+// (absent ones are zeros): every row of dy is read once per wave type, V / J times, and in order, not once per pair, and no pair
+// list is made (24 us at 300k rows of a room).  300k rows, 2.8M pairs, bf16 32 -> 32: 80 us + list -> 62, 8 -> 32 64 -> 43: the lines
+// that 64-byte rows of x lie in, 353 MB, at 6.3 TB/s.  Absent neighbours cost a slot of the address unit and matrix
+// instructions, so sparse maps stay with the pairs (100k rows of a LiDAR-like scan, 3.4 pairs a row: 16 us, from the map 23), as
+// do 64 channels of dy (300k rows 32 -> 64 95, 102) and maps of fewer pairs than about a million (60k rows of a room 17, 19).
+// Waves are on their own: batches are dealt to them, a unit (offset of a batch) has J - 1 units in flight behind it, each waited for
+// by count; the waves' sums meet in LDS and the workgroups' in k_wgrad_sum, in order.
+// A row of dy that is not finite must not meet the zeros of absent neighbours: such batches, found by their exponents, clear
+// the rows that an offset does not have.
+struct WgradMapParams {
+  const void* feats;  // [n_in][C_in]
+  const void* dout;   // [n_out][C_out]
+  const int* map;     // [rows_pad][V]
+  float* partial;     // [group][V][C_in][C_out]
+  unsigned feats_bytes, dout_bytes, map_bytes;
+  int C_in, C_out, V;
+  int batches;        // of 32 rows
+};
+
+template <int TI, int TO, int J> struct WgradMapShape {
+  static constexpr int BP = 32, NW = 8;
+  static constexpr int x_bytes = BP * TI * 2, d_bytes = BP * TO * 2;
+  static constexpr int LX = x_bytes / 1024, LD = d_bytes / 1024, LM = (J * BP + 63) / 64;  // loads of a unit, of dy, of the map
+  static constexpr int map_bytes = LM * 256;
+  static constexpr int wave_bytes = J * x_bytes + d_bytes + 2 * map_bytes;
+  static constexpr int sum_bytes = NW * TI * TO * 4;
+  static constexpr int total = NW * wave_bytes > sum_bytes ? NW * wave_bytes : sum_bytes;
+  // Loads that may be in flight when unit j of a batch is read.  A step j issues unit j - 1 of the next batch (step 0: the last one
+  // of its own), step 1 after that dy of the next batch and the map of the one after it.
+  static constexpr int in_flight(int j) {
+    int n = (J - 2) * LX;
+    if (j == 0) return n;  // (dy and the map, issued in step 1, have landed as well)
+    for (int d = 1; d < J; ++d)
+      if ((j - d + J) % J == 1 % J) n += LD + LM;
+    return n;
+  }
+  static_assert(J >= 3 && total <= 160 * 1024 && in_flight(J - 1) < 64, "");
+};
+
+template <typename F, int... I> __device__ __forceinline__ void for_constants(F f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+
+template <typename T, int TI, int TO, int J>
+__global__ void __launch_bounds__(512) k_wgrad_map(const WgradMapParams p) {
+  typedef WgradMapShape<TI, TO, J> W;
+  constexpr int CX = TI / 8, CD = TO / 8, IB = TI / 16, OB = TO / 16, LX = W::LX, LD = W::LD, NW = W::NW, BP = W::BP;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int fa = lane & 15, fg = lane >> 4;
+  unsigned char* const my = smem + wave * W::wave_bytes;  // J units of x, dy, two maps
+  const unsigned lds = (unsigned)(size_t)(__attribute__((address_space(3))) void*)my;
+  constexpr int kD = J * W::x_bytes, kMap = kD + W::d_bytes;
+  const int k0 = blockIdx.y * J, nk = min(J, p.V - k0);
+  const int first = blockIdx.x * NW + wave, step = gridDim.x * NW;
+  const int mine = p.batches > first ? (p.batches - first + step - 1) / step : 0;
+
+  const u32x4 x_rsrc = rsrc_of(p.feats, p.feats_bytes), d_rsrc = rsrc_of(p.dout, p.dout_bytes), m_rsrc = rsrc_of(p.map, p.map_bytes);
+  const unsigned x_row = (unsigned)p.C_in * 2u, d_row = (unsigned)p.C_out * 2u;
+  int x_lane_row[LX];
+  unsigned x_off[LX], d_off[LD];
+#pragma unroll
+  for (int i = 0; i < LX; ++i) {
+    const int q = i * 64 + lane, r = q / CX, c = q % CX, ch = (block_at<2, CX>(c / 2, r) * 2 + c % 2) * 8;
+    x_lane_row[i] = r;
+    x_off[i] = ch < p.C_in ? (unsigned)ch * 2u : kNoRow;
+  }
+#pragma unroll
+  for (int i = 0; i < LD; ++i) {
+    const int q = i * 64 + lane, r = q / CD, c = q % CD, ch = (block_at<2, CD>(c / 2, r) * 2 + c % 2) * 8;
+    d_off[i] = ch < p.C_out ? (unsigned)r * d_row + (unsigned)ch * 2u : kNoRow;
+  }
+  unsigned xa[IB], da[OB];  // fragment addresses
+  {
+    const int r = 8 * fg + (fa >> 2), in = (fa & 3) * 8;
+#pragma unroll
+    for (int i = 0; i < IB; ++i) xa[i] = (unsigned)(r * TI * 2 + place_of<2, CX>(i, r) * 32 + in);
+#pragma unroll
+    for (int o = 0; o < OB; ++o) da[o] = (unsigned)(kD + r * TO * 2 + place_of<2, CD>(o, r) * 32 + in);
+  }
+  auto frag = [&](const unsigned char* at, int pitch) -> u32x4 {  // (see k_wgrad)
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(at));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(at + 4 * pitch));
+    return __builtin_bit_cast(u32x4, s16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+  };
+
+  auto load_map = [&](int i) {  // entries [offset][row] of own batch i
+    const bool live = i < mine;
+    const unsigned row0 = (unsigned)(first + i * step) * BP;
+#pragma unroll
+    for (int l = 0; l < W::LM; ++l) {
+      const int e = l * 64 + lane, r = e % BP, j = e / BP;
+      load_dword_to_lds(m_rsrc, live && j < nk ? ((row0 + (unsigned)r) * (unsigned)p.V + (unsigned)(k0 + j)) * 4u : kNoRow,
+                        lds + kMap + (i & 1) * W::map_bytes + l * 256);
+    }
+  };
+  auto load_d = [&](int i) {
+    const bool live = i < mine;
+    const unsigned at = (unsigned)(first + i * step) * BP * d_row;
+#pragma unroll
+    for (int l = 0; l < LD; ++l) load_to_lds(d_rsrc, live && d_off[l] != kNoRow ? at + d_off[l] : kNoRow, 0, lds + kD + l * 1024);
+  };
+  unsigned src[LX];
+  auto read_idx = [&](int i, int j) {  // where unit j of own batch i gathers from
+    const unsigned char* at = my + kMap + (i & 1) * W::map_bytes + j * (BP * 4);
+    const bool live = i < mine && j < nk;
+    unsigned row[LX];
+#pragma unroll
+    for (int l = 0; l < LX; ++l) row[l] = *reinterpret_cast<const unsigned*>(at + x_lane_row[l] * 4);
+#pragma unroll
+    for (int l = 0; l < LX; ++l)  // (an absent neighbour, -1, wraps to just below 2^32)
+      src[l] = live && x_off[l] != kNoRow ? row[l] * x_row + x_off[l] : kNoRow;
+  };
+  auto load_x = [&](int j) {
+#pragma unroll
+    for (int l = 0; l < LX; ++l) load_to_lds(x_rsrc, src[l], 0, lds + j * W::x_bytes + l * 1024);
+  };
+
+  f32x4 acc[J][OB][IB];
+#pragma unroll
+  for (int j = 0; j < J; ++j)
+#pragma unroll
+    for (int o = 0; o < OB; ++o)
+#pragma unroll
+      for (int i = 0; i < IB; ++i) acc[j][o][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  load_map(0);
+  load_map(1);
+  load_d(0);
+  wait_loads<0>();
+#pragma unroll
+  for (int j = 0; j < J - 1; ++j) {
+    read_idx(0, j);
+    load_x(j);
+  }
+  read_idx(0, J - 1);
+  for (int b = 0; b < mine; ++b) {
+    u32x4 d[OB];
+    bool odd = false;  // some element of dy is not finite
+    auto unit = [&](auto index) {
+      constexpr int j = decltype(index)::value;
+      wait_loads<W::in_flight(j)>();
+      if (j == 0) {
+#pragma unroll
+        for (int o = 0; o < OB; ++o) d[o] = frag(my + da[o], TO * 2);
+      }
+      u32x4 x[IB];
+#pragma unroll
+      for (int i = 0; i < IB; ++i) x[i] = frag(my + j * W::x_bytes + xa[i], TI * 2);
+      load_x(j == 0 ? J - 1 : j - 1);
+      if (j == 1) {
+        load_d(b + 1);
+        load_map(b + 2);
+      }
+      read_idx(b + 1, j);
+      if (j == 0) {  // an exponent of ones carries into the sign's place
+        constexpr unsigned kExp = sizeof(T) == 2 && __is_same(T, _Float16) ? 0x7C007C00u : 0x7F807F80u;
+        constexpr unsigned kOne = __is_same(T, _Float16) ? 0x04000400u : 0x00800080u;
+        unsigned m = 0;
+#pragma unroll
+        for (int o = 0; o < OB; ++o)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) m |= (d[o][q] & kExp) + kOne;
+        odd = __any((m & 0x80008000u) != 0);
+      }
+      if (!odd) {
+#pragma unroll
+        for (int o = 0; o < OB; ++o)
+#pragma unroll
+          for (int i = 0; i < IB; ++i) acc[j][o][i] = mma<T>(d[o], x[i], acc[j][o][i]);
+      } else {
+        unsigned keep[4] = {0, 0, 0, 0};  // rows 8 fg .. 8 fg + 7, two to a word
+        if (j < nk)
+          for (int r = 0; r < 8; ++r) {
+            const long long row = (long long)(first + b * step) * BP + 8 * fg + r;
+            if (p.map[row * p.V + k0 + j] >= 0) keep[r >> 1] |= 0xFFFFu << (16 * (r & 1));
+          }
+#pragma unroll
+        for (int o = 0; o < OB; ++o) {
+          const u32x4 dk = {d[o][0] & keep[0], d[o][1] & keep[1], d[o][2] & keep[2], d[o][3] & keep[3]};
+#pragma unroll
+          for (int i = 0; i < IB; ++i) acc[j][o][i] = mma<T>(dk, x[i], acc[j][o][i]);
+        }
+      }
+    };
+    for_constants(unit, std::make_integer_sequence<int, J>{});
+  }
+  wait_loads<0>();  // (nothing may land in LDS that is used for something else next)
+  f32x4* sums = reinterpret_cast<f32x4*>(smem);  // [wave][block][lane]
+  constexpr int B = OB * IB;
+  for (int j = 0; j < nk; ++j) {
+    __syncthreads();
+#pragma unroll
+    for (int jj = 0; jj < J; ++jj)
+      if (jj == j) {
+#pragma unroll
+        for (int o = 0; o < OB; ++o)
+#pragma unroll
+          for (int i = 0; i < IB; ++i) sums[(wave * B + o * IB + i) * 64 + lane] = acc[jj][o][i];
+      }
+    __syncthreads();
+    float* dst = p.partial + ((long long)blockIdx.x * p.V + k0 + j) * p.C_in * p.C_out;
+    for (int blk = wave; blk < B; blk += NW) {
+      f32x4 v = sums[blk * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) v += sums[(w * B + blk) * 64 + lane];
+      const int o = blk / IB, i = blk % IB, ci = i * 16 + fa, co = o * 16 + fg * 4;
+      if (ci < p.C_in && co < p.C_out) *reinterpret_cast<f32x4*>(dst + (long long)ci * p.C_out + co) = v;
+    }
+  }
+}
+
+// dW[e] = sum over the groups, in order: four waves take every fourth group, their sums are added in wave order.
+__global__ void __launch_bounds__(256) k_wgrad_sum(const float* __restrict__ partial, int groups, long long elems, float* __restrict__ dw) {
+  __shared__ float4 part[4][64];
+  const int col = threadIdx.x & 63, stripe = threadIdx.x >> 6;
+  const long long e4 = ((long long)blockIdx.x * 64 + col) * 4;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (e4 < elems) {
+    for (int g0 = stripe; g0 < groups; g0 += 32) {
+      float4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        v[u] = g0 + 4 * u < groups ? *reinterpret_cast<const float4*>(partial + (g0 + 4 * u) * elems + e4) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        s.x += v[u].x;
+        s.y += v[u].y;
+        s.z += v[u].z;
+        s.w += v[u].w;
+      }
+    }
+  }
+  part[stripe][col] = s;
+  __syncthreads();
+  if (stripe == 0 && e4 < elems) {
+    float4 t = part[0][col];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) {
+      t.x += part[w][col].x;
+      t.y += part[w][col].y;
+      t.z += part[w][col].z;
+      t.w += part[w][col].w;
+    }
+    *reinterpret_cast<float4*>(dw + e4) = t;
+  }
+}
+
 }  // namespace
 
 // Tiles by channels: as wide as the layer, so that a pair's rows are gathered once.  Beyond 128 channels only
@@ -504,6 +757,55 @@ int launch_wgrad(const WgradParams& p, dim3 grid, hipStream_t st) {
   return SPCONV_OK;
 }
 }  // namespace
+
+namespace {
+constexpr int kMapChannels = 32, kMapOffsets = 7;  // of a k_wgrad_map tile and wave
+template <typename T> int launch_wgrad_map(const WgradMapParams& p, dim3 grid, hipStream_t st) {
+  typedef WgradMapShape<kMapChannels, kMapChannels, kMapOffsets> W;
+  auto kernel = k_wgrad_map<T, kMapChannels, kMapChannels, kMapOffsets>;
+  static std::atomic<bool> attr_set{false};  // (set twice by racing threads at worst: the calls are idempotent)
+  if (!attr_set.load(std::memory_order_acquire)) {
+    SPC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, W::total));
+    attr_set.store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL(kernel, grid, dim3(W::NW * 64), W::total, st, p);
+  SPC_LAUNCH_CHECK();
+  return SPCONV_OK;
+}
+}  // namespace
+
+// Whether a call without a piece length takes its gradient straight from the map: narrow layers on maps that are known to have
+// many pairs, and many per row (where the line lies: see k_wgrad_map; 120k rows of a room, 1.1M pairs, 32 -> 32 32 us and the list
+// from pairs, 27.5 from the map; 16 -> 16 22.5 and the list, 23.6).
+bool wgrad_from_map(const spconv_kmap* km, int C_in, int C_out, spconv_dtype dtype) {
+  if (dtype == SPCONV_F32 || C_in > kMapChannels || C_out > kMapChannels || km->V != 27 || km->pending) return false;
+  if (km->n_pairs < 1200000 || km->n_pairs < 7 * km->n_out) return false;
+  return (uint64_t)km->n_in * C_in * 2 < kNoRow && (uint64_t)km->n_out * C_out * 2 < kNoRow &&
+         (uint64_t)km->out_side.rows_pad * km->V * 4 < kNoRow;  // buffer descriptors address 32 bits
+}
+
+int wgrad_map_run(spconv_kmap* km, const void* feats, const void* dout, int C_in, int C_out, spconv_dtype dtype, float* dweights, hipStream_t st) {
+  const int V = km->V, types = (int)ceil_div(V, kMapOffsets), groups = 256 / types;  // one workgroup per CU
+  WgradMapParams p{};
+  const long long elems = (long long)V * C_in * C_out;
+  SPC_TRY(km->scratch.reserve((size_t)groups * elems * sizeof(float)));
+  p.feats = feats;
+  p.dout = dout;
+  p.map = km->out_side.map.as<int>();
+  p.partial = km->scratch.as<float>();
+  p.feats_bytes = (unsigned)((uint64_t)km->n_in * C_in * 2);
+  p.dout_bytes = (unsigned)((uint64_t)km->n_out * C_out * 2);
+  p.map_bytes = (unsigned)((uint64_t)km->out_side.rows_pad * V * 4);
+  p.C_in = C_in;
+  p.C_out = C_out;
+  p.V = V;
+  p.batches = (int)ceil_div(km->n_out, 32);  // (the map is padded to whole batches)
+  const dim3 grid((unsigned)groups, (unsigned)types);
+  SPC_TRY(dtype == SPCONV_F16 ? launch_wgrad_map<_Float16>(p, grid, st) : launch_wgrad_map<__bf16>(p, grid, st));
+  hipLaunchKernelGGL(k_wgrad_sum, dim3((unsigned)ceil_div(elems / 4, 64)), dim3(256), 0, st, p.partial, groups, elems, dweights);
+  SPC_LAUNCH_CHECK();
+  return SPCONV_OK;
+}
 
 // Pairs of a piece that calls without a configuration get.
 int64_t wgrad_auto_pairs(const spconv_kmap* km, int C_in, int C_out, spconv_dtype dtype) {

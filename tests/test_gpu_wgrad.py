@@ -87,3 +87,28 @@ def test_very_wide_layers_keep_their_pieces_short(dtype, ch):
             best = min(best, a.elapsed_time(b))
         return best
     assert ms(None) <= 1.4 * ms(sp.Config(wgrad_pairs=4096))
+
+
+@pytest.mark.parametrize("dtype,c_in,c_out", [("f16", 32, 32), ("bf16", 8, 24), ("f16", 24, 16)])
+def test_narrow_layers_on_dense_maps(dtype, c_in, c_out):
+    """Gradients taken straight from the map, row counts that leave a part of a batch: against the oracle, the same bits every
+    time; values that are not finite reach the offsets that have them and no others, as they do over pairs."""
+    import torch
+    import paper_2311_12862_amd as sp
+    c = gen.full_grid(38, 1, seed=9)[:54_321 if c_in == 8 else 54_880]
+    ref = oc.build_kmap(c, 3, 1)
+    assert (ref.M >= 0).sum() >= 1_200_000
+    (x32, x), _, (g32, g) = make_layer(ref.n_in, ref.n_out, c_in, c_out, 27, dtype, c_in)
+    km = sp.build_kmap(coords_dev(c), 3, 1)
+    dw = sp.wgrad(x, g, km)
+    assert norm_err(dw, oc.wgrad(x32, g32, ref.M)) <= 1e-4
+    assert torch.equal(dw, sp.wgrad(x, g, km))
+    pairs = sp.Config(wgrad_pairs=1024)
+    edge = int((ref.M < 0).sum(1).argmax())
+    for at, value in ((edge, float("inf")), (edge, float("nan")), (len(c) - 1, float("-inf"))):
+        bad = g.clone()
+        bad[at, c_out - 1] = value
+        got, want = sp.wgrad(x, bad, km), sp.wgrad(x, bad, km, pairs)
+        assert torch.equal(torch.isfinite(got), torch.isfinite(want)) and not torch.isfinite(got).all()
+        both = torch.isfinite(got)
+        assert (got[both] - want[both]).abs().max() <= 1e-4 * want[both].abs().max()
