@@ -179,6 +179,8 @@ int choose_kernel(int V, int64_t rows_dst, int64_t rows_src, int c_red, int c_co
       const int64_t tiles = ceil_div(c_cols, bn);
       if (tiles > 2 && (c.n_split > 0 || (double)tiles * c_red * (double)rows_dst > 6e7)) wave = false;
       if (c_red > 64 && c.n_split > 0) wave = false;  // (30k rows 128 -> 128: 34 us against 25 us)
+      if (!cfg && igemm_ring_shape(V, c.n_split, rows_dst, rows_src, c_red, c_cols, false, true, &k.ring) == SPCONV_OK && k.ring.nwk == 8)
+        wave = false;  // (wave_groups)
     }
     if (wave) {
       k.kind = KernelChoice::WAVE;

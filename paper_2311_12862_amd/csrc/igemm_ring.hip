@@ -13,6 +13,9 @@
 // What does bound small maps is the longest tile, one step after another: NWK groups of waves (two) therefore
 // take every other unit of the same tile and add their sums at the end through LDS (9k rows, 256 -> 256: 58
 // -> 41 us with two groups, 37 us with 32-row tiles; 94 us for the register-staged kernel on the unsorted map).
+// Beyond that, what a step takes is the CU's address unit (16 cycles per load of any wave) and waves that wait for each other at its
+// barrier; where K groups are one wave each there is no barrier, and one wave's loads are issued while another multiplies: 9k rows,
+// 256 -> 256, eight such groups on 64 x 64 tiles: 36 -> 24 us.
 // Column tiles are dealt to the XCDs, so that each L2 holds one column tile of the weights (the same
 // layer: 46 -> 37 us).
 //
@@ -70,7 +73,8 @@ __global__ void __launch_bounds__(NWM* NWN* NWK* NWR * 64) k_ring(const RingPara
   constexpr int NBW = (NBI + NW - 1) / NW;  // per wave (with fewer than NW, some waves load the same piece)
   constexpr int LPR = DGRAD ? CPR : BN / CE;  // chunks of a row of the weight tile
   constexpr int RPB = 64 / LPR;               // rows of it per load
-  static_assert((NWK == 1 || NWK == 2) && (NWR == 1 || NWR == 2), "first_piece, tmask_other");
+  static_assert((NWK & (NWK - 1)) == 0 && (NWK <= 2 || NW == 1) && (NWR == 1 || NWR == 2), "first_piece, units_of, tmask_other");
+  static_assert(NW > 1 || (NWR == 1 && MB * NB % NWK == 0), "the waves share the sums");
   static_assert(NA >= 1 && BM % (RPI * NW) == 0 && NBI >= 1 && (NBI % NW == 0 || NW % NBI == 0), "whole loads per wave");
   extern __shared__ __align__(16) unsigned char smem[];
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
@@ -170,11 +174,11 @@ __global__ void __launch_bounds__(NWM* NWN* NWK* NWR * 64) k_ring(const RingPara
     }
   }
 
-  // The units of this K group: set bits c of the tile mask, each with its pieces; with two groups every other piece,
-  // or, where their number is odd, starting with the second one for every other offset.  Which group takes a
-  // unit depends on the unit alone, not on the tile: a row's sums do not depend on the rows beside it.
+  // The units of this K group: set bits c of the tile mask, each with its pieces, dealt to the groups by their number
+  // c * n_pieces + piece.  Which group takes a unit depends on the unit alone, not on the tile: a row's sums do not depend
+  // on the rows beside it.
   const unsigned odd_start = NWK > 1 && (n_pieces & 1) ? 1u : 0u;
-  auto first_piece = [&](int c) { return NWK > 1 ? grp ^ (int)(c & odd_start) : 0; };
+  auto first_piece = [&](int c) { return (grp - c * n_pieces) & (NWK - 1); };
   struct Cursor {
     unsigned rem;
     int c, piece;
@@ -283,16 +287,66 @@ __global__ void __launch_bounds__(NWM* NWN* NWK* NWR * 64) k_ring(const RingPara
 
   wait_loads_and_sync();  // the slab is there
   fetch_idx();
-  const int mine = units_of(tmask, grp);
-  int steps = mine;  // every wave passes as many barriers
-  if (NWK > 1) steps = max(steps, units_of(tmask, grp ^ 1));
-  if (NWR > 1) steps = max(steps, max(units_of(tmask_other, 0), NWK > 1 ? units_of(tmask_other, 1) : 0));
-  if (mine > 0) load_unit(0);
-  for (int it = 0; it < steps; ++it) {
-    wait_loads_and_sync();  // this step's unit has landed, and everyone is done with the stage that is filled next
-    if (it + 1 < mine) load_unit((it + 1) & 1);
-    if (it < mine && ((wave_mask >> qc.c) & 1u)) multiply(it & 1, qc.c);
-    cursor_step(qc);
+  if constexpr (NW == 1) {
+    // every wave is a K group: nothing is shared until the end, so nothing is waited for but the wave's own loads, and one
+    // wave's loads are issued while another multiplies
+    bool more = qi.piece < n_pieces;
+    if (more) load_unit(0);
+    for (int slot = 0; more; slot ^= 1) {
+      wait_own_loads();  // (the other stage was read before: its fragments are in registers)
+      more = qi.piece < n_pieces;
+      if (more) load_unit(slot ^ 1);
+      multiply(slot, qc.c);
+      cursor_step(qc);
+    }
+  } else {
+    const int mine = units_of(tmask, grp);
+    int steps = mine;  // every wave passes as many barriers
+    if (NWK > 1) steps = max(steps, units_of(tmask, grp ^ 1));
+    if (NWR > 1) steps = max(steps, max(units_of(tmask_other, 0), NWK > 1 ? units_of(tmask_other, 1) : 0));
+    if (mine > 0) load_unit(0);
+    for (int it = 0; it < steps; ++it) {
+      wait_loads_and_sync();  // this step's unit has landed, and everyone is done with the stage that is filled next
+      if (it + 1 < mine) load_unit((it + 1) & 1);
+      if (it < mine && ((wave_mask >> qc.c) & 1u)) multiply(it & 1, qc.c);
+      cursor_step(qc);
+    }
+  }
+  const int c_out = p.c_out;
+  // a lane holds channels 4 fg + r of row fa of each block
+  auto store = [&](int to, int col, f32x4 v4) {
+    if (col >= c_out) return;
+    if (p.partial) {
+      *reinterpret_cast<f32x4*>(p.partial + ((long long)part * p.rows + to) * c_out + col) = v4;
+    } else {
+      typedef T out4 __attribute__((ext_vector_type(4)));
+      out4 v;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] = (T)v4[r];
+      *reinterpret_cast<out4*>(reinterpret_cast<T*>(p.out) + (long long)to * c_out + col) = v;
+    }
+  };
+  if constexpr (NW == 1) {  // the waves' sums meet in LDS; each adds up a share of the blocks, in order
+    static_assert(NWK * BM * BN * 4 <= 2 * L::stage, "the sums fit the stages");
+    wait_loads_and_sync();
+    f32x4* sums = reinterpret_cast<f32x4*>(smem);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) sums[(grp * MB * NB + mb * NB + nb) * 64 + lane] = acc[mb][nb];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < MB * NB / NWK; ++u) {
+      const int blk = grp * (MB * NB / NWK) + u;
+      f32x4 v = sums[blk * 64 + lane];
+#pragma unroll
+      for (int g = 1; g < NWK; ++g) v += sums[(g * MB * NB + blk) * 64 + lane];
+      int to = orow[0];
+#pragma unroll
+      for (int mb = 1; mb < MB; ++mb) to = blk / NB == mb ? orow[mb] : to;
+      if (to >= 0) store(to, n0 + (blk % NB) * 16 + fg * 4, v);
+    }
+    return;
   }
   if constexpr (NWK > 1) {  // the K groups' sums meet in LDS; group 0 adds them up in order and stores
     static_assert(NWR * (NWK - 1) * BM * BN * 4 <= 2 * L::stage, "the sums fit the stages");
@@ -314,25 +368,11 @@ __global__ void __launch_bounds__(NWM* NWN* NWK* NWR * 64) k_ring(const RingPara
         for (int nb = 0; nb < NB; ++nb) acc[mb][nb] += sums[(((half * (NWK - 1) + g) * NW + wave) * MB * NB + mb * NB + nb) * 64 + lane];
   }
 
-  // a lane holds channels 4 fg + r of row fa of each block
-  const int c_out = p.c_out;
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
     if (orow[mb] < 0) continue;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const int col = n0 + wn * WN + nb * 16 + fg * 4;
-      if (col >= c_out) continue;
-      if (p.partial) {
-        *reinterpret_cast<f32x4*>(p.partial + ((long long)part * p.rows + orow[mb]) * c_out + col) = acc[mb][nb];
-      } else {
-        typedef T out4 __attribute__((ext_vector_type(4)));
-        out4 v;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = (T)acc[mb][nb][r];
-        *reinterpret_cast<out4*>(reinterpret_cast<T*>(p.out) + (long long)orow[mb] * c_out + col) = v;
-      }
-    }
+    for (int nb = 0; nb < NB; ++nb) store(orow[mb], n0 + wn * WN + nb * 16 + fg * 4, acc[mb][nb]);
   }
 }
 
@@ -356,14 +396,16 @@ int launch_ring(const RingParams& p, bool dgrad, dim3 grid, hipStream_t st) {
 
 // the tile shapes that are built: BM, BN, waves along the rows, along the columns, K groups, tiles of a workgroup
 #define SPC_RING_SHAPES_16(X) \
-  X(32, 64, 1, 2, 2, 1) X(64, 32, 4, 1, 1, 1) X(64, 64, 2, 2, 1, 1) X(64, 64, 2, 2, 2, 1) X(64, 128, 2, 2, 1, 1) \
-  X(128, 128, 2, 2, 1, 1) X(256, 256, 2, 4, 1, 1)
+  X(32, 64, 1, 1, 4, 1) X(32, 64, 1, 1, 8, 1) X(32, 64, 1, 2, 2, 1) X(64, 32, 4, 1, 1, 1) X(64, 64, 1, 1, 8, 1) X(64, 64, 2, 2, 1, 1) \
+  X(64, 64, 2, 2, 2, 1) X(64, 128, 2, 2, 1, 1) X(128, 128, 2, 2, 1, 1) X(256, 256, 2, 4, 1, 1)
 #define SPC_RING_SHAPES_32(X) \
-  X(32, 16, 2, 1, 2, 2) X(32, 32, 1, 2, 2, 2) X(64, 16, 4, 1, 1, 1) X(64, 32, 4, 1, 1, 1) X(64, 64, 2, 2, 1, 1)
+  X(32, 16, 2, 1, 2, 2) X(32, 32, 1, 2, 2, 2) X(64, 16, 4, 1, 1, 1) X(64, 32, 1, 1, 8, 1) X(64, 32, 4, 1, 1, 1) X(64, 64, 2, 2, 1, 1)
+// (eight K groups of 128-byte pieces do not fit in LDS)
+constexpr bool ring_built(int pb, int nwk) { return nwk < 8 || pb == 64; }
 
 template <typename T, int PB> int launch_shape(const RingParams& p, bool dgrad, const RingShape& s, dim3 grid, hipStream_t st) {
 #define SPC_RING_CASE(BM, BN, NWM, NWN, NWK, NWR) \
-  if (s.bm == BM * NWR && s.bn == BN && s.nwk == NWK && s.nwr == NWR) return launch_ring<T, BM, BN, PB, NWM, NWN, NWK, NWR>(p, dgrad, grid, st);
+  if (s.bm == BM * NWR && s.bn == BN && s.nwk == NWK && s.nwr == NWR) if constexpr (ring_built(PB, NWK)) return launch_ring<T, BM, BN, PB, NWM, NWN, NWK, NWR>(p, dgrad, grid, st);
   if constexpr (sizeof(T) == 4) {
     SPC_RING_SHAPES_32(SPC_RING_CASE)
   } else {
@@ -400,6 +442,18 @@ int ring_waves(const RingShape& s, bool f32) {
 
 }  // namespace
 
+// Where eight K groups of one wave each take a 64 x 64 tile (16-bit types): small maps, whose launch is as long as the chain of
+// the longest tile.  Sorted maps, us, before (32 x 64 or 64 x 64, two K groups) and with them: 9k rows 256 -> 256 36, 24 (564 workgroups);
+// 5k 512 -> 512 65, 44; 7k 128 -> 256 20, 16; 12k 192 -> 192 30, 27; 20k 256 -> 128 35, 27; where the line lies: 15k 256 -> 256
+// (940 workgroups) 38, 38; 12k 128 -> 256 (752) 21, 23; 20k 128 -> 128 (626) 21, 21; 30k 96 -> 96 (938) 25, 27.5.  32-row tiles
+// where the map is so small that these are fewer than three per CU and pieces come in whole rounds (4k rows 256 -> 256 33, 23, with
+// 32 rows 19).  Map order, one round of workgroups (kernel 1 before): 12k rows 64 -> 64 15, 11.4; 7k 128 -> 128 23, 16; 96 -> 96 17,
+// 14; 12k 128 -> 64 22, 15; 20k 64 -> 64 (313) 15, 20; 2k scattered points, of one pair a row, 64 -> 64 8.8, 9.1.
+bool wave_groups(int V, int n_split, int c_red, int c_out, int64_t wgs) {
+  if (V < 25 || c_red < 64 || c_out < 32) return false;  // (few offsets: few units to share)
+  return wgs <= (n_split == 0 ? 256 : c_red % 64 ? 600 : std::min(900, c_red * 7 / 2));
+}
+
 // Tile shape from the row count and the produced channels.  The largest tile that still gives a few workgroups per
 // CU: a larger one gathers each row and loads each weight slice fewer times, but small maps are bound by the
 // longest tile.  Measured on sorted maps (us): 300k rows 256 -> 256, (256, 256) 435, (128, 128) 480; 96 -> 96, (128, 128)
@@ -428,16 +482,30 @@ int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
     // 2k rows 16 -> 16 8.8 (64 x 16), two 32 x 16 6.6; 5k 64 -> 64 37, 26; 20k 256 -> 256 230, 173; 30k 64 -> 64 44, 29.5; 60k
     // 64 -> 64 48, 42; and where the line lies: 30k 96 -> 96 66, 62; 50k of a dense room 64 -> 64 57, 62; 60k 96 -> 96 103 (one K
     // group), 96; 100k 128 -> 128 165 (one), 178.
+    // On maps of a few workgroups per CU eight K groups of a wave each end sooner still: 5k rows 96 -> 96 38, 28; 15k 64 -> 64 28,
+    // 20; 10k 32 -> 32 16, 13; 30k 96 -> 32 40, 27; where the line lies: 30k 64 -> 64 30, 33; 32 -> 32 24, 25; 60k 96 -> 96 104, 104.
     s->bm = 64;
     s->bn = c_out <= 16 ? 16 : 32;
-    if (small_tiles && wgs(64, s->bn) < (c_red <= 32 ? 1500 : 2000))
-      s->nwk = s->nwr = 2;
-    else if (c_out > 32)
-      s->bn = 64;
     s->piece = c_red <= 16 ? 64 : 128;
+    if (small_tiles && V >= 25 && c_red > 16 && c_out > 16 && wgs(64, 32) <= 12 * c_red) {
+      s->nwk = 8;
+      s->piece = 64;
+    } else if (small_tiles && wgs(64, s->bn) < (c_red <= 32 ? 1500 : 2000)) {
+      s->nwk = s->nwr = 2;
+    } else if (c_out > 32) {
+      s->bn = 64;
+    }
   } else {
     s->piece = (c_red % 64 == 0) ? 128 : 64;
-    if (c_out <= 32) {
+    if (small_tiles && wave_groups(V, n_split, c_red, c_out, wgs(64, 64))) {
+      s->bm = c_red % 256 == 0 && wgs(32, 64) <= 768 ? 32 : 64;
+      s->bn = 64;
+      s->nwk = 8;
+      s->piece = 64;
+    } else if (small_tiles && n_split > 0 && c_red > 64 && c_red % 64 && c_out > 32 && wgs(64, 64) <= 1600) {
+      s->bm = 32, s->bn = 64;  // (30k rows 96 -> 96 25 -> 20.5, 136 -> 72 37 -> 26)
+      s->nwk = 4;
+    } else if (c_out <= 32) {
       s->bm = 64, s->bn = 32;
     } else if (c_out > 128 && wgs(256, 256) >= 768) {
       s->bm = 256, s->bn = 256;

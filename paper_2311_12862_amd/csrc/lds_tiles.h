@@ -46,6 +46,8 @@ __device__ __forceinline__ void load_to_lds(u32x4 rsrc, unsigned voff, unsigned 
 __device__ __forceinline__ void load_dword_to_lds(u32x4 rsrc, unsigned voff, unsigned lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc) : "memory");
 }
+// Own loads have landed and own LDS reads are done.
+__device__ __forceinline__ void wait_own_loads() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
 // Own loads have landed and own LDS reads are done; after the barrier everyone's.
 __device__ __forceinline__ void wait_loads_and_sync() {
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");

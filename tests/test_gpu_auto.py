@@ -181,3 +181,38 @@ def test_fp32_tiles_in_pairs(n, c_in, c_out):
     assert info.tile_m == 64 and info.waves == 8 and info.tile_n == (16 if c_out <= 16 else 32)
     c = gen.uniform_cloud(n, max(2, int(round((4 * n) ** (1 / 3)))) + 1, seed=n)
     _check(c, 3, 1, False, "f32", c_in, c_out, 1, n)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 129, 1000, 2049])
+@pytest.mark.parametrize("dtype,c_in,c_out", [("f16", 64, 64), ("bf16", 96, 40), ("f16", 128, 136), ("bf16", 256, 72), ("f16", 264, 264), ("f32", 20, 36),
+                                              ("f32", 64, 68)])
+def test_groups_of_one_wave(n, dtype, c_in, c_out):
+    """Small maps: eight K groups of one wave each, on 64- and 32-row tiles; row counts around them, column tiles that are
+    not full, reductions whose pieces do not deal evenly to the groups; the same bits every time."""
+    import torch
+    import paper_2311_12862_amd as sp
+    info = sp.describe_launch(3, n, n, c_in, c_out, {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[dtype])
+    assert info.kernel == 2 and info.waves == 8 and info.k_steps == (16 if dtype == "f32" else 32)
+    c = gen.uniform_cloud(n, max(2, int(round((4 * n) ** (1 / 3)))) + 1, seed=n)
+    _check(c, 3, 1, False, dtype, c_in, c_out, 2, n)
+
+
+@pytest.mark.parametrize("c_in,c_out", [(256, 256), (136, 72), (96, 96)])
+def test_sorted_small_maps_have_the_bits_of_map_order(c_in, c_out):
+    """Which group takes a unit depends on the unit alone: 32- and 64-row tiles of one-wave groups, four and eight of them."""
+    import torch
+    import paper_2311_12862_amd as sp
+    c = gen.lidar_scene(53, target_n=30_000 if c_in < 200 else 3500)
+    sorted_, plain = sp.build_kmap(coords_dev(c), 3, 1), sp.build_kmap(coords_dev(c), 3, 1)
+    x, w, g = _layer_on(sp, sorted_, c_in, c_out, "f16", 3)
+    assert sp.describe_launch(3, len(c), len(c), c_in, c_out, torch.float16).sorted
+    want = sp.fwd(x, w, sorted_)
+    graph, y = torch.cuda.CUDAGraph(), torch.zeros_like(want)
+    narrow = _layer_on(sp, plain, 16, 16, "f16", 4)
+    sp.fwd(narrow[0], narrow[1], plain)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):   # (nothing is sorted under capture: the same kernel in map order)
+        sp.fwd(x, w, plain, out=y)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(y, want)
