@@ -161,7 +161,7 @@ struct KernelChoice {
   int tile_n = 0;  // k_igemm, k_igemm_wave: as passed to the kernel (0: its own default)
   RingShape ring;
 };
-int choose_kernel(int V, int64_t rows_dst, int64_t rows_src, int c_red, int c_cols, spconv_dtype dtype, const spconv_config* cfg,
+int choose_kernel(int V, int64_t rows_dst, int64_t rows_src, int c_red, int c_cols, bool dgrad, spconv_dtype dtype, const spconv_config* cfg,
                   const spconv_config& c, KernelChoice* out) {
   KernelChoice k;
   const bool f32 = dtype == SPCONV_F32, tiles_given = cfg && (cfg->tile_m != 0 || cfg->tile_n != 0);
@@ -179,7 +179,7 @@ int choose_kernel(int V, int64_t rows_dst, int64_t rows_src, int c_red, int c_co
       const int64_t tiles = ceil_div(c_cols, bn);
       if (tiles > 2 && (c.n_split > 0 || (double)tiles * c_red * (double)rows_dst > 6e7)) wave = false;
       if (c_red > 64 && c.n_split > 0) wave = false;  // (30k rows 128 -> 128: 34 us against 25 us)
-      if (!cfg && igemm_ring_shape(V, c.n_split, rows_dst, rows_src, c_red, c_cols, false, true, &k.ring) == SPCONV_OK && k.ring.nwk == 8)
+      if (!cfg && igemm_ring_shape(V, c.n_split, rows_dst, rows_src, c_red, c_cols, false, dgrad, true, &k.ring) == SPCONV_OK && k.ring.nwk == 8)
         wave = false;  // (wave_groups)
     }
     if (wave) {
@@ -191,7 +191,7 @@ int choose_kernel(int V, int64_t rows_dst, int64_t rows_src, int c_red, int c_co
   if (c.tile_n == 16) return SPCONV_EINVAL;
   // tiles loaded straight into LDS, unless the caller asks for the register-staged ones or for a tile shape
   if ((f32 || (c.kernel == 0 && !tiles_given)) &&
-      igemm_ring_shape(V, c.n_split, rows_dst, rows_src, c_red, c_cols, f32, cfg == nullptr, &k.ring) == SPCONV_OK) {
+      igemm_ring_shape(V, c.n_split, rows_dst, rows_src, c_red, c_cols, f32, dgrad, cfg == nullptr, &k.ring) == SPCONV_OK) {
     k.kind = KernelChoice::RING;
     *out = k;
     return SPCONV_OK;
@@ -342,7 +342,7 @@ int run_planes(spconv_op op, const void* src, const void* weights, spconv_kmap* 
   for (int g = 0; g < n_planes; ++g) {
     spconv_kmap* sub = km->groups[(size_t)g].get();
     sub->last_stream = st;
-    SPC_TRY(choose_kernel(sub->V, rows, rows, c_red, c_dst, dtype, cfg, c, &ls[(size_t)g].kc));
+    SPC_TRY(choose_kernel(sub->V, rows, rows, c_red, c_dst, dgrad != 0, dtype, cfg, c, &ls[(size_t)g].kc));
     SPC_TRY(plan_get(sub, sub->out_side, c.n_split, plan_flags(c), st, &ls[(size_t)g].plan));
     parts_total += ls[(size_t)g].plan->parts;
   }
@@ -412,7 +412,7 @@ int run_igemm_op(spconv_op op, const void* src, const void* weights, spconv_kmap
   const bool own_order = !cfg && auto_sorted(km->V, rows_dst, rows_src, c_red, c_cols, dtype);
   if (own_order) c.n_split = 1;
   KernelChoice kc;
-  SPC_TRY(choose_kernel(km->V, rows_dst, rows_src, c_red, c_cols, dtype, cfg, c, &kc));
+  SPC_TRY(choose_kernel(km->V, rows_dst, rows_src, c_red, c_cols, os.dgrad != 0, dtype, cfg, c, &kc));
   IgemmPlan* plan = nullptr;
   if (prepared_only) {
     if (c.n_split > km->V) return SPCONV_EINVAL;
@@ -763,7 +763,7 @@ std::vector<spconv_config> gemm_candidates(spconv_kmap* km, spconv_op op, int C_
   any.n_split = n_split;
   const int64_t rows_out = op == SPCONV_OP_DGRAD ? km->n_in : km->n_out, rows_src = op == SPCONV_OP_DGRAD ? km->n_out : km->n_in;
   KernelChoice kc;
-  if (resolve_config(&any, dtype, &c) == SPCONV_OK && choose_kernel(km->V, rows_out, rows_src, c_red, c_dst, dtype, &any, c, &kc) == SPCONV_OK &&
+  if (resolve_config(&any, dtype, &c) == SPCONV_OK && choose_kernel(km->V, rows_out, rows_src, c_red, c_dst, op == SPCONV_OP_DGRAD, dtype, &any, c, &kc) == SPCONV_OK &&
       kc.kind == KernelChoice::RING)
     cands.push_back(any);
   return cands;
@@ -1093,7 +1093,7 @@ SPCONV_API int spconv_describe_launch(int K, int64_t rows, int64_t rows_src, int
   if (rows == 0) return SPCONV_OK;  // nothing is launched
   if (!cfg && K != 5 && auto_sorted(V, rows, rows_src, C_red, C_cols, dtype)) c.n_split = 1;
   KernelChoice kc;
-  SPC_TRY(choose_kernel(V, rows, rows_src, C_red, C_cols, dtype, cfg, c, &kc));
+  SPC_TRY(choose_kernel(V, rows, rows_src, C_red, C_cols, dgrad != 0, dtype, cfg, c, &kc));
   const int tile_m = kc.kind == KernelChoice::WAVE ? 16 : kc.kind == KernelChoice::RING ? kc.ring.bm : kc.tile_m;
   PlanShape ps;
   SPC_TRY(plan_shape(V, rows, c.n_split, 16, &ps));

@@ -233,8 +233,8 @@ struct RingShape {  // igemm_ring_run (tiles loaded straight into LDS; every fp3
   unsigned feats_bytes = 0;
 };
 // small_tiles: 32-row tiles, and column tiles of fp32 that the layer's width does not ask for, may be chosen
-int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_red, int c_out, bool f32, bool small_tiles,
-                     RingShape* s);
+int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_red, int c_out, bool f32, bool dgrad,
+                     bool small_tiles, RingShape* s);
 
 // ---- plan.hip
 // flags: kPlanSlabs, kPlanOwnOrder (each combination is a plan of its own in the cache)

@@ -54,10 +54,12 @@ constexpr unsigned kNoRow = 0xFFFF0000u, kNoWeight = 0x80000000u;  // out of ran
 
 // BM x BN outputs; PB bytes of a row per unit (64 or 128), E bytes per element, NW waves in all, NWK K groups for each of
 // NWR such tiles, one below the other
+// (256-row tiles of 64-byte pieces: four stages, see the alternating halves below)
 template <int BM, int BN, int PB, int E, int NW, int NWK, int NWR> struct RingSmem {
+  static constexpr int stages = BM == 256 && PB == 64 ? 4 : 2;
   static constexpr int a_bytes = BM * PB, b_bytes = PB / E * BN * E, unit = a_bytes + b_bytes, stage = NWR * NWK * unit;
   static constexpr int slab = (NWR * BM * 27 * 4 + NW * 1024 - 1) / (NW * 1024) * (NW * 1024);  // whole loads of every wave
-  static constexpr int total = 2 * stage + slab;
+  static constexpr int total = stages * stage + slab;
 };
 
 template <typename T, int BM, int BN, int PB, int NWM, int NWN, int NWK, int NWR, bool DGRAD>
@@ -78,7 +80,7 @@ __global__ void __launch_bounds__(NWM* NWN* NWK* NWR * 64) k_ring(const RingPara
   static_assert(NA >= 1 && BM % (RPI * NW) == 0 && NBI >= 1 && (NBI % NW == 0 || NW % NBI == 0), "whole loads per wave");
   extern __shared__ __align__(16) unsigned char smem[];
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
-  const int* mapS = reinterpret_cast<const int*>(smem + 2 * L::stage);
+  const int* mapS = reinterpret_cast<const int*>(smem + L::stages * L::stage);
 
   const int lane = threadIdx.x & 63;
   const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -102,7 +104,7 @@ __global__ void __launch_bounds__(NWM* NWN* NWK* NWR * 64) k_ring(const RingPara
     const u32x4 m_rsrc = rsrc_of(p.map[part], (unsigned)((unsigned long long)p.rows_pad * width * 4));
     const unsigned bytes = (unsigned)(NWR * BM * width * 4), begin = (unsigned)(row0 * width) * 4u;
     for (unsigned o = wave_all * 1024; o < bytes; o += NW * NWK * NWR * 1024)
-      load_to_lds(m_rsrc, begin + o + lane * 16, 0, lds0 + 2 * L::stage + o);
+      load_to_lds(m_rsrc, begin + o + lane * 16, 0, lds0 + L::stages * L::stage + o);
   }
   unsigned bmask = 0;  // lane b < NWR * BM / 16: mask of the 16-row block b
   if (p.rowmask) {
@@ -252,11 +254,14 @@ __global__ void __launch_bounds__(NWM* NWN* NWK* NWR * 64) k_ring(const RingPara
       }
     }
   }
-  auto multiply = [&](int slot, int c) {
+  struct Frags {
+    u32x4 w[NB], x[MB];
+  };
+  auto read_frags = [&](int slot, int ks, Frags& f) {
     const unsigned char* st = smem + slot * L::stage + unit * L::unit;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      u32x4 w[NB], x[MB];
+    u32x4(&w)[NB] = f.w;
+    u32x4(&x)[MB] = f.x;
+    {
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         if constexpr (DGRAD) {
@@ -276,18 +281,67 @@ __global__ void __launch_bounds__(NWM* NWN* NWK* NWR * 64) k_ring(const RingPara
       }
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) x[mb] = *reinterpret_cast<const u32x4*>(st + xf[ks] + mb * 16 * PB);
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-        if ((blk[mb] >> c) & 1u) {  // (the lock-step unit: a 16-row block without this offset is skipped)
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mma<T>(w[nb], x[mb], acc[mb][nb]);
-        }
     }
+  };
+  auto multiply = [&](int c, const Frags& f) {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+      if ((blk[mb] >> c) & 1u) {  // (the lock-step unit: a 16-row block without this offset is skipped)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mma<T>(f.w[nb], f.x[mb], acc[mb][nb]);
+      }
   };
 
   wait_loads_and_sync();  // the slab is there
   fetch_idx();
-  if constexpr (NW == 1) {
+  if constexpr (L::stages == 4) {
+    // Two halves of the waves, one wave of each on every SIMD, take turns: in one slot the first half reads its fragments of a unit
+    // and issues its share of the loads three units ahead while the second half multiplies, in the next slot the other way round.
+    // A unit's loads have five slots to land (each wave waits for its own before the barrier into the slot in which the unit is
+    // first read), and its stage is filled again two slots after both halves have read it.  Beyond the last unit loads are
+    // still issued, out of range, so that the counts stay.  Measured (300k rows of a room, against two stages and all waves in step):
+    // input gradient 256 -> 256 463 -> 428 us, 136 -> 200 387 -> 315, forward 136 -> 200 289 -> 271; bound by the rows that come from
+    // beyond the L2 (4.3 GB through the CUs' address units).
+    static_assert(NWK == 1 && NWR == 1 && KS == 1 && NWM == 2, "");
+    constexpr int NL = NA + NBW;
+    const int mine = units_of(tmask, 0);
+    auto load_next = [&](int u) {
+      if (u < mine) {
+        load_unit(u & 3);
+      } else {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) load_to_lds(x_rsrc, kNoRow, 0, lds0 + (u & 3) * L::stage + (wave * NL + i) * 1024);
+      }
+    };
+    Frags f;
+    for (int u = 0; u < 3; ++u) load_next(u);
+    if (wm == 0) {
+      for (int u = 0; u < mine; ++u) {
+        wait_loads_and_sync<2 * NL>();
+        read_frags(u & 3, 0, f);
+        load_next(u + 3);
+        sync_lds();
+        __builtin_amdgcn_s_setprio(1);
+        multiply(qc.c, f);
+        __builtin_amdgcn_s_setprio(0);
+        cursor_step(qc);
+      }
+      wait_loads_and_sync();
+    } else {
+      wait_loads_and_sync<2 * NL>();
+      for (int u = 0; u < mine; ++u) {
+        sync_lds();
+        read_frags(u & 3, 0, f);
+        load_next(u + 3);
+        wait_loads_and_sync<2 * NL>();
+        __builtin_amdgcn_s_setprio(1);
+        multiply(qc.c, f);
+        __builtin_amdgcn_s_setprio(0);
+        cursor_step(qc);
+      }
+      wait_own_loads();
+    }
+  } else if constexpr (NW == 1) {
     // every wave is a K group: nothing is shared until the end, so nothing is waited for but the wave's own loads, and one
     // wave's loads are issued while another multiplies
     bool more = qi.piece < n_pieces;
@@ -295,8 +349,14 @@ __global__ void __launch_bounds__(NWM* NWN* NWK* NWR * 64) k_ring(const RingPara
     for (int slot = 0; more; slot ^= 1) {
       wait_own_loads();  // (the other stage was read before: its fragments are in registers)
       more = qi.piece < n_pieces;
+      Frags f[KS];
+      read_frags(slot, 0, f[0]);
       if (more) load_unit(slot ^ 1);
-      multiply(slot, qc.c);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        if (ks > 0) read_frags(slot, ks, f[ks]);
+        multiply(qc.c, f[ks]);
+      }
       cursor_step(qc);
     }
   } else {
@@ -308,7 +368,14 @@ __global__ void __launch_bounds__(NWM* NWN* NWK* NWR * 64) k_ring(const RingPara
     for (int it = 0; it < steps; ++it) {
       wait_loads_and_sync();  // this step's unit has landed, and everyone is done with the stage that is filled next
       if (it + 1 < mine) load_unit((it + 1) & 1);
-      if (it < mine && ((wave_mask >> qc.c) & 1u)) multiply(it & 1, qc.c);
+      if (it < mine && ((wave_mask >> qc.c) & 1u)) {
+        Frags f[KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          read_frags(it & 1, ks, f[ks]);
+          multiply(qc.c, f[ks]);
+        }
+      }
       cursor_step(qc);
     }
   }
@@ -460,8 +527,8 @@ bool wave_groups(int V, int n_split, int c_red, int c_out, int64_t wgs) {
 // 125, (64, 128) 134; 100k rows 64 -> 128, (64, 128) 30.3, (128, 128) 31.4; 128 -> 64, two K groups (64, 64) 30.2, one
 // 35.2; 30k rows 128 -> 128, (64, 64) with two K groups 24.9, (64, 128) 37.9, (128, 128) 47; 9k rows 256 -> 256, (32,
 // 64) with two K groups 36.9, (64, 64) 41.2, (64, 128) 67.
-int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_red, int c_out, bool f32, bool small_tiles,
-                     RingShape* s) {
+int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_red, int c_out, bool f32, bool dgrad,
+                     bool small_tiles, RingShape* s) {
   *s = RingShape{};
   const int q = f32 ? 4 : 8, e = f32 ? 4 : 2;
   if (rows < 1 || rows_src < 0 || c_red < q || c_out < q || c_red % q || c_out % q) return SPCONV_EINVAL;
@@ -508,7 +575,10 @@ int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
     } else if (c_out <= 32) {
       s->bm = 64, s->bn = 32;
     } else if (c_out > 128 && wgs(256, 256) >= 768) {
+      // (four stages of 64-byte pieces, whose halves of waves take turns, where the weights need no transposing reads: 300k rows
+      // 256 -> 256 input gradient 463 -> 428 us, forward 470 -> 467; 220k rows of a scan 239 -> 238, 243 -> 264)
       s->bm = 256, s->bn = 256;
+      if (dgrad) s->piece = 64;
     } else if (c_out > 64 && wgs(128, 128) >= 1024) {
       s->bm = 128, s->bn = 128;
     } else if (c_out > 64 && wgs(64, 128) >= 1024) {

@@ -48,10 +48,13 @@ __device__ __forceinline__ void load_dword_to_lds(u32x4 rsrc, unsigned voff, uns
 }
 // Own loads have landed and own LDS reads are done.
 __device__ __forceinline__ void wait_own_loads() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
-// Own loads have landed and own LDS reads are done; after the barrier everyone's.
-__device__ __forceinline__ void wait_loads_and_sync() {
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+// Own loads but the N youngest have landed and own LDS reads are done; after the barrier everyone's.
+template <int N = 0> __device__ __forceinline__ void wait_loads_and_sync() {
+  static_assert(N < 64, "vmcnt");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(N) : "memory");
 }
+// Own LDS reads are done; after the barrier everyone's.
+__device__ __forceinline__ void sync_lds() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 }  // namespace
 }  // namespace spc

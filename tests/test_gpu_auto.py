@@ -216,3 +216,22 @@ def test_sorted_small_maps_have_the_bits_of_map_order(c_in, c_out):
     graph.replay()
     torch.cuda.synchronize()
     assert torch.equal(y, want)
+
+
+@pytest.mark.parametrize("n", [196_609, 199_937])
+@pytest.mark.parametrize("c_in,c_out", [(256, 64), (136, 40)])
+def test_alternating_halves(n, c_in, c_out):
+    """256 x 256 tiles of 64-byte pieces (input gradients of wide layers, reductions that are not whole 128-byte pieces), ragged in
+    rows and columns, with row tiles that few offsets and tiles that all offsets reach, against the register-staged kernel."""
+    import paper_2311_12862_amd as sp
+    import torch
+    c = gen.full_grid(20, 26, seed=5)
+    c = np.concatenate([c[:n - 3000], np.stack([np.full(3000, 99), np.arange(3000) * 7, np.zeros(3000), np.zeros(3000)], 1)]).astype(np.int32)
+    assert sp.describe_launch(3, n, n, c_out, c_in, torch.float16, dgrad=True).tile_m == 256
+    km = sp.build_kmap(coords_dev(c), 3, 1)
+    w = (torch.randn(27, c_in, c_out, device="cuda") / 20).half()
+    g = torch.randn(n, c_out, device="cuda").half()
+    want = sp.dgrad(g, w, km, sp.Config(n_split=1, kernel=2, tile_m=64)).double().cpu().numpy()
+    got = sp.dgrad(g, w, km)
+    assert norm_err(got, want) <= 2e-3
+    assert torch.equal(got, sp.dgrad(g, w, km))
