@@ -466,7 +466,7 @@ int launch_ring(const RingParams& p, bool dgrad, dim3 grid, hipStream_t st) {
   X(32, 64, 1, 1, 4, 1) X(32, 64, 1, 1, 8, 1) X(32, 64, 1, 2, 2, 1) X(64, 32, 4, 1, 1, 1) X(64, 64, 1, 1, 8, 1) X(64, 64, 2, 2, 1, 1) \
   X(64, 64, 2, 2, 2, 1) X(64, 128, 2, 2, 1, 1) X(128, 128, 2, 2, 1, 1) X(256, 256, 2, 4, 1, 1)
 #define SPC_RING_SHAPES_32(X) \
-  X(32, 16, 2, 1, 2, 2) X(32, 32, 1, 2, 2, 2) X(64, 16, 4, 1, 1, 1) X(64, 32, 1, 1, 8, 1) X(64, 32, 4, 1, 1, 1) X(64, 64, 2, 2, 1, 1)
+  X(32, 16, 2, 1, 2, 2) X(32, 32, 1, 2, 2, 2) X(64, 16, 4, 1, 1, 1) X(64, 32, 1, 1, 8, 1) X(64, 32, 4, 1, 1, 1) X(64, 64, 2, 2, 1, 1) X(64, 64, 2, 2, 2, 1)
 // (eight K groups of 128-byte pieces do not fit in LDS)
 constexpr bool ring_built(int pb, int nwk) { return nwk < 8 || pb == 64; }
 
@@ -551,16 +551,20 @@ int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
     // group), 96; 100k 128 -> 128 165 (one), 178.
     // On maps of a few workgroups per CU eight K groups of a wave each end sooner still: 5k rows 96 -> 96 38, 28; 15k 64 -> 64 28,
     // 20; 10k 32 -> 32 16, 13; 30k 96 -> 32 40, 27; where the line lies: 30k 64 -> 64 30, 33; 32 -> 32 24, 25; 60k 96 -> 96 104, 104.
+    // Tiles of a dense room all have their 27 offsets, and are bound by the work, not by the longest: 62k rows (64 x 64 with two K
+    // groups, two 32 x 32) 64 -> 64 66, 77; 96 -> 64 94, 110; a scan of as many 57, 53; 82, 78; 45k 57, 59; 80, 86; scan 48, 42; 67,
+    // 60.  Unsorted 45k 32 -> 32 (64 x 32, two 32 x 32) 36, 42; 30k 29.5, 28.
     s->bm = 64;
     s->bn = c_out <= 16 ? 16 : 32;
     s->piece = c_red <= 16 ? 64 : 128;
     if (small_tiles && V >= 25 && c_red > 16 && c_out > 16 && wgs(64, 32) <= 12 * c_red) {
       s->nwk = 8;
       s->piece = 64;
-    } else if (small_tiles && wgs(64, s->bn) < (c_red <= 32 ? 1500 : 2000)) {
+    } else if (small_tiles && wgs(64, s->bn) < (c_out > 32 ? 1400 : c_red <= 32 ? 600 : 2000)) {
       s->nwk = s->nwr = 2;
     } else if (c_out > 32) {
       s->bn = 64;
+      if (small_tiles && wgs(64, 64) < 1024) s->nwk = 2;
     }
   } else {
     s->piece = (c_red % 64 == 0) ? 128 : 64;
