@@ -51,6 +51,8 @@ struct Ctl {
 // memory, so that no copy has to be enqueued behind the build.
 // What an asynchronous build leaves in pinned host memory, in one 8-byte word so that one store
 // publishes it: bit 63 = written, bits 48..55 = error flags, bits 0..47 = pair count.
+// Whoever waits polls `word` or `ready` and hands the block to the next build as soon as it is set: the store that is polled is the
+// last access to the block of the kernels that were given it, and no kernel stores both.
 struct HostResult {
   unsigned long long word;
   // what the other builds hand over (k_publish): written before `ready`
@@ -720,7 +722,8 @@ __global__ void __launch_bounds__(256) k_build_init(ulonglong2* __restrict__ tab
 
 // Adds up the control block and writes the figures straight into pinned host memory, where the host polls for them: a
 // copy and a stream synchronisation in its place cost about 20 us of idle GPU per use.  One wave.
-__global__ void __launch_bounds__(64) k_publish(const Ctl* __restrict__ ctl, HostResult* host) {
+// unwaited: an asynchronous build, of which only the word is read; else everything but the word.
+__global__ void __launch_bounds__(64) k_publish(const Ctl* __restrict__ ctl, HostResult* host, bool unwaited) {
   const int lane = threadIdx.x;  // kPairSlots == 64
   const unsigned long long mine = ctl->pairs[lane * 16] & ((1ull << 40) - 1);  // (above: publish_pairs' arrivals)
   unsigned long long pairs = mine, entries = ctl->entries[lane * 16], k_or = ctl->key_or[lane * 16], k_and = ctl->key_and[lane * 16];
@@ -729,6 +732,12 @@ __global__ void __launch_bounds__(64) k_publish(const Ctl* __restrict__ ctl, Hos
     entries += __shfl_xor(entries, o);
     k_or |= __shfl_xor(k_or, o);
     k_and &= __shfl_xor(k_and, o);
+  }
+  if (unwaited) {
+    if (lane == 0)
+      __hip_atomic_store(&host->word, kHostReady | ((ctl->flags & 0xFFu) << 48) | (pairs & 0xFFFFFFFFFFFFull), __ATOMIC_RELEASE,
+                         __HIP_MEMORY_SCOPE_SYSTEM);
+    return;
   }
   for (int g = 0; g < 5; ++g) {
     unsigned long long v = lane / kPlaneSlots == g ? mine : 0ull;
@@ -742,7 +751,6 @@ __global__ void __launch_bounds__(64) k_publish(const Ctl* __restrict__ ctl, Hos
     host->key_and = k_and;
     host->pairs = pairs;
     host->entries = entries;
-    host->word = kHostReady | ((ctl->flags & 0xFFu) << 48) | (pairs & 0xFFFFFFFFFFFFull);  // (what an unwaited build is asked for)
     __threadfence_system();
     __hip_atomic_store(&host->ready, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
@@ -1443,7 +1451,7 @@ int read_ctl(const Ctl* ctl, HostResult* res, hipStream_t st) {
   HostCtl* hc = host_ctl_acquire();
   if (!hc) return SPCONV_ENOMEM;
   hc->res.ready = 0;  // (pinned memory: visible to the kernel launched below)
-  hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, st, ctl, hc->dev);
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, st, ctl, hc->dev, false);
   int status = SPCONV_OK;
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
@@ -1562,7 +1570,7 @@ int build_submanifold3(spconv_kmap* km, const int4* rows, int64_t N, bool async,
     hipLaunchKernelGGL(k_probe_runs3<false>, dim3(blocks_for(ceil_div(side.rows_pad, 7), 4)), dim3(256), 0, st, rows, (int)N,
                        (long long)side.rows_pad, tab.buf.as<RunSlot>(), tab.log_cap, (const unsigned*)nullptr, side.map.as<int>(),
                        side.mask.as<unsigned>(), ctl, hc->dev);
-  if (small && async) hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, st, ctl, hc->dev);
+  if (small && async) hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, st, ctl, hc->dev, true);
   const bool ok = hipGetLastError() == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
