@@ -681,6 +681,19 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// The parts of a stride-2 build's tables that are in use, into buffers of that size (16-byte words).
+struct Copy3 {
+  const uint4* src[3];
+  uint4* dst[3];
+  long long words[3];
+};
+__global__ void __launch_bounds__(256) k_copy3(const Copy3 c) {
+  const long long step = (long long)gridDim.x * 256;
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < c.words[a]; i += step) c.dst[a][i] = c.src[a][i];
+}
+
 // Plain fills (in place of memset calls, which must stay out of anything a caller may capture).
 // The K = 1 map of a row set: row r meets itself; rows of the padding meet nothing.
 __global__ void __launch_bounds__(256) k_identity_map(int* __restrict__ map, unsigned* __restrict__ mask,
@@ -1655,28 +1668,57 @@ int build_submanifold5(spconv_kmap* km, const int4* rows, int64_t N, hipStream_t
   return km->build_status;
 }
 
-// Stride-2 builds (K = 2, 3) over a bit per cell of the coarse points' box; kRetryTable where the box is too large.
+// The tables of a stride-2 build are made for as many outputs as inputs, and the kmap keeps them.  Where more than half of that is
+// unused, and more than kKeepBytes of it, the used part moves into buffers of its own size: 300k rows of a room, 75k outputs,
+// 38 MB -> 10 MB, the build 111 -> 126 us (copy 4 us, the rest is a second wait: smaller surpluses are left: 60k rows 78 -> 90).
+// Without memory for the copy everything stays where it is.
+constexpr int64_t kKeepBytes = 16 << 20;
+int shrink_to_outputs(SideMap& side, int V, DevBuf& coarse_rows, const Ctl* ctl, hipStream_t st) {
+  const size_t used[3] = {(size_t)side.rows_pad * V * sizeof(int), (size_t)side.rows_pad * sizeof(unsigned), (size_t)side.rows * 16};
+  DevBuf* const from[3] = {&side.map, &side.mask, &coarse_rows};
+  size_t all = 0, need = 0;
+  for (int a = 0; a < 3; ++a) all += from[a]->bytes, need += used[a];
+  if (2 * need >= all || all - need <= (size_t)kKeepBytes) return SPCONV_OK;
+  DevBuf to[3];
+  Copy3 c{};
+  for (int a = 0; a < 3; ++a) {
+    if (to[a].alloc(used[a]) != SPCONV_OK) return SPCONV_OK;
+    c.src[a] = from[a]->as<uint4>();
+    c.dst[a] = to[a].as<uint4>();
+    c.words[a] = (long long)(used[a] / 16);
+  }
+  hipLaunchKernelGGL(k_copy3, dim3((unsigned)std::min<int64_t>(ceil_div((int64_t)(used[0] / 16), 1024), 2048)), dim3(256), 0, st, c);
+  SPC_LAUNCH_CHECK();
+  for (int a = 0; a < 3; ++a) {  // (the old ones go back to the pool of this stream)
+    std::swap(from[a]->p, to[a].p);
+    std::swap(from[a]->bytes, to[a].bytes);
+  }
+  HostResult again{};  // (a build that is waited for is complete when it returns)
+  return read_ctl(ctl, &again, st);
+}
+
+// Stride-2 builds (K = 2, 3) over a bit per cell of the coarse points' box; kRetryTable where the box is too large, or the
+// memory does not suffice (up to 384 bytes a row for bits and prefixes, and tables for N outputs: the hash table and tables for
+// the outputs that there are need less).
 int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t st) {
   const int V = K * K * K;
   const int64_t max_words = std::min<int64_t>(std::max<int64_t>(N * (kCellsPerRow / 64), 1 << 14), kMaxBoxWords);
   const int64_t max_chunks = ceil_div(max_words, kChunkWords);
   DevBuf ctl_buf, own_rows, coarse_rows, small, bits, prefix;
-  SPC_TRY(ctl_buf.alloc(sizeof(Ctl)));
-  Ctl* ctl = ctl_buf.as<Ctl>();
-  SPC_TRY(own_rows.alloc((size_t)N * 16));
-  SPC_TRY(coarse_rows.alloc((size_t)N * 16));
-  const size_t partial_bytes = (size_t)kBoxBlocks * 9 * sizeof(int);
-  SPC_TRY(small.alloc(sizeof(Box) + partial_bytes + (size_t)max_chunks * sizeof(unsigned)));
-  Box* box = small.as<Box>();
-  int* partial = reinterpret_cast<int*>(box + 1);
-  unsigned* totals = reinterpret_cast<unsigned*>(small.as<char>() + sizeof(Box) + partial_bytes);
-  if (bits.alloc((size_t)(max_words + 1) * 8) != SPCONV_OK || prefix.alloc((size_t)max_words * 4) != SPCONV_OK)
-    return kRetryTable;  // (the table is smaller)
   // sized for as many outputs as inputs: their number is read at the end
   SideMap& side = km->out_side;
   const int64_t most = round_up(N, kRowPad);
-  SPC_TRY(side.map.alloc((size_t)most * V * sizeof(int)));
-  SPC_TRY(side.mask.alloc((size_t)most * sizeof(unsigned)));
+  const size_t partial_bytes = (size_t)kBoxBlocks * 9 * sizeof(int);
+  if (ctl_buf.alloc(sizeof(Ctl)) != SPCONV_OK || own_rows.alloc((size_t)N * 16) != SPCONV_OK ||
+      coarse_rows.alloc((size_t)N * 16) != SPCONV_OK ||
+      small.alloc(sizeof(Box) + partial_bytes + (size_t)max_chunks * sizeof(unsigned)) != SPCONV_OK ||
+      bits.alloc((size_t)(max_words + 1) * 8) != SPCONV_OK || prefix.alloc((size_t)max_words * 4) != SPCONV_OK ||
+      side.map.alloc((size_t)most * V * sizeof(int)) != SPCONV_OK || side.mask.alloc((size_t)most * sizeof(unsigned)) != SPCONV_OK)
+    return kRetryTable;
+  Ctl* ctl = ctl_buf.as<Ctl>();
+  Box* box = small.as<Box>();
+  int* partial = reinterpret_cast<int*>(box + 1);
+  unsigned* totals = reinterpret_cast<unsigned*>(small.as<char>() + sizeof(Box) + partial_bytes);
   int* map = side.map.as<int>();
   const unsigned n_partial = (unsigned)std::min<int64_t>(ceil_div(N, 1024), kBoxBlocks);
   hipLaunchKernelGGL(k_box_bounds, dim3(n_partial), dim3(256), 0, st, rows, (int)N, own_rows.as<int4>(), partial);
@@ -1712,6 +1754,7 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
   side.rows_pad = round_up(side.rows, kRowPad);
   side.ready = true;
   km->n_pairs = (int64_t)h.pairs;
+  SPC_TRY(shrink_to_outputs(side, V, coarse_rows, ctl, st));
   std::swap(km->in_coords.p, own_rows.p);
   std::swap(km->in_coords.bytes, own_rows.bytes);
   std::swap(km->out_coords.p, coarse_rows.p);

@@ -629,3 +629,72 @@ def test_unwaited_and_waited_builds_share_no_result(sp):
         t.join()
     torch.cuda.synchronize()
     assert not wrong, wrong[:5]
+
+
+class _CountingAllocator:
+    """Device memory for the library, counted; requests beyond `limit` live bytes are refused."""
+
+    def __init__(self, sp, limit=None):
+        self.sp, self.limit, self.live, self.most = sp, limit, {}, 0
+
+    def held(self):
+        return sum(t.numel() for t in self.live.values())
+
+    def __enter__(self):
+        import gc
+        import torch
+
+        def alloc(n, stream):
+            if self.limit is not None and self.held() + n > self.limit:
+                return 0
+            t = torch.empty(max(n, 1), dtype=torch.uint8, device="cuda")
+            self.live[t.data_ptr()] = t
+            self.most = max(self.most, self.held())
+            return t.data_ptr()
+        gc.collect()
+        self.sp.set_allocator(alloc, lambda ptr, stream: self.live.pop(ptr))
+        return self
+
+    def __exit__(self, *_):
+        import gc
+        import torch
+        gc.collect()
+        torch.cuda.synchronize()
+        self.sp.set_allocator(None, None)
+
+
+@pytest.mark.parametrize("K,grid", [(2, 76), (3, 58)])
+def test_stride2_kmaps_keep_what_their_outputs_need(sp, K, grid):
+    """A dense cloud has an eighth as many outputs as inputs: the kmap does not stay as large as for one output per input, and
+    works from the smaller tables."""
+    from _util import TOL
+    c = gen.full_grid(grid, 1, seed=3)
+    ref = oc.build_kmap(c, K, 2)
+    coords = coords_dev(c)
+    with _CountingAllocator(sp) as mem:
+        km = sp.build_kmap(coords, K, 2)
+        V, rows_pad = K ** 3, -(-ref.n_out // 256) * 256
+        tables = rows_pad * (V + 1) * 4 + ref.n_out * 16
+        assert mem.held() <= len(c) * 16 + 2 * tables
+        np.testing.assert_array_equal(km.export().cpu().numpy(), ref.M)
+        np.testing.assert_array_equal(km.export_mask().cpu().numpy().view(np.uint32), oc.bitmask(ref.M))
+        np.testing.assert_array_equal(km.out_coords().cpu().numpy(), ref.out_coords)
+        (x32, x), (w32, w), _ = make_layer(ref.n_in, ref.n_out, 16, 16, V, "f16", 4)
+        assert norm_err(sp.fwd(x, w, km), oc.forward(x32, w32, ref.M)) <= TOL["f16"]
+        km.destroy()
+        assert not mem.live
+
+
+@pytest.mark.parametrize("K", [2, 3])
+def test_stride2_builds_where_memory_is_short(sp, K):
+    """Where there is no room for tables of one output per input, a build that needs far less of them still succeeds."""
+    c = gen.full_grid(30, 1, seed=4)
+    ref = oc.build_kmap(c, K, 2)
+    coords = coords_dev(c)
+    _check_kmap(sp, c, K, 2, False)
+    # room for the bits and prefixes of a build over the box, and for two sets of coordinates, but not for its map
+    with _CountingAllocator(sp, limit=len(c) * (384 + 32) + (1 << 19)) as mem:
+        km = sp.build_kmap(coords, K, 2)
+        np.testing.assert_array_equal(km.export().cpu().numpy(), ref.M)
+        km.destroy()
+        assert not mem.live
