@@ -31,7 +31,7 @@ constexpr unsigned long long kEmpty = ~0ull;
 // SORT: a sort's bounded wait ran out; BOX: the coarse points' bounding box is too large for a bit per cell
 enum : unsigned long long { FLAG_RANGE = 1, FLAG_DUP = 2, FLAG_FULL = 4, FLAG_SORT = 8, FLAG_BOX = 16 };
 constexpr int kRetryGeneralSort = 1;  // (internal) build again with the general sort
-constexpr int kRetryTable = 2;        // (internal) build again with a hash table of the coarse points
+constexpr int kRetryTable = 2;        // (internal) build with a hash table of the coarse points
 
 // Control block read back by the host at the build's synchronisation point.  The pair counter
 // is spread over 64 cache lines (one atomic per probe workgroup) so that the adds do not queue
@@ -160,19 +160,14 @@ __global__ void __launch_bounds__(256) k_insert_rows(const int4* __restrict__ co
 
 // Coarse coordinates floor(p / s): de-duplicate through a second table, append each
 // new key to ukeys (order arbitrary; sorted afterwards), and reduce OR / AND of the
-// keys so that the host knows which key bytes vary.
-__global__ void __launch_bounds__(256) k_coarse_unique(const int4* __restrict__ coords, int n, int stride,
-                                                       unsigned long long* tab, int log_cap,
-                                                       unsigned long long* __restrict__ ukeys, Ctl* ctl,
-                                                       int4* __restrict__ keep) {
+// keys so that the host knows which key bytes vary.  Every thread of a workgroup of 256; live: it has a row.
+__device__ __forceinline__ void coarse_unique(bool live, int4 c, int stride, unsigned long long* tab, int log_cap,
+                                              unsigned long long* __restrict__ ukeys, Ctl* ctl) {
   __shared__ unsigned long long s_or[4], s_and[4];
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   bool fresh = false;
   unsigned long long key = 0, k_or = 0, k_and = ~0ull;
-  if (j < n) {
-    const int4 c = coords[j];
-    if (keep) keep[j] = c;  // the kmap's own copy of the caller's rows (builds without a fine table)
+  if (live) {
     if (!coord_ok(c.x, c.y, c.z, c.w)) atomicOr(&ctl->flags, FLAG_RANGE);
     if (coord_ok(c.x, c.y, c.z, c.w)) {
       key = pack_key(c.x, floor_div(c.y, stride), floor_div(c.z, stride), floor_div(c.w, stride));
@@ -210,6 +205,19 @@ __global__ void __launch_bounds__(256) k_coarse_unique(const int4* __restrict__ 
     for (int w = 0; w < wave; ++w) before += wave_cnt[w];
     ukeys[block_base + before + __popcll(bal & ((1ull << lane) - 1ull))] = key;
   }
+}
+
+__global__ void __launch_bounds__(256) k_coarse_unique(const int4* __restrict__ coords, int n, int stride,
+                                                       unsigned long long* tab, int log_cap,
+                                                       unsigned long long* __restrict__ ukeys, Ctl* ctl,
+                                                       int4* __restrict__ keep) {
+  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  int4 c = make_int4(-1, 0, 0, 0);
+  if (j < n) {
+    c = coords[j];
+    if (keep) keep[j] = c;  // the kmap's own copy of the caller's rows (builds without a fine table)
+  }
+  coarse_unique(j < n, c, stride, tab, log_cap, ukeys, ctl);
 }
 
 // Candidate outputs of a dilated stride-1 map: q = p - delta for every input p and offset delta
@@ -400,8 +408,10 @@ __global__ void __launch_bounds__(256)
 // look-ups, whole builds in us: LiDAR-like scans of 2k rows 71 -> 36, 10k 80 -> 40, 30k 89 -> 46, 100k 109 -> 64, 200k (127k
 // outputs) 178 -> 79, 400k 227 -> 124; a room of 300k 135 -> 96.  What is left is launches of 4 to 5 us and the marks: an atomic
 // per row, which the memory side takes at 10 per ns (200k rows: 20 us of the 69 of kernels).
-// A box of more than kCellsPerRow cells a row (a scan of 5 cm voxels has about 450) is left to the table; the kernels behind
-// the first two then find nothing to do, which costs such a build 25 us (20k points spread over 60,000 cells an axis: 190 -> 215).
+// A box of more than kCellsPerRow cells a row (a scan of 5 cm voxels has about 450) is left to the table: the clearing launch
+// empties one in the bitmap's place, the marking launch fills it, and the host, which reads the box's verdict behind that, goes on
+// with the sort.  Whole builds of points spread over 60,000 cells an axis, us, all through the table and so: 2k rows 150, 152;
+// 20k 218, 219; 100k 253, 255; 200k 290, 289.
 constexpr int kBoxBlocks = 256;
 constexpr int kCellsPerRow = 2048;
 constexpr int kChunkWords = 2048;  // 64-bit words per workgroup and step
@@ -461,10 +471,12 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// Every workgroup works out the box; the bitmap is cleared as far as it reaches; the first one clears the control block and
-// leaves the box for the launches behind.
+// Every workgroup works out the box; the bitmap is cleared as far as it reaches; the first one clears the control block,
+// leaves the box for the launches behind, and its flags for the host (the word of host).  Where the box is too large, table_slots
+// empty slots of the hash tables take the bitmap's place.
 __global__ void __launch_bounds__(256)
-    k_box_clear(const int* __restrict__ partial, int n_partial, long long max_words, ulonglong2* __restrict__ bits, Box* box_out, Ctl* ctl) {
+    k_box_clear(const int* __restrict__ partial, int n_partial, long long max_words, ulonglong2* __restrict__ bits, long long table_slots,
+                Box* box_out, Ctl* ctl, HostResult* host) {
   __shared__ int red[4][9];
   __shared__ Box s_box;
   const int t = threadIdx.x;
@@ -498,15 +510,20 @@ __global__ void __launch_bounds__(256)
     if (words > (unsigned long long)max_words) b.flags |= (unsigned)FLAG_BOX;
     b.words = words > (unsigned long long)max_words ? 0u : (unsigned)words;
     s_box = b;
-    if (blockIdx.x == 0) *box_out = b;
+    if (blockIdx.x == 0) {
+      *box_out = b;
+      __hip_atomic_store(&host->word, kHostReady | ((unsigned long long)b.flags << 48), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
   }
   __syncthreads();
   const long long pairs_of_words = ((long long)s_box.words + 1) / 2;  // (the buffer holds an even number)
-  for (long long i = (long long)blockIdx.x * 256 + t; i < pairs_of_words; i += (long long)gridDim.x * 256)
-    bits[i] = make_ulonglong2(0ull, 0ull);
+  const bool table = s_box.flags & (unsigned)FLAG_BOX;
+  const unsigned long long fill = table ? kEmpty : 0ull;
+  const long long fills = table ? table_slots : pairs_of_words;
+  for (long long i = (long long)blockIdx.x * 256 + t; i < fills; i += (long long)gridDim.x * 256) bits[i] = make_ulonglong2(fill, fill);
   if (blockIdx.x == 0) {
     if (t == 0) {
-      ctl->flags = s_box.flags;
+      ctl->flags = s_box.flags & ~(unsigned)FLAG_BOX;
       ctl->count = 0;
       ctl->tick_top = 0;
     }
@@ -520,10 +537,16 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// The marks; where the box is too large, the coarse points go through the table instead (log_cap 0: it does not fit there).
 __global__ void __launch_bounds__(256)
-    k_box_mark(const int4* __restrict__ coords, int n, const Box* __restrict__ box_in, unsigned* __restrict__ bits) {
+    k_box_mark(const int4* __restrict__ coords, int n, const Box* __restrict__ box_in, unsigned* __restrict__ bits, int log_cap,
+               unsigned long long* __restrict__ ukeys, Ctl* ctl) {
   const Box box = *box_in;
   const int j = blockIdx.x * 256 + threadIdx.x;
+  if (box.flags & (unsigned)FLAG_BOX) {
+    if (log_cap) coarse_unique(j < n, j < n ? coords[j] : make_int4(-1, 0, 0, 0), 2, reinterpret_cast<unsigned long long*>(bits), log_cap, ukeys, ctl);
+    return;
+  }
   if (j >= n || !box.words) return;
   const int4 c = coords[j];
   if (!coord_ok(c.x, c.y, c.z, c.w)) return;
@@ -585,7 +608,7 @@ __global__ void __launch_bounds__(256)
   __syncthreads();
   unsigned base = s_before[0] + s_before[1] + s_before[2] + s_before[3];
   const unsigned total = s_all[0] + s_all[1] + s_all[2] + s_all[3];
-  if (blockIdx.x == 0 && threadIdx.x == 0) ctl->count = total;
+  if (blockIdx.x == 0 && threadIdx.x == 0 && words) ctl->count = total;  // (else: of the table's points, or none)
   constexpr int W = kChunkWords / 256;  // words per lane: a wave owns 64 * W consecutive ones
   for (unsigned c = c0; c < c1; ++c) {
     const unsigned first = c * kChunkWords + wib * (64 * W);
@@ -1488,6 +1511,22 @@ int read_ctl(const Ctl* ctl, HostResult* res, hipStream_t st) {
   return status;
 }
 
+// Waits for the word that work enqueued on st stores, and gives the block back.  launched: what the launches came to.
+int wait_word(HostCtl* hc, hipError_t launched, hipStream_t st, unsigned long long* word) {
+  int status = SPCONV_OK;
+  if (launched != hipSuccess) {
+    status = hip_fail(launched, "launch", __FILE__, __LINE__);
+    (void)hipStreamSynchronize(st);  // (what was launched may still store)
+  } else if (!host_ctl_ready(hc, 0.01)) {
+    const hipError_t w = hipStreamSynchronize(st);
+    if (w != hipSuccess) status = hip_fail(w, "hipStreamSynchronize", __FILE__, __LINE__);
+    else if (!host_ctl_ready(hc, 0.0)) status = SPCONV_EHIP;
+  }
+  *word = hc->res.word;
+  host_ctl_release(hc);
+  return status;
+}
+
 // counted: ctl->count rows, at most `rows`
 template <int V> int masks_from_map(const int* map, int64_t rows, unsigned* mask, Ctl* ctl, hipStream_t st, bool counted = false) {
   constexpr int kMany = V == 27 ? 8 : 1;
@@ -1697,14 +1736,22 @@ int shrink_to_outputs(SideMap& side, int V, DevBuf& coarse_rows, const Ctl* ctl,
   return read_ctl(ctl, &again, st);
 }
 
-// Stride-2 builds (K = 2, 3) over a bit per cell of the coarse points' box; kRetryTable where the box is too large, or the
-// memory does not suffice (up to 384 bytes a row for bits and prefixes, and tables for N outputs: the hash table and tables for
-// the outputs that there are need less).
-int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t st) {
+// What a stride-2 build over the box leaves where the box is too large: the caller's rows, the hash table of the coarse points and
+// their keys, an empty table for the fine points behind it (K = 2), and the control block of all this.
+struct CoarseTable {
+  DevBuf ctl, rows, slots, keys;  // slots: 2^log_cap of the coarse points, as many for the fine ones
+  int log_cap = 0;                // 0: nothing is there
+};
+
+// Stride-2 builds (K = 2, 3) over a bit per cell of the coarse points' box; kRetryTable where the box is too large (with what the
+// table needs, see CoarseTable), or the memory does not suffice (up to 384 bytes a row for bits and prefixes, and tables for
+// N outputs: the hash table and tables for the outputs that there are need less).
+int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t st, CoarseTable* fallback) {
   const int V = K * K * K;
   const int64_t max_words = std::min<int64_t>(std::max<int64_t>(N * (kCellsPerRow / 64), 1 << 14), kMaxBoxWords);
   const int64_t max_chunks = ceil_div(max_words, kChunkWords);
-  DevBuf ctl_buf, own_rows, coarse_rows, small, bits, prefix;
+  DevBuf coarse_rows, small;
+  DevBuf &ctl_buf = fallback->ctl, &own_rows = fallback->rows, &bits = fallback->slots, &prefix = fallback->keys;
   // sized for as many outputs as inputs: their number is read at the end
   SideMap& side = km->out_side;
   const int64_t most = round_up(N, kRowPad);
@@ -1716,24 +1763,56 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
       side.map.alloc((size_t)most * V * sizeof(int)) != SPCONV_OK || side.mask.alloc((size_t)most * sizeof(unsigned)) != SPCONV_OK)
     return kRetryTable;
   Ctl* ctl = ctl_buf.as<Ctl>();
+  // (two tables in the place of the bits, the keys in that of the prefixes: too large from two million rows on)
+  const int table_cap = log2_capacity(N);
+  const long long table_slots = (K == 2 ? 2ll : 1ll) << table_cap;
+  const bool table_fits = table_slots * 16 <= max_words * 8 && N * 8 <= max_words * 4;
   Box* box = small.as<Box>();
   int* partial = reinterpret_cast<int*>(box + 1);
   unsigned* totals = reinterpret_cast<unsigned*>(small.as<char>() + sizeof(Box) + partial_bytes);
   int* map = side.map.as<int>();
   const unsigned n_partial = (unsigned)std::min<int64_t>(ceil_div(N, 1024), kBoxBlocks);
+  HostCtl* hc = host_ctl_acquire();
+  if (!hc) return SPCONV_ENOMEM;
+  hc->res.word = 0;  // (pinned memory: visible to the kernels launched below)
+  hipError_t launched = hipSuccess;
+  auto check = [&]() {
+    const hipError_t e = hipGetLastError();
+    if (launched == hipSuccess) launched = e;
+  };
+  // The box's verdict is there once the second launch has run.  It is waited for where the host is ahead of the GPU anyway: small
+  // builds are as fast as their launches (2k rows 57 us, with the wait behind the marks 60).
+  bool too_large = false;
+  auto verdict = [&]() -> int {
+    unsigned long long word = 0;
+    SPC_TRY(wait_word(hc, launched, st, &word));
+    too_large = (word >> 48) & FLAG_BOX;
+    return SPCONV_OK;
+  };
+  const bool early = N >= 16384;
   hipLaunchKernelGGL(k_box_bounds, dim3(n_partial), dim3(256), 0, st, rows, (int)N, own_rows.as<int4>(), partial);
-  SPC_LAUNCH_CHECK();
+  check();
   hipLaunchKernelGGL(k_box_clear, dim3((unsigned)std::min<int64_t>(ceil_div(max_words, 2048), 1024)), dim3(256), 0, st, partial,
-                     (int)n_partial, (long long)max_words, bits.as<ulonglong2>(), box, ctl);
-  SPC_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_box_mark, dim3(blocks_for(N, 256)), dim3(256), 0, st, rows, (int)N, box, bits.as<unsigned>());
-  SPC_LAUNCH_CHECK();
-  const dim3 chunk_grid((unsigned)std::min<int64_t>(max_chunks, 1024));
-  hipLaunchKernelGGL(k_box_count, chunk_grid, dim3(256), 0, st, box, bits.as<unsigned long long>(), totals);
-  SPC_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_box_prefix, chunk_grid, dim3(256), 0, st, box, bits.as<unsigned long long>(), totals, prefix.as<unsigned>(),
-                     V, side.map.as<uint4>(), side.mask.as<unsigned>(), ctl);
-  SPC_LAUNCH_CHECK();
+                     (int)n_partial, (long long)max_words, bits.as<ulonglong2>(), table_fits ? table_slots : 0ll, box, ctl, hc->dev);
+  check();
+  hipLaunchKernelGGL(k_box_mark, dim3(blocks_for(N, 256)), dim3(256), 0, st, rows, (int)N, box, bits.as<unsigned>(),
+                     table_fits ? table_cap : 0, prefix.as<unsigned long long>(), ctl);
+  check();
+  if (early) SPC_TRY(verdict());
+  if (!too_large) {
+    const dim3 chunk_grid((unsigned)std::min<int64_t>(max_chunks, 1024));
+    hipLaunchKernelGGL(k_box_count, chunk_grid, dim3(256), 0, st, box, bits.as<unsigned long long>(), totals);
+    check();
+    hipLaunchKernelGGL(k_box_prefix, chunk_grid, dim3(256), 0, st, box, bits.as<unsigned long long>(), totals, prefix.as<unsigned>(),
+                       V, side.map.as<uint4>(), side.mask.as<unsigned>(), ctl);
+    check();
+    if (!early) SPC_TRY(verdict());
+  }
+  if (too_large) {
+    fallback->log_cap = table_fits ? table_cap : 0;
+    return kRetryTable;
+  }
+  SPC_HIP(launched);
   const dim3 scatter_grid(blocks_for(K == 3 ? N * 8 : N, 256));
   if (K == 3)
     hipLaunchKernelGGL(k_box_scatter<3>, scatter_grid, dim3(256), 0, st, rows, (int)N, box, bits.as<unsigned long long>(),
@@ -1748,7 +1827,6 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
   SPC_TRY(read_ctl(ctl, &h, st));
   if (h.entries != h.pairs) h.flags |= FLAG_DUP;  // two rows wrote one entry
   SPC_TRY(flags_status(h.flags));
-  if (h.flags & FLAG_BOX) return kRetryTable;
   km->n_in = N;
   km->n_out = side.rows = (int64_t)h.count;
   side.rows_pad = round_up(side.rows, kRowPad);
@@ -1805,7 +1883,6 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
 int kmap_build(const int32_t* coords, int64_t N, int K, int stride, int transposed, bool async, hipStream_t st,
                spconv_kmap** out, bool dilate) {
   int status = kmap_build_impl(coords, N, K, stride, transposed, async, st, out, dilate, true, true);
-  if (status == kRetryTable) status = kmap_build_impl(coords, N, K, stride, transposed, async, st, out, dilate, false, true);
   if (status == kRetryGeneralSort) status = kmap_build_impl(coords, N, K, stride, transposed, async, st, out, dilate, false, false);
   return status;
 }
@@ -1849,13 +1926,32 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
     *out = km.release();
     return SPCONV_OK;
   }
+  CoarseTable made;  // (log_cap 0: nothing of it)
   if (stride == 2 && (K == 2 || K == 3) && !transposed && bit_per_cell) {
-    SPC_TRY(build_down2(km.get(), rows, N, K, st));
-    *out = km.release();
-    return SPCONV_OK;
+    const int status = build_down2(km.get(), rows, N, K, st, &made);
+    if (status != kRetryTable) {
+      SPC_TRY(status);
+      *out = km.release();
+      return SPCONV_OK;
+    }
+    km->out_side.map.release();
+    km->out_side.mask.release();
+    if (!made.log_cap)
+      for (DevBuf* b : {&made.ctl, &made.rows, &made.slots, &made.keys}) b->release();
   }
+  const bool have_table = made.log_cap > 0;
+  auto take = [](DevBuf& to, DevBuf& from) {
+    std::swap(to.p, from.p);
+    std::swap(to.bytes, from.bytes);
+  };
   DevBuf ctl_buf, tab_fine, tab_coarse, ukeys_a, ukeys_b, hist;
-  SPC_TRY(ctl_buf.alloc(sizeof(Ctl)));
+  if (have_table) {
+    take(ctl_buf, made.ctl);
+    take(tab_coarse, made.slots);
+    take(ukeys_a, made.keys);
+  } else {
+    SPC_TRY(ctl_buf.alloc(sizeof(Ctl)));
+  }
   Ctl* ctl = ctl_buf.as<Ctl>();
 
   // Stride-2 3x3x3 maps are built from the input side and need no table of the fine points.  (Only
@@ -1866,12 +1962,20 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
   const int lc_fine = log2_capacity(N);
   // the caller's rows are kept: they are P_in (and P_out for stride 1), or the fine output set
   DevBuf own_rows;
-  SPC_TRY(own_rows.alloc((size_t)N * 16));
+  if (have_table)
+    take(own_rows, made.rows);
+  else
+    SPC_TRY(own_rows.alloc((size_t)N * 16));
+  unsigned long long* fine = nullptr;
   if (!from_inputs) {
-    SPC_TRY(tab_fine.alloc((size_t)16 << lc_fine));
-    SPC_TRY(build_init(tab_fine, 1ll << lc_fine, ctl, st));
-    hipLaunchKernelGGL(k_insert_rows, dim3(blocks_for(N, 256)), dim3(256), 0, st, rows, (int)N,
-                       tab_fine.as<unsigned long long>(), lc_fine, ctl, own_rows.as<int4>());
+    if (have_table) {
+      fine = tab_coarse.as<unsigned long long>() + (2ll << made.log_cap);
+    } else {
+      SPC_TRY(tab_fine.alloc((size_t)16 << lc_fine));
+      SPC_TRY(build_init(tab_fine, 1ll << lc_fine, ctl, st));
+      fine = tab_fine.as<unsigned long long>();
+    }
+    hipLaunchKernelGGL(k_insert_rows, dim3(blocks_for(N, 256)), dim3(256), 0, st, rows, (int)N, fine, lc_fine, ctl, own_rows.as<int4>());
     SPC_LAUNCH_CHECK();
   }
 
@@ -1879,7 +1983,9 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
   int64_t U = 0;
   DevBuf coarse_rows;
   const int lc_coarse = dilate ? log2_capacity(cand) : lc_fine;
-  if (needs_coarse) {
+  if (needs_coarse && have_table) {
+    SPC_TRY(ukeys_b.alloc((size_t)cand * 8));
+  } else if (needs_coarse) {
     SPC_TRY(tab_coarse.alloc((size_t)16 << lc_coarse));
     if (from_inputs)
       SPC_TRY(build_init(tab_coarse, 1ll << lc_coarse, ctl, st));
@@ -1980,7 +2086,7 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
     SPC_TRY(alloc_side(km->out_side, km->n_out, V, st));
     int* mp = km->out_side.map.as<int>();
     unsigned* mk = km->out_side.mask.as<unsigned>();
-    const unsigned long long* tf = tab_fine.as<unsigned long long>();
+    const unsigned long long* tf = fine;
     // (a dilated map probes like any other stride-1 map, from its derived output points)
     status = K == 3   ? launch_probe<3>(false, qrows, km->n_out, stride, tf, lc_fine, mp, mk, ctl, st)
              : K == 2 ? launch_probe<2>(false, qrows, km->n_out, stride, tf, lc_fine, mp, mk, ctl, st)
@@ -1989,8 +2095,7 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
   } else {
     km->n_in = needs_coarse ? U : N;
     km->n_out = N;
-    const unsigned long long* tab = needs_coarse ? tab_coarse.as<unsigned long long>()
-                                                 : tab_fine.as<unsigned long long>();
+    const unsigned long long* tab = needs_coarse ? tab_coarse.as<unsigned long long>() : fine;
     SPC_TRY(alloc_side(km->out_side, km->n_out, V, st));
     int* mp = km->out_side.map.as<int>();
     unsigned* mk = km->out_side.mask.as<unsigned>();

@@ -517,10 +517,13 @@ def test_stride2_masks_by_rows_of_a_wave(sp, K, n_coarse):
     (5000, (256, 64, 8), 1),           # exactly one chunk of 2048 words, and a part of another
     (5000, (258, 66, 10), -3),
     (80_000, (1016, 1010, 1160), 0),   # more chunks than workgroups: several per workgroup
-    (40, (60_000, 60_000, 60_000), -30_000), (2000, (1, 65_000, 64_000), -32_768)])  # boxes that are left to the table
+    (40, (60_000, 60_000, 60_000), -30_000), (2000, (1, 65_000, 64_000), -32_768),  # boxes that are left to the table: one
+    (16_383, (3000, 3000, 3000), -7), (16_385, (3000, 3000, 3000), 9),              # or many workgroups, the verdict taken late or early,
+    (100_000, (4000, 5000, 700), -2000), (150_000, (9000, 9000, 500), 1)])          # the one-launch and the general sort
 def test_stride2_boxes(sp, K, n, span, lo):
     """Stride-2 builds keep one bit per cell of the coarse points' box: boxes around word, chunk and workgroup limits, flat
-    and long ones, negative and odd corners, several batches, and boxes too large for it."""
+    and long ones, negative and odd corners, several batches, and boxes too large for it, whose coarse points go through a hash table
+    and a sort."""
     rng = np.random.default_rng(n + K)
     corners = np.array([[0] * 3, [s - 1 for s in span]])[:min(n, 2)]
     c = np.concatenate([corners, rng.integers(0, span, size=(2 * n, 3))])
@@ -531,6 +534,26 @@ def test_stride2_boxes(sp, K, n, span, lo):
     with pytest.raises(sp.SpconvError) as e:
         sp.build_kmap(coords_dev(dup), K, 2)
     assert e.value.status == -3
+
+
+def test_stride2_box_and_table_too_large(sp):
+    """Two million scattered rows: neither the bits of their box nor two hash tables in the bits' place are possible."""
+    n = 2_200_000
+    rng = np.random.default_rng(5)
+    flat = np.unique(rng.integers(0, 60_000 ** 3, size=n))
+    flat = flat[rng.permutation(len(flat))]
+    p = np.stack([flat // 60_000 ** 2, flat // 60_000 % 60_000, flat % 60_000], 1) - 30_000
+    c = np.concatenate([np.zeros((len(p), 1)), p], 1).astype(np.int32)
+    km = sp.build_kmap(coords_dev(c), 2, 2)
+    q = p // 2 + 40_000
+    key, place = np.unique((q[:, 0] * 100_000 + q[:, 1]) * 100_000 + q[:, 2], return_inverse=True)
+    want = np.stack([key // 100_000 ** 2, key // 100_000 % 100_000, key % 100_000], 1) - 40_000
+    np.testing.assert_array_equal(km.out_coords().cpu().numpy()[:, 1:], want)
+    M = np.full((len(key), 8), -1)
+    d = p & 1
+    M[place, d[:, 0] * 4 + d[:, 1] * 2 + d[:, 2]] = np.arange(len(p))
+    np.testing.assert_array_equal(km.export().cpu().numpy(), M)
+    km.destroy()
 
 
 @pytest.mark.parametrize("K,n", [(3, 79_999), (3, 80_000), (3, 80_321), (5, 49_999), (5, 50_007)])
