@@ -315,7 +315,9 @@ SPCONV_API int spconv_dgrad(const void* dout, const void* weights, spconv_kmap* 
 
 /* Weight gradient of Equation 1 (the wgrad kernel of Sections 4.2, 6.2):
  *   dweights[k] = sum over n with M[n][k] >= 0 of feats[M[n][k]]^T . dout[n].
- *   dweights device fp32 [K^3][C_in][C_out] whatever dtype is, fully overwritten. */
+ *   dweights device fp32 [K^3][C_in][C_out] whatever dtype is, fully overwritten.
+ * Without a piece length (wgrad_pairs) the kernel and its split go by the pair count as the first such call on the kmap knew it:
+ * on an asynchronous build, whose count spconv_kmap_status brings, ask for the status first where that is possible. */
 SPCONV_API int spconv_wgrad(const void* feats, const void* dout, spconv_kmap* km, int C_in, int C_out,
                  spconv_dtype dtype, const spconv_config* cfg_or_null, float* dweights, void* stream);
 

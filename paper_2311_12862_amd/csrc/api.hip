@@ -723,9 +723,10 @@ SPCONV_API int spconv_wgrad(const void* feats, const void* dout, spconv_kmap* km
     }
     return SPCONV_OK;
   }
+  if (km->n_pairs < 0 && !km->pending) SPC_TRY(kmap_count_pairs(km, st, nullptr));
+  if (c.wgrad_pairs == 0 && km->wgrad_known_pairs == spconv_kmap::kNotAsked) km->wgrad_known_pairs = km->n_pairs;
   if (c.wgrad_pairs == 0 && wgrad_from_map(km, C_in, C_out, dtype))
     return wgrad_map_run(km, feats, dout, C_in, C_out, dtype, dweights, st);
-  if (km->n_pairs < 0 && !km->pending) SPC_TRY(kmap_count_pairs(km, st, nullptr));
   PairList* pl = nullptr;
   SPC_TRY(pair_list_get(km, st, &pl));
   return wgrad_run(km, *pl, c.wgrad_pairs, feats, dout, C_in, C_out, dtype, dweights, st);

@@ -144,6 +144,11 @@ struct spconv_kmap {
   spconv_kmap(const spconv_kmap&) = delete;
   spconv_kmap& operator=(const spconv_kmap&) = delete;
   std::unique_ptr<spc::PairList> pair_list;
+  // The pair count that decides between the pairs and the map (wgrad_from_map): n_pairs as the first call that chose by itself
+  // knew it, -1 where a build was still pending.  It stays, so that what becomes known later does not give the same call another
+  // kernel, other bits and another workspace.
+  static constexpr int64_t kNotAsked = -2;
+  int64_t wgrad_known_pairs = kNotAsked;
   std::map<int64_t, std::unique_ptr<spc::ItemPlan>> item_plans;  // by target
   // K = 5 (125 offsets): the kmap is held as its five x-planes, each a submanifold map of 25 offsets
   // (dx = g - 2) over the same rows, so that masks, sort keys and tile masks stay 32-bit words and

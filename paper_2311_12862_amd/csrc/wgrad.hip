@@ -774,12 +774,12 @@ template <typename T> int launch_wgrad_map(const WgradMapParams& p, dim3 grid, h
 }
 }  // namespace
 
-// Whether a call without a piece length takes its gradient straight from the map: narrow layers on maps that are known to have
-// many pairs, and many per row (where the line lies: see k_wgrad_map; 120k rows of a room, 1.1M pairs, 32 -> 32 32 us and the list
+// Whether a call without a piece length takes its gradient straight from the map: narrow layers on maps that were known to have
+// many pairs, and many per row, when the kmap's first such call was made (where the line lies: see k_wgrad_map; 120k rows of a room, 1.1M pairs, 32 -> 32 32 us and the list
 // from pairs, 27.5 from the map; 16 -> 16 22.5 and the list, 23.6).
 bool wgrad_from_map(const spconv_kmap* km, int C_in, int C_out, spconv_dtype dtype) {
-  if (dtype == SPCONV_F32 || C_in > kMapChannels || C_out > kMapChannels || km->V != 27 || km->pending) return false;
-  if (km->n_pairs < 1200000 || km->n_pairs < 7 * km->n_out) return false;
+  if (dtype == SPCONV_F32 || C_in > kMapChannels || C_out > kMapChannels || km->V != 27) return false;
+  if (km->wgrad_known_pairs < 1200000 || km->wgrad_known_pairs < 7 * km->n_out) return false;
   return (uint64_t)km->n_in * C_in * 2 < kNoRow && (uint64_t)km->n_out * C_out * 2 < kNoRow &&
          (uint64_t)km->out_side.rows_pad * km->V * 4 < kNoRow;  // buffer descriptors address 32 bits
 }

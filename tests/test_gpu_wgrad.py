@@ -112,3 +112,59 @@ def test_narrow_layers_on_dense_maps(dtype, c_in, c_out):
         assert torch.equal(torch.isfinite(got), torch.isfinite(want)) and not torch.isfinite(got).all()
         both = torch.isfinite(got)
         assert (got[both] - want[both]).abs().max() <= 1e-4 * want[both].abs().max()
+
+
+def _dense():
+    return gen.full_grid(38, 1, seed=9)
+
+
+def _sides(km, c_in, c_out, seed):
+    (_, x), _, (_, g) = make_layer(km.n_in, km.n_out, c_in, c_out, 27, "f16", seed)
+    return x, g
+
+
+@pytest.mark.parametrize("wide_first", [False, True])
+def test_the_build_s_verdict_does_not_change_the_kernel(wide_first):
+    """A weight gradient called while an asynchronous build of a dense map is unresolved has the same bits when it is called
+    again after spconv_kmap_status; asked for only after that, it has those of a build that was waited for.  So it has after a wider
+    layer on the same kmap."""
+    import torch
+    import paper_2311_12862_amd as sp
+    c = coords_dev(_dense())
+    waited, early, late = sp.build_kmap(c, 3, 1), sp.build_kmap(c, 3, 1, asynchronous=True), sp.build_kmap(c, 3, 1, asynchronous=True)
+    assert waited.n_pairs() >= 1_200_000
+    x, g = _sides(waited, 16, 24, 5)
+    xw, gw = _sides(waited, 64, 64, 6)
+    if wide_first:
+        wide = sp.wgrad(xw, gw, early)
+    first = sp.wgrad(x, g, early)
+    early.status(), late.status()
+    assert early.n_pairs() == waited.n_pairs()
+    assert torch.equal(first, sp.wgrad(x, g, early))
+    if wide_first:
+        assert torch.equal(wide, sp.wgrad(xw, gw, early))
+        sp.wgrad(xw, gw, late)
+    want = sp.wgrad(x, g, waited)
+    assert torch.equal(want, sp.wgrad(x, g, late))
+    assert norm_err(first, want.double().cpu().numpy()) <= 1e-5
+
+
+@pytest.mark.parametrize("build", [dict(K=3, stride=2), dict(K=3, stride=3), dict(K=3, stride=1, dilate=True), dict(K=3, stride=2, transposed=True)])
+def test_narrow_layers_on_other_dense_maps(build):
+    """Maps with other rows on one side than on the other, and maps whose pairs nobody has counted yet: the same bits before and
+    after they are, and the sums that the pairs give."""
+    import torch
+    import paper_2311_12862_amd as sp
+    k, stride = build.pop("K"), build.pop("stride")
+    c = coords_dev(gen.full_grid(110 if stride == 3 else 74 if stride == 2 else 38, 1, seed=10))
+    km = sp.build_kmap(c, k, stride, **build)
+    x, g = _sides(km, 24, 16, 7)
+    first = sp.wgrad(x, g, km)
+    pairs = km.n_pairs()
+    assert torch.equal(first, sp.wgrad(x, g, km))
+    want = sp.wgrad(x, g, km, sp.Config(wgrad_pairs=2048))
+    assert norm_err(first, want.double().cpu().numpy()) <= 1e-5
+    assert torch.equal(first, sp.wgrad(x, g, km)) and torch.equal(want, sp.wgrad(x, g, km, sp.Config(wgrad_pairs=2048)))
+    if not build.get("transposed"):   # (a fine row has 3.4 coarse neighbours: these stay with the pairs)
+        assert pairs >= 1_200_000 and pairs >= 7 * km.n_out
+        assert not torch.equal(first, want)   # (another order of the sums: it is the map that was walked)
