@@ -31,8 +31,9 @@
  *     a map as five planes of 25 offsets (dx = g - 2; offset k is offset
  *     k % 25 of plane k / 25), runs forward and dgrad plane by plane and sums
  *     the planes like the parts of a split (16-bit layers that reduce over
- *     at most 16 channels, unless the configuration says otherwise: all
- *     planes in one launch), and sorts each plane by its own 25-bit mask.  spconv_kmap_export_perm then counts parts over the
+ *     at most 16 channels, beyond 8 onto at most 512, unless the configuration
+ *     says otherwise: all planes in one launch), and sorts each plane by its
+ *     own 25-bit mask.  spconv_kmap_export_perm then counts parts over the
  *     planes (split = plane * n_split + part); the tuners, the paired
  *     transposed kmap, fetch-on-demand and spconv_fwd_noalloc refuse a K = 5
  *     kmap with SPCONV_EINVAL;

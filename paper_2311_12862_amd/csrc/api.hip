@@ -306,10 +306,15 @@ int auto_plan_get(spconv_kmap* km, SideMap& side, bool make, hipStream_t st, Ige
 // that slice; dgrad on the submanifold map mirrors the offset, 124 - k, which is offset 24 - j of
 // plane 4 - g.
 // Where the configuration leaves the kernel, the tile and the order to the library, a narrow layer takes one launch for all
-// planes instead of five and their reduction (60k rows f16 8 -> 32: 63 us against 27).
+// planes instead of five and their reduction.  Each column tile walks the map again, the five launches read partial sums back
+// instead; one launch and five, us:
+//   8 channels    60k rows of a room -> 32 28, 60; -> 256 100, 243; -> 1024 365, 859; 300k -> 256 553, 1149; -> 1024 1996, 4484
+//   9 to 16       60k rows -> 32 34, 66; -> 256 181, 245; -> 1024 677, 853; 300k -> 64 294, 371; -> 256 1135, 1252; 200k of a scan
+//                 -> 1024 2485, 2996; where the line lies, input gradients at 300k rows of a room -> 512 2236, 2238; -> 1024 4373, 4309
 bool planes_in_one(int64_t rows, int64_t rows_src, int c_red, int c_dst, spconv_dtype dtype, const spconv_config* cfg,
                    const spconv_config& c) {
   if (dtype == SPCONV_F32 || c.kernel != 0 || c.n_split != 0 || (cfg && (cfg->tile_m != 0 || cfg->tile_n != 0))) return false;
+  if (c_red > 8 && c_dst > 512) return false;
   WaveShape s;
   return igemm_wave_planes_shape(rows, rows_src, c_red, c_dst, &s) == SPCONV_OK;
 }
@@ -1094,7 +1099,11 @@ SPCONV_API int spconv_describe_launch(int K, int64_t rows, int64_t rows_src, int
   if (rows == 0) return SPCONV_OK;  // nothing is launched
   if (!cfg && K != 5 && auto_sorted(V, rows, rows_src, C_red, C_cols, dtype)) c.n_split = 1;
   KernelChoice kc;
-  SPC_TRY(choose_kernel(V, rows, rows_src, C_red, C_cols, dgrad != 0, dtype, cfg, c, &kc));
+  const bool one_launch = K == 5 && planes_in_one(rows, rows_src, C_red, C_cols, dtype, cfg, c);  // (asked first, as in run_planes)
+  if (one_launch)
+    kc.kind = KernelChoice::WAVE;
+  else
+    SPC_TRY(choose_kernel(V, rows, rows_src, C_red, C_cols, dgrad != 0, dtype, cfg, c, &kc));
   const int tile_m = kc.kind == KernelChoice::WAVE ? 16 : kc.kind == KernelChoice::RING ? kc.ring.bm : kc.tile_m;
   PlanShape ps;
   SPC_TRY(plan_shape(V, rows, c.n_split, 16, &ps));
@@ -1118,7 +1127,7 @@ SPCONV_API int spconv_describe_launch(int K, int64_t rows, int64_t rows_src, int
     for (int i = 0; i < 3; ++i) out->grid[i] = (int32_t)kc.ring.grid[i];
   } else if (kc.kind == KernelChoice::WAVE) {
     WaveShape w;
-    if (K == 5 && planes_in_one(rows, rows_src, C_red, C_cols, dtype, cfg, c))
+    if (one_launch)
       SPC_TRY(igemm_wave_planes_shape(rows, rows_src, C_red, C_cols, &w));
     else
       SPC_TRY(igemm_wave_shape(V, c.n_split, rows, rows_src, C_red, C_cols, kc.tile_n, &w));

@@ -31,6 +31,13 @@ def test_row_counts(n, c_in, c_out, K):
     _run(sp, _cloud(n), K, 1, False, "f16", c_in, c_out, None, n)
 
 
+@pytest.mark.parametrize("c_in,c_out", [(16, 264), (8, 520), (16, 512), (16, 520), (264, 16), (520, 16)])
+def test_planes_of_wide_layers(c_in, c_out):
+    """K = 5 in one launch with many column tiles, and on both sides of the width from which 16 channels take a launch per plane."""
+    import paper_2311_12862_amd as sp
+    _run(sp, _cloud(777), 5, 1, False, "bf16", c_in, c_out, None, c_in)
+
+
 @pytest.mark.parametrize("K,stride,transposed", [(1, 1, False), (2, 2, False), (2, 2, True), (3, 2, False), (3, 2, True), (3, 1, False)])
 @pytest.mark.parametrize("n_split", [0, 1, 2, 3, 4])
 @pytest.mark.parametrize("c_in,c_out", [(8, 16), (16, 8)])

@@ -163,3 +163,26 @@ def test_calls_without_a_configuration(dtype):
     assert seen_tile_m == ({32, 64, 128, 256} if dtype == torch.float16 else {64})
     assert not sp.describe_launch(5, 300_000, 300_000, 256, 256, dtype).sorted   # (planes run in map order)
     assert not sp.describe_launch(1, 300_000, 300_000, 256, 256, dtype).sorted
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("dgrad", [False, True])
+def test_planes_in_one_launch(dtype, dgrad):
+    """5x5x5 layers that reduce over at most 16 channels: one launch over all planes at every size and width, beyond 8 channels up
+    to 512 columns; its blocks are all visited and its LDS fits."""
+    for rows, c_red, c_cols in itertools.product(ROWS + [1_000_003], [8, 16], [8, 32, 40, 128, 256, 512, 520, 1024]):
+        info = sp.describe_launch(5, rows, rows, c_red, c_cols, dtype, None, dgrad)
+        pack = 4 if c_red == 8 else 2
+        weights = (5 * -(-25 // pack) * pack + 1) * info.tile_n * 64 // pack
+        one = info.kernel == 1 and info.lds_bytes == weights + info.waves * info.slab_bytes
+        assert one == (c_red == 8 or c_cols <= 512), (rows, c_red, c_cols)
+        if not one:
+            continue
+        assert info.tile_m == 16 and info.parts == 1 and not info.sorted and info.lds_bytes + 64 <= LDS_PER_CU
+        assert info.grid[1] == -(-c_cols // info.tile_n) and info.grid[2] == 1
+        assert info.slab_bytes >= info.slab_map_bytes + 16 * info.tile_n * 2 and info.slab_map_bytes >= 16 * 25 * 4
+        if info.n_tiles < 10_000:
+            seen = [b for x in range(info.grid[0]) for b in _wave_blocks(info, x)]
+            assert sorted(seen) == list(range(info.n_tiles))
+    assert sp.describe_launch(5, 4097, 4097, 16, 64, dtype, sp.Config(tile_n=32), dgrad).lds_bytes != \
+        sp.describe_launch(5, 4097, 4097, 16, 64, dtype, None, dgrad).lds_bytes
