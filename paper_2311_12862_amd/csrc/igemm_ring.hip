@@ -551,13 +551,20 @@ int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
     // group), 96; 100k 128 -> 128 165 (one), 178.
     // On maps of a few workgroups per CU eight K groups of a wave each end sooner still: 5k rows 96 -> 96 38, 28; 15k 64 -> 64 28,
     // 20; 10k 32 -> 32 16, 13; 30k 96 -> 32 40, 27; where the line lies: 30k 64 -> 64 30, 33; 32 -> 32 24, 25; 60k 96 -> 96 104, 104.
+    // One of them fits on a CU, so that the rounds add up: wide layers (without and with these groups, scan; room) lie, by workgroups,
+    //   1,264  512 -> 512 5k rows 211, 167; 353, 311       1,504  256 -> 128 24k 160, 95; 198, 192; 512 -> 128 24k 314, 168; 387, 358
+    //   3,008  256 -> 256 24k 222, 176; 342, 361           3,128  512 -> 128 50k 492, 330; 717, 740
+    //   3,008  512 -> 512 12k 465, 494; 678, 730           3,008  1024 -> 256 24k 874, 585; 1360, 1310
+    //   4,032  1024 -> 1024 8k 1179, 804; 1697, 1679       6,016  512 -> 512 24k 578, 695; 1222, 1368
+    //   6,256  1024 -> 256 50k 1170, 1183; 2576, 2747      11,880  1024 -> 256 95k 2290, 2600; 4010, 4500
+    // and the line between: past it most scans still gain what rooms lose, 5 %, or less.
     // Tiles of a dense room all have their 27 offsets, and are bound by the work, not by the longest: 62k rows (64 x 64 with two K
     // groups, two 32 x 32) 64 -> 64 66, 77; 96 -> 64 94, 110; a scan of as many 57, 53; 82, 78; 45k 57, 59; 80, 86; scan 48, 42; 67,
     // 60.  Unsorted 45k 32 -> 32 (64 x 32, two 32 x 32) 36, 42; 30k 29.5, 28.
     s->bm = 64;
     s->bn = c_out <= 16 ? 16 : 32;
     s->piece = c_red <= 16 ? 64 : 128;
-    if (small_tiles && V >= 25 && c_red > 16 && c_out > 16 && wgs(64, 32) <= 12 * c_red) {
+    if (small_tiles && V >= 25 && c_red > 16 && c_out > 16 && wgs(64, 32) <= std::min(12 * c_red, 2560 + 2 * c_red)) {
       s->nwk = 8;
       s->piece = 64;
     } else if (small_tiles && wgs(64, s->bn) < (c_out > 32 ? 1400 : c_red <= 32 ? 600 : 2000)) {

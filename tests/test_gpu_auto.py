@@ -173,14 +173,41 @@ def test_without_memory_for_the_order():
 @pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 64, 65, 97, 2049])
 @pytest.mark.parametrize("c_in,c_out", [(4, 16), (12, 20), (16, 64), (36, 36), (68, 100)])
 def test_fp32_tiles_in_pairs(n, c_in, c_out):
-    """fp32 layers of small maps: a workgroup holds two 32-row tiles, whose masks, units and sums are their own; row counts
-    around their edges (a last workgroup with an empty or a partial second tile), odd and even numbers of pieces."""
+    """fp32 layers of small maps: a workgroup holds two 32-row tiles, whose masks, units and sums are their own (at most 16
+    channels, or 16 columns), or eight K groups of a wave each; row counts around their edges (a last workgroup with an empty or a
+    partial second tile)."""
     import torch
     import paper_2311_12862_amd as sp
     info = sp.describe_launch(3, n, n, c_in, c_out, torch.float32)
     assert info.tile_m == 64 and info.waves == 8 and info.tile_n == (16 if c_out <= 16 else 32)
+    # (two stages of units: 32-row tiles, two of two groups each; 64-row tiles, eight groups)
+    slab = 8192
+    assert info.lds_bytes == (2 * 4 * (32 + info.tile_n) * 64 + slab if c_in <= 16 else 2 * 8 * (64 + 32) * 64 + slab)
     c = gen.uniform_cloud(n, max(2, int(round((4 * n) ** (1 / 3)))) + 1, seed=n)
     _check(c, 3, 1, False, "f32", c_in, c_out, 1, n)
+
+
+@pytest.mark.parametrize("n,c_in,c_out,tile_n", [
+    (14_001, 20, 36, 32), (20_033, 36, 36, 32), (27_001, 96, 96, 32),  # two 32 x 32 tiles, 128-byte pieces: one, two, three an offset
+    (31_009, 40, 72, 64), (48_001, 64, 64, 64), (64_999, 36, 52, 64)])  # 64 x 64, two K groups
+def test_fp32_tiles_of_maps_in_between(n, c_in, c_out, tile_n):
+    """fp32 maps too large for eight K groups and too small for single ones, all 27 offsets: ragged last tiles and columns, odd and
+    even numbers of pieces."""
+    import torch
+    import paper_2311_12862_amd as sp
+    c = gen.lidar_scene(n, target_n=n + 3000)[:n]
+    info = sp.describe_launch(3, n, n, c_in, c_out, torch.float32)
+    assert len(c) == n and (info.tile_m, info.tile_n, info.waves, info.k_steps) == (64, tile_n, 8, 32)
+    _check(c, 3, 1, False, "f32", c_in, c_out, 1, n)
+
+
+@pytest.mark.parametrize("c_red,c_cols,last", [(64, 64, 24_576), (256, 256, 24_576), (512, 512, 14_336), (1024, 256, 36_864)])
+def test_where_fp32_stops_taking_eight_groups(c_red, c_cols, last):
+    """Workgroups of eight groups have a CU to themselves: wide layers of larger maps go on with other tiles."""
+    import torch
+    import paper_2311_12862_amd as sp
+    assert sp.describe_launch(3, last, last, c_red, c_cols, torch.float32).k_steps == 16
+    assert sp.describe_launch(3, last + 1, last + 1, c_red, c_cols, torch.float32).k_steps == 32
 
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 129, 1000, 2049])
