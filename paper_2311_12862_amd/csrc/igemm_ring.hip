@@ -467,8 +467,8 @@ int launch_ring(const RingParams& p, bool dgrad, dim3 grid, hipStream_t st) {
   X(64, 64, 2, 2, 2, 1) X(64, 128, 2, 2, 1, 1) X(128, 128, 2, 2, 1, 1) X(256, 256, 2, 4, 1, 1)
 #define SPC_RING_SHAPES_32(X) \
   X(32, 16, 2, 1, 2, 2) X(32, 32, 1, 2, 2, 2) X(64, 16, 4, 1, 1, 1) X(64, 32, 1, 1, 8, 1) X(64, 32, 4, 1, 1, 1) X(64, 64, 2, 2, 1, 1) X(64, 64, 2, 2, 2, 1)
-// (eight K groups of 128-byte pieces do not fit in LDS)
-constexpr bool ring_built(int pb, int nwk) { return nwk < 8 || pb == 64; }
+// (eight K groups of 128-byte pieces do not fit in LDS, four are for layers of 64-byte pieces)
+constexpr bool ring_built(int pb, int nwk) { return nwk < 4 || pb == 64; }
 
 template <typename T, int PB> int launch_shape(const RingParams& p, bool dgrad, const RingShape& s, dim3 grid, hipStream_t st) {
 #define SPC_RING_CASE(BM, BN, NWM, NWN, NWK, NWR) \

@@ -1554,9 +1554,12 @@ int build_init(const DevBuf& tab, long long words /*of 16 bytes*/, Ctl* ctl, hip
   return SPCONV_OK;
 }
 
-// The table of z-runs of a submanifold build, and from a number of rows on the probe's filter.  Whole builds without and with it,
-// us: 3x3x3 50k rows 44, 46; 100k 62, 60; 200k 95, 81; 400k 155, 124; 300k of a room 118, 98; 5x5x5 20k 40, 43; 60k 73, 72;
-// 120k 126, 109.
+// The table of z-runs of a submanifold build, and from a number of rows on the probe's filter.  Whole waited builds without and
+// with it, us (3x3x3 also the GPU's time of unwaited builds, one behind the other):
+//   3x3x3  scan     60k rows 61, 62 (35.6, 36.9); 80k 63, 58 (37.8, 31.5); 100k 69, 65 (44.4, 38.0); 200k 102, 88 (78, 60); 300k 135, 107
+//          room     60k 63, 69 (39, 45); 80k 60.5, 60.3 (36.6, 33.3); 100k 67, 65 (43, 38); 130k 81, 81 (57, 54); 200k 101, 93 (76, 65); 300k 129, 110
+//          uniform  60k 67, 69 (42, 45); 80k 68, 64.5 (44, 37.5); 100k 79, 75 (55, 48); 200k 114, 102 (91, 74); 300k 143, 121
+//   5x5x5  scan 20k 50, 52; 50k 72, 71; 80k 93, 80; 120k 134, 113; room 20k 47, 48; 50k 65, 65; 80k 90, 82; uniform 50k 79, 78.5; 80k 106, 92
 struct RunTable {
   DevBuf buf;  // entries, then (with a filter) its marks and its bits
   int log_cap = 0;

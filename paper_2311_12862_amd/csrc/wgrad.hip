@@ -454,7 +454,7 @@ __global__ void __launch_bounds__(256) k_wgrad_reduce(const float* __restrict__ 
 // list is made (24 us at 300k rows of a room).  300k rows, 2.8M pairs, bf16 32 -> 32: 80 us + list -> 62, 8 -> 32 64 -> 43: the lines
 // that 64-byte rows of x lie in, 353 MB, at 6.3 TB/s.  Absent neighbours cost a slot of the address unit and matrix
 // instructions, so sparse maps stay with the pairs (100k rows of a LiDAR-like scan, 3.4 pairs a row: 16 us, from the map 23), as
-// do 64 channels of dy (300k rows 32 -> 64 95, 102) and maps of fewer pairs than about a million (60k rows of a room 17, 19).
+// do 64 channels of dy (300k rows 32 -> 64 95, 102) and maps of fewer pairs than about a million (wgrad_from_map).
 // Waves are on their own: batches are dealt to them, a unit (offset of a batch) has J - 1 units in flight behind it, each waited for
 // by count; the waves' sums meet in LDS and the workgroups' in k_wgrad_sum, in order.
 // A row of dy that is not finite must not meet the zeros of absent neighbours: such batches, found by their exponents, clear
@@ -775,8 +775,15 @@ template <typename T> int launch_wgrad_map(const WgradMapParams& p, dim3 grid, h
 }  // namespace
 
 // Whether a call without a piece length takes its gradient straight from the map: narrow layers on maps that were known to have
-// many pairs, and many per row, when the kmap's first such call was made (where the line lies: see k_wgrad_map; 120k rows of a room, 1.1M pairs, 32 -> 32 32 us and the list
-// from pairs, 27.5 from the map; 16 -> 16 22.5 and the list, 23.6).
+// many pairs, and many per row, when the kmap's first such call was made.  Over pairs and from the map, us, f16, once the list is
+// there (a first call over pairs makes it, 14 to 25 us more; it serves every layer on the kmap and fetch-on-demand):
+//   pairs   0.53M        0.74M         0.91M         1.13M       1.28M (uniform)  1.44M       1.69M (uniform)  2.8M
+//   16->16  12.6, 16.7   14.9, 18.5    18.4, 21.7    22.2, 23.4  20.5, 23.2       28.7, 27.0  28.1, 26.8       60.5, 49.6
+//   32->32  15.8, 18.5   21.2, 20.6    27.8, 24.7    31.8, 27.8  31.2, 28.2       42.0, 33.6  40.7, 35.5       80.8, 64.1
+//   8->32   13.0, 16.6   15.6, 18.3    18.6, 21.1    21.2, 22.9  21.4, 23.0       29.0, 26.2  27.2, 25.9       65.4, 41.5
+//   32->8   12.9, 16.8   15.6, 18.2    19.8, 21.8    25.0, 24.8  23.3, 25.4       31.1, 30.8  31.1, 32.5       59.2, 59.0
+// The line lies where the kernels alone are about equal, so that layers which share a list lose nothing to speak of; one narrow layer
+// on a map of its own would gain from 0.3M pairs on (34 with the list, 15).
 bool wgrad_from_map(const spconv_kmap* km, int C_in, int C_out, spconv_dtype dtype) {
   if (dtype == SPCONV_F32 || C_in > kMapChannels || C_out > kMapChannels || km->V != 27) return false;
   if (km->wgrad_known_pairs < 1200000 || km->wgrad_known_pairs < 7 * km->n_out) return false;

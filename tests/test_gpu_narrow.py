@@ -63,11 +63,12 @@ def test_weights_that_no_row_uses_stay_out():
     assert norm_err(sp.fwd(x, w, km), want) <= TOL["f16"]
 
 
-def test_same_bits_sorted_or_not():
-    """Which offsets share an instruction is fixed: a row's sums do not depend on the rows beside it."""
+@pytest.mark.parametrize("c_in", [8, 16])
+def test_same_bits_sorted_or_not(c_in):
+    """Which offsets share an instruction (8 channels) is fixed: a row's sums do not depend on the rows beside it."""
     import torch
     import paper_2311_12862_amd as sp
     c = gen.lidar_scene(62, target_n=5000)
-    (_, x), (_, w), _ = make_layer(len(c), len(c), 16, 32, 27, "f16", 3)
+    (_, x), (_, w), _ = make_layer(len(c), len(c), c_in, 32, 27, "f16", 3)
     km = sp.build_kmap(coords_dev(c), 3, 1)
     assert torch.equal(sp.fwd(x, w, km, sp.Config(kernel=1)), sp.fwd(x, w, km, sp.Config(n_split=1, kernel=1)))
