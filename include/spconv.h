@@ -330,7 +330,8 @@ SPCONV_API int spconv_wgrad(const void* feats, const void* dout, spconv_kmap* km
  * the mapping cost, Section 4.2).  Blocking: allocates scratch tensors, runs
  * and times every candidate on `stream`.  best receives the winner;
  * best_us (may be NULL) its time in microseconds.  (Candidates are configurations: the library's own
- * row order, which only calls without one use, is not among them.) */
+ * row order, the tiles it takes on small maps and weight gradients straight from the map, which only calls
+ * without one use, are not among them.) */
 SPCONV_API int spconv_tune(spconv_kmap* km, int C_in, int C_out, spconv_dtype dtype, spconv_op op,
                 int layers_sharing_kmap, spconv_config* best, float* best_us, void* stream);
 

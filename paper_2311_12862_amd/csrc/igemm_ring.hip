@@ -546,10 +546,10 @@ int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
     // The matrix cores' fp32 rate makes a tile with all 27 offsets last: 64 x 64 outputs of 64 channels 23 us of a CU
     // on its own.  So a workgroup takes two tiles of 32 x 32 outputs, each with two K groups, unless there are workgroups
     // enough for the longest not to matter.  Measured on sorted maps (us; 64 x 64 with two K groups, two 32 x 32, 64 x 32):
-    // 2k rows 16 -> 16 8.8 (64 x 16), two 32 x 16 6.6; 5k 64 -> 64 37, 26; 20k 256 -> 256 230, 173; 30k 64 -> 64 44, 29.5; 60k
-    // 64 -> 64 48, 42; and where the line lies: 30k 96 -> 96 66, 62; 50k of a dense room 64 -> 64 57, 62; 60k 96 -> 96 103 (one K
+    // 2k rows 16 -> 16 8.8 (64 x 16), two 32 x 16 6.6; 5k 64 -> 64 37, 26; 30k 64 -> 64 44, 29.5; 60k 64 -> 64
+    // 48, 42; and where the line lies: 30k 96 -> 96 66, 62; 50k of a dense room 64 -> 64 57, 62; 60k 96 -> 96 103 (one K
     // group), 96; 100k 128 -> 128 165 (one), 178.
-    // On maps of a few workgroups per CU eight K groups of a wave each end sooner still: 5k rows 96 -> 96 38, 28; 15k 64 -> 64 28,
+    // On smaller maps, the more so the longer the reduction, eight K groups of a wave each end sooner still: 5k rows 96 -> 96 38, 28; 15k 64 -> 64 28,
     // 20; 10k 32 -> 32 16, 13; 30k 96 -> 32 40, 27; where the line lies: 30k 64 -> 64 30, 33; 32 -> 32 24, 25; 60k 96 -> 96 104, 104.
     // One of them fits on a CU, so that the rounds add up: wide layers (without and with these groups, scan; room) lie, by workgroups,
     //   1,264  512 -> 512 5k rows 211, 167; 353, 311       1,504  256 -> 128 24k 160, 95; 198, 192; 512 -> 128 24k 314, 168; 387, 358
