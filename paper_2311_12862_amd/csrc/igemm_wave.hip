@@ -68,6 +68,7 @@ struct WaveParams {
   const unsigned* blkmask[kMaxSplit];
   const unsigned* rowmask;  // unsorted maps: per-row masks; the 16-row block mask is their OR (no plan kernel)
   int lo[kMaxSplit], width[kMaxSplit];
+  unsigned pitch_inv[kMaxSplit];  // packed offsets: see over_pitch
   long long rows, n_blocks;
   int parts, V;
   int c_red, c_out;
@@ -133,6 +134,10 @@ __global__ void __launch_bounds__(DEPTH > 4 && PACK == 1 ? 512 : 1024) k_igemm_w
   const int c_red = p.c_red, c_out = p.c_out;
 
   const int pitch = PACK > 1 ? (width + PACK - 1) / PACK * PACK : width;  // offsets per plane in LDS: whole groups
+  // e / pitch for the few hundred entries of a block's map rows and slices of its weights.  (Divisions by a number that only the
+  // run knows would stand before every wave's first loads: 0.3 to 0.5 of 7 to 10 us.)
+  const unsigned pitch_inv = PACK > 1 ? p.pitch_inv[part] : 0u;
+  auto over_pitch = [&](int e) { return (int)(__umul24((unsigned)e, pitch_inv) >> 16); };
   unsigned short* Ws = reinterpret_cast<unsigned short*>(smem);  // [plane][pitch][BN][ROW_HALFS] swizzled; PACK > 1: and a slice of zeros
   unsigned char* slab = smem + p.weight_bytes + (size_t)wave * p.slab_bytes;
   int* mapW = reinterpret_cast<int*>(slab);
@@ -193,7 +198,7 @@ __global__ void __launch_bounds__(DEPTH > 4 && PACK == 1 ? 512 : 1024) k_igemm_w
   if constexpr (PACK > 1) {
 #pragma unroll
     for (int i = 0; i < kMapVecs; ++i) {
-      const int e = lane + 64 * i, r = e / pitch, c = e - r * pitch;
+      const int e = lane + 64 * i, r = over_pitch(e), c = e - r * pitch;
       msrc[i] = r < 16 && c < width ? (unsigned)(r * width + c) * 4u : 0xFFFFFFFFu;
     }
   }
@@ -296,7 +301,7 @@ __global__ void __launch_bounds__(DEPTH > 4 && PACK == 1 ? 512 : 1024) k_igemm_w
         for (int u = 0; u < kFill; ++u) {
           const int e = e0 + u * blockDim.x;
           const int q = e % ROW_CHUNKS, n = (e / ROW_CHUNKS) % BN, cp = e / (ROW_CHUNKS * BN);
-          const int plane = PLANES > 1 ? cp / pitch : PACK > 1 && cp >= pitch, c = cp - plane * pitch;
+          const int plane = PLANES > 1 ? over_pitch(cp) : PACK > 1 && cp >= pitch, c = cp - plane * pitch;
           const int k = lo + plane * width + c;
           const int ci = n0 + n, co = q * 8;
           const bool ok = e < chunks && (PACK == 1 || (c < width && plane < PLANES)) && ci < p.C_in && co < p.C_out;
@@ -324,7 +329,7 @@ __global__ void __launch_bounds__(DEPTH > 4 && PACK == 1 ? 512 : 1024) k_igemm_w
         for (int u = 0; u < kQuad; ++u) {
           const int e = e0 + u * blockDim.x;
           const int ng = e % (BN / 8), k4 = (e / (BN / 8)) % (ROW_HALFS / 4), cp = e / ((BN / 8) * (ROW_HALFS / 4));
-          const int plane = PLANES > 1 ? cp / pitch : PACK > 1 && cp >= pitch, c = cp - plane * pitch;
+          const int plane = PLANES > 1 ? over_pitch(cp) : PACK > 1 && cp >= pitch, c = cp - plane * pitch;
           const int k = lo + plane * width + c;
           const int co = n0 + ng * 8;
           const unsigned base = (unsigned)(p.mirror ? p.V - 1 - k : k) * slice;
@@ -514,6 +519,9 @@ constexpr size_t kLdsBudget = 160 * 1024 - 64;  // (64 bytes for the static tick
 // 11.9 us against 11.6).  A 1x1x1 map has nothing to share.
 int pack_for(int c_red, int width, bool planes = false) { return width < 2 || c_red > 16 ? 1 : c_red <= 8 ? 4 : planes ? 2 : 1; }
 
+// 2^16 / pitch rounded up: (e * this) >> 16 is e / pitch while e * pitch < 2^16 (e < 16 * 28, 5 * 28 + 1).
+unsigned pitch_inverse(int width, int pack) { return (unsigned)ceil_div(65536, round_up(width, pack)); }
+
 size_t map_bytes_for(int max_width, int pack) { return (size_t)round_up(16 * round_up(max_width, pack) * 4, 16); }
 
 size_t slab_bytes_for(int max_width, int pack, int bn, int parts) {
@@ -645,6 +653,7 @@ int igemm_wave_planes_run(const spconv_kmap* km, const IgemmArgs& a, hipStream_t
   }
   const uint64_t rows_pad = (uint64_t)km->groups[0]->out_side.rows_pad;
   p.width[0] = km->groups[0]->V;
+  p.pitch_inv[0] = pitch_inverse(p.width[0], sh.pack);
   p.map_part_bytes[0] = (unsigned)(rows_pad * p.width[0] * 4);
   p.rows_pad_bytes = (unsigned)(rows_pad * 4);
   p.slab_bytes = sh.slab_bytes;
@@ -686,6 +695,7 @@ int igemm_wave_run(const spconv_kmap* km, const SideMap& side, const IgemmPlan& 
   for (int i = 0; i < plan.parts; ++i) {
     p.lo[i] = plan.lo[i];
     p.width[i] = plan.width[i];
+    p.pitch_inv[i] = pitch_inverse(plan.width[i], sh.pack);
     p.blkmask[i] = plan.tilemask.as<unsigned>() + (size_t)i * tiles_alloc;
     if (plan.n_split == 0) {
       p.map[i] = side.map.as<int>();
