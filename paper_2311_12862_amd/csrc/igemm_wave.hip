@@ -516,8 +516,13 @@ constexpr size_t kLdsBudget = 160 * 1024 - 64;  // (64 bytes for the static tick
 
 // Offsets that share a matrix instruction.  Reductions over 9 to 16 channels only pair offsets where that makes their weights fit
 // (PLANES): pairs of consecutive offsets are both absent too rarely (100k rows 16 -> 16: 14 pairs a block against 18 offsets,
-// 11.9 us against 11.6).  A 1x1x1 map has nothing to share.
-int pack_for(int c_red, int width, bool planes = false) { return width < 2 || c_red > 16 ? 1 : c_red <= 8 ? 4 : planes ? 2 : 1; }
+// 11.9 us against 11.6).  A 1x1x1 map has nothing to share, and a part of a split too little: its blocks have few offsets, and those side
+// by side (200k rows 8 -> 8, one offset an instruction and four, us: a scan in two parts 23.2, 26.9, in four 36.2, 42.4; 20k 8.6, 9.3; 2k 7.8,
+// 8.5).  Whole maps of 8 -> 8, the same: scans of 2k rows 6.0, 6.7; 8k 6.4, 7.0; 20k 8.7, 8.1; rooms 2k 7.7, 7.3; 20k 9.9, 8.4; K = 2, stride 2,
+// 20k 6.9, 7.0, its input gradient 7.7, 7.2.
+int pack_for(int c_red, int width, int parts, bool planes = false) {
+  return width < 2 || parts > 1 || c_red > 16 ? 1 : c_red <= 8 ? 4 : planes ? 2 : 1;
+}
 
 // 2^16 / pitch rounded up: (e * this) >> 16 is e / pitch while e * pitch < 2^16 (e < 16 * 28, 5 * 28 + 1).
 unsigned pitch_inverse(int width, int pack) { return (unsigned)ceil_div(65536, round_up(width, pack)); }
@@ -545,7 +550,7 @@ int igemm_wave_pick_bn(int V, int n_split, int c_red, int c_out, int tile_n, int
     // unsorted maps: two 32-column tiles beat one of 64 (100k voxels, 32 -> 64: 24.3 us against 26.7 us)
     if (tile_n == 0 && bn == 64 && n_split == 0) continue;
     const size_t w = (size_t)max_width * bn * ks * 64;
-    const size_t slab = slab_bytes_for(max_width, pack_for(c_red, max_width), bn, parts);
+    const size_t slab = slab_bytes_for(max_width, pack_for(c_red, max_width, parts), bn, parts);
     for (int waves : {16, 8}) {
       if (w + (size_t)waves * slab <= kLdsBudget) {
         if (waves_out) *waves_out = waves;
@@ -576,7 +581,7 @@ int igemm_wave_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
   for (int i = 0; i < ps.parts; ++i) s->max_width = std::max(s->max_width, ps.width[i]);
   // the map, the permutation and the masks are read through 32-bit buffer offsets as well
   if ((uint64_t)ps.rows_pad * s->max_width * 4 >= 0xFFFF0000ull) return SPCONV_EINVAL;
-  s->pack = pack_for(c_red, s->max_width);
+  s->pack = pack_for(c_red, s->max_width, ps.parts);
   s->slab_bytes = (int)slab_bytes_for(s->max_width, s->pack, s->bn, ps.parts);
   s->map_bytes = (int)map_bytes_for(s->max_width, s->pack);
   s->weight_bytes = s->max_width * s->bn * s->ks * 64;  // (more than packed weights need)
@@ -601,7 +606,7 @@ int igemm_wave_planes_shape(int64_t rows, int64_t rows_src, int c_red, int c_out
   if (c_red > 16) return SPCONV_EINVAL;
   WaveShape one;
   SPC_TRY(igemm_wave_shape(kWidth, 0, rows, rows_src, c_red, c_out, 0, &one));
-  one.pack = pack_for(c_red, kWidth, true);
+  one.pack = pack_for(c_red, kWidth, 1, true);
   one.map_bytes = (int)map_bytes_for(kWidth, one.pack);
   for (int bn : {32, 16}) {
     for (int waves : {16, 8}) {

@@ -42,7 +42,7 @@ def test_planes_of_wide_layers(c_in, c_out):
 @pytest.mark.parametrize("n_split", [0, 1, 2, 3, 4])
 @pytest.mark.parametrize("c_in,c_out", [(8, 16), (16, 8)])
 def test_maps_and_splits(K, stride, transposed, n_split, c_in, c_out):
-    """Parts of 27 offsets are 27, 13 and 14, 9, 6 and 7 wide: a part's last group is full, half full or a single offset."""
+    """27 and 8 offsets in groups of four (the last one full or short of one), and parts of a split, which do not share instructions."""
     import paper_2311_12862_amd as sp
     if n_split > K ** 3:
         pytest.skip("more parts than offsets")
