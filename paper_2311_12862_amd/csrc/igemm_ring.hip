@@ -557,17 +557,19 @@ int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
     //   3,008  512 -> 512 12k 465, 494; 678, 730           3,008  1024 -> 256 24k 874, 585; 1360, 1310
     //   4,032  1024 -> 1024 8k 1179, 804; 1697, 1679       6,016  512 -> 512 24k 578, 695; 1222, 1368
     //   6,256  1024 -> 256 50k 1170, 1183; 2576, 2747      11,880  1024 -> 256 95k 2290, 2600; 4010, 4500
-    // and the line between: past it most scans still gain what rooms lose, 5 %, or less.
+    // The line lies between these: up to it scans gain up to a half, and rooms, whose tiles are all long, lose 7 % at most.
     // Tiles of a dense room all have their 27 offsets, and are bound by the work, not by the longest: 62k rows (64 x 64 with two K
     // groups, two 32 x 32) 64 -> 64 66, 77; 96 -> 64 94, 110; a scan of as many 57, 53; 82, 78; 45k 57, 59; 80, 86; scan 48, 42; 67,
-    // 60.  Unsorted 45k 32 -> 32 (64 x 32, two 32 x 32) 36, 42; 30k 29.5, 28.
+    // 60.  Unsorted 45k 32 -> 32 (64 x 32, two 32 x 32) 36, 42; 30k 29.5, 28.  Short reductions have little to share between the K
+    // groups: sorted 40k 32 -> 64 (1,250 workgroups; 64 x 64 with two K groups, two 32 x 32) of a dense scan 27, 35, a room 28, 34; 30k (938)
+    // 22.5, 19; 27, 25; 64 -> 32 (64 x 32, two 32 x 32) of a scan and a room 80k (1,250) 46, 38; 50, 51; 100k (1,563) 48, 45; 53, 58.
     s->bm = 64;
     s->bn = c_out <= 16 ? 16 : 32;
     s->piece = c_red <= 16 ? 64 : 128;
     if (small_tiles && V >= 25 && c_red > 16 && c_out > 16 && wgs(64, 32) <= std::min(12 * c_red, 2560 + 2 * c_red)) {
       s->nwk = 8;
       s->piece = 64;
-    } else if (small_tiles && wgs(64, s->bn) < (c_out > 32 ? 1400 : c_red <= 32 ? 600 : 2000)) {
+    } else if (small_tiles && wgs(64, s->bn) < (c_out > 32 ? (c_red <= 32 ? 1000 : 1400) : c_red <= 32 ? 600 : c_red <= 64 ? 1500 : 2000)) {
       s->nwk = s->nwr = 2;
     } else if (c_out > 32) {
       s->bn = 64;

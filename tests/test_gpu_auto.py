@@ -201,13 +201,17 @@ def test_fp32_tiles_of_maps_in_between(n, c_in, c_out, tile_n):
     _check(c, 3, 1, False, "f32", c_in, c_out, 1, n)
 
 
-@pytest.mark.parametrize("c_red,c_cols,last", [(64, 64, 24_576), (256, 256, 24_576), (512, 512, 14_336), (1024, 256, 36_864)])
-def test_where_fp32_stops_taking_eight_groups(c_red, c_cols, last):
-    """Workgroups of eight groups have a CU to themselves: wide layers of larger maps go on with other tiles."""
+@pytest.mark.parametrize("c_red,c_cols,last,tile,beyond", [
+    (64, 64, 24_576, (32, 16), (32, 32)), (256, 256, 24_576, (32, 16), (64, 32)), (512, 512, 14_336, (32, 16), (64, 32)),
+    (1024, 256, 36_864, (32, 16), (64, 32)),                                            # eight K groups
+    (32, 64, 31_936, (32, 32), (64, 32)), (64, 32, 95_936, (32, 32), (32, 32)), (96, 32, 127_936, (32, 32), (32, 32))])  # pairs
+def test_where_fp32_tiles_end(c_red, c_cols, last, tile, beyond):
+    """Columns and channels a unit of the tiles on both sides of the lines between them."""
     import torch
     import paper_2311_12862_amd as sp
-    assert sp.describe_launch(3, last, last, c_red, c_cols, torch.float32).k_steps == 16
-    assert sp.describe_launch(3, last + 1, last + 1, c_red, c_cols, torch.float32).k_steps == 32
+    a, b = (sp.describe_launch(3, n, n, c_red, c_cols, torch.float32) for n in (last, last + 1))
+    assert (a.tile_n, a.k_steps) == tile and (b.tile_n, b.k_steps) == beyond
+    assert (a.tile_n, a.k_steps, a.waves) != (b.tile_n, b.k_steps, b.waves)
 
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 129, 1000, 2049])
