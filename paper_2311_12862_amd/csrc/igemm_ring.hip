@@ -582,8 +582,16 @@ int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
       s->bn = 64;
       s->nwk = 8;
       s->piece = 64;
-    } else if (small_tiles && n_split > 0 && c_red > 64 && c_red % 64 && c_out > 32 && wgs(64, 64) <= 1600) {
-      s->bm = 32, s->bn = 64;  // (30k rows 96 -> 96 25 -> 20.5, 136 -> 72 37 -> 26)
+    } else if (small_tiles && n_split > 0 && c_red > 64 && c_red % 64 && c_out > 32 && wgs(64, 64) <= (c_red < 128 ? 1000 : 1600)) {
+      // 32-row tiles with four K groups of a wave each: where tiles are of unequal length.  64 x 64 with two K groups, and these (sparse scan;
+      // uniform; dense scan; room), by workgroups of 64 x 64:
+      //   844    96 -> 96 -; 24.1, 18.8; 27.0, 28.5; 28.3, 30.0      136 -> 72 -; 36.0, 25.6; 39.3, 36.0; 43.8, 41.1
+      //   940    96 -> 96 23.5, 18.2; 24.2, 20.1; -; 28.1, 30.4      136 -> 72 35.1, 25.0; 36.0, 25.7; -; 43.6, 41.4
+      //   1,094  96 -> 96 -; 24.6, 22.4; 32.2, 33.8; 32.5, 35.2      200 -> 128 -; 49.6, 34.9; 59.8, 59.6; 64.5, 63.3
+      //   1,250  96 -> 96 -; 25.4, 25.1; 32.9, 36.3; 34.8, 39.7      200 -> 128 -; 50.7, 40.0; 63.2, 64.0; 68.6, 72.0
+      //   1,410  96 -> 96 29.5, 27.7; 26.1, 27.3; -; 36.9, 42.8      200 -> 128 57.5, 44.5; 51.0, 43.1; -; 73.8, 78.7
+      //   1,564  96 -> 96 26.9, 28.4; 26.9, 29.6; -; 43.1, 48.9      200 -> 128 53.6, 44.8; 52.0, 46.7; -; 85.4, 92.4
+      s->bm = 32, s->bn = 64;
       s->nwk = 4;
     } else if (c_out <= 32) {
       s->bm = 64, s->bn = 32;
