@@ -258,14 +258,15 @@ int static_scratch(void** out) {
 //   fp32, 10k, 20k, 60k, 150k rows  16 -> 32 12 -> 11, 14 -> 11, 23 -> 13, 51 -> 21; 32 -> 32 16 -> 13, 19 -> 14, 33 -> 16,
 //                         86 -> 32; 64 -> 64 31 -> 21, 48 -> 23, 106 -> 36, 268 -> 84; 96 -> 96 53 -> 33, 86 -> 44, 224 -> 77, 582 -> 178
 // f16 32 -> 32 saves 0 to 3 us at every size.  96 -> 32 is faster on the unsorted map with resident weights than sorted with
-// tiles (100k rows 34, 41).  2x2x2 maps have few offsets to skip (up to 100k rows 128 -> 64 27 -> 15, 256 -> 256 131 -> 44).
+// tiles (100k rows 34, 41).  2x2x2 maps have few offsets to skip (up to 100k rows 128 -> 64 27 -> 15, 256 -> 256 131 -> 44), but
+// a finer side's rows have one each: fp32 input gradient 96 -> 96 of 12k rows 32 -> 9.8.
 bool auto_sorted(int V, int64_t rows, int64_t rows_src, int c_red, int c_cols, spconv_dtype dtype) {
   if (V < 8) return false;
   const bool f32 = dtype == SPCONV_F32;
   if (!f32 && c_red > 64 && c_red <= 128 && c_cols <= 32) return false;
   if (f32) {  // (its time goes by whole pieces and column tiles)
     c_red = (int)round_up(c_red, c_red <= 16 ? 16 : 32);
-    c_cols = (int)round_up(c_cols, c_cols <= 16 ? 16 : 32);
+    c_cols = (int)round_up(c_cols, V == 8 && c_cols > 32 ? 64 : c_cols <= 16 ? 16 : 32);
   }
   // us saved per row and channel pair
   const double unit = V == 8 ? (f32 ? 1e-7 : 1.5e-8) : f32 ? 2.5e-7 : c_red <= 64 ? 2e-8 : 4.5e-8;
