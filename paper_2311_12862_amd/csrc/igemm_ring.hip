@@ -566,10 +566,23 @@ int igemm_ring_shape(int V, int n_split, int64_t rows, int64_t rows_src, int c_r
     s->bm = 64;
     s->bn = c_out <= 16 ? 16 : 32;
     s->piece = c_red <= 16 ? 64 : 128;
-    if (small_tiles && V >= 25 && c_red > 16 && c_out > 16 && wgs(64, 32) <= std::min(12 * c_red, 2560 + 2 * c_red)) {
+    // In map order all tiles are of about the same length, so that a second round of workgroups counts in full: sorted 30k rows 32 -> 64
+    // (938 workgroups) gain, unsorted lose (uniform 10k rows, eight groups or pairs, 314: 22.6, 25; 24k, pairs, 750: 34, 43; planes of K = 5, 30k
+    // 64 -> 64, 938: 279, 308), while one round gains most (8k, 250: 22, 13.4; 4.5k 64 -> 128, 280: 39, 31; planes of K = 5, 8k of a room, without groups, pairs, eight groups, 96 -> 96, 375, -, 232, 215;
+    // 128 -> 128, 500, -, 285, 270).
+    // 2x2x2 maps have short chains.  Pairs, by workgroups: 32 -> 64 242 9.7, 8.0; 276 9.8, 10.3; 752 14.7, 17.5; 64 -> 128 552 23.5,
+    // 20.9; 636 24.2, 24.4; 964 19, 20.8; 96 -> 96 414 32, 21.5; 477 18.6, 22.4; 723 25.2, 27.8; 128 -> 64 376 25.3, 26.7; sorted, 938, 11.7,
+    // 13.3; 128 -> 256 1,104 27, 20.
+    const bool ordered = n_split > 0;
+    const int eight_to = V < 25 || c_red <= 16 || c_out <= 16 ? 0 : ordered ? std::min(12 * c_red, 2560 + 2 * c_red) : c_red <= 32 ? 288 : 512;
+    const int pairs_to = V < 25         ? (c_red <= 32 ? 257 : c_red < 128 || c_out <= 64 ? 600 : 1300)
+                         : c_out <= 32  ? (c_red <= 32 || !ordered ? 600 : c_red <= 64 ? 1500 : 2000)
+                         : !ordered     ? (c_red <= 32 ? 289 : 512)
+                                        : (c_red <= 32 ? 1000 : 1400);
+    if (small_tiles && wgs(64, 32) <= eight_to) {
       s->nwk = 8;
       s->piece = 64;
-    } else if (small_tiles && wgs(64, s->bn) < (c_out > 32 ? (c_red <= 32 ? 1000 : 1400) : c_red <= 32 ? 600 : c_red <= 64 ? 1500 : 2000)) {
+    } else if (small_tiles && wgs(64, s->bn) < pairs_to) {
       s->nwk = s->nwr = 2;
     } else if (c_out > 32) {
       s->bn = 64;

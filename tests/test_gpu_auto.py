@@ -188,7 +188,7 @@ def test_fp32_tiles_in_pairs(n, c_in, c_out):
 
 
 @pytest.mark.parametrize("n,c_in,c_out,tile_n", [
-    (14_001, 20, 36, 32), (20_033, 36, 36, 32), (27_001, 96, 96, 32),  # two 32 x 32 tiles, 128-byte pieces: one, two, three an offset
+    (22_001, 20, 36, 32), (20_033, 36, 36, 32), (27_001, 96, 96, 32),  # two 32 x 32 tiles, 128-byte pieces: one, two, three an offset
     (31_009, 40, 72, 64), (48_001, 64, 64, 64), (64_999, 36, 52, 64)])  # 64 x 64, two K groups
 def test_fp32_tiles_of_maps_in_between(n, c_in, c_out, tile_n):
     """fp32 maps too large for eight K groups and too small for single ones, all 27 offsets: ragged last tiles and columns, odd and
