@@ -4,9 +4,9 @@
 //
 // The paper counts these mapping operations as a cost centre (Sections 4.2,
 // 6.1, 6.3) but gives no algorithm for them; the design below is this
-// library's own.  Submanifold 3x3x3 maps, the common case, hash runs of four
-// cells along z (one 32-byte entry per run) and read 13.5 entries per voxel,
-// each row writing its own map row and mask.  The other maps use one 16-byte
+// library's own.  Submanifold 3x3x3 maps, the common case, deal their rows into buckets
+// of neighbouring blocks, each of which one workgroup hashes into LDS and looks up there;
+// 5x5x5 maps hash runs of four cells along z into a table in memory.  The other maps use one 16-byte
 // slot per key (64-bit packed coordinate + row index) in an open-addressing
 // table at load factor <= 0.5 and one probe lane per (output row, offset), so
 // that map writes are contiguous per wave and the bitmask comes from a wave
@@ -43,7 +43,6 @@ struct Ctl {
   unsigned long long pairs[kPairSlots * 16];
   unsigned long long key_or[kPairSlots * 16], key_and[kPairSlots * 16];  // spread like pairs
   unsigned long long entries[kPairSlots * 16];  // present map entries, counted from the finished map
-  unsigned tick[kPairSlots * 16];  // arrivals per pair slot (submanifold probe)
   unsigned tick_top, pad2[15];     // pair slots whose workgroups have all arrived
 };
 
@@ -529,7 +528,6 @@ __global__ void __launch_bounds__(256)
     }
     if (t < kPairSlots) {
       ctl->pairs[t * 16] = 0;
-      ctl->tick[t * 16] = 0;
       ctl->entries[t * 16] = 0;
       ctl->key_or[t * 16] = 0;
       ctl->key_and[t * 16] = ~0ull;
@@ -748,7 +746,6 @@ __global__ void __launch_bounds__(256) k_build_init(ulonglong2* __restrict__ tab
     }
     if (threadIdx.x < kPairSlots) {
       ctl->pairs[threadIdx.x * 16] = 0;
-      ctl->tick[threadIdx.x * 16] = 0;
       ctl->entries[threadIdx.x * 16] = 0;
       ctl->key_or[threadIdx.x * 16] = 0;
       ctl->key_and[threadIdx.x * 16] = ~0ull;
@@ -792,14 +789,12 @@ __global__ void __launch_bounds__(64) k_publish(const Ctl* __restrict__ ctl, Hos
   }
 }
 
-// ---- submanifold 3x3x3 build over a table of z-runs ----
+// ---- submanifold 5x5x5 build over a table of z-runs ----
 // One table entry holds four cells that are neighbours along z: the key is (b, x, y, z >> 2) and
-// rows[z & 3] the input row there.  A voxel's three neighbours in a column (x + dx, y + dy,
-// z - 1 .. z + 1) lie in one entry, or in two when the range crosses a multiple of four, so the
-// whole 27-neighbourhood takes 13.5 entry reads on average (as many as the 13 single-voxel lookups
-// that the symmetry M[n][k] = j <=> M[j][26 - k] = n leaves), and every read returns up to three
-// neighbours.  Each row then writes its own 27 map entries and its own mask: no entry of another
-// row is touched, so the map needs no preset and the masks no atomics.
+// rows[z & 3] the input row there.  A voxel's five neighbours in a column (x + dx, y + dy,
+// z - 2 .. z + 2) lie in two entries, so the whole neighbourhood takes 50 entry reads.  Each row then
+// writes its own map entries and masks: no entry of another row is touched, so the maps need no preset and the
+// masks no atomics.
 struct RunSlot {
   unsigned long long key;
   int rows[4];
@@ -816,12 +811,9 @@ __device__ __forceinline__ unsigned hash_run(unsigned long long key) {
 }
 __device__ __forceinline__ unsigned hash_slot(unsigned long long key, int log_cap) { return hash_run(key) >> (32 - log_cap); }
 
-// Which runs exist, one bit per hash value: 128 KB, which a workgroup of the probe holds in LDS.  Of the 13.5 entries that a
-// row looks up most do not exist, and the filter lets only 7 to 15 % of the absent ones through: 100k rows of a LiDAR-like
-// scan, 1.81 M -> 0.73 M line requests, misses of the L2 0.88 M -> 0.34 M, probe 27 -> 23.5 us; 300k rows of a room 74 -> 54 us.
-// (What remains is a wave's chain of loads, coordinates, entry, next entry, and about 450 instructions for seven rows; contiguous
-// stores through LDS and coordinates fetched a step ahead changed nothing.)  The insert marks bytes (plain stores: every writer stores the
-// same, and an atomic per row costs 1 us for 10,000), k_filter_pack makes bits of them.
+// Which runs exist, one bit per hash value: 128 KB, which a workgroup of the probe holds in LDS.  Of the 50 entries that a
+// row looks up most do not exist, and the filter lets only 7 to 15 % of the absent ones through.  The insert marks bytes (plain
+// stores: every writer stores the same, and an atomic per row costs 1 us for 10,000), k_filter_pack makes bits of them.
 constexpr int kFilterBits = 20;
 constexpr int kMarkWords = (1 << kFilterBits) / 16, kFilterWords = (1 << kFilterBits) / 32;
 __device__ __forceinline__ unsigned filter_bit(unsigned hash) { return hash >> (32 - kFilterBits); }
@@ -863,22 +855,18 @@ __global__ void __launch_bounds__(256) k_insert_runs(const int4* __restrict__ co
   atomicOr(&ctl->flags, FLAG_FULL);
 }
 
-// Finishes a lookup whose first entry (slot s) is already loaded: a = key and cells 0, 1.  FULL
-// also fetches cells 2, 3.
-template <bool FULL>
+// Finishes a lookup whose first entry (slot s) is already loaded: a = key and cells 0, 1.
 __device__ __forceinline__ void run_resolve(const RunSlot* tab, int log_cap, unsigned long long key, unsigned s,
                                             uint4 a, int cells[4]) {
   const unsigned slot_mask = (1u << log_cap) - 1u;
   for (unsigned it = 0; it <= slot_mask; ++it) {
     const unsigned long long k = (unsigned long long)a.x | ((unsigned long long)a.y << 32);
     if (k == key) {
+      const uint2 b = *reinterpret_cast<const uint2*>(&tab[s].rows[2]);
       cells[0] = (int)a.z;
       cells[1] = (int)a.w;
-      if (FULL) {
-        const uint2 b = *reinterpret_cast<const uint2*>(&tab[s].rows[2]);
-        cells[2] = (int)b.x;
-        cells[3] = (int)b.y;
-      }
+      cells[2] = (int)b.x;
+      cells[3] = (int)b.y;
       return;
     }
     if (k == kEmpty) return;
@@ -887,79 +875,26 @@ __device__ __forceinline__ void run_resolve(const RunSlot* tab, int log_cap, uns
   }
 }
 
-// The workgroup that arrives last sums the pair counters and writes the result into pinned host
-// memory.  A pair slot is one 64-bit counter: pairs in its low 40 bits, arrivals above, so that one
-// atomic both adds the workgroup's pairs and tells it whether it was the slot's last (a second
-// level counts the finished slots: no address sees more than gridDim/64 or 64 atomics).  Called by
-// the first wave only, after the others have left: two returning atomics in a row, awaited by the
-// whole workgroup, kept every wave of the probe resident for 7 us.  Every value the last workgroup
-// reads was produced by an atomic whose return its producer waited for before counting itself in,
-// and is read with an atomic, so no cache write-back is needed.
-__device__ __forceinline__ void publish_pairs(unsigned wg_pairs, Ctl* ctl, HostResult* host) {
-  constexpr unsigned long long kArrive = 1ull << 40;
-  int last = 0;
-  if (threadIdx.x == 0) {
-    const unsigned slot = blockIdx.x % kPairSlots;
-    const unsigned long long before = atomicAdd(&ctl->pairs[slot * 16], (unsigned long long)wg_pairs + kArrive);
-    const unsigned slot_wgs = (gridDim.x - slot + kPairSlots - 1) / kPairSlots;
-    const unsigned used_slots = gridDim.x < (unsigned)kPairSlots ? gridDim.x : (unsigned)kPairSlots;
-    if ((unsigned)(before >> 40) + 1 == slot_wgs) last = atomicAdd(&ctl->tick_top, 1u) + 1 == used_slots;
-  }
-  last = __builtin_amdgcn_readfirstlane(last);
-  if (last) {
-    unsigned long long v = atomicAdd(&ctl->pairs[threadIdx.x * 16], 0ull) & (kArrive - 1);  // kPairSlots == 64 lanes
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if (threadIdx.x == 0)
-      host->word = kHostReady | ((unsigned long long)(ctl->flags & 0xFFu) << 48) | (v & 0xFFFFFFFFFFFFull);
-  }
-}
-
-__device__ __forceinline__ unsigned spread3(unsigned g) {  // bit c of 9 -> bit 3c
-  g = (g | (g << 16)) & 0x030000FFu;
-  g = (g | (g << 8)) & 0x0300F00Fu;
-  g = (g | (g << 4)) & 0x030C30C3u;
-  return (g | (g << 2)) & 0x09249249u;
-}
-
-// The neighbours of a row in column (tx, ty): cells z - R .. z + R.  They are 2 R + 1 in a row of the window [run q_lo | run
-// q_lo + 1], starting at (z - R) & 3.  (z itself is in range, so the runs' indices fit the key's field; cells beside the
+// The neighbours of a row in column (tx, ty): cells z - 2 .. z + 2.  They are five in a row of the window [run q_lo | run
+// q_lo + 1], starting at (z - 2) & 3.  (z itself is in range, so the runs' indices fit the key's field; cells beside the
 // range are dropped.)  FILTER: absent runs are mostly known without a look at the table.
-template <int R, bool FILTER>
+template <bool FILTER>
 __device__ __forceinline__ void probe_column(int b, int tx, int ty, int z, const RunSlot* __restrict__ tab, int log_cap,
                                              const unsigned* filter, int* nb) {
-  constexpr int D = 2 * R + 1;
-  const int q_lo = (z - R) >> 2, i0 = (z - R) & 3;
+  const int q_lo = (z - 2) >> 2, i0 = (z - 2) & 3;
   const unsigned long long key_lo = pack_key(b, tx, ty, q_lo), key_hi = key_lo + 1;
   const unsigned h_lo = hash_run(key_lo), h_hi = hash_run(key_hi);
   const unsigned s_lo = h_lo >> (32 - log_cap), s_hi = h_hi >> (32 - log_cap);
-  // (the upper run is only read where the window reaches into it; with R = 1 that is cells 0 and 1 at most, which come
-  // with its key)
-  bool want_lo = true, want_hi = i0 + D > 4;
-  if constexpr (FILTER) {
-    const unsigned f_lo = filter_bit(h_lo), f_hi = filter_bit(h_hi);
-    want_lo = (filter[f_lo >> 5] >> (f_lo & 31)) & 1u;
-    want_hi = want_hi && ((filter[f_hi >> 5] >> (f_hi & 31)) & 1u);
-  }
   int w[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
   if constexpr (!FILTER) {
-    // (with R = 1 cells 2 and 3 of the lower run are fetched with its key; else only where the key matches: without the filter
-    // most entries are not there)
-    const uint4 a_lo = *reinterpret_cast<const uint4*>(tab + s_lo);  // all in flight
-    uint2 b_lo = make_uint2(~0u, ~0u);
-    if (R == 1) b_lo = *reinterpret_cast<const uint2*>(&tab[s_lo].rows[2]);
-    uint4 a_hi = make_uint4(~0u, ~0u, 0u, 0u);
-    if (want_hi) a_hi = *reinterpret_cast<const uint4*>(tab + s_hi);
-    const unsigned long long k = (unsigned long long)a_lo.x | ((unsigned long long)a_lo.y << 32);
-    if (R == 1 && k == key_lo) {
-      w[0] = (int)a_lo.z;
-      w[1] = (int)a_lo.w;
-      w[2] = (int)b_lo.x;
-      w[3] = (int)b_lo.y;
-    } else if (R > 1 || k != kEmpty) {
-      run_resolve<true>(tab, log_cap, key_lo, s_lo, a_lo, w);
-    }
-    if (want_hi) run_resolve<(R > 1)>(tab, log_cap, key_hi, s_hi, a_hi, w + 4);
+    // (cells 2 and 3 are fetched only where the key matches: without the filter most entries are not there)
+    const uint4 a_lo = *reinterpret_cast<const uint4*>(tab + s_lo);  // both in flight
+    const uint4 a_hi = *reinterpret_cast<const uint4*>(tab + s_hi);
+    run_resolve(tab, log_cap, key_lo, s_lo, a_lo, w);
+    run_resolve(tab, log_cap, key_hi, s_hi, a_hi, w + 4);
   } else {
+    const unsigned f_lo = filter_bit(h_lo), f_hi = filter_bit(h_hi);
+    bool want_lo = (filter[f_lo >> 5] >> (f_lo & 31)) & 1u, want_hi = (filter[f_hi >> 5] >> (f_hi & 31)) & 1u;
     const unsigned slot_mask = (1u << log_cap) - 1u;
     unsigned at_lo = s_lo, at_hi = s_hi;
     // both runs advance together: a wave's lookups take as many rounds as the longest chain of any of them
@@ -972,7 +907,7 @@ __device__ __forceinline__ void probe_column(int b, int tx, int ty, int z, const
       }
       if (want_hi) {
         a_hi = *reinterpret_cast<const uint4*>(tab + at_hi);
-        if (R > 1) b_hi = *reinterpret_cast<const uint2*>(&tab[at_hi].rows[2]);
+        b_hi = *reinterpret_cast<const uint2*>(&tab[at_hi].rows[2]);
       }
       if (want_lo) {
         const unsigned long long k = (unsigned long long)a_lo.x | ((unsigned long long)a_lo.y << 32);
@@ -982,10 +917,7 @@ __device__ __forceinline__ void probe_column(int b, int tx, int ty, int z, const
       }
       if (want_hi) {
         const unsigned long long k = (unsigned long long)a_hi.x | ((unsigned long long)a_hi.y << 32);
-        if (k == key_hi) {
-          w[4] = (int)a_hi.z, w[5] = (int)a_hi.w;
-          if (R > 1) w[6] = (int)b_hi.x, w[7] = (int)b_hi.y;
-        }
+        if (k == key_hi) w[4] = (int)a_hi.z, w[5] = (int)a_hi.w, w[6] = (int)b_hi.x, w[7] = (int)b_hi.y;
         want_hi = k != key_hi && k != kEmpty;
         at_hi = (at_hi + 1) & slot_mask;
       }
@@ -993,9 +925,9 @@ __device__ __forceinline__ void probe_column(int b, int tx, int ty, int z, const
   }
   const bool b1 = i0 & 1, b2 = i0 & 2;
 #pragma unroll
-  for (int d = 0; d < D; ++d) {
+  for (int d = 0; d < 5; ++d) {
     const int v = b2 ? (b1 ? w[3 + d] : w[2 + d]) : (b1 ? w[1 + d] : w[d]);
-    nb[d] = coord_ok(b, tx, ty, z + d - R) ? v : -1;
+    nb[d] = coord_ok(b, tx, ty, z + d - 2) ? v : -1;
   }
 }
 
@@ -1011,56 +943,352 @@ __device__ __forceinline__ void load_filter(const unsigned* __restrict__ bits, u
   __syncthreads();
 }
 
-// Nine lanes per row, one per column (dx, dy); seven rows per wave.  Rows of the padding
-// (n_rows <= row < rows_pad) get an empty neighbourhood, as does a row beside the range (it fails the build).
-template <bool FILTER>
-__global__ void __launch_bounds__(FILTER ? kProbeThreads : 256)
-    k_probe_runs3(const int4* __restrict__ rows, int n_rows, long long rows_pad, const RunSlot* __restrict__ tab,
-                  int log_cap, const unsigned* __restrict__ filter_bits, int* __restrict__ map, unsigned* __restrict__ mask,
-                  Ctl* ctl, HostResult* host) {
-  constexpr int V = 27, LPR = 9, RPW = 7, kWaves = FILTER ? kProbeThreads / 64 : 4;
-  __shared__ unsigned wave_pairs[kWaves];
-  extern __shared__ unsigned filter[];
-  const int lane = threadIdx.x & 63;
-  const long long waves = (long long)gridDim.x * kWaves;
+// ---- submanifold 3x3x3 builds in buckets ----
+// The rows are dealt into buckets by the block of 8 x 8 x 8 cells that they lie in (hashed: several blocks share a bucket), and a
+// row at a face of its block is copied into the neighbours' buckets as well.  A row's whole neighbourhood then lies in its own
+// bucket, and one workgroup per bucket hashes the bucket into LDS and looks its rows up there: no table in memory that has to be
+// cleared, no atomic and no look-up that leaves the CU.  The table in LDS holds runs of four cells along z: a voxel's three neighbours
+// in a column (x + dx, y + dy, z - 1 .. z + 1) lie in one run, or in two when the range crosses a multiple of four.  Each row writes its
+// own 27 map entries and its own mask: no entry of another row is touched, so the map needs no preset and the masks no atomics.
+// GPU time of unwaited builds, a table of runs in memory (cleared, filled with an atomic per row, probed with 13.5 reads per row
+// of which a filter in LDS answered some) and so, us: a scan of 30k rows 27, 17.5; 60k 35, 23; 100k 44, 26; 200k 67, 41; 400k
+// 114, 67; a room of 60k 31, 26; 100k 41, 35; 300k 82, 64; 7k rows 16, 15.  What bounds it: the longest bucket's chain of barriers (a
+// block holds up to 100 rows of a surface, and buckets of 256 rows on average up to 700), and launch and publication, 5 us.
+constexpr int kBlockBits = 3;      // (16 cells a side: 1.5 copies of a row in place of 2, but buckets of up to 1,800 rows: 300k rows of a room 124 us)
+constexpr int kDealThreads = 512;
+constexpr int kDealers = 256;      // workgroups of k_deal_rows at most
+constexpr int kCopies = 8;         // buckets that a row may be dealt into
+constexpr int kMaxBucketBits = 14;
+// (1,024 threads: 100k rows 31 us; 512: three workgroups fit on a CU and take longer than two of 768 by more than that)
+constexpr int kBucketThreads = 768;
+constexpr int kOwnRows = 512;      // rows of a bucket whose coordinates are in LDS at a time
+constexpr int kBucketRows = 1536;  // rows of a bucket, with the copies, that are in the table at a time
+constexpr int kRunSlotBits = 11;
+static_assert(kBucketRows < (1 << kRunSlotBits), "every chain of slots ends");
+__host__ __device__ constexpr int deal_lds(int log_b) { return (2 << log_b) * 4; }
+
+struct Dealt {
+  unsigned lo, hi;  // the key
+  int row;
+};
+
+__device__ __forceinline__ unsigned bucket_of(int b, int x, int y, int z, int log_b) {
+  return hash_run(pack_key(b, x, y, z)) >> (32 - log_b);
+}
+
+// f(bucket, halo) for every bucket that a row is dealt into, once each; the row's own one first.
+template <typename F> __device__ __forceinline__ void for_buckets(int4 c, int log_b, F f) {
+  constexpr int S = 1 << kBlockBits;
+  const int p[3] = {c.y, c.z, c.w};
+  int q[3], d[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const int o = p[a] & (S - 1);
+    q[a] = p[a] >> kBlockBits;
+    d[a] = o == 0 ? -1 : o == S - 1 ? 1 : 0;
+  }
+  unsigned seen[kCopies];
+  seen[0] = bucket_of(c.x, q[0], q[1], q[2], log_b);
+  f(seen[0], 0);
+#pragma unroll
+  for (int m = 1; m < kCopies; ++m) {
+    seen[m] = seen[0];
+    if (((m & 1) && !d[0]) || ((m & 2) && !d[1]) || ((m & 4) && !d[2])) continue;
+    const unsigned to = bucket_of(c.x, q[0] + (m & 1 ? d[0] : 0), q[1] + (m & 2 ? d[1] : 0), q[2] + (m & 4 ? d[2] : 0), log_b);
+    bool fresh = true;
+#pragma unroll
+    for (int i = 0; i < m; ++i) fresh = fresh && to != seen[i];
+    if (!fresh) continue;
+    seen[m] = to;
+    f(to, 1);
+  }
+}
+
+// Workgroup w deals rows [w per, w per + per) and leaves them, ordered by bucket (a bucket's own rows before the copies), at
+// entries + 8 per w; starts[w][2 bucket + copies] says where each begins.  Also the kmap's own copy of the
+// caller's rows, the map of the padding and of rows beside the range (no neighbours; they fail the build), and the control block.
+__global__ void __launch_bounds__(kDealThreads)
+    k_deal_rows(const int4* __restrict__ coords, int n, int per, int log_b, Dealt* __restrict__ entries, unsigned* __restrict__ starts,
+                unsigned* __restrict__ dealer_flags, int4* __restrict__ keep, long long rows_pad, int* __restrict__ map,
+                unsigned* __restrict__ mask, Ctl* ctl) {
+  constexpr int V = 27, U = 2;
+  extern __shared__ __align__(16) unsigned place[];  // [2 << log_b]
+  __shared__ unsigned wave_sum[kDealThreads / 64], flags;
+  const int t = threadIdx.x, lane = t & 63, wib = t >> 6, w = blockIdx.x;
+  const int cells = 2 << log_b;
+  const int first = (int)min((long long)w * per, (long long)n), last = (int)min((long long)first + per, (long long)n);
+  for (int i = t; i < cells; i += kDealThreads) place[i] = 0;
+  if (t == 0) flags = 0;
+  __syncthreads();
+  auto visit = [&](auto f) {
+    for (long long r0 = first + t; r0 < last; r0 += U * kDealThreads) {
+      int4 c[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) c[u] = r0 + u * kDealThreads < last ? coords[r0 + u * kDealThreads] : make_int4(-1, 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (r0 + u * kDealThreads < last) f((int)r0 + u * kDealThreads, c[u]);
+    }
+  };
+  visit([&](int r, int4 c) {
+    keep[r] = c;
+    if (coord_ok(c.x, c.y, c.z, c.w)) {
+      for_buckets(c, log_b, [&](unsigned b, int halo) { atomicAdd(&place[2 * b + halo], 1u); });
+    } else {
+      flags = (unsigned)FLAG_RANGE;
+      for (int k = 0; k < V; ++k) map[(long long)r * V + k] = -1;
+      mask[r] = 0u;
+    }
+  });
+  __syncthreads();
+  if (t == 0) dealer_flags[w] = flags;
+  // counts -> first places, as many cells per thread as there are, four at a time
+  const int share = max(cells / kDealThreads, 4), c0 = min(t * share, cells), c1 = min(c0 + share, cells);
+  unsigned mine = 0;
+  for (int i = c0; i < c1; i += 4) {
+    const uint4 v = *reinterpret_cast<const uint4*>(place + i);
+    mine += v.x + v.y + v.z + v.w;
+  }
+  unsigned incl = mine;
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned up = __shfl_up(incl, o);
+    if (lane >= o) incl += up;
+  }
+  if (lane == 63) wave_sum[wib] = incl;
+  __syncthreads();
+  unsigned at = incl - mine, all = 0;
+  for (int i = 0; i < kDealThreads / 64; ++i) {
+    if (i < wib) at += wave_sum[i];
+    all += wave_sum[i];
+  }
+  for (int i = c0; i < c1; i += 4) {
+    const uint4 v = *reinterpret_cast<const uint4*>(place + i);
+    *reinterpret_cast<uint4*>(place + i) = make_uint4(at, at + v.x, at + v.x + v.y, at + v.x + v.y + v.z);
+    at += v.x + v.y + v.z + v.w;
+  }
+  __syncthreads();
+  unsigned* const my_starts = starts + (long long)w * (cells + 1);
+  for (int i = t; i < cells; i += kDealThreads) my_starts[i] = place[i];
+  if (t == 0) my_starts[cells] = all;
+  __syncthreads();
+  Dealt* const my_entries = entries + (long long)w * per * kCopies;
+  visit([&](int r, int4 c) {
+    if (!coord_ok(c.x, c.y, c.z, c.w)) return;
+    const unsigned long long key = pack_key(c.x, c.y, c.z, c.w);
+    const Dealt e{(unsigned)key, (unsigned)(key >> 32), r};
+    for_buckets(c, log_b, [&](unsigned b, int halo) { my_entries[atomicAdd(&place[2 * b + halo], 1u)] = e; });
+  });
+  if (w == 0) {
+    if (t == 0) ctl->flags = 0, ctl->count = 0, ctl->tick_top = 0;
+    if (t < kPairSlots) {
+      ctl->pairs[t * 16] = 0;
+      ctl->entries[t * 16] = 0;
+      ctl->key_or[t * 16] = 0;
+      ctl->key_and[t * 16] = ~0ull;
+    }
+  }
+  if (w == (int)gridDim.x - 1) {
+    for (long long i = (long long)n * V + t; i < rows_pad * V; i += kDealThreads) map[i] = -1;
+    if (n + t < rows_pad) mask[n + t] = 0u;  // (fewer than kRowPad)
+  }
+}
+
+// The workgroup that arrives last sums the pair counters and writes the result into pinned host
+// memory.  A pair slot is one 64-bit counter: pairs in its low 40 bits, arrivals above, so that one
+// atomic both adds the workgroup's pairs and tells it whether it was the slot's last (a second
+// level counts the finished slots: no address sees more than gridDim/64 or 64 atomics).  Called by
+// the first wave only, after the others have left: two returning atomics in a row, awaited by the
+// whole workgroup, would keep all of its waves.  Every value the last workgroup
+// reads was produced by an atomic whose return its producer waited for before counting itself in,
+// and is read with an atomic, so no cache write-back is needed.
+__device__ __forceinline__ void publish_pairs(unsigned wg_pairs, unsigned wg_flags, Ctl* ctl, HostResult* host) {
+  constexpr unsigned long long kArrive = 1ull << 40;
+  int last = 0;
+  if (threadIdx.x == 0) {
+    unsigned long long before = wg_flags ? atomicOr(&ctl->flags, (unsigned long long)wg_flags) : 0ull;
+    asm volatile("" : "+v"(before));  // (the flags have arrived)
+    const unsigned slot = blockIdx.x % kPairSlots;
+    before = atomicAdd(&ctl->pairs[slot * 16], (unsigned long long)wg_pairs + kArrive);
+    const unsigned slot_wgs = (gridDim.x - slot + kPairSlots - 1) / kPairSlots;
+    const unsigned used_slots = gridDim.x < (unsigned)kPairSlots ? gridDim.x : (unsigned)kPairSlots;
+    if ((unsigned)(before >> 40) + 1 == slot_wgs) last = atomicAdd(&ctl->tick_top, 1u) + 1 == used_slots;
+  }
+  last = __builtin_amdgcn_readfirstlane(last);
+  if (last) {
+    unsigned long long v = atomicAdd(&ctl->pairs[threadIdx.x * 16], 0ull) & (kArrive - 1);  // kPairSlots == 64 lanes
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if (threadIdx.x == 0)
+      host->word = kHostReady | ((atomicOr(&ctl->flags, 0ull) & 0xFFull) << 48) | (v & 0xFFFFFFFFFFFFull);
+  }
+}
+
+__device__ __forceinline__ unsigned spread3(unsigned g) {  // bit c of 9 -> bit 3c
+  g = (g | (g << 16)) & 0x030000FFu;
+  g = (g | (g << 8)) & 0x0300F00Fu;
+  g = (g | (g << 4)) & 0x030C30C3u;
+  return (g | (g << 2)) & 0x09249249u;
+}
+
+// A run of the table in LDS: the key, and the places in the bucket of the rows in its four cells (16 bits each).
+struct __align__(16) BucketRun {
+  unsigned long long key, cells;
+};
+constexpr unsigned kNoCell = 0xFFFFu;
+
+// The places of a row's neighbours in column (tx, ty): cells z - 1 .. z + 1, three in a row of the window [run q_lo | run q_lo + 1],
+// starting at (z - 1) & 3.  (z itself is in range, so the runs' indices fit the key's field; cells beside the range are dropped.)
+__device__ __forceinline__ void probe_bucket_column(int b, int tx, int ty, int z, const BucketRun* tab, unsigned* cell) {
+  constexpr unsigned slot_mask = (1u << kRunSlotBits) - 1u;
+  const int q_lo = (z - 1) >> 2, i0 = (z - 1) & 3;
+  const unsigned long long key = pack_key(b, tx, ty, q_lo);
+  unsigned s_lo = hash_run(key) >> (32 - kRunSlotBits), s_hi = hash_run(key + 1) >> (32 - kRunSlotBits);
+  unsigned long long lo = ~0ull, hi = ~0ull;
+  bool want_lo = true, want_hi = i0 + 3 > 4;
+  for (unsigned it = 0; it <= slot_mask && (want_lo || want_hi); ++it) {  // both advance together
+    const BucketRun e_lo = tab[s_lo], e_hi = tab[s_hi];
+    if (want_lo && e_lo.key == key) lo = e_lo.cells;
+    if (want_hi && e_hi.key == key + 1) hi = e_hi.cells;
+    want_lo = want_lo && e_lo.key != key && e_lo.key != kEmpty;
+    want_hi = want_hi && e_hi.key != key + 1 && e_hi.key != kEmpty;
+    s_lo = (s_lo + 1) & slot_mask;
+    s_hi = (s_hi + 1) & slot_mask;
+  }
+  const int sh = i0 * 16;
+  const unsigned long long w = sh ? (lo >> sh) | (hi << (64 - sh)) : lo;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) cell[d] = coord_ok(b, tx, ty, z + d - 1) ? (unsigned)(w >> (16 * d)) & 0xFFFFu : kNoCell;
+}
+
+// One workgroup per bucket; nine lanes per row, one per column (dx, dy), seven rows per wave.  kBucketRows rows of the bucket are in the
+// table at a time, kOwnRows of those that are looked up in LDS: a bucket is almost always within both, and one of any size is walked
+// in as many rounds as it takes.
+__global__ void __launch_bounds__(kBucketThreads)
+    k_probe_buckets(const Dealt* __restrict__ entries, const unsigned* __restrict__ starts, const unsigned* __restrict__ dealer_flags,
+                    int dealers, int per, int log_b, int* __restrict__ map, unsigned* __restrict__ mask, Ctl* ctl, HostResult* host) {
+  constexpr int V = 27, LPR = 9, RPW = 7, kWaves = kBucketThreads / 64;
+  constexpr unsigned slot_mask = (1u << kRunSlotBits) - 1u;
+  __shared__ BucketRun tab[1 << kRunSlotBits];
+  __shared__ Dealt own[kOwnRows];
+  __shared__ int row_of[kBucketRows];
+  // rows of a bucket: its own ones dealer by dealer, then the copies; [.][w]: how many before dealer w's, and where they stand
+  __shared__ int before[2][kDealers + 1];
+  __shared__ unsigned src[2][kDealers];
+  __shared__ int wave_sum[2][kDealers / 64];
+  __shared__ unsigned wave_pairs[kWaves], s_flags;
+  static_assert(kBucketThreads >= kDealers, "a thread per dealer");
+  const int t = threadIdx.x, lane = t & 63, wib = t >> 6;
+  const int cells = 2 << log_b;
+  if (t == 0) s_flags = 0;
+  int n[2] = {0, 0}, incl[2];
+  if (t < dealers) {
+    const unsigned* const s = starts + (long long)t * (cells + 1) + 2 * blockIdx.x;
+    const unsigned a = s[0], b = s[1], c = s[2];
+    src[0][t] = a, src[1][t] = b;
+    n[0] = (int)(b - a), n[1] = (int)(c - b);
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    incl[h] = n[h];
+    for (int o = 1; o < 64; o <<= 1) {
+      const int up = __shfl_up(incl[h], o);
+      if (lane >= o) incl[h] += up;
+    }
+    if (t < kDealers && lane == 63) wave_sum[h][wib] = incl[h];
+  }
+  __syncthreads();
+  if (t < kDealers) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      int at = incl[h];
+      for (int i = 0; i < wib; ++i) at += wave_sum[h][i];
+      before[h][t + 1] = at;
+      if (t == 0) before[h][0] = 0;
+    }
+  }
+  __syncthreads();
+  const int n_own = before[0][kDealers], n_all = n_own + before[1][kDealers];
+  auto entry = [&](int i) {
+    const int h = i >= n_own ? 1 : 0;
+    const int j = h ? i - n_own : i;
+    int w = 0;  // the dealer: before[h][w] <= j < before[h][w + 1]
+#pragma unroll
+    for (int o = kDealers / 2; o > 0; o >>= 1)
+      if (before[h][w + o] <= j) w += o;
+    return entries[(long long)w * per * kCopies + src[h][w] + (j - before[h][w])];
+  };
   const int sub = lane / LPR, col = lane - sub * LPR;
-  unsigned pairs = 0;
-  if constexpr (FILTER) load_filter(filter_bits, filter);
-  for (long long wave = (long long)blockIdx.x * kWaves + (threadIdx.x >> 6); wave * RPW < rows_pad; wave += waves) {
-    const long long row = wave * RPW + sub;
-    const bool active = (sub < RPW) && (row < rows_pad);
-    int nb[3] = {-1, -1, -1};
-    if (active && row < n_rows) {
-      const int4 c = rows[row];
-      const int tx = c.y + col / 3 - 1, ty = c.z + col % 3 - 1;
-      if (coord_ok(c.x, c.y, c.z, c.w) && coord_ok(c.x, tx, ty, c.w)) {
-        probe_column<1, FILTER>(c.x, tx, ty, c.w, tab, log_cap, filter, nb);
-        // a row that does not find itself at its own place shares it with another row
-        if (col == 4 && nb[1] != (int)row) atomicOr(&ctl->flags, FLAG_DUP);
+  unsigned pairs = 0, bad = 0;
+  for (int c0 = 0; n_own && (c0 == 0 || c0 < n_all); c0 += kBucketRows) {
+    const int in_table = min(kBucketRows, n_all - c0);
+    if (c0) __syncthreads();
+    for (int i = t; i <= (int)slot_mask; i += kBucketThreads) reinterpret_cast<ulonglong2*>(tab)[i] = make_ulonglong2(kEmpty, ~0ull);
+    __syncthreads();
+    for (int i = t; i < in_table; i += kBucketThreads) {
+      const Dealt e = entry(c0 + i);
+      row_of[i] = e.row;
+      if (c0 == 0 && i < kOwnRows && i < n_own) own[i] = e;
+      const unsigned long long key = (unsigned long long)e.lo | ((unsigned long long)e.hi << 32);
+      const unsigned long long run = (key & ~0xFFFFull) | (unsigned)((((int)(e.lo & 0xFFFFu) - 32768) >> 2) + 32768);
+      unsigned s = hash_run(run) >> (32 - kRunSlotBits);
+      for (unsigned it = 0; it <= slot_mask; ++it) {
+        const unsigned long long old = atomicCAS(&tab[s].key, kEmpty, run);
+        if (old == kEmpty || old == run) {
+          reinterpret_cast<unsigned short*>(&tab[s].cells)[e.lo & 3u] = (unsigned short)i;
+          break;
+        }
+        s = (s + 1) & slot_mask;
       }
     }
-    if (active) {
-      int* dst = map + row * V + 3 * col;
-      dst[0] = nb[0];
-      dst[1] = nb[1];
-      dst[2] = nb[2];
+    for (int o0 = 0; o0 < n_own; o0 += kOwnRows) {
+      const int n_here = min(kOwnRows, n_own - o0);
+      if (c0 || o0) {
+        __syncthreads();
+        for (int i = t; i < n_here; i += kBucketThreads) own[i] = entry(o0 + i);
+      }
+      __syncthreads();
+      for (int i0 = wib * RPW; i0 < n_here; i0 += kWaves * RPW) {
+        const int i = i0 + sub;
+        const bool active = sub < RPW && i < n_here;
+        const Dealt e = own[active ? i : 0];
+        const int row = e.row, b = (int)(e.hi >> 16), x = (int)(e.hi & 0xFFFFu) - 32768, y = (int)(e.lo >> 16) - 32768,
+                  z = (int)(e.lo & 0xFFFFu) - 32768;
+        const int tx = x + col / 3 - 1, ty = y + col % 3 - 1;
+        unsigned cell[3] = {kNoCell, kNoCell, kNoCell};
+        if (active && coord_ok(b, tx, ty, z)) probe_bucket_column(b, tx, ty, z, tab, cell);
+        // a row that does not find itself at its own place shares it with another row
+        if (active && col == 4) {
+          const int mine = o0 + i - c0;
+          if (cell[1] != (mine >= 0 && mine < in_table ? (unsigned)mine : kNoCell)) bad = (unsigned)FLAG_DUP;
+        }
+        int nb[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) nb[d] = cell[d] == kNoCell ? -1 : row_of[cell[d]];
+        if (active) {
+          int* const dst = map + (long long)row * V + 3 * col;
+#pragma unroll
+          for (int d = 0; d < 3; ++d)
+            if (c0 == 0 || nb[d] >= 0) dst[d] = nb[d];
+        }
+        const unsigned long long b0 = __ballot(nb[0] >= 0), b1 = __ballot(nb[1] >= 0), b2 = __ballot(nb[2] >= 0);
+        pairs += (unsigned)(__popcll(b0) + __popcll(b1) + __popcll(b2));
+        if (active && col == 0) {
+          const int sh = sub * LPR;
+          const unsigned m = spread3((unsigned)(b0 >> sh) & 0x1FFu) | (spread3((unsigned)(b1 >> sh) & 0x1FFu) << 1) |
+                             (spread3((unsigned)(b2 >> sh) & 0x1FFu) << 2);
+          mask[row] = c0 ? mask[row] | m : m;
+        }
+      }
     }
-    const unsigned long long b0 = __ballot(nb[0] >= 0), b1 = __ballot(nb[1] >= 0), b2 = __ballot(nb[2] >= 0);
-    if (active && col == 0) {
-      const int sh = sub * LPR;
-      mask[row] = spread3((unsigned)(b0 >> sh) & 0x1FFu) | (spread3((unsigned)(b1 >> sh) & 0x1FFu) << 1) |
-                  (spread3((unsigned)(b2 >> sh) & 0x1FFu) << 2);
-    }
-    pairs += (unsigned)(__popcll(b0) + __popcll(b1) + __popcll(b2));
-    if (!FILTER) break;  // (the grid covers the rows)
   }
-  if (lane == 0) wave_pairs[threadIdx.x >> 6] = pairs;
+  if (blockIdx.x == 0 && t < dealers) bad |= dealer_flags[t];
+  if (lane == 0) wave_pairs[wib] = pairs;
+  if (bad) atomicOr(&s_flags, bad);
   __syncthreads();
-  if (threadIdx.x >= 64) return;
+  if (t >= 64) return;
   unsigned sum = 0;
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) sum += wave_pairs[w];
-  publish_pairs(sum, ctl, host);
+  publish_pairs(sum, s_flags, ctl, host);
 }
 
 // ---- small submanifold 3x3x3 builds in one launch ----
@@ -1231,7 +1459,7 @@ __global__ void __launch_bounds__(FILTER ? kProbeThreads : 256)
       const int4 c = rows[row];
       const int tx = c.y + g - 2, ty = c.z + col - 2;
       if (coord_ok(c.x, c.y, c.z, c.w) && coord_ok(c.x, tx, ty, c.w)) {
-        probe_column<2, FILTER>(c.x, tx, ty, c.w, tab, log_cap, filter, nb);
+        probe_column<FILTER>(c.x, tx, ty, c.w, tab, log_cap, filter, nb);
         // a row that does not find itself at its own place shares it with another row
         if (g == 2 && col == 2 && nb[2] != (int)row) atomicOr(&ctl->flags, FLAG_DUP);
       }
@@ -1554,19 +1782,17 @@ int build_init(const DevBuf& tab, long long words /*of 16 bytes*/, Ctl* ctl, hip
   return SPCONV_OK;
 }
 
-// The table of z-runs of a submanifold build, and from a number of rows on the probe's filter.  Whole waited builds without and
-// with it, us (3x3x3 also the GPU's time of unwaited builds, one behind the other):
-//   3x3x3  scan     60k rows 61, 62 (35.6, 36.9); 80k 63, 58 (37.8, 31.5); 100k 69, 65 (44.4, 38.0); 200k 102, 88 (78, 60); 300k 135, 107
-//          room     60k 63, 69 (39, 45); 80k 60.5, 60.3 (36.6, 33.3); 100k 67, 65 (43, 38); 130k 81, 81 (57, 54); 200k 101, 93 (76, 65); 300k 129, 110
-//          uniform  60k 67, 69 (42, 45); 80k 68, 64.5 (44, 37.5); 100k 79, 75 (55, 48); 200k 114, 102 (91, 74); 300k 143, 121
-//   5x5x5  scan 20k 50, 52; 50k 72, 71; 80k 93, 80; 120k 134, 113; room 20k 47, 48; 50k 65, 65; 80k 90, 82; uniform 50k 79, 78.5; 80k 106, 92
+// The table of z-runs of a 5x5x5 build, and from a number of rows on the probe's filter.  Whole waited builds without and with it, us:
+//   scan 20k rows 50, 52; 50k 72, 71; 80k 93, 80; 120k 134, 113; room 20k 47, 48; 50k 65, 65; 80k 90, 82; uniform 50k 79, 78.5; 80k 106, 92
+// (In buckets, as 3x3x3 builds are, a row has 2.5 times the copies and 2.8 times the look-ups: 9k rows of a scan 29, 35; 30k 51,
+// 50; 60k 67, 60 to 72; 80k 67, 75 to 80: neither is ahead.)
 struct RunTable {
   DevBuf buf;  // entries, then (with a filter) its marks and its bits
   int log_cap = 0;
   unsigned char* marks = nullptr;
   unsigned* bits = nullptr;
 };
-constexpr int64_t kFilterRows3 = 80000, kFilterRows5 = 50000;
+constexpr int64_t kFilterRows5 = 50000;
 int build_runs(const int4* rows, int64_t N, bool filter, Ctl* ctl, int4* keep, RunTable* t, hipStream_t st) {
   t->log_cap = log2_capacity(N);  // entries >= 2 N >= twice the z-runs
   const size_t table = sizeof(RunSlot) << t->log_cap;
@@ -1591,26 +1817,42 @@ template <typename F> int allow_lds(F kernel, int bytes, std::atomic<bool>& done
   return SPCONV_OK;
 }
 
-// Submanifold 3x3x3 build: init, insert, probe (whose last workgroup publishes the result to
+// The buckets of a submanifold 3x3x3 build.  Up to 512, of 64 rows at least: they all run at once; from then on 256 rows a bucket,
+// which weighs a workgroup's fixed 5 us against the longest bucket (us, with 128, 256 rows a bucket: 60k rows of a scan 23, 28; of a room 26, 35;
+// 100k 30, 26; 400k 82, 67; with 350: buckets beyond kBucketRows, 300k of a room 83 against 64).
+struct Buckets {
+  int dealers, per, log_b = 6;
+  size_t entries, starts, bytes;
+  explicit Buckets(int64_t N) {
+    per = (int)std::max<int64_t>(round_up(ceil_div(N, kDealers), kDealThreads), kDealThreads);
+    dealers = (int)ceil_div(N, per);
+    while (log_b < kMaxBucketBits && (log_b < 9 ? (int64_t)64 << log_b : (int64_t)256 << log_b) < N) ++log_b;
+    entries = (size_t)dealers * per * kCopies * sizeof(Dealt);
+    starts = (size_t)dealers * ((2 << log_b) + 1) * sizeof(unsigned);
+    bytes = entries + starts + (size_t)dealers * sizeof(unsigned);
+  }
+};
+
+// Submanifold 3x3x3 build: rows into buckets, look-ups (whose last workgroup publishes the result to
 // pinned host memory); small maps: one launch, and k_publish.
 int build_submanifold3(spconv_kmap* km, const int4* rows, int64_t N, bool async, hipStream_t st) {
   const int V = 27;
-  DevBuf ctl_buf, own_rows;
-  RunTable tab;
+  DevBuf ctl_buf, own_rows, dealt;
   SPC_TRY(ctl_buf.alloc(sizeof(Ctl)));
   Ctl* ctl = ctl_buf.as<Ctl>();
-  const bool small = N <= kSmallRows, filter = N >= kFilterRows3;
+  const bool small = N <= kSmallRows;
+  const Buckets bk(N);
   const int small_lds = (int)round_up(N, 2) * 8 + small_slots((int)std::min<int64_t>(N, kSmallRows)) * 4;
-  static std::atomic<bool> filter_lds{false}, small_lds_set{false};
+  static std::atomic<bool> deal_lds_set{false}, small_lds_set{false};
   if (small) SPC_TRY(allow_lds(k_build_small3, kSmallRows * 8 + small_slots(kSmallRows) * 4, small_lds_set));
-  if (filter) SPC_TRY(allow_lds(k_probe_runs3<true>, kFilterWords * 4, filter_lds));
+  else SPC_TRY(allow_lds(k_deal_rows, deal_lds(kMaxBucketBits), deal_lds_set));
   SPC_TRY(own_rows.alloc((size_t)N * 16));
   SideMap& side = km->out_side;
   side.rows = N;
   side.rows_pad = round_up(N, kRowPad);
   SPC_TRY(side.map.alloc((size_t)side.rows_pad * V * sizeof(int)));
   SPC_TRY(side.mask.alloc((size_t)side.rows_pad * sizeof(unsigned)));
-  if (!small) SPC_TRY(build_runs(rows, N, filter, ctl, own_rows.as<int4>(), &tab, st));
+  if (!small) SPC_TRY(dealt.alloc(bk.bytes));
   HostCtl* hc = host_ctl_acquire();
   if (!hc) return SPCONV_ENOMEM;
   hc->res.word = 0;  // (pinned memory: visible to the kernel launched below)
@@ -1618,13 +1860,16 @@ int build_submanifold3(spconv_kmap* km, const int4* rows, int64_t N, bool async,
     hipLaunchKernelGGL(k_build_small3, dim3((unsigned)std::min<int64_t>(ceil_div(side.rows_pad, 32), kSmallWgs)), dim3(kSmallThreads),
                        small_lds, st, rows, (int)N, (int)side.rows_pad, own_rows.as<int4>(), side.map.as<int>(),
                        side.mask.as<unsigned>(), ctl);
-  else if (filter)
-    hipLaunchKernelGGL(k_probe_runs3<true>, dim3(256), dim3(kProbeThreads), kFilterWords * 4, st, rows, (int)N, (long long)side.rows_pad,
-                       tab.buf.as<RunSlot>(), tab.log_cap, tab.bits, side.map.as<int>(), side.mask.as<unsigned>(), ctl, hc->dev);
-  else
-    hipLaunchKernelGGL(k_probe_runs3<false>, dim3(blocks_for(ceil_div(side.rows_pad, 7), 4)), dim3(256), 0, st, rows, (int)N,
-                       (long long)side.rows_pad, tab.buf.as<RunSlot>(), tab.log_cap, (const unsigned*)nullptr, side.map.as<int>(),
-                       side.mask.as<unsigned>(), ctl, hc->dev);
+  else {
+    Dealt* const entries = dealt.as<Dealt>();
+    unsigned* const starts = reinterpret_cast<unsigned*>(dealt.as<char>() + bk.entries);
+    unsigned* const flags = reinterpret_cast<unsigned*>(dealt.as<char>() + bk.entries + bk.starts);
+    hipLaunchKernelGGL(k_deal_rows, dim3((unsigned)bk.dealers), dim3(kDealThreads), deal_lds(bk.log_b), st, rows, (int)N, bk.per, bk.log_b,
+                       entries, starts, flags, own_rows.as<int4>(), (long long)side.rows_pad, side.map.as<int>(),
+                       side.mask.as<unsigned>(), ctl);
+    hipLaunchKernelGGL(k_probe_buckets, dim3(1u << bk.log_b), dim3(kBucketThreads), 0, st, entries, starts, flags, bk.dealers, bk.per,
+                       bk.log_b, side.map.as<int>(), side.mask.as<unsigned>(), ctl, hc->dev);
+  }
   if (small && async) hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, st, ctl, hc->dev, true);
   const bool ok = hipGetLastError() == hipSuccess;
   if (!ok) {

@@ -721,3 +721,28 @@ def test_stride2_builds_where_memory_is_short(sp, K):
         np.testing.assert_array_equal(km.export().cpu().numpy(), ref.M)
         km.destroy()
         assert not mem.live
+
+
+@pytest.mark.parametrize("side,lo,batches", [(18, -32768, 1), (40, 32768 - 40, 1), (18, -9, 7), (12, 32768 - 12, 31)])
+def test_dense_submanifold_builds_in_buckets(sp, side, lo, batches):
+    """Blocks of 512 rows, several to a bucket: more rows than a workgroup looks up, and holds in its table, at a time; rows at both ends
+    of the range; the same cells in several batches.  A row twice and a row beside the range fail such a build."""
+    g = np.arange(lo, lo + side)
+    c = np.stack(np.meshgrid(np.arange(batches), g, g, g, indexing="ij"), -1).reshape(-1, 4).astype(np.int32)
+    c = c[np.random.default_rng(side).permutation(len(c))]
+    _check_kmap(sp, c, 3, 1, False)
+    km = sp.build_kmap(coords_dev(c), 3, 1, asynchronous=True)
+    km.status()
+    assert km.n_pairs() == int((oc.build_kmap(c, 3, 1).M >= 0).sum())
+    for bad, status in ((np.vstack([c, c[len(c) // 2:][:1]]), -3), (np.vstack([c[:-1], [[0, 0, 40000, 0]]]).astype(np.int32), -2)):
+        with pytest.raises(sp.SpconvError) as e:
+            sp.build_kmap(coords_dev(bad), 3, 1)
+        assert e.value.status == status
+
+
+@pytest.mark.parametrize("n", [8191, 8193, 32769, 131071, 131329])
+def test_scattered_submanifold_builds_in_buckets(sp, n):
+    """On both sides of the numbers of buckets and of dealers; most blocks hold one row."""
+    c = gen.uniform_cloud(n, 200, seed=n, lo=-100)
+    c[: n // 3, 0] = 65534
+    _check_kmap(sp, c, 3, 1, False)
