@@ -18,13 +18,15 @@ namespace spc {
 namespace {
 
 constexpr int kBucketBits = 8, kBuckets = 1 << kBucketBits;
-constexpr int kCountThreads = 256, kCountWaves = 4;
+constexpr int kCountThreads = 256;
+constexpr int kScatterThreads = 1024, kScatterWaves = 16;
 constexpr int kMaxCountWgs = 256;               // rows of the counter matrix
 constexpr int kChunk = 2048;                    // places that are sorted together in LDS
 constexpr int kPlaceBits = 11;
 constexpr int kLocalThreads = 1024, kLocalWaves = 16, kLocalItems = kChunk / kLocalThreads;
 constexpr int kKeyBits = 20, kDigitBits = 7, kDigits = 1 << kDigitBits;
-static_assert(kChunk == 1 << kPlaceBits && kBuckets == kCountThreads && kLocalItems == 2, "index arithmetic below");
+static_assert(kChunk == 1 << kPlaceBits && kBuckets == kCountThreads && kLocalItems == 2 && kScatterThreads == 4 * kBuckets,
+              "index arithmetic below");
 
 // V = 27: which corner layers dz = -1, +1 have a neighbour (2 bits), 12 edges, 6 faces.  Other maps: the mask itself.
 __device__ __forceinline__ unsigned local_key(unsigned m, int V) {
@@ -40,10 +42,9 @@ __device__ __forceinline__ unsigned local_key(unsigned m, int V) {
 // a flat surface has the edges of one plane), the face neighbours along z.
 __device__ __forceinline__ unsigned bucket_bits(unsigned m, int V) {
   if (V != 27) return V > kBucketBits ? (m >> (V - kBucketBits)) & (kBuckets - 1) : m;
-  auto any = [&](unsigned bits, int to) { return (m & bits ? 1u : 0u) << to; };
-  return any(0x05140145u, 7) | any((1u << 1) | (1u << 7), 6) | any((1u << 19) | (1u << 25), 5) | any((1u << 3) | (1u << 5), 4) |
-         any((1u << 21) | (1u << 23), 3) | any((1u << 9) | (1u << 11), 2) | any((1u << 15) | (1u << 17), 1) |
-         any((1u << 12) | (1u << 14), 0);
+  const unsigned six = m | (m >> 6), two = m | (m >> 2);  // bit i: offsets i and i + 6, i and i + 2
+  return (m & 0x05140145u ? 128u : 0u) | ((six >> 1) & 1u) << 6 | ((six >> 19) & 1u) << 5 | ((two >> 3) & 1u) << 4 |
+         ((two >> 21) & 1u) << 3 | ((two >> 9) & 1u) << 2 | ((two >> 15) & 1u) << 1 | ((two >> 12) & 1u);
 }
 // The buckets in the order of their set bits: rows with many neighbours stand at the end of the order, where the
 // kernels start (the heaviest tiles first).
@@ -98,78 +99,74 @@ __device__ __forceinline__ void rank_of(unsigned digit, int bits, bool valid, in
 }
 
 // Rows of one workgroup to their places: bucketed[place] = (local key, row), stable.  The workgroup finds its first
-// places by adding up the counter matrix (at most 256 x 256 counters from L2) instead of waiting for a scan launch.
-__global__ void __launch_bounds__(kCountThreads)
+// places by adding up the counter matrix (at most 256 x 256 counters from L2, a quarter of the rows per 256 threads: with 256 threads
+// in all, 200k rows took 13 us) instead of waiting for a scan launch.
+__global__ void __launch_bounds__(kScatterThreads)
     k_order_scatter(const unsigned* __restrict__ mask, int rows, int wg_rows, int V, const unsigned* __restrict__ counts,
                     uint2* __restrict__ bucketed) {
-  __shared__ unsigned off[kCountWaves][kBuckets];  // of a round of 1024 rows: the waves' counts, then first places
-  __shared__ unsigned wave_sum[kCountWaves];
-  const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
+  __shared__ unsigned off[kScatterWaves][kBuckets];  // of a round of 1024 rows: the waves' counts, then first places
+  __shared__ unsigned part_before[4][kBuckets], part_all[4][kBuckets], wave_sum[4], place[kBuckets];
+  const int t = threadIdx.x, lane = t & 63, wib = t >> 6, d = t & (kBuckets - 1), part = t / kBuckets;
   const int begin = blockIdx.x * wg_rows, end = min(rows, begin + wg_rows);
-  unsigned m[4], bkt[4], rank[4];
-  auto fetch = [&](int r0) {  // a wave takes 256 consecutive rows
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = r0 + wib * 256 + i * 64 + lane;
-      m[i] = r < end ? mask[r] : 0u;
-    }
-  };
-  fetch(begin);
-  unsigned place;  // next place of this thread's bucket
+  unsigned m = begin + t < end ? mask[begin + t] : 0u;
   {
     unsigned before = 0, all = 0;
-    const unsigned* col = counts + threadIdx.x;
-    constexpr int R = 32;  // rows in flight: a load that waits for the one before it costs a round trip each
-    for (int w0 = 0; w0 < (int)gridDim.x; w0 += R) {
+    constexpr int R = 16;  // rows in flight: a load that waits for the one before it costs a round trip each
+    for (int w0 = part; w0 < (int)gridDim.x; w0 += 4 * R) {
       unsigned c[R];
 #pragma unroll
-      for (int i = 0; i < R; ++i) c[i] = w0 + i < (int)gridDim.x ? col[(w0 + i) * kBuckets] : 0u;
+      for (int i = 0; i < R; ++i) c[i] = w0 + 4 * i < (int)gridDim.x ? counts[(w0 + 4 * i) * kBuckets + d] : 0u;
 #pragma unroll
       for (int i = 0; i < R; ++i) {
         all += c[i];
-        before += w0 + i < (int)blockIdx.x ? c[i] : 0u;
+        before += w0 + 4 * i < (int)blockIdx.x ? c[i] : 0u;
       }
     }
-    unsigned incl = all;
+    part_before[part][d] = before;
+    part_all[part][d] = all;
+  }
+  __syncthreads();
+  unsigned incl = 0, all = 0;
+  if (t < kBuckets) {
+    for (int i = 0; i < 4; ++i) all += part_all[i][t];
+    incl = all;
     for (int o = 1; o < 64; o <<= 1) {
       const unsigned up = __shfl_up(incl, o);
       if (lane >= o) incl += up;
     }
     if (lane == 63) wave_sum[wib] = incl;
-    __syncthreads();
-    place = incl - all + before;
-    for (int w = 0; w < wib; ++w) place += wave_sum[w];
   }
-  for (int r0 = begin; r0 < end; r0 += 1024) {
-    if (r0 > begin) fetch(r0);
-    for (int d = threadIdx.x; d < kCountWaves * kBuckets; d += kCountThreads) (&off[0][0])[d] = 0;
+  __syncthreads();
+  if (t < kBuckets) {
+    unsigned at = incl - all;
+    for (int i = 0; i < 4; ++i) at += part_before[i][t];
+    for (int w = 0; w < wib; ++w) at += wave_sum[w];
+    place[t] = at;  // next place of the bucket
+  }
+  for (int r0 = begin; r0 < end; r0 += kScatterThreads) {
+    const int r = r0 + t;
+    const bool valid = r < end;
+    if (r0 > begin) m = valid ? mask[r] : 0u;
+    for (int i = t; i < kScatterWaves * kBuckets; i += kScatterThreads) (&off[0][0])[i] = 0;
     __syncthreads();
+    const unsigned bkt = d_ranks.of[bucket_bits(m, V)];
+    unsigned rank, peers;
+    rank_of(bkt, kBucketBits, valid, lane, &rank, &peers);
+    if (valid && rank == 0) off[wib][bkt] = peers;
+    __syncthreads();
+    if (t < kBuckets) {
+      unsigned at = place[t];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {  // rank within the wave's rows; off ends as the wave's counts
-      const bool valid = r0 + wib * 256 + i * 64 + lane < end;
-      bkt[i] = d_ranks.of[bucket_bits(m[i], V)];
-      unsigned peers;
-      rank_of(bkt[i], kBucketBits, valid, lane, &rank[i], &peers);
-      const unsigned have = valid ? off[wib][bkt[i]] : 0u;
-      __builtin_amdgcn_wave_barrier();  // every lane has read the count before a leader advances it
-      if (valid && rank[i] == 0) off[wib][bkt[i]] = have + peers;
-      __builtin_amdgcn_wave_barrier();
-      rank[i] += have;
+      for (int w = 0; w < kScatterWaves; ++w) {
+        const unsigned c = off[w][t];
+        off[w][t] = at;
+        at += c;
+      }
+      place[t] = at;
     }
     __syncthreads();
-#pragma unroll
-    for (int w = 0; w < kCountWaves; ++w) {
-      const unsigned c = off[w][threadIdx.x];
-      off[w][threadIdx.x] = place;
-      place += c;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = r0 + wib * 256 + i * 64 + lane;
-      const unsigned at = off[wib][bkt[i]] + rank[i];
-      if (r < end && at < (unsigned)rows) bucketed[at] = make_uint2(local_key(m[i], V), (unsigned)r);
-    }
+    const unsigned at = off[wib][bkt] + rank;
+    if (valid && at < (unsigned)rows) bucketed[at] = make_uint2(local_key(m, V), (unsigned)r);
     __syncthreads();
   }
 }
@@ -238,7 +235,7 @@ __global__ void __launch_bounds__(kLocalThreads)
 #pragma unroll
     for (int i = 0; i < kLocalItems; ++i) v[i] = comp[wib * (64 * kLocalItems) + i * 64 + lane];
   }
-  const int share = kChunk / gridDim.y, lo = blockIdx.y * share;  // (a power of two, at least 512)
+  const int share = kChunk / gridDim.y, lo = blockIdx.y * share;  // (a power of two, at least 128)
 #pragma unroll
   for (int i = 0; i < kLocalItems; ++i) {
     const int at = wib * (64 * kLocalItems) + i * 64 + lane;
@@ -291,10 +288,11 @@ int order_rows(const SideMap& side, int V, IgemmPlan& p, hipStream_t st) {
   const unsigned* mask = side.mask.as<unsigned>();
   hipLaunchKernelGGL(k_order_count, dim3(wgs), dim3(kCountThreads), 0, st, mask, rows, wg_rows, V, counts);
   SPC_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_order_scatter, dim3(wgs), dim3(kCountThreads), 0, st, mask, rows, wg_rows, V, counts, bucketed);
+  hipLaunchKernelGGL(k_order_scatter, dim3(wgs), dim3(kScatterThreads), 0, st, mask, rows, wg_rows, V, counts, bucketed);
   SPC_LAUNCH_CHECK();
   const unsigned chunks = (unsigned)ceil_div(p.rows_pad, kChunk);
-  const unsigned shares = chunks * 4 <= 256 ? 4 : chunks * 2 <= 256 ? 2 : 1;
+  unsigned shares = 16;  // (9k rows with 4: 12.5 us, so 10.5; two workgroups on one CU take longer than one after the other: 200k rows 27, 19.6)
+  while (shares > 1 && chunks * shares > 256) shares /= 2;
   hipLaunchKernelGGL(k_order_local, dim3(chunks, shares), dim3(kLocalThreads), 0, st, bucketed, mask,
                      side.map.as<int>(), V, rows, (long long)p.rows_pad, (long long)p.n_tiles, p.perm.as<int>(), p.maps.as<int>(),
                      p.tilemask.as<unsigned>());

@@ -266,3 +266,19 @@ def test_alternating_halves(n, c_in, c_out):
     got = sp.dgrad(g, w, km)
     assert norm_err(got, want) <= 2e-3
     assert torch.equal(got, sp.dgrad(g, w, km))
+
+
+@pytest.mark.parametrize("n", [2048, 8191, 16385, 33_000, 132_000, 263_000])
+def test_orders_hold_every_row(n):
+    """Around the stretches of places, the shares that workgroups write of them, and 256 workgroups that count: every row is in the
+    order once (the layers agree with one that walks the map as built)."""
+    import paper_2311_12862_amd as sp
+    import torch
+    c = gen.lidar_scene(50, target_n=n + n // 4)[:n] if n < 50_000 else gen.uniform_cloud(n, 150, seed=n)
+    assert len(c) == n
+    km = sp.build_kmap(coords_dev(c), 3, 1)
+    (_, x), (_, w), (_, g) = make_layer(n, n, ci := 512 if n < 8192 else 128, co := 512 if n < 4100 else 192, 27, "f16", 6)
+    assert sp.describe_launch(3, n, n, ci, co, torch.float16).sorted
+    cfg = sp.Config(n_split=0, kernel=2, tile_m=64)
+    for got, want in ((sp.fwd(x, w, km), sp.fwd(x, w, km, cfg)), (sp.dgrad(g, w, km), sp.dgrad(g, w, km, cfg))):
+        assert norm_err(got, want.double().cpu().numpy()) <= 2e-3  # (two roundings to fp16 of equal sums)
