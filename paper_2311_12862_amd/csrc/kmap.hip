@@ -50,11 +50,11 @@ struct Ctl {
 // memory, so that no copy has to be enqueued behind the build.
 // What an asynchronous build leaves in pinned host memory, in one 8-byte word so that one store
 // publishes it: bit 63 = written, bits 48..55 = error flags, bits 0..47 = pair count.
-// Whoever waits polls `word` or `ready` and hands the block to the next build as soon as it is set: the store that is polled is the
-// last access to the block of the kernels that were given it, and no kernel stores both.
+// Whoever waits polls all that the kernels given the block store last, each of them once, and then hands it to the next build.
 struct HostResult {
   unsigned long long word;
-  // what the other builds hand over (k_publish): written before `ready`
+  unsigned long long outputs;  // with bit 63 like word (kPublishOutputs)
+  // what builds over hash tables hand over (kPublishAll): written before `ready`
   unsigned long long flags, count, key_or, key_and, pairs, entries, plane_pairs[5];
   unsigned long long ready;
 };
@@ -753,23 +753,40 @@ __global__ void __launch_bounds__(256) k_build_init(ulonglong2* __restrict__ tab
   }
 }
 
-// Adds up the control block and writes the figures straight into pinned host memory, where the host polls for them: a
-// copy and a stream synchronisation in its place cost about 20 us of idle GPU per use.  One wave.
-// unwaited: an asynchronous build, of which only the word is read; else everything but the word.
-__global__ void __launch_bounds__(64) k_publish(const Ctl* __restrict__ ctl, HostResult* host, bool unwaited) {
+// The figures of a build straight into pinned host memory, where the host polls for them: a copy and a stream synchronisation in
+// their place cost about 20 us of idle GPU per use.  One wave; all its loads are in flight together, and where the figures fit into words of
+// eight bytes, each with a ready bit of its own, nothing waits for a store to arrive (a fence between figures and a flag took 1.5 us).
+enum Publish {
+  kPublishWord,     // flags and pairs
+  kPublishOutputs,  // and the number of outputs; rows that share an entry are flagged
+  kPublishAll,      // everything, behind a fence
+  kPublishEnd       // nothing: the kernels before this one have ended (a submanifold probe stores the word itself)
+};
+template <Publish WHAT> __global__ void __launch_bounds__(64) k_publish(const Ctl* __restrict__ ctl, HostResult* host) {
   const int lane = threadIdx.x;  // kPairSlots == 64
+  if constexpr (WHAT == kPublishEnd) {
+    if (lane == 0) __hip_atomic_store(&host->ready, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    return;
+  }
   const unsigned long long mine = ctl->pairs[lane * 16] & ((1ull << 40) - 1);  // (above: publish_pairs' arrivals)
-  unsigned long long pairs = mine, entries = ctl->entries[lane * 16], k_or = ctl->key_or[lane * 16], k_and = ctl->key_and[lane * 16];
+  unsigned long long pairs = mine, flags = ctl->flags, count = 0, entries = 0, k_or = 0, k_and = ~0ull;
+  if constexpr (WHAT != kPublishWord) count = ctl->count, entries = ctl->entries[lane * 16];
+  if constexpr (WHAT == kPublishAll) k_or = ctl->key_or[lane * 16], k_and = ctl->key_and[lane * 16];
   for (int o = 32; o > 0; o >>= 1) {
     pairs += __shfl_xor(pairs, o);
-    entries += __shfl_xor(entries, o);
-    k_or |= __shfl_xor(k_or, o);
-    k_and &= __shfl_xor(k_and, o);
+    if constexpr (WHAT != kPublishWord) entries += __shfl_xor(entries, o);
+    if constexpr (WHAT == kPublishAll) {
+      k_or |= __shfl_xor(k_or, o);
+      k_and &= __shfl_xor(k_and, o);
+    }
   }
-  if (unwaited) {
-    if (lane == 0)
-      __hip_atomic_store(&host->word, kHostReady | ((ctl->flags & 0xFFu) << 48) | (pairs & 0xFFFFFFFFFFFFull), __ATOMIC_RELEASE,
+  if constexpr (WHAT != kPublishAll) {
+    if (WHAT == kPublishOutputs && entries != pairs) flags |= FLAG_DUP;
+    if (lane == 0) {
+      if (WHAT == kPublishOutputs) __hip_atomic_store(&host->outputs, kHostReady | count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(&host->word, kHostReady | ((flags & 0xFFu) << 48) | (pairs & 0xFFFFFFFFFFFFull), __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_SYSTEM);
+    }
     return;
   }
   for (int g = 0; g < 5; ++g) {
@@ -778,8 +795,8 @@ __global__ void __launch_bounds__(64) k_publish(const Ctl* __restrict__ ctl, Hos
     if (lane == 0) host->plane_pairs[g] = v;
   }
   if (lane == 0) {
-    host->flags = ctl->flags;
-    host->count = ctl->count;
+    host->flags = flags;
+    host->count = count;
     host->key_or = k_or;
     host->key_and = k_and;
     host->pairs = pairs;
@@ -1710,47 +1727,47 @@ void host_ctl_release(HostCtl* h) {
   g_host_free.push_back(h);
 }
 
-// Launches k_publish behind the work enqueued so far and waits for its figures.
-int read_ctl(const Ctl* ctl, HostResult* res, hipStream_t st) {
-  HostCtl* hc = host_ctl_acquire();
-  if (!hc) return SPCONV_ENOMEM;
-  hc->res.ready = 0;  // (pinned memory: visible to the kernel launched below)
-  hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, st, ctl, hc->dev, false);
-  int status = SPCONV_OK;
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) {
-    status = hip_fail(e, "k_publish", __FILE__, __LINE__);
-    (void)hipStreamSynchronize(st);
-  } else {
-    const volatile unsigned long long* ready = &hc->res.ready;
-    const auto t0 = std::chrono::steady_clock::now();
-    while (!*ready) {  // polled: the work behind it usually takes well under a millisecond
-      if (std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() > 0.01) {
-        const hipError_t w = hipStreamSynchronize(st);
-        if (w != hipSuccess) status = hip_fail(w, "hipStreamSynchronize", __FILE__, __LINE__);
-        else if (!*ready) status = SPCONV_EHIP;
-        break;
-      }
-    }
-    std::atomic_thread_fence(std::memory_order_acquire);
-    if (status == SPCONV_OK) *res = hc->res;
+// Waits for what the work enqueued on st stores into a block.  launched: what the launches came to.
+enum : unsigned { kWaitWord = 1, kWaitOutputs = 2, kWaitReady = 4 };
+int wait_block(const HostCtl* hc, unsigned what, hipError_t launched, hipStream_t st) {
+  if (launched != hipSuccess) {
+    (void)hipStreamSynchronize(st);  // (what was launched may still store)
+    return hip_fail(launched, "launch", __FILE__, __LINE__);
   }
-  host_ctl_release(hc);
-  return status;
+  const volatile HostResult* r = &hc->res;
+  auto there = [&]() {
+    return (!(what & kWaitWord) || (r->word & kHostReady)) && (!(what & kWaitOutputs) || (r->outputs & kHostReady)) &&
+           (!(what & kWaitReady) || r->ready);
+  };
+  const auto t0 = std::chrono::steady_clock::now();
+  while (!there()) {  // polled: the work behind it usually takes well under a millisecond
+    const double waited = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+    if (waited > 2e-4) std::this_thread::yield();
+    if (waited <= 0.01) continue;
+    SPC_HIP(hipStreamSynchronize(st));
+    if (!there()) return SPCONV_EHIP;
+    break;
+  }
+  std::atomic_thread_fence(std::memory_order_acquire);
+  return SPCONV_OK;
 }
 
-// Waits for the word that work enqueued on st stores, and gives the block back.  launched: what the launches came to.
-int wait_word(HostCtl* hc, hipError_t launched, hipStream_t st, unsigned long long* word) {
-  int status = SPCONV_OK;
-  if (launched != hipSuccess) {
-    status = hip_fail(launched, "launch", __FILE__, __LINE__);
-    (void)hipStreamSynchronize(st);  // (what was launched may still store)
-  } else if (!host_ctl_ready(hc, 0.01)) {
-    const hipError_t w = hipStreamSynchronize(st);
-    if (w != hipSuccess) status = hip_fail(w, "hipStreamSynchronize", __FILE__, __LINE__);
-    else if (!host_ctl_ready(hc, 0.0)) status = SPCONV_EHIP;
+// Launches k_publish behind the work enqueued so far and waits for its figures.
+template <Publish WHAT = kPublishAll> int read_ctl(const Ctl* ctl, HostResult* res, hipStream_t st) {
+  HostCtl* hc = host_ctl_acquire();
+  if (!hc) return SPCONV_ENOMEM;
+  hc->res.word = hc->res.outputs = hc->res.ready = 0;  // (pinned memory: visible to the kernel launched below)
+  hipLaunchKernelGGL(k_publish<WHAT>, dim3(1), dim3(64), 0, st, ctl, hc->dev);
+  const int status = wait_block(hc, WHAT == kPublishWord ? kWaitWord : WHAT == kPublishOutputs ? kWaitWord | kWaitOutputs : kWaitReady,
+                                hipGetLastError(), st);
+  if (status == SPCONV_OK) {
+    *res = hc->res;
+    if (WHAT == kPublishWord || WHAT == kPublishOutputs) {
+      res->flags = (res->word >> 48) & 0xFFu;
+      res->pairs = res->word & 0xFFFFFFFFFFFFull;
+      res->count = res->outputs & ~kHostReady;
+    }
   }
-  *word = hc->res.word;
   host_ctl_release(hc);
   return status;
 }
@@ -1855,7 +1872,7 @@ int build_submanifold3(spconv_kmap* km, const int4* rows, int64_t N, bool async,
   if (!small) SPC_TRY(dealt.alloc(bk.bytes));
   HostCtl* hc = host_ctl_acquire();
   if (!hc) return SPCONV_ENOMEM;
-  hc->res.word = 0;  // (pinned memory: visible to the kernel launched below)
+  hc->res.word = hc->res.ready = 0;  // (pinned memory: visible to the kernels launched below)
   if (small)
     hipLaunchKernelGGL(k_build_small3, dim3((unsigned)std::min<int64_t>(ceil_div(side.rows_pad, 32), kSmallWgs)), dim3(kSmallThreads),
                        small_lds, st, rows, (int)N, (int)side.rows_pad, own_rows.as<int4>(), side.map.as<int>(),
@@ -1870,7 +1887,9 @@ int build_submanifold3(spconv_kmap* km, const int4* rows, int64_t N, bool async,
     hipLaunchKernelGGL(k_probe_buckets, dim3(1u << bk.log_b), dim3(kBucketThreads), 0, st, entries, starts, flags, bk.dealers, bk.per,
                        bk.log_b, side.map.as<int>(), side.mask.as<unsigned>(), ctl, hc->dev);
   }
-  if (small && async) hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, st, ctl, hc->dev, true);
+  // (a waited build: a kernel of its own reports the end, and once it runs, the stores before it are visible to every stream)
+  if (small) hipLaunchKernelGGL(k_publish<kPublishWord>, dim3(1), dim3(64), 0, st, ctl, hc->dev);
+  else if (!async) hipLaunchKernelGGL(k_publish<kPublishEnd>, dim3(1), dim3(64), 0, st, ctl, hc->dev);
   const bool ok = hipGetLastError() == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
@@ -1885,16 +1904,15 @@ int build_submanifold3(spconv_kmap* km, const int4* rows, int64_t N, bool async,
   km->n_pairs = -1;
   // (ctl_buf returns to the pool here; reuse is ordered behind the probe on this stream)
   if (!async) {
-    // A kernel of its own reports the end: once it runs, the probe's stores are visible to every stream.
-    HostResult h{};
-    const int rc = read_ctl(ctl, &h, st);
+    const int rc = wait_block(hc, small ? kWaitWord : kWaitWord | kWaitReady, hipSuccess, st);
+    const unsigned long long word = hc->res.word;
     km->pending = false;
     km->pending_host = nullptr;
     if (rc != SPCONV_OK) (void)hipStreamSynchronize(st);  // (the probe still writes to hc)
     host_ctl_release(hc);
     SPC_TRY(rc);
-    km->n_pairs = (int64_t)h.pairs;
-    km->build_status = flags_status(h.flags);
+    km->n_pairs = (int64_t)(word & 0xFFFFFFFFFFFFull);
+    km->build_status = flags_status((word >> 48) & 0xFFu);
     SPC_TRY(km->build_status);
   }
   std::swap(km->in_coords.p, own_rows.p);  // P_out == P_in: out_coords stays empty
@@ -1981,7 +1999,7 @@ int shrink_to_outputs(SideMap& side, int V, DevBuf& coarse_rows, const Ctl* ctl,
     std::swap(from[a]->bytes, to[a].bytes);
   }
   HostResult again{};  // (a build that is waited for is complete when it returns)
-  return read_ctl(ctl, &again, st);
+  return read_ctl<kPublishEnd>(ctl, &again, st);
 }
 
 // What a stride-2 build over the box leaves where the box is too large: the caller's rows, the hash table of the coarse points and
@@ -2032,8 +2050,10 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
   // builds are as fast as their launches (2k rows 57 us, with the wait behind the marks 60).
   bool too_large = false;
   auto verdict = [&]() -> int {
-    unsigned long long word = 0;
-    SPC_TRY(wait_word(hc, launched, st, &word));
+    const int status = wait_block(hc, kWaitWord, launched, st);
+    const unsigned long long word = hc->res.word;
+    host_ctl_release(hc);
+    SPC_TRY(status);
     too_large = (word >> 48) & FLAG_BOX;
     return SPCONV_OK;
   };
@@ -2072,8 +2092,7 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
   SPC_TRY(K == 3 ? masks_from_map<27>(map, N, side.mask.as<unsigned>(), ctl, st, true)
                  : masks_from_map<8>(map, N, side.mask.as<unsigned>(), ctl, st, true));
   HostResult h{};
-  SPC_TRY(read_ctl(ctl, &h, st));
-  if (h.entries != h.pairs) h.flags |= FLAG_DUP;  // two rows wrote one entry
+  SPC_TRY(read_ctl<kPublishOutputs>(ctl, &h, st));
   SPC_TRY(flags_status(h.flags));
   km->n_in = N;
   km->n_out = side.rows = (int64_t)h.count;
