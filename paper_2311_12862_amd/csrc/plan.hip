@@ -107,12 +107,13 @@ __global__ void __launch_bounds__(256)
 // hist[workgroup][value], and waits until every workgroup of the launch has done so (all of them
 // are resident: at most kSortMaxWgs workgroups on 256 CUs; the wait is bounded all the same, and a
 // wait that runs out fails the sort).  It then finds its own offsets by summing the rows in front
-// of it (a coalesced read of at most 256 KB, in place of a scan launch) and ranks its items with
+// of it (a coalesced read of at most 768 KB, in place of a scan launch) and ranks its items with
 // ballots as the general sort does.  The first digit's keys come straight from the masks, the last
 // digit writes only the row order.
 constexpr int kSortWg = 2048, kSortWaves = 4, kSortThreads = 64 * kSortWaves;
 constexpr int kSortWave = kSortWg / kSortWaves, kSortSteps = kSortWave / 64;
-constexpr int kSortMaxWgs = 64;
+// (300k rows, three digits: 61 us, with histograms, scans and scatters in launches of their own 87)
+constexpr int kSortMaxWgs = 192;
 constexpr int kSortMaxBits = 10, kSortMaxBins = 1 << kSortMaxBits;
 constexpr unsigned kSortSpinLimit = 1u << 20;  // polls of the arrival counter (about a second)
 // head of the counter buffer: arrive[16 * pass], error at [48]

@@ -276,6 +276,16 @@ def test_sort_invariants_across_the_sizes_that_change_the_sort(sp, target_n):
             _check_order(perm, (mask >> np.uint64(lo)) & np.uint64((1 << (hi - lo)) - 1), len(c))
 
 
+@pytest.mark.parametrize("n", [300_000, 192 * 2048, 192 * 2048 + 1])
+def test_sort_invariants_with_many_workgroups(sp, n):
+    """The few-launch sort with up to 192 workgroups, and the general sort one row beyond."""
+    c = gen.uniform_cloud(n, 150, seed=n)
+    km = sp.build_kmap(coords_dev(c), 3, 1)
+    mask = km.export_mask().cpu().numpy().view(np.uint32).astype(np.uint64)
+    perm = km.export_perm(sp.OP_FWD, _cfg(sp, 1), 0).cpu().numpy()
+    _check_order(perm, mask, n)
+
+
 @pytest.mark.parametrize("kernel", [1, 2])
 @pytest.mark.parametrize("n_split", [1, 2, 3])
 def test_spatial_slabs_in_front_of_the_sort_keys(sp, cloud, kernel, n_split):
