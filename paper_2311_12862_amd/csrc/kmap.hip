@@ -159,10 +159,11 @@ __global__ void __launch_bounds__(256) k_insert_rows(const int4* __restrict__ co
 
 // Coarse coordinates floor(p / s): de-duplicate through a second table, append each
 // new key to ukeys (order arbitrary; sorted afterwards), and reduce OR / AND of the
-// keys so that the host knows which key bytes vary.  Every thread of a workgroup of 256; live: it has a row.
+// keys so that the host knows which key bytes vary.  Every thread of a workgroup; live: it has a row.
+template <int WAVES = 4>  // of the workgroup
 __device__ __forceinline__ void coarse_unique(bool live, int4 c, int stride, unsigned long long* tab, int log_cap,
                                               unsigned long long* __restrict__ ukeys, Ctl* ctl) {
-  __shared__ unsigned long long s_or[4], s_and[4];
+  __shared__ unsigned long long s_or[WAVES], s_and[WAVES];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   bool fresh = false;
   unsigned long long key = 0, k_or = 0, k_and = ~0ull;
@@ -178,7 +179,7 @@ __device__ __forceinline__ void coarse_unique(bool live, int4 c, int stride, uns
     }
   }
   // workgroup-aggregated append: one counter atomic per workgroup, ranks from ballots
-  __shared__ unsigned wave_cnt[4];
+  __shared__ unsigned wave_cnt[WAVES];
   __shared__ unsigned long long block_base;
   const unsigned long long bal = __ballot(fresh);
   if (lane == 0) wave_cnt[wave] = (unsigned)__popcll(bal);
@@ -192,11 +193,13 @@ __device__ __forceinline__ void coarse_unique(bool live, int4 c, int stride, uns
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    const unsigned total = wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3];
+    unsigned total = 0;
+    unsigned long long all_or = 0, all_and = ~0ull;
+    for (int w = 0; w < WAVES; ++w) total += wave_cnt[w], all_or |= s_or[w], all_and &= s_and[w];
     block_base = total ? atomicAdd(&ctl->count, (unsigned long long)total) : 0ull;
     const int slot = (blockIdx.x % kPairSlots) * 16;
-    atomicOr(&ctl->key_or[slot], s_or[0] | s_or[1] | s_or[2] | s_or[3]);
-    atomicAnd(&ctl->key_and[slot], s_and[0] & s_and[1] & s_and[2] & s_and[3]);
+    atomicOr(&ctl->key_or[slot], all_or);
+    atomicAnd(&ctl->key_and[slot], all_and);
   }
   __syncthreads();
   if (fresh) {
@@ -401,26 +404,37 @@ __global__ void __launch_bounds__(256)
 // ---- stride-2 builds over a bit per cell ----
 // The coarse points floor(p / 2) of a scan fill a box of a few hundred cells per row.  One bit per cell, set by the rows, is the
 // de-duplication, the lexicographic sort (the order of the bits) and the look-up table (a point's row is the number of set
-// bits before its own: a prefix per 64-bit word and a population count) at once; nothing is hashed, sorted or probed, and the
-// host waits once, at the end.  Launches: the box, clearing, marking, counting, prefixes (and the presets of
+// bits before its own: a prefix per 32 cells and a population count) at once; nothing is hashed, sorted or probed, and the
+// host waits once, at the end.  The cells are cut into chunks of equal length, the rows dealt to the chunks of their coarse
+// points, and one workgroup per chunk sets its bits in LDS and writes them with their prefixes: nothing is cleared beforehand and no
+// atomic leaves the CU.  Launches: the box, dealing, bits, chunk prefixes (and the presets of
 // the map), the map from the input side (and the coordinates), masks.  Against de-duplication through a hash table, a radix sort and table
-// look-ups, whole builds in us: LiDAR-like scans of 2k rows 71 -> 36, 10k 80 -> 40, 30k 89 -> 46, 100k 109 -> 64, 200k (127k
-// outputs) 178 -> 79, 400k 227 -> 124; a room of 300k 135 -> 96.  What is left is launches of 4 to 5 us and the marks: an atomic
-// per row, which the memory side takes at 10 per ns (200k rows: 20 us of the 69 of kernels).
-// A box of more than kCellsPerRow cells a row (a scan of 5 cm voxels has about 450) is left to the table: the clearing launch
-// empties one in the bitmap's place, the marking launch fills it, and the host, which reads the box's verdict behind that, goes on
+// look-ups, and with bits in memory (cleared, marked by an atomic per row, which the memory side takes at 10 per ns, counted), whole
+// 3x3x3 builds in us: LiDAR-like scans of 2k rows 71, 34 -> 35, 10k 80, 36 -> 36, 30k 89, 42 -> 38, 100k 109, 62 -> 49, 200k (127k
+// outputs) 178, 78 -> 64, 400k 227, 118 -> 88; a room of 60k 51 -> 41, 300k 135, 101 -> 79.
+// A box of more than kCellsPerRow cells a row (a scan of 5 cm voxels has about 450) is left to the table: the dealing launch
+// empties one in the bitmap's place, the launch behind it fills it, and the host, which reads the box's verdict behind that, goes on
 // with the sort.  Whole builds of points spread over 60,000 cells an axis, us, all through the table and so: 2k rows 150, 152;
 // 20k 218, 219; 100k 253, 255; 200k 290, 289.
 constexpr int kBoxBlocks = 256;
 constexpr int kCellsPerRow = 2048;
-constexpr int kChunkWords = 2048;  // 64-bit words per workgroup and step
-constexpr int64_t kMaxBoxWords = 1ll << 25;
+constexpr int64_t kMaxBoxWords = 1ll << 26;
+constexpr int kBoxDealers = 256, kBoxDealThreads = 512;  // workgroups of k_box_deal at most: one per thread of k_box_bits
+constexpr int kMaxChunks = 2048;
+constexpr int kLdsWords = 8192;    // words of a chunk that are in LDS at a time
+constexpr int kBitsThreads = 1024;  // (256: the chunks at a scanner's place, of thousands of rows, took 22 us)
 
 struct Box {
   int lo[4];         // of (b, x, y, z)
   unsigned span[4];  // (up to 65536 each)
-  unsigned words;    // 64-bit words of the bitmap; 0: nothing to do
+  unsigned words;    // of 32 cells; 0: nothing to do
+  unsigned shift;    // a chunk is 2^shift words
   unsigned flags;
+};
+
+// 32 cells: which are there, and how many are before them in their chunk.
+struct __align__(8) Cells {
+  unsigned bits, before;
 };
 
 __device__ __forceinline__ unsigned cell_of(const Box& box, int b, int x, int y, int z) {  // (in the box: below 2^31)
@@ -470,28 +484,35 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// Every workgroup works out the box; the bitmap is cleared as far as it reaches; the first one clears the control block,
-// leaves the box for the launches behind, and its flags for the host (the word of host).  Where the box is too large, table_slots
-// empty slots of the hash tables take the bitmap's place.
-__global__ void __launch_bounds__(256)
-    k_box_clear(const int* __restrict__ partial, int n_partial, long long max_words, ulonglong2* __restrict__ bits, long long table_slots,
-                Box* box_out, Ctl* ctl, HostResult* host) {
+// Every workgroup works out the box; the first one clears the control block, leaves the box for the launches behind, and its flags
+// for the host (the word of host).  Workgroup w then deals rows [w per, w per + per): their cells, chunk by chunk, from entries + w per
+// on; starts[w][chunk] says where each chunk begins.  Where the box is too large, table_slots empty slots of the hash tables take the
+// bitmap's place.
+__global__ void __launch_bounds__(kBoxDealThreads)
+    k_box_deal(const int* __restrict__ partial, int n_partial, long long max_words, const int4* __restrict__ coords, int n, int per, int chunks,
+               unsigned* __restrict__ entries, unsigned* __restrict__ starts, ulonglong2* __restrict__ table, long long table_slots,
+               Box* box_out, Ctl* ctl, HostResult* host) {
+  constexpr int U = 2, kWaves = kBoxDealThreads / 64;
   __shared__ int red[4][9];
+  __shared__ unsigned place[kMaxChunks], wave_sum[kWaves];
   __shared__ Box s_box;
-  const int t = threadIdx.x;
-  int v[9];  // (kBoxBlocks == 256 partials at most: one per thread)
+  const int t = threadIdx.x, lane = t & 63, wib = t >> 6, w = blockIdx.x;
+  if (t < 256) {
+    int v[9];  // (kBoxBlocks == 256 partials at most: one per thread)
 #pragma unroll
-  for (int a = 0; a < 9; ++a)
-    v[a] = t < n_partial ? partial[t * 9 + a] : a < 4 ? 0x7FFFFFFF : a < 8 ? (int)0x80000000 : 0;
+    for (int a = 0; a < 9; ++a)
+      v[a] = t < n_partial ? partial[t * 9 + a] : a < 4 ? 0x7FFFFFFF : a < 8 ? (int)0x80000000 : 0;
 #pragma unroll
-  for (int a = 0; a < 9; ++a)
-    for (int o = 32; o > 0; o >>= 1) {
-      const int w = __shfl_xor(v[a], o);
-      v[a] = a < 4 ? min(v[a], w) : a < 8 ? max(v[a], w) : v[a] | w;
-    }
-  if ((t & 63) == 0)
+    for (int a = 0; a < 9; ++a)
+      for (int o = 32; o > 0; o >>= 1) {
+        const int x = __shfl_xor(v[a], o);
+        v[a] = a < 4 ? min(v[a], x) : a < 8 ? max(v[a], x) : v[a] | x;
+      }
+    if (lane == 0)
 #pragma unroll
-    for (int a = 0; a < 9; ++a) red[t >> 6][a] = v[a];
+      for (int a = 0; a < 9; ++a) red[wib][a] = v[a];
+  }
+  for (int i = t; i < kMaxChunks; i += kBoxDealThreads) place[i] = 0;
   __syncthreads();
   if (t == 0) {
     Box b;
@@ -505,24 +526,22 @@ __global__ void __launch_bounds__(256)
       b.span[a] = lo <= hi ? (unsigned)(hi - lo) + 1u : 0u;  // (no valid row: an empty box)
       cells = cells > (1ull << 40) ? cells : cells * b.span[a];
     }
-    const unsigned long long words = (cells + 63) / 64;
+    const unsigned long long words = (cells + 31) / 32;
     if (words > (unsigned long long)max_words) b.flags |= (unsigned)FLAG_BOX;
     b.words = words > (unsigned long long)max_words ? 0u : (unsigned)words;
+    b.shift = 2;  // (whole fours: k_box_bits writes them)
+    while (((unsigned long long)chunks << b.shift) < b.words) ++b.shift;
     s_box = b;
-    if (blockIdx.x == 0) {
+    if (w == 0) {
       *box_out = b;
       __hip_atomic_store(&host->word, kHostReady | ((unsigned long long)b.flags << 48), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
   __syncthreads();
-  const long long pairs_of_words = ((long long)s_box.words + 1) / 2;  // (the buffer holds an even number)
-  const bool table = s_box.flags & (unsigned)FLAG_BOX;
-  const unsigned long long fill = table ? kEmpty : 0ull;
-  const long long fills = table ? table_slots : pairs_of_words;
-  for (long long i = (long long)blockIdx.x * 256 + t; i < fills; i += (long long)gridDim.x * 256) bits[i] = make_ulonglong2(fill, fill);
-  if (blockIdx.x == 0) {
+  const Box box = s_box;
+  if (w == 0) {
     if (t == 0) {
-      ctl->flags = s_box.flags & ~(unsigned)FLAG_BOX;
+      ctl->flags = box.flags & ~(unsigned)FLAG_BOX;
       ctl->count = 0;
       ctl->tick_top = 0;
     }
@@ -533,128 +552,209 @@ __global__ void __launch_bounds__(256)
       ctl->key_and[t * 16] = ~0ull;
     }
   }
-}
-
-// The marks; where the box is too large, the coarse points go through the table instead (log_cap 0: it does not fit there).
-__global__ void __launch_bounds__(256)
-    k_box_mark(const int4* __restrict__ coords, int n, const Box* __restrict__ box_in, unsigned* __restrict__ bits, int log_cap,
-               unsigned long long* __restrict__ ukeys, Ctl* ctl) {
-  const Box box = *box_in;
-  const int j = blockIdx.x * 256 + threadIdx.x;
   if (box.flags & (unsigned)FLAG_BOX) {
-    if (log_cap) coarse_unique(j < n, j < n ? coords[j] : make_int4(-1, 0, 0, 0), 2, reinterpret_cast<unsigned long long*>(bits), log_cap, ukeys, ctl);
+    for (long long i = (long long)w * kBoxDealThreads + t; i < table_slots; i += (long long)gridDim.x * kBoxDealThreads)
+      table[i] = make_ulonglong2(kEmpty, kEmpty);
     return;
   }
-  if (j >= n || !box.words) return;
-  const int4 c = coords[j];
-  if (!coord_ok(c.x, c.y, c.z, c.w)) return;
-  const unsigned cell = cell_of(box, c.x, c.y >> 1, c.z >> 1, c.w >> 1);
-  atomicOr(&bits[cell >> 5], 1u << (cell & 31));
-}
-
-// totals[chunk] = set bits of kChunkWords words
-__global__ void __launch_bounds__(256)
-    k_box_count(const Box* __restrict__ box_in, const unsigned long long* __restrict__ bits, unsigned* __restrict__ totals) {
-  __shared__ unsigned red[4];
-  const unsigned words = box_in->words, chunks = (words + kChunkWords - 1) / kChunkWords;
-  for (unsigned c = blockIdx.x; c < chunks; c += gridDim.x) {
-    unsigned long long w[kChunkWords / 256];
+  const int first = (int)min((long long)w * per, (long long)n), last = (int)min((long long)first + per, (long long)n);
+  auto visit = [&](auto f) {
+    for (long long r0 = first + t; r0 < last; r0 += U * kBoxDealThreads) {
+      int4 c[U];
 #pragma unroll
-    for (int i = 0; i < kChunkWords / 256; ++i) {
-      const unsigned at = c * kChunkWords + i * 256 + threadIdx.x;
-      w[i] = at < words ? bits[at] : 0ull;
+      for (int u = 0; u < U; ++u) c[u] = r0 + u * kBoxDealThreads < last ? coords[r0 + u * kBoxDealThreads] : make_int4(-1, 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (r0 + u * kBoxDealThreads < last && coord_ok(c[u].x, c[u].y, c[u].z, c[u].w))
+          f(cell_of(box, c[u].x, c[u].y >> 1, c[u].z >> 1, c[u].w >> 1));
     }
-    unsigned sum = 0;
-#pragma unroll
-    for (int i = 0; i < kChunkWords / 256; ++i) sum += (unsigned)__popcll(w[i]);
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
-    __syncthreads();
-    if (threadIdx.x == 0) totals[c] = red[0] + red[1] + red[2] + red[3];
-    __syncthreads();
-  }
-}
-
-// The prefix of every word, and the presets of the map (rows up to the padding) and of the padding's masks.  A workgroup
-// takes consecutive chunks; it adds up the totals before them itself.
-__global__ void __launch_bounds__(256)
-    k_box_prefix(const Box* __restrict__ box_in, const unsigned long long* __restrict__ bits, const unsigned* __restrict__ totals,
-               unsigned* __restrict__ prefix, int V, uint4* __restrict__ map, unsigned* __restrict__ mask, Ctl* ctl) {
-  __shared__ unsigned s_before[4], s_all[4], s_wave[4];
-  const unsigned words = box_in->words, chunks = (words + kChunkWords - 1) / kChunkWords;
-  const unsigned per = (chunks + gridDim.x - 1) / gridDim.x, c0 = blockIdx.x * per, c1 = min(chunks, c0 + per);
-  const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
-  unsigned before = 0, all = 0;
-  for (unsigned i0 = 0; i0 < chunks; i0 += 8 * 256) {
-    unsigned v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const unsigned i = i0 + u * 256 + threadIdx.x;
-      v[u] = i < chunks ? totals[i] : 0u;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      all += v[u];
-      if (i0 + u * 256 + threadIdx.x < c0) before += v[u];
-    }
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    before += __shfl_xor(before, o);
-    all += __shfl_xor(all, o);
-  }
-  if (lane == 0) s_before[wib] = before, s_all[wib] = all;
+  };
+  const unsigned to_chunk = 5 + box.shift;
+  visit([&](unsigned cell) { atomicAdd(&place[cell >> to_chunk], 1u); });
   __syncthreads();
-  unsigned base = s_before[0] + s_before[1] + s_before[2] + s_before[3];
-  const unsigned total = s_all[0] + s_all[1] + s_all[2] + s_all[3];
-  if (blockIdx.x == 0 && threadIdx.x == 0 && words) ctl->count = total;  // (else: of the table's points, or none)
-  constexpr int W = kChunkWords / 256;  // words per lane: a wave owns 64 * W consecutive ones
-  for (unsigned c = c0; c < c1; ++c) {
-    const unsigned first = c * kChunkWords + wib * (64 * W);
-    unsigned long long w[W];
+  constexpr int S = kMaxChunks / kBoxDealThreads;  // counts -> first places, four per thread
+  static_assert(S == 4, "");
+  const uint4 v = *reinterpret_cast<const uint4*>(place + t * S);
+  const unsigned mine = v.x + v.y + v.z + v.w;
+  unsigned incl = mine;
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned up = __shfl_up(incl, o);
+    if (lane >= o) incl += up;
+  }
+  if (lane == 63) wave_sum[wib] = incl;
+  __syncthreads();
+  unsigned at = incl - mine, all = 0;
 #pragma unroll
-    for (int i = 0; i < W; ++i) {
-      const unsigned at = first + i * 64 + lane;
-      w[i] = at < words ? bits[at] : 0ull;
-    }
-    unsigned mine[W], run = 0;  // set bits of the wave before this lane's word
-#pragma unroll
-    for (int i = 0; i < W; ++i) {
-      const unsigned cnt = (unsigned)__popcll(w[i]);
-      unsigned incl = cnt;
-      for (int o = 1; o < 64; o <<= 1) {
-        const unsigned up = __shfl_up(incl, o);
-        if (lane >= o) incl += up;
+  for (int i = 0; i < kWaves; ++i) {
+    if (i < wib) at += wave_sum[i];
+    all += wave_sum[i];
+  }
+  *reinterpret_cast<uint4*>(place + t * S) = make_uint4(at, at + v.x, at + v.x + v.y, at + v.x + v.y + v.z);
+  __syncthreads();
+  unsigned* const my_starts = starts + (long long)w * (chunks + 1);
+  for (int i = t; i < chunks; i += kBoxDealThreads) my_starts[i] = place[i];
+  if (t == 0) my_starts[chunks] = all;
+  __syncthreads();
+  unsigned* const my_entries = entries + (long long)w * per;
+  visit([&](unsigned cell) { my_entries[atomicAdd(&place[cell >> to_chunk], 1u)] = cell; });
+}
+
+// One workgroup per chunk: its bits in LDS, from there with their prefixes to memory; totals[chunk] = set bits.  A chunk of more than
+// kLdsWords (a sparse box) takes rounds.  Where the box is too large, the coarse points go through the table instead (log_cap 0: it
+// does not fit there).
+__global__ void __launch_bounds__(kBitsThreads)
+    k_box_bits(const Box* __restrict__ box_in, const unsigned* __restrict__ entries, const unsigned* __restrict__ starts, int dealers,
+               int per, Cells* __restrict__ cells, unsigned* __restrict__ totals, const int4* __restrict__ coords, int n, int log_cap,
+               unsigned long long* __restrict__ table, unsigned long long* __restrict__ ukeys, Ctl* ctl) {
+  __shared__ __align__(16) unsigned bits[kLdsWords];
+  constexpr int kWaves = kBitsThreads / 64, U = 4;
+  __shared__ int before[kBoxDealers + 1], wave_sum[kWaves];
+  __shared__ unsigned src[kBoxDealers], wave_bits[kWaves];
+  const Box box = *box_in;
+  const int t = threadIdx.x, lane = t & 63, wib = t >> 6;
+  if (box.flags & (unsigned)FLAG_BOX) {
+    if (log_cap) {
+      const int each = (long long)gridDim.x * 256 >= n ? 256 : kBitsThreads;  // (few rows: to as many workgroups as there are)
+      for (long long j0 = (long long)blockIdx.x * each; j0 < n; j0 += (long long)gridDim.x * each) {
+        const long long j = t < each ? j0 + t : n;
+        __syncthreads();
+        coarse_unique<kWaves>(j < n, j < n ? coords[j] : make_int4(-1, 0, 0, 0), 2, table, log_cap, ukeys, ctl);
       }
-      mine[i] = run + incl - cnt;
-      run += __shfl(incl, 63);
     }
+    return;
+  }
+  const unsigned lo = blockIdx.x << box.shift, hi = min(box.words, lo + (1u << box.shift));
+  if (lo >= box.words) {
+    if (t == 0) totals[blockIdx.x] = 0;
+    return;
+  }
+  int count = 0;
+  if (t < dealers) {
+    const unsigned* const s = starts + (long long)t * (gridDim.x + 1) + blockIdx.x;
+    const unsigned a = s[0], b = s[1];
+    src[t] = a;
+    count = (int)(b - a);
+  }
+  int incl = count;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int up = __shfl_up(incl, o);
+    if (lane >= o) incl += up;
+  }
+  if (lane == 63) wave_sum[wib] = incl;
+  __syncthreads();
+  if (t < kBoxDealers) {
+    for (int i = 0; i < wib; ++i) incl += wave_sum[i];
+    before[t + 1] = incl;
+    if (t == 0) before[0] = 0;
+  }
+  unsigned total = 0;
+  for (unsigned w0 = lo; w0 < hi; w0 += kLdsWords) {
+    const int here = (int)min((unsigned)kLdsWords, hi - w0);
+    for (int i = t; i < (here + 3) / 4; i += kBitsThreads) reinterpret_cast<uint4*>(bits)[i] = make_uint4(0, 0, 0, 0);
     __syncthreads();
-    if (lane == 0) s_wave[wib] = run;
-    __syncthreads();
-    unsigned at0 = base;
-    for (int i = 0; i < wib; ++i) at0 += s_wave[i];
-    base += s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
+    const int rows = before[kBoxDealers];
+    for (int i0 = t; i0 < rows; i0 += U * kBitsThreads) {
+      int w[U] = {};  // the dealers: before[w] <= i < before[w + 1]
 #pragma unroll
-    for (int i = 0; i < W; ++i) {
-      const unsigned at = first + i * 64 + lane;
-      if (at < words) prefix[at] = at0 + mine[i];
+      for (int o = kBoxDealers / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (before[w[u] + o] <= i0 + u * kBitsThreads) w[u] += o;
+      unsigned cell[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * kBitsThreads;
+        cell[u] = i < rows ? entries[(long long)w[u] * per + src[w[u]] + (i - before[w[u]])] : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const unsigned at = (cell[u] >> 5) - w0;
+        if (i0 + u * kBitsThreads < rows && at < (unsigned)here) atomicOr(&bits[at], 1u << (cell[u] & 31));
+      }
     }
+    __syncthreads();
+    // a wave takes consecutive words, 256 at a time, four to a lane
+    const int share = ((here + kWaves - 1) / kWaves + 255) / 256 * 256, from = min(here, wib * share), to = min(here, from + share);
+    unsigned sum = 0;
+    for (int i = from + 4 * lane; i < to; i += 256) {
+      const uint4 v = *reinterpret_cast<const uint4*>(bits + i);  // (the words up to a multiple of four are zeros)
+      sum += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+    }
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    if (lane == 0) wave_bits[wib] = sum;
+    __syncthreads();
+    unsigned run = total;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) {
+      if (i < wib) run += wave_bits[i];
+      total += wave_bits[i];
+    }
+    for (int i0 = from; i0 < to; i0 += 256) {
+      const int i = i0 + 4 * lane;
+      const uint4 v = i < to ? *reinterpret_cast<const uint4*>(bits + i) : make_uint4(0, 0, 0, 0);
+      const unsigned n0 = __popc(v.x), n1 = n0 + __popc(v.y), n2 = n1 + __popc(v.z), n3 = n2 + __popc(v.w);
+      unsigned in = n3;
+      for (int o = 1; o < 64; o <<= 1) {
+        const unsigned up = __shfl_up(in, o);
+        if (lane >= o) in += up;
+      }
+      const unsigned b = run + in - n3;
+      if (i < to) {  // (the buffer holds whole fours)
+        uint4* const dst = reinterpret_cast<uint4*>(cells + w0 + i);
+        dst[0] = make_uint4(v.x, b, v.y, b + n0);
+        dst[1] = make_uint4(v.z, b + n1, v.w, b + n2);
+      }
+      run += __shfl(in, 63);
+    }
+    __syncthreads();
+  }
+  if (t == 0) totals[blockIdx.x] = total;
+}
+
+// base[chunk] = set bits before the chunk, and the presets of the map (rows up to the padding) and of the padding's masks.
+__global__ void __launch_bounds__(256)
+    k_box_base(const Box* __restrict__ box_in, const unsigned* __restrict__ totals, int chunks, unsigned* __restrict__ base, int V,
+               uint4* __restrict__ map, unsigned* __restrict__ mask, Ctl* ctl) {
+  constexpr int S = kMaxChunks / 256;
+  __shared__ unsigned wave_sum[4];
+  const int t = threadIdx.x, lane = t & 63, wib = t >> 6;
+  const unsigned words = box_in->words;
+  unsigned v[S], mine = 0;
+#pragma unroll
+  for (int i = 0; i < S; ++i) v[i] = words && t * S + i < chunks ? totals[t * S + i] : 0u;  // (no box: no totals)
+#pragma unroll
+  for (int i = 0; i < S; ++i) mine += v[i];
+  unsigned incl = mine;
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned up = __shfl_up(incl, o);
+    if (lane >= o) incl += up;
+  }
+  if (lane == 63) wave_sum[wib] = incl;
+  __syncthreads();
+  const unsigned total = wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3];
+  if (blockIdx.x == 0) {
+    unsigned at = incl - mine;
+    for (int i = 0; i < wib; ++i) at += wave_sum[i];
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+      if (t * S + i < chunks) base[t * S + i] = at;
+      at += v[i];
+    }
+    if (t == 0 && words) ctl->count = total;  // (else: of the table's points, or none)
   }
   const unsigned rows_pad = (total + kRowPad - 1) / kRowPad * kRowPad;
   const long long vecs = (long long)rows_pad * V / 4;
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < vecs; i += (long long)gridDim.x * 256)
-    map[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
-  if (blockIdx.x == 0 && total + threadIdx.x < rows_pad) mask[total + threadIdx.x] = 0u;
+  for (long long i = (long long)blockIdx.x * 256 + t; i < vecs; i += (long long)gridDim.x * 256) map[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+  if (blockIdx.x == 0 && total + t < rows_pad) mask[total + t] = 0u;
 }
 
 // Row of a coarse point, or -1.
-__device__ __forceinline__ int box_find(const Box& box, const unsigned long long* bits, const unsigned* prefix, int b, int x, int y, int z) {
+__device__ __forceinline__ int box_find(const Box& box, const Cells* cells, const unsigned* base, int b, int x, int y, int z) {
   if ((unsigned)(x - box.lo[1]) >= box.span[1] || (unsigned)(y - box.lo[2]) >= box.span[2] || (unsigned)(z - box.lo[3]) >= box.span[3]) return -1;
   const unsigned cell = cell_of(box, b, x, y, z);
-  const unsigned long long w = bits[cell >> 6];
-  const unsigned before = prefix[cell >> 6];
-  const unsigned long long bit = 1ull << (cell & 63);
-  return w & bit ? (int)(before + (unsigned)__popcll(w & (bit - 1))) : -1;
+  const Cells w = cells[cell >> 5];
+  const unsigned before = base[cell >> (5 + box.shift)], bit = 1u << (cell & 31);
+  return w.bits & bit ? (int)(before + w.before + (unsigned)__popc(w.bits & (bit - 1))) : -1;
 }
 
 // The map from the input side (see k_scatter_down3), and the coarse points: every input meets the output floor(p / 2) (K = 2:
@@ -662,8 +762,8 @@ __device__ __forceinline__ int box_find(const Box& box, const unsigned long long
 // many stand in one word).
 template <int K>
 __global__ void __launch_bounds__(256)
-    k_box_scatter(const int4* __restrict__ rows, int n_rows, const Box* __restrict__ box_in, const unsigned long long* __restrict__ bits,
-                  const unsigned* __restrict__ prefix, int* __restrict__ map, int4* __restrict__ coarse, Ctl* ctl) {
+    k_box_scatter(const int4* __restrict__ rows, int n_rows, const Box* __restrict__ box_in, const Cells* __restrict__ cells,
+                  const unsigned* __restrict__ base, int* __restrict__ map, int4* __restrict__ coarse, Ctl* ctl) {
   __shared__ unsigned wave_pairs[4];
   constexpr int LPR = K == 3 ? 8 : 1, V = K * K * K;
   const Box box = *box_in;
@@ -685,7 +785,7 @@ __global__ void __launch_bounds__(256)
       k = k * K + (K == 3 ? d + 1 : d);
     }
     if (ok) {
-      const int n = box_find(box, bits, prefix, c.x, q[0], q[1], q[2]);
+      const int n = box_find(box, cells, base, c.x, q[0], q[1], q[2]);
       if (n >= 0) {
         map[(long long)n * V + k] = (int)row;
         if (cand == 0) coarse[n] = make_int4(c.x, q[0], q[1], q[2]);
@@ -2010,32 +2110,37 @@ struct CoarseTable {
 };
 
 // Stride-2 builds (K = 2, 3) over a bit per cell of the coarse points' box; kRetryTable where the box is too large (with what the
-// table needs, see CoarseTable), or the memory does not suffice (up to 384 bytes a row for bits and prefixes, and tables for
+// table needs, see CoarseTable), or the memory does not suffice (up to 520 bytes a row for bits and prefixes, and tables for
 // N outputs: the hash table and tables for the outputs that there are need less).
 int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t st, CoarseTable* fallback) {
   const int V = K * K * K;
-  const int64_t max_words = std::min<int64_t>(std::max<int64_t>(N * (kCellsPerRow / 64), 1 << 14), kMaxBoxWords);
-  const int64_t max_chunks = ceil_div(max_words, kChunkWords);
+  const int64_t max_words = std::min<int64_t>(std::max<int64_t>(N * (kCellsPerRow / 32), 1 << 15), kMaxBoxWords);
+  // about 400 rows to a chunk; dealers of 512 rows and more
+  int chunks = 64;
+  while (chunks < kMaxChunks && (int64_t)chunks * 400 < N) chunks *= 2;
+  const int per = (int)std::max<int64_t>(round_up(ceil_div(N, kBoxDealers), kBoxDealThreads), kBoxDealThreads);
+  const int dealers = (int)ceil_div(N, per);
   DevBuf coarse_rows, small;
-  DevBuf &ctl_buf = fallback->ctl, &own_rows = fallback->rows, &bits = fallback->slots, &prefix = fallback->keys;
+  DevBuf &ctl_buf = fallback->ctl, &own_rows = fallback->rows, &cells = fallback->slots, &keys = fallback->keys;
   // sized for as many outputs as inputs: their number is read at the end
   SideMap& side = km->out_side;
   const int64_t most = round_up(N, kRowPad);
   const size_t partial_bytes = (size_t)kBoxBlocks * 9 * sizeof(int);
   if (ctl_buf.alloc(sizeof(Ctl)) != SPCONV_OK || own_rows.alloc((size_t)N * 16) != SPCONV_OK ||
       coarse_rows.alloc((size_t)N * 16) != SPCONV_OK ||
-      small.alloc(sizeof(Box) + partial_bytes + (size_t)max_chunks * sizeof(unsigned)) != SPCONV_OK ||
-      bits.alloc((size_t)(max_words + 1) * 8) != SPCONV_OK || prefix.alloc((size_t)max_words * 4) != SPCONV_OK ||
+      small.alloc(sizeof(Box) + partial_bytes + (2 * (size_t)chunks + (size_t)dealers * (chunks + 1)) * sizeof(unsigned)) != SPCONV_OK ||
+      cells.alloc((size_t)max_words * sizeof(Cells)) != SPCONV_OK || keys.alloc((size_t)N * 8) != SPCONV_OK ||
       side.map.alloc((size_t)most * V * sizeof(int)) != SPCONV_OK || side.mask.alloc((size_t)most * sizeof(unsigned)) != SPCONV_OK)
     return kRetryTable;
   Ctl* ctl = ctl_buf.as<Ctl>();
-  // (two tables in the place of the bits, the keys in that of the prefixes: too large from two million rows on)
+  // (two tables in the place of the cells, the keys in that of the rows' cells: too large from two million rows on)
   const int table_cap = log2_capacity(N);
   const long long table_slots = (K == 2 ? 2ll : 1ll) << table_cap;
-  const bool table_fits = table_slots * 16 <= max_words * 8 && N * 8 <= max_words * 4;
+  const bool table_fits = table_slots * 16 <= max_words * 8 / 2;
   Box* box = small.as<Box>();
   int* partial = reinterpret_cast<int*>(box + 1);
   unsigned* totals = reinterpret_cast<unsigned*>(small.as<char>() + sizeof(Box) + partial_bytes);
+  unsigned *base = totals + chunks, *starts = base + chunks;
   int* map = side.map.as<int>();
   const unsigned n_partial = (unsigned)std::min<int64_t>(ceil_div(N, 1024), kBoxBlocks);
   HostCtl* hc = host_ctl_acquire();
@@ -2060,19 +2165,18 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
   const bool early = N >= 16384;
   hipLaunchKernelGGL(k_box_bounds, dim3(n_partial), dim3(256), 0, st, rows, (int)N, own_rows.as<int4>(), partial);
   check();
-  hipLaunchKernelGGL(k_box_clear, dim3((unsigned)std::min<int64_t>(ceil_div(max_words, 2048), 1024)), dim3(256), 0, st, partial,
-                     (int)n_partial, (long long)max_words, bits.as<ulonglong2>(), table_fits ? table_slots : 0ll, box, ctl, hc->dev);
+  hipLaunchKernelGGL(k_box_deal, dim3((unsigned)dealers), dim3(kBoxDealThreads), 0, st, partial, (int)n_partial, (long long)max_words, rows,
+                     (int)N, per, chunks, keys.as<unsigned>(), starts, cells.as<ulonglong2>(), table_fits ? table_slots : 0ll, box, ctl,
+                     hc->dev);
   check();
-  hipLaunchKernelGGL(k_box_mark, dim3(blocks_for(N, 256)), dim3(256), 0, st, rows, (int)N, box, bits.as<unsigned>(),
-                     table_fits ? table_cap : 0, prefix.as<unsigned long long>(), ctl);
+  hipLaunchKernelGGL(k_box_bits, dim3((unsigned)chunks), dim3(kBitsThreads), 0, st, box, keys.as<unsigned>(), starts, dealers, per,
+                     cells.as<Cells>(), totals, rows, (int)N, table_fits ? table_cap : 0, cells.as<unsigned long long>(),
+                     keys.as<unsigned long long>(), ctl);
   check();
   if (early) SPC_TRY(verdict());
   if (!too_large) {
-    const dim3 chunk_grid((unsigned)std::min<int64_t>(max_chunks, 1024));
-    hipLaunchKernelGGL(k_box_count, chunk_grid, dim3(256), 0, st, box, bits.as<unsigned long long>(), totals);
-    check();
-    hipLaunchKernelGGL(k_box_prefix, chunk_grid, dim3(256), 0, st, box, bits.as<unsigned long long>(), totals, prefix.as<unsigned>(),
-                       V, side.map.as<uint4>(), side.mask.as<unsigned>(), ctl);
+    hipLaunchKernelGGL(k_box_base, dim3((unsigned)std::min<int64_t>(ceil_div(N * V, 8192), 1024)), dim3(256), 0, st, box, totals, chunks,
+                       base, V, side.map.as<uint4>(), side.mask.as<unsigned>(), ctl);
     check();
     if (!early) SPC_TRY(verdict());
   }
@@ -2083,11 +2187,9 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
   SPC_HIP(launched);
   const dim3 scatter_grid(blocks_for(K == 3 ? N * 8 : N, 256));
   if (K == 3)
-    hipLaunchKernelGGL(k_box_scatter<3>, scatter_grid, dim3(256), 0, st, rows, (int)N, box, bits.as<unsigned long long>(),
-                       prefix.as<unsigned>(), map, coarse_rows.as<int4>(), ctl);
+    hipLaunchKernelGGL(k_box_scatter<3>, scatter_grid, dim3(256), 0, st, rows, (int)N, box, cells.as<Cells>(), base, map, coarse_rows.as<int4>(), ctl);
   else
-    hipLaunchKernelGGL(k_box_scatter<2>, scatter_grid, dim3(256), 0, st, rows, (int)N, box, bits.as<unsigned long long>(),
-                       prefix.as<unsigned>(), map, coarse_rows.as<int4>(), ctl);
+    hipLaunchKernelGGL(k_box_scatter<2>, scatter_grid, dim3(256), 0, st, rows, (int)N, box, cells.as<Cells>(), base, map, coarse_rows.as<int4>(), ctl);
   SPC_LAUNCH_CHECK();
   SPC_TRY(K == 3 ? masks_from_map<27>(map, N, side.mask.as<unsigned>(), ctl, st, true)
                  : masks_from_map<8>(map, N, side.mask.as<unsigned>(), ctl, st, true));

@@ -514,9 +514,11 @@ def test_stride2_masks_by_rows_of_a_wave(sp, K, n_coarse):
 @pytest.mark.parametrize("K", [2, 3])
 @pytest.mark.parametrize("n,span,lo", [
     (1, (1, 1, 1), 0), (3, (2, 1, 3), -5), (64, (1, 1, 64), -1), (65, (1, 1, 130), 7), (900, (40, 1, 33), -21),
-    (5000, (256, 64, 8), 1),           # exactly one chunk of 2048 words, and a part of another
+    (5000, (256, 64, 8), 1),           # chunks of 16 words
     (5000, (258, 66, 10), -3),
-    (80_000, (1016, 1010, 1160), 0),   # more chunks than workgroups: several per workgroup
+    (26_000, (64, 64, 8), 3),          # chunks of four words, hundreds of rows each; most chunks are beyond the box
+    (30_000, (700, 900, 500), -9),     # chunks of more words than LDS holds, by a part of a round, and by several
+    (80_000, (1016, 1010, 1160), 0),
     (40, (60_000, 60_000, 60_000), -30_000), (2000, (1, 65_000, 64_000), -32_768),  # boxes that are left to the table: one
     (16_383, (3000, 3000, 3000), -7), (16_385, (3000, 3000, 3000), 9),              # or many workgroups, the verdict taken late or early,
     (100_000, (4000, 5000, 700), -2000), (150_000, (9000, 9000, 500), 1)])          # the one-launch and the general sort
