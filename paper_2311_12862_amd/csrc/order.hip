@@ -11,6 +11,7 @@
 // of 128 (100k-voxel scan; 300k-voxel room): this order 1.28, 1.55, 1.71; 1.04, 1.12, 1.21; the full sort by the plain
 // mask 1.22, 1.50, 1.74; 1.02, 1.04, 1.06; map order 4.37, 5.64, 5.85; 2.44, 2.76, 2.78.
 #include "common.h"
+#include "lds_tiles.h"
 
 #include <algorithm>
 
@@ -155,12 +156,13 @@ __global__ void __launch_bounds__(kScatterThreads)
     if (valid && rank == 0) off[wib][bkt] = peers;
     __syncthreads();
     if (t < kBuckets) {
-      unsigned at = place[t];
+      unsigned at = place[t], c[kScatterWaves];  // (read before the first is written: else each read waits for the write before it)
+#pragma unroll
+      for (int w = 0; w < kScatterWaves; ++w) c[w] = off[w][t];
 #pragma unroll
       for (int w = 0; w < kScatterWaves; ++w) {
-        const unsigned c = off[w][t];
         off[w][t] = at;
-        at += c;
+        at += c[w];
       }
       place[t] = at;
     }
@@ -180,7 +182,7 @@ __global__ void __launch_bounds__(kLocalThreads)
                   unsigned* __restrict__ blkmask) {
   __shared__ int row_of[kChunk];            // by place within the bucket order
   __shared__ unsigned comp[kChunk];         // key << 11 | place
-  __shared__ unsigned off[kLocalWaves][kDigits];
+  __shared__ __align__(8) unsigned off[kLocalWaves][kDigits];
   __shared__ int src_of[kChunk];            // rows in the final order
   const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
   const long long base = (long long)blockIdx.x * kChunk;
@@ -210,23 +212,29 @@ __global__ void __launch_bounds__(kLocalThreads)
     }
     __syncthreads();
     if (threadIdx.x < 64) {  // first places: digits in order, within a digit the waves in order; two digits per lane
-      unsigned c0 = 0, c1 = 0;
+      unsigned c[2][kLocalWaves], both = 0;  // (read before the first is written: else each read waits for the write before it)
 #pragma unroll
-      for (int w = 0; w < kLocalWaves; ++w) c0 += off[w][2 * lane], c1 += off[w][2 * lane + 1];
-      unsigned incl = c0 + c1;
+      for (int w = 0; w < kLocalWaves; ++w) {
+        const uint2 v = *reinterpret_cast<const uint2*>(&off[w][2 * lane]);
+        c[0][w] = v.x, c[1][w] = v.y;
+        both += v.x + v.y;
+      }
+      unsigned incl = both;
       for (int o = 1; o < 64; o <<= 1) {
         const unsigned up = __shfl_up(incl, o);
         if (lane >= o) incl += up;
       }
-      unsigned run = incl - c0 - c1;
+      unsigned run = incl - both;
 #pragma unroll
       for (int d = 0; d < 2; ++d)
 #pragma unroll
         for (int w = 0; w < kLocalWaves; ++w) {
-          const unsigned c = off[w][2 * lane + d];
-          off[w][2 * lane + d] = run;
-          run += c;
+          const unsigned n = c[d][w];
+          c[d][w] = run;
+          run += n;
         }
+#pragma unroll
+      for (int w = 0; w < kLocalWaves; ++w) *reinterpret_cast<uint2*>(&off[w][2 * lane]) = make_uint2(c[0][w], c[1][w]);
     }
     __syncthreads();
 #pragma unroll
@@ -236,23 +244,20 @@ __global__ void __launch_bounds__(kLocalThreads)
     for (int i = 0; i < kLocalItems; ++i) v[i] = comp[wib * (64 * kLocalItems) + i * 64 + lane];
   }
   const int share = kChunk / gridDim.y, lo = blockIdx.y * share;  // (a power of two, at least 128)
+  unsigned m[kLocalItems];
 #pragma unroll
   for (int i = 0; i < kLocalItems; ++i) {
     const int at = wib * (64 * kLocalItems) + i * 64 + lane;
-    const long long g = base + at;
     const int src = row_of[v[i] & (kChunk - 1)];
     src_of[at] = src;
-    if (at < lo || at >= lo + share) continue;
-    unsigned m = src >= 0 ? mask[src] : 0u;
-    for (int o = 1; o < 16; o <<= 1) m |= __shfl_xor(m, o);
-    if (g < rows_pad) perm[g] = src;
-    if ((lane & 15) == 0 && g / 16 < n_blocks) blkmask[g / 16] = m;
+    const bool mine = at >= lo && at < lo + share;
+    if (mine && base + at < rows_pad) perm[base + at] = src;
+    m[i] = mine && src >= 0 ? mask[src] : 0u;
   }
-  __syncthreads();
+  sync_lds();  // (the masks are still on their way while the map's rows are asked for)
   // e / V by a multiply: (e + 0.5) / V stays 0.5 / 27 away from every integer for e < 55296
   const long long first = base + lo;
-  if (first >= rows_pad) return;
-  const int n = (int)min((long long)share, rows_pad - first) * V;
+  const int n = first >= rows_pad ? 0 : (int)min((long long)share, rows_pad - first) * V;
   int* dst = reordered + first * V;
   const float inv = 1.0f / (float)V;
   constexpr int U = 14;  // loads in flight per thread
@@ -270,6 +275,13 @@ __global__ void __launch_bounds__(kLocalThreads)
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (e0 + u * kLocalThreads < n) dst[e0 + u * kLocalThreads] = val[u];
+  }
+#pragma unroll
+  for (int i = 0; i < kLocalItems; ++i) {
+    const int at = wib * (64 * kLocalItems) + i * 64 + lane;
+    for (int o = 1; o < 16; o <<= 1) m[i] |= __shfl_xor(m[i], o);
+    const long long block = (base + at) / 16;
+    if (at >= lo && at < lo + share && (lane & 15) == 0 && block < n_blocks) blkmask[block] = m[i];
   }
 }
 
