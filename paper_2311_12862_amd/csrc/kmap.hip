@@ -757,20 +757,24 @@ __device__ __forceinline__ int box_find(const Box& box, const Cells* cells, cons
   return w.bits & bit ? (int)(before + w.before + (unsigned)__popc(w.bits & (bit - 1))) : -1;
 }
 
+// Outputs floor(p / 2) + (0 or 1 along each axis) that an input row of a stride-2 map may have an offset to.
+constexpr int cands_of(int K) { return K == 3 ? 8 : 1; }
+
 // The map from the input side (see k_scatter_down3), and the coarse points: every input meets the output floor(p / 2) (K = 2:
 // only that one) and writes its coordinates; inputs of one output write the same (expanding the bits instead took 35 us where
 // many stand in one word).
 template <int K>
 __global__ void __launch_bounds__(256)
     k_box_scatter(const int4* __restrict__ rows, int n_rows, const Box* __restrict__ box_in, const Cells* __restrict__ cells,
-                  const unsigned* __restrict__ base, int* __restrict__ map, int4* __restrict__ coarse, Ctl* ctl) {
+                  const unsigned* __restrict__ base, int* __restrict__ map, int4* __restrict__ coarse, int* __restrict__ cands, Ctl* ctl) {
   __shared__ unsigned wave_pairs[4];
-  constexpr int LPR = K == 3 ? 8 : 1, V = K * K * K;
+  constexpr int LPR = cands_of(K), V = K * K * K;
   const Box box = *box_in;
   const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
   const long long row = t / LPR;
   const int cand = K == 3 ? (int)(t & 7) : 0;
   bool found = false;
+  int at = -1;
   if (row < n_rows && box.words) {
     const int4 c = rows[row];
     const int pc[3] = {c.y, c.z, c.w};
@@ -790,9 +794,11 @@ __global__ void __launch_bounds__(256)
         map[(long long)n * V + k] = (int)row;
         if (cand == 0) coarse[n] = make_int4(c.x, q[0], q[1], q[2]);
         found = true;
+        at = n;
       }
     }
   }
+  if (cands && row < n_rows) cands[t] = at;
   const unsigned long long bal = __ballot(found);
   if ((threadIdx.x & 63) == 0) wave_pairs[threadIdx.x >> 6] = (unsigned)__popcll(bal);
   __syncthreads();
@@ -1621,6 +1627,60 @@ __global__ void __launch_bounds__(256) k_scatter_in_side(const int* __restrict__
   }
 }
 
+// The input side of a stride-2 map from its rows' candidates, every entry and mask in one pass (presets, k_scatter_in_side and
+// k_mask_from_map took 6, 8.5 and 7 us at 200k rows).  A wave takes 64 rows, a lane one of them; the entries are written in order.
+// Along an axis, an even coordinate has offset 0 to the first candidate, an odd one 1 to the first and -1 to the second.
+template <int K>
+__global__ void __launch_bounds__(256) k_in_side(const int4* __restrict__ rows, const int* __restrict__ cands, long long n_rows,
+                                                 int* __restrict__ map, unsigned* __restrict__ mask) {
+  constexpr int C = cands_of(K), V = K * K * K, P = C + 1;
+  __shared__ int lds[4][64 * P];  // a row's candidates, and which of its coordinates are odd
+  const int lane = threadIdx.x & 63;
+  int* const s = lds[threadIdx.x >> 6];
+  const long long row0 = ((long long)blockIdx.x * 256 + threadIdx.x) & ~63ll, row = row0 + lane;  // (rows_pad is a multiple of 256)
+  int c[C], odd = 0;
+#pragma unroll
+  for (int u = 0; u < C; ++u) c[u] = -1;
+  if (row < n_rows) {
+    if constexpr (C == 8) {
+      const int4 a = reinterpret_cast<const int4*>(cands)[row * 2], b = reinterpret_cast<const int4*>(cands)[row * 2 + 1];
+      c[0] = a.x, c[1] = a.y, c[2] = a.z, c[3] = a.w, c[4] = b.x, c[5] = b.y, c[6] = b.z, c[7] = b.w;
+    } else {
+      c[0] = cands[row];
+    }
+    const int4 p = rows[row];
+    odd = (p.y & 1) << 2 | (p.z & 1) << 1 | (p.w & 1);
+  }
+  unsigned m = 0;
+#pragma unroll
+  for (int u = 0; u < C; ++u) {
+    int k = 0;
+    for (int a = 2; a >= 0; --a) {
+      const int o = (odd >> a) & 1;
+      k = k * K + (K == 2 ? o : o ? ((u >> a) & 1 ? 0 : 2) : 1);
+    }
+    if (c[u] >= 0) m |= 1u << k;
+    s[lane * P + u] = c[u];
+  }
+  s[lane * P + C] = odd;
+  mask[row] = m;
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int i = 0; i < V; ++i) {
+    const int e = i * 64 + lane, r = e / V, k = e - r * V, o = s[r * P + C];
+    const int d[3] = {k / (K * K), k / K % K, k % K};
+    bool ok = true;
+    int u = 0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int b = (o >> (2 - a)) & 1;
+      ok = ok && (K == 2 ? d[a] == b : b ? d[a] != 1 : d[a] == 1);
+      if (K == 3 && b && d[a] == 0) u |= 4 >> a;
+    }
+    map[row0 * V + e] = ok ? s[r * P + u] : -1;
+  }
+}
+
 // Masks of finished map rows.  One load covers two rows of 27 entries; on large maps a wave has eight in flight and
 // stores their 16 masks together (200k -> 127k rows and back: 9.5 -> 6.9 us), on small ones the
 // waves are few and one load each is quicker (10k to 30k rows: 3.4 us against 5.0).
@@ -2120,7 +2180,7 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
   while (chunks < kMaxChunks && (int64_t)chunks * 400 < N) chunks *= 2;
   const int per = (int)std::max<int64_t>(round_up(ceil_div(N, kBoxDealers), kBoxDealThreads), kBoxDealThreads);
   const int dealers = (int)ceil_div(N, per);
-  DevBuf coarse_rows, small;
+  DevBuf coarse_rows, small, cands;
   DevBuf &ctl_buf = fallback->ctl, &own_rows = fallback->rows, &cells = fallback->slots, &keys = fallback->keys;
   // sized for as many outputs as inputs: their number is read at the end
   SideMap& side = km->out_side;
@@ -2185,11 +2245,14 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
     return kRetryTable;
   }
   SPC_HIP(launched);
+  (void)cands.alloc((size_t)N * cands_of(K) * sizeof(int));  // (done without where there is no room)
   const dim3 scatter_grid(blocks_for(K == 3 ? N * 8 : N, 256));
   if (K == 3)
-    hipLaunchKernelGGL(k_box_scatter<3>, scatter_grid, dim3(256), 0, st, rows, (int)N, box, cells.as<Cells>(), base, map, coarse_rows.as<int4>(), ctl);
+    hipLaunchKernelGGL(k_box_scatter<3>, scatter_grid, dim3(256), 0, st, rows, (int)N, box, cells.as<Cells>(), base, map, coarse_rows.as<int4>(),
+                       cands.as<int>(), ctl);
   else
-    hipLaunchKernelGGL(k_box_scatter<2>, scatter_grid, dim3(256), 0, st, rows, (int)N, box, cells.as<Cells>(), base, map, coarse_rows.as<int4>(), ctl);
+    hipLaunchKernelGGL(k_box_scatter<2>, scatter_grid, dim3(256), 0, st, rows, (int)N, box, cells.as<Cells>(), base, map, coarse_rows.as<int4>(),
+                       cands.as<int>(), ctl);
   SPC_LAUNCH_CHECK();
   SPC_TRY(K == 3 ? masks_from_map<27>(map, N, side.mask.as<unsigned>(), ctl, st, true)
                  : masks_from_map<8>(map, N, side.mask.as<unsigned>(), ctl, st, true));
@@ -2202,6 +2265,10 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
   side.ready = true;
   km->n_pairs = (int64_t)h.pairs;
   SPC_TRY(shrink_to_outputs(side, V, coarse_rows, ctl, st));
+  if (cands.p && cands.bytes <= (size_t)side.rows * V * sizeof(int)) {
+    std::swap(km->in_cands.p, cands.p);
+    std::swap(km->in_cands.bytes, cands.bytes);
+  }
   std::swap(km->in_coords.p, own_rows.p);
   std::swap(km->in_coords.bytes, own_rows.bytes);
   std::swap(km->out_coords.p, coarse_rows.p);
@@ -2514,6 +2581,24 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
 int kmap_build_in_side(spconv_kmap* km, hipStream_t st) {
   if (km->in_side.ready) return SPCONV_OK;
   const int V = km->V;
+  if (km->in_cands.p) {
+    SideMap& side = km->in_side;
+    side.rows = km->n_in;
+    side.rows_pad = round_up(side.rows, kRowPad);
+    SPC_TRY(side.map.alloc((size_t)side.rows_pad * V * sizeof(int)));
+    SPC_TRY(side.mask.alloc((size_t)side.rows_pad * sizeof(unsigned)));
+    const dim3 grid((unsigned)(side.rows_pad / 256));
+    const int4* const rows = km->in_coords.as<int4>();
+    if (V == 27)
+      hipLaunchKernelGGL(k_in_side<3>, grid, dim3(256), 0, st, rows, km->in_cands.as<int>(), (long long)side.rows, side.map.as<int>(),
+                         side.mask.as<unsigned>());
+    else
+      hipLaunchKernelGGL(k_in_side<2>, grid, dim3(256), 0, st, rows, km->in_cands.as<int>(), (long long)side.rows, side.map.as<int>(),
+                         side.mask.as<unsigned>());
+    SPC_LAUNCH_CHECK();
+    side.ready = true;
+    return SPCONV_OK;
+  }
   SPC_TRY(alloc_side(km->in_side, km->n_in, V, st, true));
   if (km->n_in > 0) {
     const long long entries = (long long)km->n_out * V;

@@ -748,3 +748,21 @@ def test_scattered_submanifold_builds_in_buckets(sp, n):
     c = gen.uniform_cloud(n, 200, seed=n, lo=-100)
     c[: n // 3, 0] = 65534
     _check_kmap(sp, c, 3, 1, False)
+
+
+@pytest.mark.parametrize("K", [2, 3])
+@pytest.mark.parametrize("n,side", [(1, 3), (63, 9), (64, 200), (257, 40), (1000, 11), (4099, 60)])
+def test_input_side_of_stride2_maps(sp, K, n, side):
+    """Made from the rows' candidates, and searched where these would be more than the output side is (3x3x3, 1,000 rows): around the
+    ends of waves and of the padding, coordinates of both signs."""
+    rng = np.random.default_rng(n)
+    flat = rng.permutation(side ** 3)[:n]
+    c = np.stack([rng.integers(0, 1 if 2 * n > side ** 3 else 2, n), *np.unravel_index(flat, (side,) * 3)], 1).astype(np.int32)
+    c[:, 1:] -= side // 2
+    ref = oc.build_kmap(c, K, 2)
+    up = sp.build_kmap(coords_dev(c), K, 2).transpose()
+    T = np.full((n, K ** 3), -1, np.int32)
+    out, k = np.nonzero(ref.M >= 0)
+    T[ref.M[out, k], k] = out
+    np.testing.assert_array_equal(up.export().cpu().numpy(), T)
+    np.testing.assert_array_equal(up.export_mask().cpu().numpy().view(np.uint32), oc.bitmask(T))
