@@ -1628,57 +1628,41 @@ __global__ void __launch_bounds__(256) k_scatter_in_side(const int* __restrict__
 }
 
 // The input side of a stride-2 map from its rows' candidates, every entry and mask in one pass (presets, k_scatter_in_side and
-// k_mask_from_map took 6, 8.5 and 7 us at 200k rows).  A wave takes 64 rows, a lane one of them; the entries are written in order.
+// k_mask_from_map took 6, 8.5 and 7 us at 200k rows).  A workgroup puts the candidates of 64 rows into their places in LDS and writes
+// the rows from there (with an address worked out for every entry instead of every candidate: 12 us).
 // Along an axis, an even coordinate has offset 0 to the first candidate, an odd one 1 to the first and -1 to the second.
 template <int K>
 __global__ void __launch_bounds__(256) k_in_side(const int4* __restrict__ rows, const int* __restrict__ cands, long long n_rows,
-                                                 int* __restrict__ map, unsigned* __restrict__ mask) {
-  constexpr int C = cands_of(K), V = K * K * K, P = C + 1;
-  __shared__ int lds[4][64 * P];  // a row's candidates, and which of its coordinates are odd
-  const int lane = threadIdx.x & 63;
-  int* const s = lds[threadIdx.x >> 6];
-  const long long row0 = ((long long)blockIdx.x * 256 + threadIdx.x) & ~63ll, row = row0 + lane;  // (rows_pad is a multiple of 256)
-  int c[C], odd = 0;
+                                                 uint4* __restrict__ map, unsigned* __restrict__ mask) {
+  constexpr int C = cands_of(K), V = K * K * K, R = 64, U = (R * C + 255) / 256;
+  __shared__ __align__(16) int s[R * V];
+  __shared__ unsigned m[R];
+  const int t = threadIdx.x;
+  const long long row0 = (long long)blockIdx.x * R;  // (rows_pad is a multiple of 256)
+  int c[U];
+  int4 p[U];
 #pragma unroll
-  for (int u = 0; u < C; ++u) c[u] = -1;
-  if (row < n_rows) {
-    if constexpr (C == 8) {
-      const int4 a = reinterpret_cast<const int4*>(cands)[row * 2], b = reinterpret_cast<const int4*>(cands)[row * 2 + 1];
-      c[0] = a.x, c[1] = a.y, c[2] = a.z, c[3] = a.w, c[4] = b.x, c[5] = b.y, c[6] = b.z, c[7] = b.w;
-    } else {
-      c[0] = cands[row];
-    }
-    const int4 p = rows[row];
-    odd = (p.y & 1) << 2 | (p.z & 1) << 1 | (p.w & 1);
+  for (int i = 0; i < U; ++i) {
+    const int q = i * 256 + t;
+    const bool live = q < R * C && row0 + q / C < n_rows;
+    c[i] = live ? cands[row0 * C + q] : -1;
+    p[i] = live ? rows[row0 + q / C] : make_int4(0, 0, 0, 0);
   }
-  unsigned m = 0;
+  for (int i = t; i < R * V / 4; i += 256) reinterpret_cast<uint4*>(s)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+  if (t < R) m[t] = 0u;
+  __syncthreads();
 #pragma unroll
-  for (int u = 0; u < C; ++u) {
-    int k = 0;
-    for (int a = 2; a >= 0; --a) {
-      const int o = (odd >> a) & 1;
-      k = k * K + (K == 2 ? o : o ? ((u >> a) & 1 ? 0 : 2) : 1);
-    }
-    if (c[u] >= 0) m |= 1u << k;
-    s[lane * P + u] = c[u];
+  for (int i = 0; i < U; ++i) {
+    if (c[i] < 0) continue;
+    const int q = i * 256 + t, r = q / C, u = q % C;
+    auto digit = [&](int x, int second) { return K == 2 ? x & 1 : x & 1 ? (second ? 0 : 2) : 1; };
+    const int k = (digit(p[i].y, u & 4) * K + digit(p[i].z, u & 2)) * K + digit(p[i].w, u & 1);
+    s[r * V + k] = c[i];
+    atomicOr(&m[r], 1u << k);
   }
-  s[lane * P + C] = odd;
-  mask[row] = m;
-  __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int i = 0; i < V; ++i) {
-    const int e = i * 64 + lane, r = e / V, k = e - r * V, o = s[r * P + C];
-    const int d[3] = {k / (K * K), k / K % K, k % K};
-    bool ok = true;
-    int u = 0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const int b = (o >> (2 - a)) & 1;
-      ok = ok && (K == 2 ? d[a] == b : b ? d[a] != 1 : d[a] == 1);
-      if (K == 3 && b && d[a] == 0) u |= 4 >> a;
-    }
-    map[row0 * V + e] = ok ? s[r * P + u] : -1;
-  }
+  __syncthreads();
+  for (int i = t; i < R * V / 4; i += 256) map[row0 * V / 4 + i] = reinterpret_cast<const uint4*>(s)[i];
+  if (t < R) mask[row0 + t] = m[t];
 }
 
 // Masks of finished map rows.  One load covers two rows of 27 entries; on large maps a wave has eight in flight and
@@ -2587,13 +2571,13 @@ int kmap_build_in_side(spconv_kmap* km, hipStream_t st) {
     side.rows_pad = round_up(side.rows, kRowPad);
     SPC_TRY(side.map.alloc((size_t)side.rows_pad * V * sizeof(int)));
     SPC_TRY(side.mask.alloc((size_t)side.rows_pad * sizeof(unsigned)));
-    const dim3 grid((unsigned)(side.rows_pad / 256));
+    const dim3 grid((unsigned)(side.rows_pad / 64));
     const int4* const rows = km->in_coords.as<int4>();
     if (V == 27)
-      hipLaunchKernelGGL(k_in_side<3>, grid, dim3(256), 0, st, rows, km->in_cands.as<int>(), (long long)side.rows, side.map.as<int>(),
+      hipLaunchKernelGGL(k_in_side<3>, grid, dim3(256), 0, st, rows, km->in_cands.as<int>(), (long long)side.rows, side.map.as<uint4>(),
                          side.mask.as<unsigned>());
     else
-      hipLaunchKernelGGL(k_in_side<2>, grid, dim3(256), 0, st, rows, km->in_cands.as<int>(), (long long)side.rows, side.map.as<int>(),
+      hipLaunchKernelGGL(k_in_side<2>, grid, dim3(256), 0, st, rows, km->in_cands.as<int>(), (long long)side.rows, side.map.as<uint4>(),
                          side.mask.as<unsigned>());
     SPC_LAUNCH_CHECK();
     side.ready = true;
