@@ -417,9 +417,8 @@ def main():
         "kmap_build_frac_hbm": round(build_bytes / (t_build * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
         "kmap_build_bytes_per_voxel": {"counted": build_bytes // n, "survey_estimate": 460,
                                        "note": "counted = a build with one lookup per offset: coords 16 + slot written 16 + "
-                                               "27 slots of 16 B probed + map row 108 + mask 4 (the table of z-runs that the "
-                                               "library builds reads 13.5 entries of 32 B per voxel instead: 592 B by the same "
-                                               "count); the survey's 460 prices a probed slot at 12 useful bytes"},
+                                               "27 slots of 16 B probed + map row 108 + mask 4 (the buckets that the library "
+                                               "deals its rows into, looked up in LDS, move about 230 B per voxel instead); the survey's 460 prices a probed slot at 12 useful bytes"},
         "kmap_build_gbs_survey_bytes": round(build_bytes_survey / (t_build * 1e-3) / 1e9, 1),
         "kmap_build_frac_hbm_survey_bytes": round(build_bytes_survey / (t_build * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
         "measured_peaks": {"hbm_copy_gbs": round(hbm_meas, 1), "mfma_f16_tflops": round(mfma_meas, 1),
