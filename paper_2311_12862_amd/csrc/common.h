@@ -111,6 +111,9 @@ struct SideMap {      // one output-stationary table: rows x V
   int64_t rows = 0, rows_pad = 0;
   DevBuf map;         // int32 [rows_pad][V]
   DevBuf mask;        // uint32 [rows_pad]
+  // The input side of a stride-2 build over the box: int32 [n_in][8] (K = 2: [n_in][1]), the outputs that each input row has an offset
+  // to, -1 where there is none; the side is made from them without a search.  Empty where they would be more than the output side is.
+  DevBuf cands;
   bool ready = false;
   std::map<std::pair<int, int>, std::unique_ptr<IgemmPlan>> plans;  // (n_split, flags)
 };
@@ -143,9 +146,6 @@ struct spconv_kmap {
         in_side(*in_ref) {}
   spconv_kmap(const spconv_kmap&) = delete;
   spconv_kmap& operator=(const spconv_kmap&) = delete;
-  // Stride-2 builds over the box: int32 [n_in][8] (K = 2: [n_in][1]), the outputs that each input row has an offset to, -1 where there
-  // is none; the input side is made from them without a search.  Empty where they would be more than the output side is.
-  spc::DevBuf in_cands;
   std::unique_ptr<spc::PairList> pair_list;
   // The pair count that decides between the pairs and the map (wgrad_from_map): n_pairs as the first call that chose by itself
   // knew it, -1 where a build was still pending.  It stays, so that what becomes known later does not give the same call another

@@ -2250,8 +2250,8 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
   km->n_pairs = (int64_t)h.pairs;
   SPC_TRY(shrink_to_outputs(side, V, coarse_rows, ctl, st));
   if (cands.p && cands.bytes <= (size_t)side.rows * V * sizeof(int)) {
-    std::swap(km->in_cands.p, cands.p);
-    std::swap(km->in_cands.bytes, cands.bytes);
+    std::swap(km->in_side.cands.p, cands.p);
+    std::swap(km->in_side.cands.bytes, cands.bytes);
   }
   std::swap(km->in_coords.p, own_rows.p);
   std::swap(km->in_coords.bytes, own_rows.bytes);
@@ -2565,7 +2565,7 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
 int kmap_build_in_side(spconv_kmap* km, hipStream_t st) {
   if (km->in_side.ready) return SPCONV_OK;
   const int V = km->V;
-  if (km->in_cands.p) {
+  if (km->in_side.cands.p) {
     SideMap& side = km->in_side;
     side.rows = km->n_in;
     side.rows_pad = round_up(side.rows, kRowPad);
@@ -2574,10 +2574,10 @@ int kmap_build_in_side(spconv_kmap* km, hipStream_t st) {
     const dim3 grid((unsigned)(side.rows_pad / 64));
     const int4* const rows = km->in_coords.as<int4>();
     if (V == 27)
-      hipLaunchKernelGGL(k_in_side<3>, grid, dim3(256), 0, st, rows, km->in_cands.as<int>(), (long long)side.rows, side.map.as<uint4>(),
+      hipLaunchKernelGGL(k_in_side<3>, grid, dim3(256), 0, st, rows, km->in_side.cands.as<int>(), (long long)side.rows, side.map.as<uint4>(),
                          side.mask.as<unsigned>());
     else
-      hipLaunchKernelGGL(k_in_side<2>, grid, dim3(256), 0, st, rows, km->in_cands.as<int>(), (long long)side.rows, side.map.as<uint4>(),
+      hipLaunchKernelGGL(k_in_side<2>, grid, dim3(256), 0, st, rows, km->in_side.cands.as<int>(), (long long)side.rows, side.map.as<uint4>(),
                          side.mask.as<unsigned>());
     SPC_LAUNCH_CHECK();
     side.ready = true;
