@@ -1284,7 +1284,9 @@ __device__ __forceinline__ void probe_bucket_column(int b, int tx, int ty, int z
 
 // One workgroup per bucket; nine lanes per row, one per column (dx, dy), seven rows per wave.  kBucketRows rows of the bucket are in the
 // table at a time, kOwnRows of those that are looked up in LDS: a bucket is almost always within both, and one of any size is walked
-// in as many rounds as it takes.
+// in as many rounds as it takes.  Rows that stand in one cell all lie in one bucket (rows padded with zeros: any number of them, and the
+// rounds grow with its square), so a bucket of several rounds is left as soon as one has shown two such rows: the build fails, and the
+// rows that were not looked up have no neighbours.
 __global__ void __launch_bounds__(kBucketThreads)
     k_probe_buckets(const Dealt* __restrict__ entries, const unsigned* __restrict__ starts, const unsigned* __restrict__ dealer_flags,
                     int dealers, int per, int log_b, int* __restrict__ map, unsigned* __restrict__ mask, Ctl* ctl, HostResult* host) {
@@ -1330,6 +1332,7 @@ __global__ void __launch_bounds__(kBucketThreads)
   }
   __syncthreads();
   const int n_own = before[0][kDealers], n_all = n_own + before[1][kDealers];
+  const bool rounds = n_all > kBucketRows;
   auto entry = [&](int i) {
     const int h = i >= n_own ? 1 : 0;
     const int j = h ? i - n_own : i;
@@ -1340,8 +1343,14 @@ __global__ void __launch_bounds__(kBucketThreads)
     return entries[(long long)w * per * kCopies + src[h][w] + (j - before[h][w])];
   };
   const int sub = lane / LPR, col = lane - sub * LPR;
+  auto run_of = [](const Dealt& e) {
+    const unsigned long long key = (unsigned long long)e.lo | ((unsigned long long)e.hi << 32);
+    return (key & ~0xFFFFull) | (unsigned)((((int)(e.lo & 0xFFFFu) - 32768) >> 2) + 32768);
+  };
   unsigned pairs = 0, bad = 0;
-  for (int c0 = 0; n_own && (c0 == 0 || c0 < n_all); c0 += kBucketRows) {
+  int looked_up = 0;  // own rows that have their map rows
+  bool leave = false;
+  for (int c0 = 0; n_own && !leave && (c0 == 0 || c0 < n_all); c0 += kBucketRows) {
     const int in_table = min(kBucketRows, n_all - c0);
     if (c0) __syncthreads();
     for (int i = t; i <= (int)slot_mask; i += kBucketThreads) reinterpret_cast<ulonglong2*>(tab)[i] = make_ulonglong2(kEmpty, ~0ull);
@@ -1350,8 +1359,7 @@ __global__ void __launch_bounds__(kBucketThreads)
       const Dealt e = entry(c0 + i);
       row_of[i] = e.row;
       if (c0 == 0 && i < kOwnRows && i < n_own) own[i] = e;
-      const unsigned long long key = (unsigned long long)e.lo | ((unsigned long long)e.hi << 32);
-      const unsigned long long run = (key & ~0xFFFFull) | (unsigned)((((int)(e.lo & 0xFFFFu) - 32768) >> 2) + 32768);
+      const unsigned long long run = run_of(e);
       unsigned s = hash_run(run) >> (32 - kRunSlotBits);
       for (unsigned it = 0; it <= slot_mask; ++it) {
         const unsigned long long old = atomicCAS(&tab[s].key, kEmpty, run);
@@ -1362,10 +1370,23 @@ __global__ void __launch_bounds__(kBucketThreads)
         s = (s + 1) & slot_mask;
       }
     }
+    if (rounds) {  // a row (or a copy) whose place another one has taken
+      __syncthreads();
+      for (int i = t; i < in_table; i += kBucketThreads) {
+        const Dealt e = entry(c0 + i);
+        const unsigned long long run = run_of(e);
+        unsigned s = hash_run(run) >> (32 - kRunSlotBits);
+        for (unsigned it = 0; it <= slot_mask && tab[s].key != run; ++it) s = (s + 1) & slot_mask;
+        if (((unsigned)(tab[s].cells >> (16 * (e.lo & 3u))) & 0xFFFFu) != (unsigned)i) bad = (unsigned)FLAG_DUP;
+      }
+      if (bad) atomicOr(&s_flags, bad);
+    }
     for (int o0 = 0; o0 < n_own; o0 += kOwnRows) {
       const int n_here = min(kOwnRows, n_own - o0);
-      if (c0 || o0) {
+      if (rounds || o0) {
         __syncthreads();
+        leave = rounds && s_flags;  // (nobody writes it between this barrier and the next)
+        if (leave) break;
         for (int i = t; i < n_here; i += kBucketThreads) own[i] = entry(o0 + i);
       }
       __syncthreads();
@@ -1401,8 +1422,16 @@ __global__ void __launch_bounds__(kBucketThreads)
           mask[row] = c0 ? mask[row] | m : m;
         }
       }
+      if (c0 == 0) looked_up = o0 + n_here;
+      if (rounds && bad) atomicOr(&s_flags, bad);
     }
   }
+  if (leave)
+    for (int i = looked_up + t; i < n_own; i += kBucketThreads) {
+      const int row = entry(i).row;
+      for (int k = 0; k < V; ++k) map[(long long)row * V + k] = -1;
+      mask[row] = 0u;
+    }
   if (blockIdx.x == 0 && t < dealers) bad |= dealer_flags[t];
   if (lane == 0) wave_pairs[wib] = pairs;
   if (bad) atomicOr(&s_flags, bad);

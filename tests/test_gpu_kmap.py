@@ -766,3 +766,37 @@ def test_input_side_of_stride2_maps(sp, K, n, side):
     T[ref.M[out, k], k] = out
     np.testing.assert_array_equal(up.export().cpu().numpy(), T)
     np.testing.assert_array_equal(up.export_mask().cpu().numpy().view(np.uint32), oc.bitmask(T))
+
+
+@pytest.mark.parametrize("n,cells,side", [(6000, 1, 1), (300_000, 1, 1), (300_000, 3, 12), (300_000, 1700, 12), (60_000, 30_000, 32)])
+def test_submanifold_builds_over_rows_that_share_cells(sp, n, cells, side):
+    """Any number of rows in one cell (rows padded with zeros), in a few, or in all cells of many blocks: the build fails, in a time
+    that grows with the rows (a walk of the one bucket to its end takes 115,000 passes with 300,000 of them, tenths of a second, against
+    30 ms asked for here), and what an unwaited one leaves in its map are rows or nothing, which a layer may walk before the status is
+    asked for."""
+    import time
+    import torch
+    rng = np.random.default_rng(n + cells)
+    at = np.stack(np.unravel_index(np.arange(cells), (side,) * 3), 1)
+    dup = np.concatenate([np.zeros((n, 1)), at[rng.integers(0, cells, n)]], 1).astype(np.int32)
+    cloud = gen.uniform_cloud(4000, 60, seed=n, lo=20)
+    for c in (dup, rng.permutation(np.concatenate([cloud, dup]))):
+        coords = coords_dev(c)
+        torch.cuda.synchronize()
+        took = []
+        for _ in range(3):
+            t0 = time.perf_counter()
+            with pytest.raises(sp.SpconvError) as e:
+                sp.build_kmap(coords, 3, 1)
+            took.append(time.perf_counter() - t0)
+            assert e.value.status == -3
+        assert min(took) < 0.03, took
+        km = sp.build_kmap(coords, 3, 1, asynchronous=True)
+        x, w = torch.ones(len(c), 16, dtype=torch.float16, device="cuda"), torch.ones(27, 16, 16, dtype=torch.float16, device="cuda")
+        assert torch.isfinite(sp.fwd(x, w, km, sp.Config(n_split=0, kernel=1))).all()
+        M = km.export().cpu().numpy()
+        assert M.min() >= -1 and M.max() < len(c)
+        with pytest.raises(sp.SpconvError) as e:
+            km.status()
+        assert e.value.status == -3
+        km.destroy()
