@@ -405,9 +405,10 @@ __global__ void __launch_bounds__(256)
 // The coarse points floor(p / 2) of a scan fill a box of a few hundred cells per row.  One bit per cell, set by the rows, is the
 // de-duplication, the lexicographic sort (the order of the bits) and the look-up table (a point's row is the number of set
 // bits before its own: a prefix per 32 cells and a population count) at once; nothing is hashed, sorted or probed, and the
-// host waits once, at the end.  The cells are cut into chunks of equal length, the rows dealt to the chunks of their coarse
+// host waits once, at the end.  The cells are cut into groups of equal length, and the groups dealt out to as many chunks as there are
+// workgroups, neighbouring groups to different ones (group_at).  The rows are dealt to the chunks of their coarse
 // points, and one workgroup per chunk sets its bits in LDS and writes them with their prefixes: nothing is cleared beforehand and no
-// atomic leaves the CU.  Launches: the box, dealing, bits, chunk prefixes (and the presets of
+// atomic leaves the CU.  Launches: the box, dealing, bits, group prefixes (and the presets of
 // the map), the map from the input side (and the coordinates), masks.  Against de-duplication through a hash table, a radix sort and table
 // look-ups, and with bits in memory (cleared, marked by an atomic per row, which the memory side takes at 10 per ns, counted), whole
 // 3x3x3 builds in us: LiDAR-like scans of 2k rows 71, 34 -> 35, 10k 80, 36 -> 36, 30k 89, 42 -> 38, 100k 109, 62 -> 49, 200k (127k
@@ -420,19 +421,37 @@ constexpr int kBoxBlocks = 256;
 constexpr int kCellsPerRow = 2048;
 constexpr int64_t kMaxBoxWords = 1ll << 26;
 constexpr int kBoxDealers = 256, kBoxDealThreads = 512;  // workgroups of k_box_deal at most: one per thread of k_box_bits
-constexpr int kMaxChunks = 2048;
+constexpr int kMaxChunks = 2048, kMaxGroups = 32768;
 constexpr int kLdsWords = 8192;    // words of a chunk that are in LDS at a time
+constexpr int kBaseThreads = 1024;
+static_assert(kMaxBoxWords / kMaxGroups <= kLdsWords && kMaxGroups % (4 * kBaseThreads) == 0 && kMaxChunks % kBaseThreads == 0, "");
 constexpr int kBitsThreads = 1024;  // (256: the chunks at a scanner's place, of thousands of rows, took 22 us)
 
 struct Box {
   int lo[4];         // of (b, x, y, z)
   unsigned span[4];  // (up to 65536 each)
   unsigned words;    // of 32 cells; 0: nothing to do
-  unsigned shift;    // a chunk is 2^shift words
+  unsigned shift;    // a group is 2^shift words
   unsigned flags;
+  __host__ __device__ unsigned groups() const { return (words + (1u << shift) - 1u) >> shift; }
 };
 
-// 32 cells: which are there, and how many are before them in their chunk.
+// Most groups of a box.  A chunk has up to 64, so that rows which crowd into a part of the box are shared among many workgroups all the
+// same: with chunks of neighbouring cells, one point far from a plane of 200k rows left nearly all of them to one workgroup.  Whole 3x3x3
+// builds without and with such a point, us, so and in groups: a plane of 200k 74, 395 and 72, 96; a room of 60k 51, 105 and 51, 60; scans
+// of 100k 62, 98 and 61, 70; 400k 103, 138 and 102, 139 (the cells of the larger box, which are written, are the rest).
+__host__ __device__ constexpr unsigned most_groups(int chunks) { return chunks * 64 < kMaxGroups ? chunks * 64 : kMaxGroups; }
+// Which chunk a group belongs to, and the i-th group of a chunk: every run of `chunks` groups has one of each chunk, and the runs are
+// turned against each other, so that cells at any regular distance (a wall along the first axis) do not meet in one chunk.
+__device__ __forceinline__ unsigned turn_of(unsigned i, int log_chunks) { return (i * 0x9E3779B1u) >> (32 - log_chunks); }
+__device__ __forceinline__ unsigned chunk_of(unsigned group, int log_chunks) {
+  return (group + turn_of(group >> log_chunks, log_chunks)) & ((1u << log_chunks) - 1u);
+}
+__device__ __forceinline__ unsigned group_at(unsigned chunk, unsigned i, int log_chunks) {
+  return (i << log_chunks) | ((chunk - turn_of(i, log_chunks)) & ((1u << log_chunks) - 1u));
+}
+
+// 32 cells: which are there, and how many are before them in their group.
 struct __align__(8) Cells {
   unsigned bits, before;
 };
@@ -489,14 +508,14 @@ __global__ void __launch_bounds__(256)
 // on; starts[w][chunk] says where each chunk begins.  Where the box is too large, table_slots empty slots of the hash tables take the
 // bitmap's place.
 __global__ void __launch_bounds__(kBoxDealThreads)
-    k_box_deal(const int* __restrict__ partial, int n_partial, long long max_words, const int4* __restrict__ coords, int n, int per, int chunks,
-               unsigned* __restrict__ entries, unsigned* __restrict__ starts, ulonglong2* __restrict__ table, long long table_slots,
+    k_box_deal(const int* __restrict__ partial, int n_partial, long long max_words, const int4* __restrict__ coords, int n, int per,
+               int log_chunks, unsigned* __restrict__ entries, unsigned* __restrict__ starts, ulonglong2* __restrict__ table, long long table_slots,
                Box* box_out, Ctl* ctl, HostResult* host) {
   constexpr int U = 2, kWaves = kBoxDealThreads / 64;
   __shared__ int red[4][9];
   __shared__ unsigned place[kMaxChunks], wave_sum[kWaves];
   __shared__ Box s_box;
-  const int t = threadIdx.x, lane = t & 63, wib = t >> 6, w = blockIdx.x;
+  const int t = threadIdx.x, lane = t & 63, wib = t >> 6, w = blockIdx.x, chunks = 1 << log_chunks;
   if (t < 256) {
     int v[9];  // (kBoxBlocks == 256 partials at most: one per thread)
 #pragma unroll
@@ -529,8 +548,9 @@ __global__ void __launch_bounds__(kBoxDealThreads)
     const unsigned long long words = (cells + 31) / 32;
     if (words > (unsigned long long)max_words) b.flags |= (unsigned)FLAG_BOX;
     b.words = words > (unsigned long long)max_words ? 0u : (unsigned)words;
-    b.shift = 2;  // (whole fours: k_box_bits writes them)
-    while (((unsigned long long)chunks << b.shift) < b.words) ++b.shift;
+    // whole fours (k_box_bits writes them), and lines of 16 words where every chunk has one
+    b.shift = 2;
+    while (b.groups() > (b.shift < 4 ? (unsigned)chunks : most_groups(chunks))) ++b.shift;
     s_box = b;
     if (w == 0) {
       *box_out = b;
@@ -569,8 +589,8 @@ __global__ void __launch_bounds__(kBoxDealThreads)
           f(cell_of(box, c[u].x, c[u].y >> 1, c[u].z >> 1, c[u].w >> 1));
     }
   };
-  const unsigned to_chunk = 5 + box.shift;
-  visit([&](unsigned cell) { atomicAdd(&place[cell >> to_chunk], 1u); });
+  const unsigned to_group = 5 + box.shift;
+  visit([&](unsigned cell) { atomicAdd(&place[chunk_of(cell >> to_group, log_chunks)], 1u); });
   __syncthreads();
   constexpr int S = kMaxChunks / kBoxDealThreads;  // counts -> first places, four per thread
   static_assert(S == 4, "");
@@ -596,15 +616,15 @@ __global__ void __launch_bounds__(kBoxDealThreads)
   if (t == 0) my_starts[chunks] = all;
   __syncthreads();
   unsigned* const my_entries = entries + (long long)w * per;
-  visit([&](unsigned cell) { my_entries[atomicAdd(&place[cell >> to_chunk], 1u)] = cell; });
+  visit([&](unsigned cell) { my_entries[atomicAdd(&place[chunk_of(cell >> to_group, log_chunks)], 1u)] = cell; });
 }
 
-// One workgroup per chunk: its bits in LDS, from there with their prefixes to memory; totals[chunk] = set bits.  A chunk of more than
-// kLdsWords (a sparse box) takes rounds.  Where the box is too large, the coarse points go through the table instead (log_cap 0: it
+// One workgroup per chunk: its bits in LDS, from there with their prefixes to memory; base[group] = set bits of the group,
+// totals[chunk] of all of them.  A chunk of more than kLdsWords (a sparse box) takes rounds.  Where the box is too large, the coarse points go through the table instead (log_cap 0: it
 // does not fit there).
 __global__ void __launch_bounds__(kBitsThreads)
     k_box_bits(const Box* __restrict__ box_in, const unsigned* __restrict__ entries, const unsigned* __restrict__ starts, int dealers,
-               int per, Cells* __restrict__ cells, unsigned* __restrict__ totals, const int4* __restrict__ coords, int n, int log_cap,
+               int per, int log_chunks, Cells* __restrict__ cells, unsigned* __restrict__ base, unsigned* __restrict__ totals, const int4* __restrict__ coords, int n, int log_cap,
                unsigned long long* __restrict__ table, unsigned long long* __restrict__ ukeys, Ctl* ctl) {
   __shared__ __align__(16) unsigned bits[kLdsWords];
   constexpr int kWaves = kBitsThreads / 64, U = 4;
@@ -623,8 +643,9 @@ __global__ void __launch_bounds__(kBitsThreads)
     }
     return;
   }
-  const unsigned lo = blockIdx.x << box.shift, hi = min(box.words, lo + (1u << box.shift));
-  if (lo >= box.words) {
+  const unsigned groups = box.groups(), shift = box.shift, in_group = (1u << shift) - 1u;
+  const unsigned n_groups = (groups + gridDim.x - 1) >> log_chunks;  // of this chunk (the last one may be beyond the box)
+  if (blockIdx.x >= groups) {
     if (t == 0) totals[blockIdx.x] = 0;
     return;
   }
@@ -647,10 +668,12 @@ __global__ void __launch_bounds__(kBitsThreads)
     before[t + 1] = incl;
     if (t == 0) before[0] = 0;
   }
-  unsigned total = 0;
-  for (unsigned w0 = lo; w0 < hi; w0 += kLdsWords) {
-    const int here = (int)min((unsigned)kLdsWords, hi - w0);
-    for (int i = t; i < (here + 3) / 4; i += kBitsThreads) reinterpret_cast<uint4*>(bits)[i] = make_uint4(0, 0, 0, 0);
+  unsigned total = 0;  // of this wave's groups
+  const unsigned per_round = kLdsWords >> shift;
+  for (unsigned g0 = 0; g0 < n_groups; g0 += per_round) {
+    const unsigned w0 = g0 << shift;
+    const int here = (int)(min(per_round, n_groups - g0) << shift);
+    for (int i = t; i < here / 4; i += kBitsThreads) reinterpret_cast<uint4*>(bits)[i] = make_uint4(0, 0, 0, 0);
     __syncthreads();
     const int rows = before[kBoxDealers];
     for (int i0 = t; i0 < rows; i0 += U * kBitsThreads) {
@@ -668,62 +691,81 @@ __global__ void __launch_bounds__(kBitsThreads)
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const unsigned at = (cell[u] >> 5) - w0;
+        const unsigned word = cell[u] >> 5, at = ((word >> shift >> log_chunks) << shift | (word & in_group)) - w0;
         if (i0 + u * kBitsThreads < rows && at < (unsigned)here) atomicOr(&bits[at], 1u << (cell[u] & 31));
       }
     }
     __syncthreads();
-    // a wave takes consecutive words, 256 at a time, four to a lane
-    const int share = ((here + kWaves - 1) / kWaves + 255) / 256 * 256, from = min(here, wib * share), to = min(here, from + share);
-    unsigned sum = 0;
-    for (int i = from + 4 * lane; i < to; i += 256) {
-      const uint4 v = *reinterpret_cast<const uint4*>(bits + i);  // (the words up to a multiple of four are zeros)
-      sum += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
-    }
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-    if (lane == 0) wave_bits[wib] = sum;
-    __syncthreads();
-    unsigned run = total;
-#pragma unroll
-    for (int i = 0; i < kWaves; ++i) {
-      if (i < wib) run += wave_bits[i];
-      total += wave_bits[i];
-    }
-    for (int i0 = from; i0 < to; i0 += 256) {
-      const int i = i0 + 4 * lane;
-      const uint4 v = i < to ? *reinterpret_cast<const uint4*>(bits + i) : make_uint4(0, 0, 0, 0);
-      const unsigned n0 = __popc(v.x), n1 = n0 + __popc(v.y), n2 = n1 + __popc(v.z), n3 = n2 + __popc(v.w);
-      unsigned in = n3;
-      for (int o = 1; o < 64; o <<= 1) {
-        const unsigned up = __shfl_up(in, o);
-        if (lane >= o) in += up;
+    // a wave takes 256 consecutive words at a time, four to a lane: several groups, or a part of one, which it then takes whole
+    const int unit = max(256, 1 << shift), seg = min(64, 1 << (shift - 2));
+    for (int u0 = wib * unit; u0 < here; u0 += kWaves * unit) {
+      unsigned run = 0;
+      for (int i0 = u0; i0 < min(u0 + unit, here); i0 += 256) {
+        const int i = i0 + 4 * lane;
+        const uint4 v = i < here ? *reinterpret_cast<const uint4*>(bits + i) : make_uint4(0, 0, 0, 0);
+        const unsigned n0 = __popc(v.x), n1 = n0 + __popc(v.y), n2 = n1 + __popc(v.z), n3 = n2 + __popc(v.w);
+        unsigned in = n3;
+        for (int o = 1; o < seg; o <<= 1) {
+          const unsigned up = __shfl_up(in, o);
+          if ((lane & (seg - 1)) >= o) in += up;
+        }
+        const unsigned b = run + in - n3, group = group_at(blockIdx.x, g0 + ((unsigned)i >> shift), log_chunks);
+        const unsigned word = (group << shift) + ((unsigned)i & in_group);
+        if (i < here && group < groups) {
+          if (word < box.words) {  // (the buffer holds whole fours)
+            uint4* const dst = reinterpret_cast<uint4*>(cells + word);
+            dst[0] = make_uint4(v.x, b, v.y, b + n0);
+            dst[1] = make_uint4(v.z, b + n1, v.w, b + n2);
+          }
+          if ((((unsigned)i + 4u) & in_group) == 0u) {
+            base[group] = run + in;
+            total += run + in;
+          }
+        }
+        run += __shfl(in, 63);
       }
-      const unsigned b = run + in - n3;
-      if (i < to) {  // (the buffer holds whole fours)
-        uint4* const dst = reinterpret_cast<uint4*>(cells + w0 + i);
-        dst[0] = make_uint4(v.x, b, v.y, b + n0);
-        dst[1] = make_uint4(v.z, b + n1, v.w, b + n2);
-      }
-      run += __shfl(in, 63);
     }
     __syncthreads();
   }
-  if (t == 0) totals[blockIdx.x] = total;
+  for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
+  if (lane == 0) wave_bits[wib] = total;
+  __syncthreads();
+  if (t == 0) {
+    for (int i = 1; i < kWaves; ++i) total += wave_bits[i];
+    totals[blockIdx.x] = total;
+  }
 }
 
-// base[chunk] = set bits before the chunk, and the presets of the map (rows up to the padding) and of the padding's masks.
-__global__ void __launch_bounds__(256)
+// base[group]: the set bits of the group become those before it (the first workgroup's work); the others preset the map (rows up to the
+// padding).
+__global__ void __launch_bounds__(kBaseThreads)
     k_box_base(const Box* __restrict__ box_in, const unsigned* __restrict__ totals, int chunks, unsigned* __restrict__ base, int V,
                uint4* __restrict__ map, unsigned* __restrict__ mask, Ctl* ctl) {
-  constexpr int S = kMaxChunks / 256;
-  __shared__ unsigned wave_sum[4];
+  constexpr int kWaves = kBaseThreads / 64, Q = kMaxGroups / kBaseThreads / 4, S = kMaxChunks / kBaseThreads;
+  __shared__ unsigned wave_sum[kWaves];
   const int t = threadIdx.x, lane = t & 63, wib = t >> 6;
-  const unsigned words = box_in->words;
-  unsigned v[S], mine = 0;
+  const unsigned groups = box_in->groups();  // (no box: none, and no totals)
+  const unsigned each = (groups + 4 * kBaseThreads - 1) / (4 * kBaseThreads) * 4, first = t * each;  // at most 4 Q
+  uint4 v[Q];
+  unsigned mine = 0;
+  if (blockIdx.x == 0) {
 #pragma unroll
-  for (int i = 0; i < S; ++i) v[i] = words && t * S + i < chunks ? totals[t * S + i] : 0u;  // (no box: no totals)
+    for (int q = 0; q < Q; ++q) {
+      const unsigned g = first + 4 * q;
+      v[q] = 4 * q < (int)each && g < groups ? reinterpret_cast<const uint4*>(base)[g / 4] : make_uint4(0, 0, 0, 0);
+    }
 #pragma unroll
-  for (int i = 0; i < S; ++i) mine += v[i];
+    for (int q = 0; q < Q; ++q) {
+      const unsigned g = first + 4 * q;  // (the last four may be incomplete)
+      if (g + 1 >= groups) v[q].y = 0;
+      if (g + 2 >= groups) v[q].z = 0;
+      if (g + 3 >= groups) v[q].w = 0;
+      mine += v[q].x + v[q].y + v[q].z + v[q].w;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < S; ++i) mine += groups && t * S + i < chunks ? totals[t * S + i] : 0u;
+  }
   unsigned incl = mine;
   for (int o = 1; o < 64; o <<= 1) {
     const unsigned up = __shfl_up(incl, o);
@@ -731,21 +773,26 @@ __global__ void __launch_bounds__(256)
   }
   if (lane == 63) wave_sum[wib] = incl;
   __syncthreads();
-  const unsigned total = wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3];
-  if (blockIdx.x == 0) {
-    unsigned at = incl - mine;
-    for (int i = 0; i < wib; ++i) at += wave_sum[i];
+  unsigned total = 0, at = incl - mine;
 #pragma unroll
-    for (int i = 0; i < S; ++i) {
-      if (t * S + i < chunks) base[t * S + i] = at;
-      at += v[i];
-    }
-    if (t == 0 && words) ctl->count = total;  // (else: of the table's points, or none)
+  for (int i = 0; i < kWaves; ++i) {
+    if (i < wib) at += wave_sum[i];
+    total += wave_sum[i];
   }
   const unsigned rows_pad = (total + kRowPad - 1) / kRowPad * kRowPad;
-  const long long vecs = (long long)rows_pad * V / 4;
-  for (long long i = (long long)blockIdx.x * 256 + t; i < vecs; i += (long long)gridDim.x * 256) map[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
-  if (blockIdx.x == 0 && total + t < rows_pad) mask[total + t] = 0u;
+  if (blockIdx.x == 0) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const unsigned g = first + 4 * q, y = at + v[q].x, z = y + v[q].y, w = z + v[q].z;
+      if (4 * q < (int)each && g < groups) reinterpret_cast<uint4*>(base)[g / 4] = make_uint4(at, y, z, w);
+      at = w + v[q].w;
+    }
+    if (t == 0 && groups) ctl->count = total;  // (else: of the table's points, or none)
+    if (total + t < rows_pad) mask[total + t] = 0u;
+    return;
+  }
+  const long long vecs = (long long)rows_pad * V / 4, step = (long long)(gridDim.x - 1) * kBaseThreads;
+  for (long long i = (long long)(blockIdx.x - 1) * kBaseThreads + t; i < vecs; i += step) map[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
 }
 
 // Row of a coarse point, or -1.
@@ -2189,8 +2236,9 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
   const int V = K * K * K;
   const int64_t max_words = std::min<int64_t>(std::max<int64_t>(N * (kCellsPerRow / 32), 1 << 15), kMaxBoxWords);
   // about 400 rows to a chunk; dealers of 512 rows and more
-  int chunks = 64;
-  while (chunks < kMaxChunks && (int64_t)chunks * 400 < N) chunks *= 2;
+  int log_chunks = 6;
+  while ((1 << log_chunks) < kMaxChunks && ((int64_t)400 << log_chunks) < N) ++log_chunks;
+  const int chunks = 1 << log_chunks;
   const int per = (int)std::max<int64_t>(round_up(ceil_div(N, kBoxDealers), kBoxDealThreads), kBoxDealThreads);
   const int dealers = (int)ceil_div(N, per);
   DevBuf coarse_rows, small, cands;
@@ -2198,10 +2246,10 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
   // sized for as many outputs as inputs: their number is read at the end
   SideMap& side = km->out_side;
   const int64_t most = round_up(N, kRowPad);
-  const size_t partial_bytes = (size_t)kBoxBlocks * 9 * sizeof(int);
+  const size_t base_bytes = most_groups(chunks) * sizeof(unsigned), partial_bytes = (size_t)kBoxBlocks * 9 * sizeof(int);
   if (ctl_buf.alloc(sizeof(Ctl)) != SPCONV_OK || own_rows.alloc((size_t)N * 16) != SPCONV_OK ||
       coarse_rows.alloc((size_t)N * 16) != SPCONV_OK ||
-      small.alloc(sizeof(Box) + partial_bytes + (2 * (size_t)chunks + (size_t)dealers * (chunks + 1)) * sizeof(unsigned)) != SPCONV_OK ||
+      small.alloc(base_bytes + sizeof(Box) + partial_bytes + ((size_t)chunks + (size_t)dealers * (chunks + 1)) * sizeof(unsigned)) != SPCONV_OK ||
       cells.alloc((size_t)max_words * sizeof(Cells)) != SPCONV_OK || keys.alloc((size_t)N * 8) != SPCONV_OK ||
       side.map.alloc((size_t)most * V * sizeof(int)) != SPCONV_OK || side.mask.alloc((size_t)most * sizeof(unsigned)) != SPCONV_OK)
     return kRetryTable;
@@ -2210,10 +2258,10 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
   const int table_cap = log2_capacity(N);
   const long long table_slots = (K == 2 ? 2ll : 1ll) << table_cap;
   const bool table_fits = table_slots * 16 <= max_words * 8 / 2;
-  Box* box = small.as<Box>();
+  unsigned* base = small.as<unsigned>();
+  Box* box = reinterpret_cast<Box*>(small.as<char>() + base_bytes);
   int* partial = reinterpret_cast<int*>(box + 1);
-  unsigned* totals = reinterpret_cast<unsigned*>(small.as<char>() + sizeof(Box) + partial_bytes);
-  unsigned *base = totals + chunks, *starts = base + chunks;
+  unsigned *totals = reinterpret_cast<unsigned*>(partial) + kBoxBlocks * 9, *starts = totals + chunks;
   int* map = side.map.as<int>();
   const unsigned n_partial = (unsigned)std::min<int64_t>(ceil_div(N, 1024), kBoxBlocks);
   HostCtl* hc = host_ctl_acquire();
@@ -2239,17 +2287,17 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
   hipLaunchKernelGGL(k_box_bounds, dim3(n_partial), dim3(256), 0, st, rows, (int)N, own_rows.as<int4>(), partial);
   check();
   hipLaunchKernelGGL(k_box_deal, dim3((unsigned)dealers), dim3(kBoxDealThreads), 0, st, partial, (int)n_partial, (long long)max_words, rows,
-                     (int)N, per, chunks, keys.as<unsigned>(), starts, cells.as<ulonglong2>(), table_fits ? table_slots : 0ll, box, ctl,
+                     (int)N, per, log_chunks, keys.as<unsigned>(), starts, cells.as<ulonglong2>(), table_fits ? table_slots : 0ll, box, ctl,
                      hc->dev);
   check();
   hipLaunchKernelGGL(k_box_bits, dim3((unsigned)chunks), dim3(kBitsThreads), 0, st, box, keys.as<unsigned>(), starts, dealers, per,
-                     cells.as<Cells>(), totals, rows, (int)N, table_fits ? table_cap : 0, cells.as<unsigned long long>(),
+                     log_chunks, cells.as<Cells>(), base, totals, rows, (int)N, table_fits ? table_cap : 0, cells.as<unsigned long long>(),
                      keys.as<unsigned long long>(), ctl);
   check();
   if (early) SPC_TRY(verdict());
   if (!too_large) {
-    hipLaunchKernelGGL(k_box_base, dim3((unsigned)std::min<int64_t>(ceil_div(N * V, 8192), 1024)), dim3(256), 0, st, box, totals, chunks,
-                       base, V, side.map.as<uint4>(), side.mask.as<unsigned>(), ctl);
+    hipLaunchKernelGGL(k_box_base, dim3(1 + (unsigned)std::min<int64_t>(ceil_div(N * V, 32768), 256)), dim3(kBaseThreads), 0, st, box, totals,
+                       chunks, base, V, side.map.as<uint4>(), side.mask.as<unsigned>(), ctl);
     check();
     if (!early) SPC_TRY(verdict());
   }
