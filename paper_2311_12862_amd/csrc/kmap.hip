@@ -1174,14 +1174,17 @@ template <typename F> __device__ __forceinline__ void for_buckets(int4 c, int lo
   }
 }
 
-// Workgroup w deals rows [w per, w per + per) and leaves them, ordered by bucket (a bucket's own rows before the copies), at
-// entries + 8 per w; starts[w][2 bucket + copies] says where each begins.  Also the kmap's own copy of the
-// caller's rows, the map of the padding and of rows beside the range (no neighbours; they fail the build), and the control block.
+// Workgroup w deals rows [w per, w per + per) and leaves those of buckets [part 2^log_b, part 2^log_b + 2^log_b), ordered by bucket (a
+// bucket's own rows before the copies), at entries + 8 per w; starts[w][2 bucket + copies] says where each begins.  The first part also
+// makes the kmap's own copy of the caller's rows, the map of the padding and of rows beside the range (no neighbours; they fail the
+// build), and clears the control block.
+template <bool PARTS>
 __global__ void __launch_bounds__(kDealThreads)
-    k_deal_rows(const int4* __restrict__ coords, int n, int per, int log_b, Dealt* __restrict__ entries, unsigned* __restrict__ starts,
+    k_deal_rows(const int4* __restrict__ coords, int n, int per, int log_b, int log_parts, unsigned part_of, Dealt* __restrict__ entries, unsigned* __restrict__ starts,
                 unsigned* __restrict__ dealer_flags, int4* __restrict__ keep, long long rows_pad, int* __restrict__ map,
                 unsigned* __restrict__ mask, Ctl* ctl) {
   constexpr int V = 27, U = 2;
+  const unsigned part = PARTS ? part_of : 0u;
   extern __shared__ __align__(16) unsigned place[];  // [2 << log_b]
   __shared__ unsigned wave_sum[kDealThreads / 64], flags;
   const int t = threadIdx.x, lane = t & 63, wib = t >> 6, w = blockIdx.x;
@@ -1200,18 +1203,27 @@ __global__ void __launch_bounds__(kDealThreads)
         if (r0 + u * kDealThreads < last) f((int)r0 + u * kDealThreads, c[u]);
     }
   };
+  auto visit_copies = [&](int4 c, auto f) {  // f(place)
+    for_buckets(c, PARTS ? log_b + log_parts : log_b, [&](unsigned b, int halo) {
+      if constexpr (PARTS) {
+        if (b >> log_b != part) return;
+        b &= (1u << log_b) - 1u;
+      }
+      f(2 * b + halo);
+    });
+  };
   visit([&](int r, int4 c) {
-    keep[r] = c;
+    if (part == 0) keep[r] = c;
     if (coord_ok(c.x, c.y, c.z, c.w)) {
-      for_buckets(c, log_b, [&](unsigned b, int halo) { atomicAdd(&place[2 * b + halo], 1u); });
-    } else {
+      visit_copies(c, [&](unsigned at) { atomicAdd(&place[at], 1u); });
+    } else if (part == 0) {
       flags = (unsigned)FLAG_RANGE;
       for (int k = 0; k < V; ++k) map[(long long)r * V + k] = -1;
       mask[r] = 0u;
     }
   });
   __syncthreads();
-  if (t == 0) dealer_flags[w] = flags;
+  if (t == 0 && part == 0) dealer_flags[w] = flags;
   // counts -> first places, as many cells per thread as there are, four at a time
   const int share = max(cells / kDealThreads, 4), c0 = min(t * share, cells), c1 = min(c0 + share, cells);
   unsigned mine = 0;
@@ -1246,8 +1258,9 @@ __global__ void __launch_bounds__(kDealThreads)
     if (!coord_ok(c.x, c.y, c.z, c.w)) return;
     const unsigned long long key = pack_key(c.x, c.y, c.z, c.w);
     const Dealt e{(unsigned)key, (unsigned)(key >> 32), r};
-    for_buckets(c, log_b, [&](unsigned b, int halo) { my_entries[atomicAdd(&place[2 * b + halo], 1u)] = e; });
+    visit_copies(c, [&](unsigned at) { my_entries[atomicAdd(&place[at], 1u)] = e; });
   });
+  if (part) return;
   if (w == 0) {
     if (t == 0) ctl->flags = 0, ctl->count = 0, ctl->tick_top = 0;
     if (t < kPairSlots) {
@@ -1270,8 +1283,8 @@ __global__ void __launch_bounds__(kDealThreads)
 // the first wave only, after the others have left: two returning atomics in a row, awaited by the
 // whole workgroup, would keep all of its waves.  Every value the last workgroup
 // reads was produced by an atomic whose return its producer waited for before counting itself in,
-// and is read with an atomic, so no cache write-back is needed.
-__device__ __forceinline__ void publish_pairs(unsigned wg_pairs, unsigned wg_flags, Ctl* ctl, HostResult* host) {
+// and is read with an atomic, so no cache write-back is needed.  launches: one after the other, of equal grids.
+__device__ __forceinline__ void publish_pairs(unsigned wg_pairs, unsigned wg_flags, unsigned launches, Ctl* ctl, HostResult* host) {
   constexpr unsigned long long kArrive = 1ull << 40;
   int last = 0;
   if (threadIdx.x == 0) {
@@ -1281,7 +1294,7 @@ __device__ __forceinline__ void publish_pairs(unsigned wg_pairs, unsigned wg_fla
     before = atomicAdd(&ctl->pairs[slot * 16], (unsigned long long)wg_pairs + kArrive);
     const unsigned slot_wgs = (gridDim.x - slot + kPairSlots - 1) / kPairSlots;
     const unsigned used_slots = gridDim.x < (unsigned)kPairSlots ? gridDim.x : (unsigned)kPairSlots;
-    if ((unsigned)(before >> 40) + 1 == slot_wgs) last = atomicAdd(&ctl->tick_top, 1u) + 1 == used_slots;
+    if ((unsigned)(before >> 40) + 1 == slot_wgs * launches) last = atomicAdd(&ctl->tick_top, 1u) + 1 == used_slots;
   }
   last = __builtin_amdgcn_readfirstlane(last);
   if (last) {
@@ -1336,7 +1349,8 @@ __device__ __forceinline__ void probe_bucket_column(int b, int tx, int ty, int z
 // rows that were not looked up have no neighbours.
 __global__ void __launch_bounds__(kBucketThreads)
     k_probe_buckets(const Dealt* __restrict__ entries, const unsigned* __restrict__ starts, const unsigned* __restrict__ dealer_flags,
-                    int dealers, int per, int log_b, int* __restrict__ map, unsigned* __restrict__ mask, Ctl* ctl, HostResult* host) {
+                    int dealers, int per, int log_b, unsigned parts, int* __restrict__ map, unsigned* __restrict__ mask, Ctl* ctl,
+                    HostResult* host) {
   constexpr int V = 27, LPR = 9, RPW = 7, kWaves = kBucketThreads / 64;
   constexpr unsigned slot_mask = (1u << kRunSlotBits) - 1u;
   __shared__ BucketRun tab[1 << kRunSlotBits];
@@ -1487,7 +1501,7 @@ __global__ void __launch_bounds__(kBucketThreads)
   unsigned sum = 0;
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) sum += wave_pairs[w];
-  publish_pairs(sum, s_flags, ctl, host);
+  publish_pairs(sum, s_flags, parts, ctl, host);
 }
 
 // ---- small submanifold 3x3x3 builds in one launch ----
@@ -2056,14 +2070,19 @@ template <typename F> int allow_lds(F kernel, int bytes, std::atomic<bool>& done
 
 // The buckets of a submanifold 3x3x3 build.  Up to 512, of 64 rows at least: they all run at once; from then on 256 rows a bucket,
 // which weighs a workgroup's fixed 5 us against the longest bucket (us, with 128, 256 rows a bucket: 60k rows of a scan 23, 28; of a room 26, 35;
-// 100k 30, 26; 400k 82, 67; with 350: buckets beyond kBucketRows, 300k of a room 83 against 64).
+// 100k 30, 26; 400k 82, 67; with 350: buckets beyond kBucketRows, 300k of a room 83 against 64).  There are 2^kMaxBucketBits of them at
+// most, whose counts are what a dealer holds in LDS.  Where they would have more than 512 rows (with the copies up to kBucketRows, and
+// beyond that look-ups once per round), the rows are dealt in parts, each a dealing and a look-up launch over its share of the buckets.
+// Waited builds with a table of runs in memory, in rounds, in parts, ms: 8M rows, 15 % of the cells of their box 3.6, 1.6, 1.6; 16M 7.9, 5.0,
+// 3.6; 40M 22, 31, 15; 0.2 % 4.9, 1.4, 1.4; 10.5, 7.0, 3.1; 23, 42, 13.
 struct Buckets {
-  int dealers, per, log_b = 6;
+  int dealers, per, log_b = 6, log_parts = 0;
   size_t entries, starts, bytes;
   explicit Buckets(int64_t N) {
     per = (int)std::max<int64_t>(round_up(ceil_div(N, kDealers), kDealThreads), kDealThreads);
     dealers = (int)ceil_div(N, per);
     while (log_b < kMaxBucketBits && (log_b < 9 ? (int64_t)64 << log_b : (int64_t)256 << log_b) < N) ++log_b;
+    while (((int64_t)512 << (kMaxBucketBits + log_parts)) < N) ++log_parts;
     entries = (size_t)dealers * per * kCopies * sizeof(Dealt);
     starts = (size_t)dealers * ((2 << log_b) + 1) * sizeof(unsigned);
     bytes = entries + starts + (size_t)dealers * sizeof(unsigned);
@@ -2080,9 +2099,10 @@ int build_submanifold3(spconv_kmap* km, const int4* rows, int64_t N, bool async,
   const bool small = N <= kSmallRows;
   const Buckets bk(N);
   const int small_lds = (int)round_up(N, 2) * 8 + small_slots((int)std::min<int64_t>(N, kSmallRows)) * 4;
-  static std::atomic<bool> deal_lds_set{false}, small_lds_set{false};
+  static std::atomic<bool> deal_lds_set{false}, deal_parts_lds_set{false}, small_lds_set{false};
   if (small) SPC_TRY(allow_lds(k_build_small3, kSmallRows * 8 + small_slots(kSmallRows) * 4, small_lds_set));
-  else SPC_TRY(allow_lds(k_deal_rows, deal_lds(kMaxBucketBits), deal_lds_set));
+  else if (bk.log_parts) SPC_TRY(allow_lds(k_deal_rows<true>, deal_lds(kMaxBucketBits), deal_parts_lds_set));
+  else SPC_TRY(allow_lds(k_deal_rows<false>, deal_lds(kMaxBucketBits), deal_lds_set));
   SPC_TRY(own_rows.alloc((size_t)N * 16));
   SideMap& side = km->out_side;
   side.rows = N;
@@ -2101,11 +2121,14 @@ int build_submanifold3(spconv_kmap* km, const int4* rows, int64_t N, bool async,
     Dealt* const entries = dealt.as<Dealt>();
     unsigned* const starts = reinterpret_cast<unsigned*>(dealt.as<char>() + bk.entries);
     unsigned* const flags = reinterpret_cast<unsigned*>(dealt.as<char>() + bk.entries + bk.starts);
-    hipLaunchKernelGGL(k_deal_rows, dim3((unsigned)bk.dealers), dim3(kDealThreads), deal_lds(bk.log_b), st, rows, (int)N, bk.per, bk.log_b,
-                       entries, starts, flags, own_rows.as<int4>(), (long long)side.rows_pad, side.map.as<int>(),
-                       side.mask.as<unsigned>(), ctl);
-    hipLaunchKernelGGL(k_probe_buckets, dim3(1u << bk.log_b), dim3(kBucketThreads), 0, st, entries, starts, flags, bk.dealers, bk.per,
-                       bk.log_b, side.map.as<int>(), side.mask.as<unsigned>(), ctl, hc->dev);
+    const unsigned parts = 1u << bk.log_parts;
+    for (unsigned part = 0; part < parts; ++part) {
+      hipLaunchKernelGGL(parts > 1 ? k_deal_rows<true> : k_deal_rows<false>, dim3((unsigned)bk.dealers), dim3(kDealThreads), deal_lds(bk.log_b), st, rows, (int)N, bk.per, bk.log_b,
+                         bk.log_parts, part, entries, starts, flags, own_rows.as<int4>(), (long long)side.rows_pad, side.map.as<int>(),
+                         side.mask.as<unsigned>(), ctl);
+      hipLaunchKernelGGL(k_probe_buckets, dim3(1u << bk.log_b), dim3(kBucketThreads), 0, st, entries, starts, flags, bk.dealers, bk.per,
+                         bk.log_b, parts, side.map.as<int>(), side.mask.as<unsigned>(), ctl, hc->dev);
+    }
   }
   // (a waited build: a kernel of its own reports the end, and once it runs, the stores before it are visible to every stream)
   if (small) hipLaunchKernelGGL(k_publish<kPublishWord>, dim3(1), dim3(64), 0, st, ctl, hc->dev);

@@ -47,3 +47,67 @@ def test_fp32_tensors_beyond_4_gib():
                 want[k] += x[b].double().t().contiguous() @ g[a].double()
         for cfg in (None, sp.Config(wgrad_pairs=5000)):
             assert _err(sp.wgrad(x, g, km, cfg), want) <= 1e-4
+
+
+def _scattered_rows(n, fill, gen):
+    side = int((n / fill) ** (1 / 3)) + 1
+    flat = torch.unique(torch.randint(0, side ** 3, (int(n * 1.3),), generator=gen, device="cuda"))
+    flat = flat[torch.randperm(len(flat), generator=gen, device="cuda")][:n]
+    assert len(flat) == n
+    return side, flat, torch.stack([torch.zeros_like(flat), flat // side ** 2, flat // side % side, flat % side], 1).to(torch.int32)
+
+
+@pytest.mark.parametrize("n,fill", [(8_388_608, 0.2), (8_388_609, 0.2), (17_000_001, 0.003)])
+def test_submanifold_builds_of_many_millions_of_rows(n, fill):
+    """From 8,388,609 rows on the rows are dealt into their buckets in two parts, from 16,777,217 on in four.  Reference: a sorted list
+    of the cells, searched offset by offset.  A row twice, in whichever part, and a row beside the range fail the build."""
+    import paper_2311_12862_amd as sp
+    gen = torch.Generator(device="cuda").manual_seed(n % 1000)
+    side, flat, c = _scattered_rows(n, fill, gen)
+    km = sp.build_kmap(c, 3, 1, asynchronous=n % 2 == 1)
+    M, mask = km.export(), km.export_mask()
+    cells, order = torch.sort(flat)
+    pairs, bits = 0, torch.zeros(n, dtype=torch.int32, device="cuda")
+    for k in range(27):
+        d = (k // 9 - 1, k // 3 % 3 - 1, k % 3 - 1)
+        ok = torch.ones(n, dtype=torch.bool, device="cuda")
+        for a in range(3):
+            ok &= (c[:, 1 + a] + d[a] >= 0) & (c[:, 1 + a] + d[a] < side)
+        to = flat + (d[0] * side + d[1]) * side + d[2]
+        at = torch.searchsorted(cells, to).clamp_(max=n - 1)
+        want = torch.where(ok & (cells[at] == to), order[at], -1).to(torch.int32)
+        assert torch.equal(M[:, k], want), k
+        pairs += int((want >= 0).sum())
+        bits |= (want >= 0).int() << k
+    assert torch.equal(mask, bits)
+    km.status()
+    assert km.n_pairs() == pairs
+    assert torch.equal(km.in_coords(), c)
+    km.destroy()
+    for i in (1, n // 2, n - 1):
+        for bad, status in ((c[i - 1], -3), (torch.tensor([0, 0, 40_000, 0]), -2)):
+            keep = c[i].clone()
+            c[i] = bad
+            with pytest.raises(sp.SpconvError) as e:
+                sp.build_kmap(c, 3, 1)
+            assert e.value.status == status
+            c[i] = keep
+
+
+def test_submanifold_builds_grow_with_the_rows():
+    """24 million rows take 3 to 5 times as long as 8 million (in buckets that a workgroup walks in rounds 9.6 times)."""
+    import time
+    import paper_2311_12862_amd as sp
+    took = []
+    for n in (8_000_000, 24_000_000):
+        c = _scattered_rows(n, 0.002, torch.Generator(device="cuda").manual_seed(7))[2]
+        runs = []
+        for _ in range(6):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            sp.build_kmap(c, 3, 1).destroy()
+            torch.cuda.synchronize()
+            runs.append(time.perf_counter() - t0)
+        took.append(min(runs))
+        del c
+    assert took[1] < 7 * took[0], took
