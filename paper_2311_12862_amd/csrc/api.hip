@@ -99,6 +99,16 @@ void dev_free(void* p) {
   g_pooled_bytes += bytes;
 }
 
+// While a stream is being captured nothing may be allocated, and what is launched runs at the replays, not now.
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) != hipSuccess) {  // (the null stream beside another stream's capture)
+    (void)hipGetLastError();
+    return true;
+  }
+  return status != hipStreamCaptureStatusNone;
+}
+
 namespace {
 
 bool dtype_ok(int d) { return d == SPCONV_F32 || d == SPCONV_F16 || d == SPCONV_BF16; }
@@ -273,16 +283,6 @@ bool auto_sorted(int V, int64_t rows, int64_t rows_src, int c_red, int c_cols, s
   // a submanifold map (as many rows on both sides) serves the layers of a stage, a strided one its layer and a gradient
   const double calls = rows == rows_src ? 2.5 : 2.0;
   return calls * unit * (double)rows * c_red * c_cols >= 23.0 + 1.3e-4 * (double)rows;
-}
-
-// While a stream is being captured nothing may be allocated, and what is launched runs at the replays, not now.
-bool capturing(hipStream_t st) {
-  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &status) != hipSuccess) {  // (the null stream beside another stream's capture)
-    (void)hipGetLastError();
-    return true;
-  }
-  return status != hipStreamCaptureStatusNone;
 }
 
 // The plan of a call without a configuration: the library's own order where it exists; where it does not, the order is made
@@ -625,6 +625,7 @@ SPCONV_API int spconv_kmap_drop_plans(spconv_kmap* km) {
   if (km->in_ref.use_count() == 1) {  // (a transposed partner uses this table as its own map)
     km->in_side.map.release();
     km->in_side.mask.release();
+    km->in_side.cands.release();
     km->in_side.ready = false;
   }
   km->pair_list.reset();

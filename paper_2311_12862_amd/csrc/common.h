@@ -30,6 +30,7 @@ int hip_fail(hipError_t e, const char* what, const char* file, int line);
   } while (0)
 #define SPC_LAUNCH_CHECK() SPC_HIP(hipGetLastError())
 
+bool capturing(hipStream_t st);
 void* dev_alloc(size_t bytes);
 void dev_free(void* p);
 // Names the stream that the pool's requests and returns of this thread belong to.
@@ -112,7 +113,8 @@ struct SideMap {      // one output-stationary table: rows x V
   DevBuf map;         // int32 [rows_pad][V]
   DevBuf mask;        // uint32 [rows_pad]
   // The input side of a stride-2 build over the box: int32 [n_in][8] (K = 2: [n_in][1]), the outputs that each input row has an offset
-  // to, -1 where there is none; the side is made from them without a search.  Empty where they would be more than the output side is.
+  // to, -1 where there is none; the side is made from them without a search, and they go when it is there.  Empty where they would be
+  // more than the output side is.
   DevBuf cands;
   bool ready = false;
   std::map<std::pair<int, int>, std::unique_ptr<IgemmPlan>> plans;  // (n_split, flags)

@@ -2681,6 +2681,9 @@ int kmap_build_in_side(spconv_kmap* km, hipStream_t st) {
                          side.mask.as<unsigned>());
     SPC_LAUNCH_CHECK();
     side.ready = true;
+    // Nothing else reads them: the build that wrote them was waited for, so their next user on this stream comes behind the launch above.
+    // (Under capture that launch runs at the replays.)
+    if (!capturing(st)) side.cands.release();
     return SPCONV_OK;
   }
   SPC_TRY(alloc_side(km->in_side, km->n_in, V, st, true));

@@ -848,3 +848,64 @@ def test_stride2_build_with_a_far_point_takes_little_longer(sp):
             took.append(time.perf_counter() - t0)
         best.append(min(took))
     assert best[1] < 2.5 * best[0], best
+
+
+@pytest.mark.parametrize("K", [2, 3])
+def test_candidates_go_when_the_input_side_is_there(sp, K):
+    """What a stride-2 kmap holds beside its tables is given back: with the input side that is made from it, and when plans are dropped
+    (behind which the input side is searched for, and the same)."""
+    from _util import TOL
+    c = gen.lidar_scene(31, target_n=20_000)
+    ref = oc.build_kmap(c, K, 2)
+    V, n = K ** 3, len(c)
+    out_pad, in_pad = -(-ref.n_out // 256) * 256, -(-n // 256) * 256
+    (x32, x), (w32, w), (g32, g) = make_layer(ref.n_in, ref.n_out, 16, 16, V, "f16", 4)
+    want, coords, map_order = oc.dgrad(g32, w32, ref.M, ref.n_in), coords_dev(c), sp.Config(n_split=0)
+    tables = n * 16 + max(ref.n_out, n) * 16 + max(out_pad, in_pad) * (V + 1) * 4  # (at most: made for as many outputs as inputs)
+    with _CountingAllocator(sp) as mem:
+        km = sp.build_kmap(coords, K, 2)
+        built = mem.held()
+        assert built > tables
+        assert norm_err(sp.dgrad(g, w, km, map_order), want) <= TOL["f16"]
+        km.n_pairs()
+        assert mem.held() <= tables + in_pad * (V + 1) * 4
+        for _ in range(2):
+            km.drop_plans()
+            assert mem.held() <= tables
+            assert norm_err(sp.dgrad(g, w, km, map_order), want) <= TOL["f16"]
+        km.destroy()
+        km = sp.build_kmap(coords, K, 2)
+        assert mem.held() == built
+        km.drop_plans()
+        assert mem.held() <= tables
+        assert norm_err(sp.dgrad(g, w, km, map_order), want) <= TOL["f16"]
+        km.destroy()
+        assert not mem.live
+
+
+@pytest.mark.parametrize("K", [2, 3])
+def test_partner_of_a_kmap_that_goes_at_once(sp, K):
+    """The partner's table is made on another stream, from what the source's build left; the source goes before that has run, and its
+    memory to builds on its own stream."""
+    import torch
+    c = gen.lidar_scene(32, target_n=30_000)
+    ref = oc.build_kmap(c, K, 2)
+    T = np.full((len(c), K ** 3), -1, np.int32)
+    out, k = np.nonzero(ref.M >= 0)
+    T[ref.M[out, k], k] = out
+    coords, other = coords_dev(c), coords_dev(c[::-1].copy())
+    here, there = torch.cuda.Stream(), torch.cuda.Stream()
+    busy = torch.randn(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+    for _ in range(5):
+        km = sp.build_kmap(coords, K, 2, stream=here)
+        with torch.cuda.stream(there):
+            for _ in range(4):
+                busy @ busy   # (the partner's launch waits behind these)
+        up = km.transpose(stream=there)
+        km.destroy()
+        for _ in range(3):
+            sp.build_kmap(other, K, 2, stream=here).destroy()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(up.export().cpu().numpy(), T)
+        up.destroy()
