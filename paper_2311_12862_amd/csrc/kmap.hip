@@ -2253,11 +2253,12 @@ struct CoarseTable {
 };
 
 // Stride-2 builds (K = 2, 3) over a bit per cell of the coarse points' box; kRetryTable where the box is too large (with what the
-// table needs, see CoarseTable), or the memory does not suffice (up to 520 bytes a row for bits and prefixes, and tables for
-// N outputs: the hash table and tables for the outputs that there are need less).
+// table needs, see CoarseTable), or the memory does not suffice: up to 512 bytes a row for bits and prefixes, else two thirds of that
+// for boxes of two thirds as many cells (a scan's has a fifth), and tables for N outputs.  The hash table and tables for the outputs
+// that there are need less.
 int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t st, CoarseTable* fallback) {
   const int V = K * K * K;
-  const int64_t max_words = std::min<int64_t>(std::max<int64_t>(N * (kCellsPerRow / 32), 1 << 15), kMaxBoxWords);
+  int64_t max_words = std::min<int64_t>(std::max<int64_t>(N * (kCellsPerRow / 32), 1 << 15), kMaxBoxWords);
   // about 400 rows to a chunk; dealers of 512 rows and more
   int log_chunks = 6;
   while ((1 << log_chunks) < kMaxChunks && ((int64_t)400 << log_chunks) < N) ++log_chunks;
@@ -2270,12 +2271,21 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
   SideMap& side = km->out_side;
   const int64_t most = round_up(N, kRowPad);
   const size_t base_bytes = most_groups(chunks) * sizeof(unsigned), partial_bytes = (size_t)kBoxBlocks * 9 * sizeof(int);
-  if (ctl_buf.alloc(sizeof(Ctl)) != SPCONV_OK || own_rows.alloc((size_t)N * 16) != SPCONV_OK ||
-      coarse_rows.alloc((size_t)N * 16) != SPCONV_OK ||
-      small.alloc(base_bytes + sizeof(Box) + partial_bytes + ((size_t)chunks + (size_t)dealers * (chunks + 1)) * sizeof(unsigned)) != SPCONV_OK ||
-      cells.alloc((size_t)max_words * sizeof(Cells)) != SPCONV_OK || keys.alloc((size_t)N * 8) != SPCONV_OK ||
-      side.map.alloc((size_t)most * V * sizeof(int)) != SPCONV_OK || side.mask.alloc((size_t)most * sizeof(unsigned)) != SPCONV_OK)
-    return kRetryTable;
+  auto buffers = [&]() {
+    SPC_TRY(ctl_buf.alloc(sizeof(Ctl)));
+    SPC_TRY(own_rows.alloc((size_t)N * 16));
+    SPC_TRY(coarse_rows.alloc((size_t)N * 16));
+    SPC_TRY(small.alloc(base_bytes + sizeof(Box) + partial_bytes + ((size_t)chunks + (size_t)dealers * (chunks + 1)) * sizeof(unsigned)));
+    SPC_TRY(cells.alloc((size_t)max_words * sizeof(Cells)));
+    SPC_TRY(keys.alloc((size_t)N * 8));
+    SPC_TRY(side.map.alloc((size_t)most * V * sizeof(int)));
+    return side.mask.alloc((size_t)most * sizeof(unsigned));
+  };
+  if (buffers() != SPCONV_OK) {
+    max_words = max_words * 2 / 3 / 4 * 4;
+    for (DevBuf* b : {&cells, &side.map, &side.mask}) b->release();
+    if (buffers() != SPCONV_OK) return kRetryTable;
+  }
   Ctl* ctl = ctl_buf.as<Ctl>();
   // (two tables in the place of the cells, the keys in that of the rows' cells: too large from two million rows on)
   const int table_cap = log2_capacity(N);

@@ -660,7 +660,7 @@ class _CountingAllocator:
     """Device memory for the library, counted; requests beyond `limit` live bytes are refused."""
 
     def __init__(self, sp, limit=None):
-        self.sp, self.limit, self.live, self.most = sp, limit, {}, 0
+        self.sp, self.limit, self.live, self.most, self.refused = sp, limit, {}, 0, []
 
     def held(self):
         return sum(t.numel() for t in self.live.values())
@@ -671,6 +671,7 @@ class _CountingAllocator:
 
         def alloc(n, stream):
             if self.limit is not None and self.held() + n > self.limit:
+                self.refused.append(n)
                 return 0
             t = torch.empty(max(n, 1), dtype=torch.uint8, device="cuda")
             self.live[t.data_ptr()] = t
@@ -717,12 +718,30 @@ def test_stride2_builds_where_memory_is_short(sp, K):
     ref = oc.build_kmap(c, K, 2)
     coords = coords_dev(c)
     _check_kmap(sp, c, K, 2, False)
-    # room for the bits and prefixes of a build over the box, and for two sets of coordinates, but not for its map
-    with _CountingAllocator(sp, limit=len(c) * (384 + 32) + (1 << 19)) as mem:
+    # room for the (fewer) bits and prefixes of a build over the box, cells and two sets of coordinates, but not for its map
+    with _CountingAllocator(sp, limit=len(c) * (342 + 8 + 32) + 300_000) as mem:
         km = sp.build_kmap(coords, K, 2)
+        assert -(-len(c) // 256) * 256 * K ** 3 * 4 in mem.refused
         np.testing.assert_array_equal(km.export().cpu().numpy(), ref.M)
         km.destroy()
         assert not mem.live
+
+
+@pytest.mark.parametrize("K", [2, 3])
+def test_stride2_builds_over_fewer_cells_where_memory_is_short(sp, K):
+    """Without 512 bytes a row for bits and prefixes, but with 384 of them: the box is still taken, and one that is too large for these is
+    left to the table."""
+    c = gen.lidar_scene(41, target_n=30_000)
+    ref, n = oc.build_kmap(c, K, 2), len(c)
+    far = _with_far_point(c, 1, 1900)
+    for rows, over_box in ((c, True), (far, False)):
+        with _CountingAllocator(sp, limit=n * (384 + 32 + 8 + 4 * K ** 3 + 4)) as mem:
+            km = sp.build_kmap(coords_dev(rows), K, 2)
+            assert mem.refused and mem.refused[0] >= 512 * n and mem.most > n * 350
+            M = km.export().cpu().numpy()
+            km.destroy()
+            assert not mem.live
+        np.testing.assert_array_equal(M, ref.M if over_box else oc.build_kmap(rows, K, 2).M)
 
 
 @pytest.mark.parametrize("side,lo,batches", [(18, -32768, 1), (40, 32768 - 40, 1), (18, -9, 7), (12, 32768 - 12, 31)])
