@@ -100,19 +100,21 @@ __global__ void __launch_bounds__(256)
   val[r] = r;
 }
 
-// ---- bitmask argsort in few launches (maps of up to kSortMaxWgs * kSortWg rows) ----
+// ---- bitmask argsort in few launches (maps of up to sort_max_wgs() * kSortWg rows) ----
 // Stable least-significant-digit radix sort of (key, row): one launch per digit, and one in front
 // that clears three counters.  A workgroup owns kSortWg consecutive items, each of its four waves
 // a quarter.  It counts its items per digit value, publishes the counts as a row of the matrix
-// hist[workgroup][value], and waits until every workgroup of the launch has done so (all of them
-// are resident: at most kSortMaxWgs workgroups on 256 CUs; the wait is bounded all the same, and a
+// hist[workgroup][value], and waits until every workgroup of the launch has done so (the GPU holds all of
+// them at once, see sort_max_wgs; the wait is bounded all the same, and a
 // wait that runs out fails the sort).  It then finds its own offsets by summing the rows in front
 // of it (a coalesced read of at most 768 KB, in place of a scan launch) and ranks its items with
 // ballots as the general sort does.  The first digit's keys come straight from the masks, the last
 // digit writes only the row order.
 constexpr int kSortWg = 2048, kSortWaves = 4, kSortThreads = 64 * kSortWaves;
 constexpr int kSortWave = kSortWg / kSortWaves, kSortSteps = kSortWave / 64;
-// (300k rows, three digits: 61 us, with histograms, scans and scatters in launches of their own 87)
+// Whole plans of one part, with histograms, scans and scatters in launches of their own and so, us: 100k rows 95, 52; 131k 98, 56; 200k
+// 106, 67; 300k 116, 81; 393k 129, 95; of two parts 300k 139, 90; 393k 150, 105.  It stays ahead beyond (254 workgroups at 520k rows: 142,
+// 126), but a launch that needs a place on nearly every CU waits for whatever other streams run on any of them.
 constexpr int kSortMaxWgs = 192;
 constexpr int kSortMaxBits = 10, kSortMaxBins = 1 << kSortMaxBits;
 constexpr unsigned kSortSpinLimit = 1u << 20;  // polls of the arrival counter (about a second)
@@ -595,10 +597,33 @@ __global__ void __launch_bounds__(256) k_make_items(const int* __restrict__ seg,
   }
 }
 
+// Workgroups of a digit's launch: kSortMaxWgs, or as many as the GPU (or the partition of one that the process sees) holds at once.
+// They wait for each other, so a launch of more would spin its waits out.
+int sort_max_wgs() {
+  static const int most = [] {
+    int dev = 0, cus = 0, per_cu = kSortMaxWgs;
+    bool known = hipGetDevice(&dev) == hipSuccess &&
+                 hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess;
+    auto fits = [&](auto kernel) {
+      int n = 0;
+      known = known && hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, kSortThreads, 0) == hipSuccess;
+      per_cu = std::min(per_cu, n);
+    };
+    fits(k_msort_pass<true, true>);
+    fits(k_msort_pass<true, false>);
+    fits(k_msort_pass<false, false>);
+    fits(k_msort_pass<false, true>);
+    fits(k_msort_pass<false, false, true>);
+    if (!known) (void)hipGetLastError();
+    return known ? std::min(kSortMaxWgs, cus * per_cu) : 0;
+  }();
+  return most;
+}
+
 }  // namespace
 
 // Sorts n 32-bit keys of key_bits significant bits with the one-launch-per-digit sort above (at
-// most kSortMaxWgs * kSortWg keys: SPCONV_EINVAL beyond, and the caller takes the general sort).
+// most sort_max_wgs() * kSortWg keys: SPCONV_EINVAL beyond, and the caller takes the general sort).
 // A wait that runs out sets error_bit in *error_word (device memory that the caller reads back
 // later): the keys are then not sorted and the caller must sort them again.
 int msort_keys_u32(uint32_t* key_a, uint32_t* key_b, int64_t n, int key_bits, unsigned* error_word, unsigned error_bit,
@@ -606,7 +631,7 @@ int msort_keys_u32(uint32_t* key_a, uint32_t* key_b, int64_t n, int key_bits, un
   *in_b = 0;
   if (n <= 1 || key_bits <= 0) return SPCONV_OK;
   const int n_wg = (int)ceil_div(n, kSortWg);
-  if (n_wg > kSortMaxWgs || key_bits > 32) return SPCONV_EINVAL;
+  if (n_wg > sort_max_wgs() || key_bits > 32) return SPCONV_EINVAL;
   DevBuf hist;
   const size_t hist_elems = (size_t)n_wg * kSortMaxBins;
   const int passes = (key_bits + kSortMaxBits - 1) / kSortMaxBits;
@@ -702,7 +727,7 @@ int plan_get(spconv_kmap* km, SideMap& side, int n_split, int flags, hipStream_t
       DevBuf key_a, key_b, val_a, val_b, hist;
       const size_t n = (size_t)p->rows;
       const int n_wg = (int)ceil_div(p->rows, kSortWg);
-      const bool few_launches = n_wg <= kSortMaxWgs;
+      const bool few_launches = n_wg <= sort_max_wgs();
       SPC_TRY(key_a.alloc(n * 4));
       SPC_TRY(key_b.alloc(n * 4));
       SPC_TRY(val_a.alloc(n * 4));
