@@ -262,8 +262,7 @@ def test_sort_invariants_on_the_input_side_of_a_strided_map(sp, n_split):
 
 @pytest.mark.parametrize("target_n", [2048, 2049, 131072, 140000])
 def test_sort_invariants_across_the_sizes_that_change_the_sort(sp, target_n):
-    """One workgroup of the few-launch sort, one row more, its largest map (64 workgroups), and a
-    map beyond it (the general radix sort).  The masks come from the library's own map, which
+    """One workgroup of the few-launch sort, one row more, and 64 and 69 workgroups.  The masks come from the library's own map, which
     test_gpu_kmap holds against the oracle bit by bit; here only the order is at stake."""
     c = gen.lidar_scene(79, target_n=target_n + 200)[:target_n]
     km = sp.build_kmap(coords_dev(c), 3, 1)
@@ -278,12 +277,15 @@ def test_sort_invariants_across_the_sizes_that_change_the_sort(sp, target_n):
 
 @pytest.mark.parametrize("n", [300_000, 192 * 2048, 192 * 2048 + 1])
 def test_sort_invariants_with_many_workgroups(sp, n):
-    """The few-launch sort with up to 192 workgroups, and the general sort one row beyond."""
+    """The few-launch sort with up to 192 workgroups, and the general sort one row beyond, of the whole mask and of two parts."""
     c = gen.uniform_cloud(n, 150, seed=n)
     km = sp.build_kmap(coords_dev(c), 3, 1)
     mask = km.export_mask().cpu().numpy().view(np.uint32).astype(np.uint64)
     perm = km.export_perm(sp.OP_FWD, _cfg(sp, 1), 0).cpu().numpy()
     _check_order(perm, mask, n)
+    for i, (lo, hi) in enumerate(oc.split_ranges(27, 2)):
+        perm = km.export_perm(sp.OP_FWD, _cfg(sp, 2), i).cpu().numpy()
+        _check_order(perm, (mask >> np.uint64(lo)) & np.uint64((1 << (hi - lo)) - 1), n)
 
 
 @pytest.mark.parametrize("kernel", [1, 2])

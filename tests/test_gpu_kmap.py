@@ -521,7 +521,9 @@ def test_stride2_masks_by_rows_of_a_wave(sp, K, n_coarse):
     (80_000, (1016, 1010, 1160), 0),
     (40, (60_000, 60_000, 60_000), -30_000), (2000, (1, 65_000, 64_000), -32_768),  # boxes that are left to the table: one
     (16_383, (3000, 3000, 3000), -7), (16_385, (3000, 3000, 3000), 9),              # or many workgroups, the verdict taken late or early,
-    (100_000, (4000, 5000, 700), -2000), (150_000, (9000, 9000, 500), 1)])          # the one-launch and the general sort
+    (100_000, (4000, 5000, 700), -2000), (150_000, (9000, 9000, 500), 1),           # keys of more than 32 bits
+    (150_000, (1600, 1600, 1600), 0),  # K = 3: the sort of one launch per digit,
+    (450_000, (2000, 2000, 2000), 0)])  # and the general one (from 393,217 coarse points on)
 def test_stride2_boxes(sp, K, n, span, lo):
     """Stride-2 builds keep one bit per cell of the coarse points' box: boxes around word, chunk and workgroup limits, flat
     and long ones, negative and odd corners, several batches, and boxes too large for it, whose coarse points go through a hash table
@@ -560,7 +562,7 @@ def test_stride2_box_and_table_too_large(sp):
 
 @pytest.mark.parametrize("K,n", [(3, 79_999), (3, 80_000), (3, 80_321), (5, 49_999), (5, 50_007)])
 def test_submanifold_builds_on_both_sides_of_the_filter(sp, K, n):
-    """From 80,000 (5x5x5: 50,000) rows on the probe keeps a filter of the existing runs: half of the rows in a dense slab,
+    """5x5x5: from 50,000 rows on the probe keeps a filter of the existing runs (3x3x3 builds of these sizes go through buckets): half of the rows in a dense slab,
     half scattered, two batches, negative coordinates; and duplicates are still found."""
     rng = np.random.default_rng(n)
     c = np.concatenate([rng.integers(0, (300, 300, 3), size=(n, 3)), rng.integers(-9000, 9000, size=(n, 3))])
