@@ -31,7 +31,7 @@ constexpr unsigned long long kEmpty = ~0ull;
 // SORT: a sort's bounded wait ran out; BOX: the coarse points' bounding box is too large for a bit per cell
 enum : unsigned long long { FLAG_RANGE = 1, FLAG_DUP = 2, FLAG_FULL = 4, FLAG_SORT = 8, FLAG_BOX = 16 };
 constexpr int kRetryGeneralSort = 1;  // (internal) build again with the general sort
-constexpr int kRetryTable = 2;        // (internal) build with a hash table of the coarse points
+constexpr int kRetryTable = 2;        // (internal) build with a hash table (of the coarse points, or of a submanifold map's rows)
 
 // Control block read back by the host at the build's synchronisation point.  The pair counter
 // is spread over 64 cache lines (one atomic per probe workgroup) so that the adds do not queue
@@ -2090,7 +2090,8 @@ struct Buckets {
 };
 
 // Submanifold 3x3x3 build: rows into buckets, look-ups (whose last workgroup publishes the result to
-// pinned host memory); small maps: one launch, and k_publish.
+// pinned host memory); small maps: one launch, and k_publish.  kRetryTable where there is no memory for the buckets (about 100 bytes a
+// row, room for a row in eight of them; a table of single rows takes 32 to 64).
 int build_submanifold3(spconv_kmap* km, const int4* rows, int64_t N, bool async, hipStream_t st) {
   const int V = 27;
   DevBuf ctl_buf, own_rows, dealt;
@@ -2109,7 +2110,7 @@ int build_submanifold3(spconv_kmap* km, const int4* rows, int64_t N, bool async,
   side.rows_pad = round_up(N, kRowPad);
   SPC_TRY(side.map.alloc((size_t)side.rows_pad * V * sizeof(int)));
   SPC_TRY(side.mask.alloc((size_t)side.rows_pad * sizeof(unsigned)));
-  if (!small) SPC_TRY(dealt.alloc(bk.bytes));
+  if (!small && dealt.alloc(bk.bytes) != SPCONV_OK) return capturing(st) ? SPCONV_ENOMEM : kRetryTable;  // (that build waits)
   HostCtl* hc = host_ctl_acquire();
   if (!hc) return SPCONV_ENOMEM;
   hc->res.word = hc->res.ready = 0;  // (pinned memory: visible to the kernels launched below)
@@ -2452,9 +2453,12 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
     return SPCONV_OK;
   }
   if (K == 3 && stride == 1 && !transposed && !dilate) {
-    SPC_TRY(build_submanifold3(km.get(), rows, N, async, st));
-    *out = km.release();
-    return SPCONV_OK;
+    const int status = build_submanifold3(km.get(), rows, N, async, st);
+    if (status != kRetryTable) {
+      SPC_TRY(status);
+      *out = km.release();
+      return SPCONV_OK;
+    }
   }
   CoarseTable made;  // (log_cap 0: nothing of it)
   if (stride == 2 && (K == 2 || K == 3) && !transposed && bit_per_cell) {
@@ -2642,7 +2646,8 @@ int kmap_build_impl(const int32_t* coords, int64_t N, int K, int stride, int tra
     // (the probe ran before this synchronisation: its pair count is final)
     if (from_inputs && h.entries != h.pairs) h.flags |= FLAG_DUP;  // two rows wrote one entry
     if (h.flags & FLAG_SORT) return kRetryGeneralSort;
-    SPC_TRY(flags_status(h.flags));
+    km->build_status = flags_status(h.flags);
+    if (!(async && K == 3 && km->submanifold())) SPC_TRY(km->build_status);  // (an unwaited build's verdict is spconv_kmap_status's)
     km->n_pairs = (int64_t)h.pairs;
   }
 

@@ -930,3 +930,37 @@ def test_partner_of_a_kmap_that_goes_at_once(sp, K):
         torch.cuda.synchronize()
         np.testing.assert_array_equal(up.export().cpu().numpy(), T)
         up.destroy()
+
+
+@pytest.mark.parametrize("asynchronous", [False, True])
+def test_submanifold_builds_where_memory_is_short(sp, asynchronous):
+    """Without room for the buckets (96 bytes a row and more) the map is built over a table, as it was where 64 were enough; failed builds
+    report as ever, waited for or not, and what an unwaited one leaves can be walked."""
+    c = gen.uniform_cloud(60_000, 80, seed=3, lo=-40)
+    ref, n = oc.build_kmap(c, 3, 1), len(c)
+    pad = -(-n // 256) * 256
+    with _CountingAllocator(sp, limit=n * (16 + 75) + pad * 28 * 4 + 100_000) as mem:
+        km = sp.build_kmap(coords_dev(c), 3, 1, asynchronous=asynchronous)
+        assert mem.refused and min(mem.refused) >= 96 * n
+        np.testing.assert_array_equal(km.export().cpu().numpy(), ref.M)
+        np.testing.assert_array_equal(km.export_mask().cpu().numpy().view(np.uint32)[:n], oc.bitmask(ref.M))
+        np.testing.assert_array_equal(km.in_coords().cpu().numpy(), c)
+        km.status()
+        assert km.n_pairs() == int((ref.M >= 0).sum())
+        km.destroy()
+        for row, status in ((c[5], -3), ([0, 0, 40_000, 0], -2)):
+            bad = c.copy()
+            bad[n // 2] = row
+            if not asynchronous:
+                with pytest.raises(sp.SpconvError) as e:
+                    sp.build_kmap(coords_dev(bad), 3, 1)
+            else:
+                km = sp.build_kmap(coords_dev(bad), 3, 1, asynchronous=True)
+                M = km.export().cpu().numpy()
+                assert M.min() >= -1 and M.max() < n
+                for _ in range(2):
+                    with pytest.raises(sp.SpconvError) as e:
+                        km.status()
+                km.destroy()
+            assert e.value.status == status
+        assert not mem.live
