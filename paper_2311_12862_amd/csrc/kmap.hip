@@ -1992,11 +1992,11 @@ template <Publish WHAT = kPublishAll> int read_ctl(const Ctl* ctl, HostResult* r
   if (!hc) return SPCONV_ENOMEM;
   hc->res.word = hc->res.outputs = hc->res.ready = 0;  // (pinned memory: visible to the kernel launched below)
   hipLaunchKernelGGL(k_publish<WHAT>, dim3(1), dim3(64), 0, st, ctl, hc->dev);
-  const int status = wait_block(hc, WHAT == kPublishWord ? kWaitWord : WHAT == kPublishOutputs ? kWaitWord | kWaitOutputs : kWaitReady,
-                                hipGetLastError(), st);
+  static_assert(WHAT != kPublishWord, "(read by the builds themselves)");
+  const int status = wait_block(hc, WHAT == kPublishOutputs ? kWaitWord | kWaitOutputs : kWaitReady, hipGetLastError(), st);
   if (status == SPCONV_OK) {
     *res = hc->res;
-    if (WHAT == kPublishWord || WHAT == kPublishOutputs) {
+    if (WHAT == kPublishOutputs) {
       res->flags = (res->word >> 48) & 0xFFu;
       res->pairs = res->word & 0xFFFFFFFFFFFFull;
       res->count = res->outputs & ~kHostReady;
