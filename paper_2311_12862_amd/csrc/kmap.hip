@@ -736,61 +736,70 @@ __global__ void __launch_bounds__(kBitsThreads)
   }
 }
 
-// base[group]: the set bits of the group become those before it (the first workgroup's work); the others preset the map (rows up to the
+// base[group]: the set bits of the group become those before it (the first workgroup's work: a quarter of a wave's 256 groups per lane, so
+// that its lines are read once; with each thread's groups in a row it took 8 us at 200k rows); the others preset the map (rows up to the
 // padding).
 __global__ void __launch_bounds__(kBaseThreads)
     k_box_base(const Box* __restrict__ box_in, const unsigned* __restrict__ totals, int chunks, unsigned* __restrict__ base, int V,
                uint4* __restrict__ map, unsigned* __restrict__ mask, Ctl* ctl) {
   constexpr int kWaves = kBaseThreads / 64, Q = kMaxGroups / kBaseThreads / 4, S = kMaxChunks / kBaseThreads;
-  __shared__ unsigned wave_sum[kWaves];
+  __shared__ unsigned sums[Q * kWaves], all;
   const int t = threadIdx.x, lane = t & 63, wib = t >> 6;
   const unsigned groups = box_in->groups();  // (no box: none, and no totals)
-  const unsigned each = (groups + 4 * kBaseThreads - 1) / (4 * kBaseThreads) * 4, first = t * each;  // at most 4 Q
-  uint4 v[Q];
-  unsigned mine = 0;
+  auto scan = [&](unsigned incl) {
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned up = __shfl_up(incl, o);
+      if (lane >= o) incl += up;
+    }
+    return incl;
+  };
   if (blockIdx.x == 0) {
+    uint4 v[Q];
+    unsigned at[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      const unsigned g = first + 4 * q;
-      v[q] = 4 * q < (int)each && g < groups ? reinterpret_cast<const uint4*>(base)[g / 4] : make_uint4(0, 0, 0, 0);
+      const unsigned g = 4 * (q * kBaseThreads + t);
+      v[q] = g < groups ? reinterpret_cast<const uint4*>(base)[g / 4] : make_uint4(0, 0, 0, 0);
     }
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      const unsigned g = first + 4 * q;  // (the last four may be incomplete)
+      const unsigned g = 4 * (q * kBaseThreads + t);  // (the last four may be incomplete)
       if (g + 1 >= groups) v[q].y = 0;
       if (g + 2 >= groups) v[q].z = 0;
       if (g + 3 >= groups) v[q].w = 0;
-      mine += v[q].x + v[q].y + v[q].z + v[q].w;
+      const unsigned mine = v[q].x + v[q].y + v[q].z + v[q].w, incl = 4u * q * kBaseThreads < groups ? scan(mine) : 0u;
+      if (lane == 63) sums[q * kWaves + wib] = incl;
+      at[q] = incl - mine;
     }
-  } else {
-#pragma unroll
-    for (int i = 0; i < S; ++i) mine += groups && t * S + i < chunks ? totals[t * S + i] : 0u;
-  }
-  unsigned incl = mine;
-  for (int o = 1; o < 64; o <<= 1) {
-    const unsigned up = __shfl_up(incl, o);
-    if (lane >= o) incl += up;
-  }
-  if (lane == 63) wave_sum[wib] = incl;
-  __syncthreads();
-  unsigned total = 0, at = incl - mine;
-#pragma unroll
-  for (int i = 0; i < kWaves; ++i) {
-    if (i < wib) at += wave_sum[i];
-    total += wave_sum[i];
-  }
-  const unsigned rows_pad = (total + kRowPad - 1) / kRowPad * kRowPad;
-  if (blockIdx.x == 0) {
+    __syncthreads();
+    if (wib == 0) {
+      static_assert(Q * kWaves == 128, "two sums per lane");
+      const unsigned a = sums[2 * lane], b = sums[2 * lane + 1], incl = scan(a + b);
+      sums[2 * lane] = incl - a - b;
+      sums[2 * lane + 1] = incl - b;
+      if (lane == 63) all = incl;
+    }
+    __syncthreads();
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      const unsigned g = first + 4 * q, y = at + v[q].x, z = y + v[q].y, w = z + v[q].z;
-      if (4 * q < (int)each && g < groups) reinterpret_cast<uint4*>(base)[g / 4] = make_uint4(at, y, z, w);
-      at = w + v[q].w;
+      const unsigned g = 4 * (q * kBaseThreads + t), x = at[q] + sums[q * kWaves + wib], y = x + v[q].x, z = y + v[q].y;
+      if (g < groups) reinterpret_cast<uint4*>(base)[g / 4] = make_uint4(x, y, z, z + v[q].z);
     }
+    const unsigned total = all;
     if (t == 0 && groups) ctl->count = total;  // (else: of the table's points, or none)
-    if (total + t < rows_pad) mask[total + t] = 0u;
+    if (total + t < (total + kRowPad - 1) / kRowPad * kRowPad) mask[total + t] = 0u;
     return;
   }
+  unsigned mine = 0;
+#pragma unroll
+  for (int i = 0; i < S; ++i) mine += groups && i * kBaseThreads + t < chunks ? totals[i * kBaseThreads + t] : 0u;
+  for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
+  if (lane == 0) sums[wib] = mine;
+  __syncthreads();
+  unsigned total = 0;
+#pragma unroll
+  for (int i = 0; i < kWaves; ++i) total += sums[i];
+  const unsigned rows_pad = (total + kRowPad - 1) / kRowPad * kRowPad;
   const long long vecs = (long long)rows_pad * V / 4, step = (long long)(gridDim.x - 1) * kBaseThreads;
   for (long long i = (long long)(blockIdx.x - 1) * kBaseThreads + t; i < vecs; i += step) map[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
 }
@@ -1393,7 +1402,7 @@ __global__ void __launch_bounds__(kBucketThreads)
   }
   __syncthreads();
   const int n_own = before[0][kDealers], n_all = n_own + before[1][kDealers];
-  const bool rounds = n_all > kBucketRows;
+  const bool rounds = __builtin_expect(n_all > kBucketRows, 0);
   auto entry = [&](int i) {
     const int h = i >= n_own ? 1 : 0;
     const int j = h ? i - n_own : i;
@@ -2330,7 +2339,7 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
   check();
   if (early) SPC_TRY(verdict());
   if (!too_large) {
-    hipLaunchKernelGGL(k_box_base, dim3(1 + (unsigned)std::min<int64_t>(ceil_div(N * V, 32768), 256)), dim3(kBaseThreads), 0, st, box, totals,
+    hipLaunchKernelGGL(k_box_base, dim3(1 + (unsigned)std::min<int64_t>(ceil_div(N * V, 16384), 512)), dim3(kBaseThreads), 0, st, box, totals,
                        chunks, base, V, side.map.as<uint4>(), side.mask.as<unsigned>(), ctl);
     check();
     if (!early) SPC_TRY(verdict());
