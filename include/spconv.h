@@ -178,6 +178,8 @@ SPCONV_API int spconv_build_kmap(const int32_t* coords, int64_t N, int K, int st
  * typically one iteration behind).  Until then the pair count is unknown: wgrad sizes its work
  * list from the bound n_out * K^3 (surplus workgroups exit immediately).  A kmap built from
  * invalid rows is safe to run (all indices stay in range) but its results are meaningless.
+ * Where there is no memory for the buckets of such a build (96 bytes a row and more) it goes through a table and is waited for;
+ * its errors still come with spconv_kmap_status.
  * Other map kinds are built synchronously, exactly as by spconv_build_kmap. */
 SPCONV_API int spconv_build_kmap_async(const int32_t* coords, int64_t N, int K, int stride, int transposed,
                                        void* stream, spconv_kmap** out);

@@ -409,10 +409,10 @@ __global__ void __launch_bounds__(256)
 // workgroups, neighbouring groups to different ones (group_at).  The rows are dealt to the chunks of their coarse
 // points, and one workgroup per chunk sets its bits in LDS and writes them with their prefixes: nothing is cleared beforehand and no
 // atomic leaves the CU.  Launches: the box, dealing, bits, group prefixes (and the presets of
-// the map), the map from the input side (and the coordinates), masks.  Against de-duplication through a hash table, a radix sort and table
-// look-ups, and with bits in memory (cleared, marked by an atomic per row, which the memory side takes at 10 per ns, counted), whole
-// 3x3x3 builds in us: LiDAR-like scans of 2k rows 71, 34 -> 35, 10k 80, 36 -> 36, 30k 89, 42 -> 38, 100k 109, 62 -> 49, 200k (127k
-// outputs) 178, 78 -> 64, 400k 227, 118 -> 88; a room of 60k 51 -> 41, 300k 135, 101 -> 79.
+// the map), the map from the input side (and the coordinates), masks.  Whole waited 3x3x3 builds with bits in memory (cleared, marked by an
+// atomic per row, which the memory side takes at 10 per ns, counted) and so, us: LiDAR-like scans of 2k rows 72, 45; 10k 67, 47; 30k 72, 49;
+// 100k 90, 60; 200k (127k outputs) 110, 77; 400k 152, 103; a room of 60k 79, 51; 300k 141, 107 (with the copy of shrink_to_outputs).
+// De-duplication through a hash table, a radix sort and table look-ups took 1.3 to 2.3 times as long as bits in memory.
 // A box of more than kCellsPerRow cells a row (a scan of 5 cm voxels has about 450) is left to the table: the dealing launch
 // empties one in the bitmap's place, the launch behind it fills it, and the host, which reads the box's verdict behind that, goes on
 // with the sort.  Whole builds of points spread over 60,000 cells an axis, us, all through the table and so: 2k rows 150, 152;
@@ -736,9 +736,8 @@ __global__ void __launch_bounds__(kBitsThreads)
   }
 }
 
-// base[group]: the set bits of the group become those before it (the first workgroup's work: a quarter of a wave's 256 groups per lane, so
-// that its lines are read once; with each thread's groups in a row it took 8 us at 200k rows); the others preset the map (rows up to the
-// padding).
+// base[group]: the set bits of the group become those before it (the first workgroup's work, four neighbouring groups to a lane, so that a
+// line is read once: 200k rows 7.2 us, with up to 32 groups in a row per thread 8.0); the others preset the map (rows up to the padding).
 __global__ void __launch_bounds__(kBaseThreads)
     k_box_base(const Box* __restrict__ box_in, const unsigned* __restrict__ totals, int chunks, unsigned* __restrict__ base, int V,
                uint4* __restrict__ map, unsigned* __restrict__ mask, Ctl* ctl) {
@@ -1130,9 +1129,10 @@ __device__ __forceinline__ void load_filter(const unsigned* __restrict__ bits, u
 // in a column (x + dx, y + dy, z - 1 .. z + 1) lie in one run, or in two when the range crosses a multiple of four.  Each row writes its
 // own 27 map entries and its own mask: no entry of another row is touched, so the map needs no preset and the masks no atomics.
 // GPU time of unwaited builds, a table of runs in memory (cleared, filled with an atomic per row, probed with 13.5 reads per row
-// of which a filter in LDS answered some) and so, us: a scan of 30k rows 27, 17.5; 60k 35, 23; 100k 44, 26; 200k 67, 41; 400k
-// 114, 67; a room of 60k 31, 26; 100k 41, 35; 300k 82, 64; 7k rows 16, 15.  What bounds it: the longest bucket's chain of barriers (a
-// block holds up to 100 rows of a surface, and buckets of 256 rows on average up to 700), and launch and publication, 5 us.
+// of which a filter in LDS answered some) and so, us: a scan of 30k rows 28, 17; 60k 36, 25; 100k 44, 28.5; 200k 67, 45; 400k
+// 115, 71; a room of 60k 32, 27; 100k 41.5, 37; 300k 83, 63; 7k rows 18, 14.  What bounds it: round trips behind barriers (the waves of
+// k_probe_buckets wait in 6 of 10 cycles, with 14 reads in flight per CU, 1.6 TB/s and 1 % of the cycles waiting for LDS; a block holds
+// up to 100 rows of a surface, and buckets of 256 rows on average up to 700), and launch and publication, 5 us.
 constexpr int kBlockBits = 3;      // (16 cells a side: 1.5 copies of a row in place of 2, but buckets of up to 1,800 rows: 300k rows of a room 124 us)
 constexpr int kDealThreads = 512;
 constexpr int kDealers = 256;      // workgroups of k_deal_rows at most
@@ -2228,7 +2228,7 @@ int build_submanifold5(spconv_kmap* km, const int4* rows, int64_t N, hipStream_t
 
 // The tables of a stride-2 build are made for as many outputs as inputs, and the kmap keeps them.  Where more than half of that is
 // unused, and more than kKeepBytes of it, the used part moves into buffers of its own size: 300k rows of a room, 75k outputs,
-// 38 MB -> 10 MB, the build 111 -> 126 us (copy 4 us, the rest is a second wait: smaller surpluses are left: 60k rows 78 -> 90).
+// 38 MB -> 10 MB, the build 80 -> 107 us (copy 4 us, the rest is a second wait: smaller surpluses are left: 60k rows 51 -> 82).
 // Without memory for the copy everything stays where it is.
 constexpr int64_t kKeepBytes = 16 << 20;
 int shrink_to_outputs(SideMap& side, int V, DevBuf& coarse_rows, const Ctl* ctl, hipStream_t st) {
