@@ -422,7 +422,9 @@ constexpr int kCellsPerRow = 2048;
 constexpr int64_t kMaxBoxWords = 1ll << 26;
 constexpr int kBoxDealers = 256, kBoxDealThreads = 512;  // workgroups of k_box_deal at most: one per thread of k_box_bits
 constexpr int kMaxChunks = 2048, kMaxGroups = 32768;
-constexpr int kLdsWords = 8192;    // words of a chunk that are in LDS at a time
+constexpr int kLogLdsWords = 13, kLdsWords = 1 << kLogLdsWords;  // words of a chunk that are in LDS at a time: a window
+constexpr int kMaxWindows = 4;     // (a chunk has kMaxBoxWords / kMaxChunks words at most, fewer chunks 400 kCellsPerRow / 32 and a group)
+static_assert(kMaxBoxWords / kMaxChunks <= kMaxWindows * kLdsWords && 400 * kCellsPerRow / 32 + kLdsWords / 2 <= kMaxWindows * kLdsWords, "");
 constexpr int kBaseThreads = 1024;
 static_assert(kMaxBoxWords / kMaxGroups <= kLdsWords && kMaxGroups % (4 * kBaseThreads) == 0 && kMaxChunks % kBaseThreads == 0, "");
 constexpr int kBitsThreads = 1024;  // (256: the chunks at a scanner's place, of thousands of rows, took 22 us)
@@ -432,6 +434,7 @@ struct Box {
   unsigned span[4];  // (up to 65536 each)
   unsigned words;    // of 32 cells; 0: nothing to do
   unsigned shift;    // a group is 2^shift words
+  unsigned windows;  // of a chunk (1 except in sparse boxes)
   unsigned flags;
   __host__ __device__ unsigned groups() const { return (words + (1u << shift) - 1u) >> shift; }
 };
@@ -440,6 +443,9 @@ struct Box {
 // same: with chunks of neighbouring cells, one point far from a plane of 200k rows left nearly all of them to one workgroup.  Whole 3x3x3
 // builds without and with such a point, us, so and in groups: a plane of 200k 74, 395 and 72, 96; a room of 60k 51, 105 and 51, 60; scans
 // of 100k 62, 98 and 61, 70; 400k 103, 138 and 102, 139 (the cells of the larger box, which are written, are the rest).
+// Rows are dealt to the windows of a chunk, so that none is looked at for a window that it is not in, and a crowded window takes its rows
+// dealer by dealer: planes of 203k, 400k and 1M rows without a gap, and such a point, with bits in memory, by chunks of neighbouring cells, in
+// groups alone, and so, us: 145, 422, 174, 115; 188, 768, 285, 174; 318, 1903, 553, 350.
 __host__ __device__ constexpr unsigned most_groups(int chunks) { return chunks * 64 < kMaxGroups ? chunks * 64 : kMaxGroups; }
 // Which chunk a group belongs to, and the i-th group of a chunk: every run of `chunks` groups has one of each chunk, and the runs are
 // turned against each other, so that cells at any regular distance (a wall along the first axis) do not meet in one chunk.
@@ -505,7 +511,7 @@ __global__ void __launch_bounds__(256)
 
 // Every workgroup works out the box; the first one clears the control block, leaves the box for the launches behind, and its flags
 // for the host (the word of host).  Workgroup w then deals rows [w per, w per + per): their cells, chunk by chunk, from entries + w per
-// on; starts[w][chunk] says where each chunk begins.  Where the box is too large, table_slots empty slots of the hash tables take the
+// on; starts[w][chunk, window] says where each begins.  Where the box is too large, table_slots empty slots of the hash tables take the
 // bitmap's place.
 __global__ void __launch_bounds__(kBoxDealThreads)
     k_box_deal(const int* __restrict__ partial, int n_partial, long long max_words, const int4* __restrict__ coords, int n, int per,
@@ -513,7 +519,8 @@ __global__ void __launch_bounds__(kBoxDealThreads)
                Box* box_out, Ctl* ctl, HostResult* host) {
   constexpr int U = 2, kWaves = kBoxDealThreads / 64;
   __shared__ int red[4][9];
-  __shared__ unsigned place[kMaxChunks], wave_sum[kWaves];
+  __shared__ __align__(16) unsigned place[kMaxChunks * kMaxWindows];  // by chunk and window
+  __shared__ unsigned wave_sum[kWaves];
   __shared__ Box s_box;
   const int t = threadIdx.x, lane = t & 63, wib = t >> 6, w = blockIdx.x, chunks = 1 << log_chunks;
   if (t < 256) {
@@ -551,6 +558,8 @@ __global__ void __launch_bounds__(kBoxDealThreads)
     // whole fours (k_box_bits writes them), and lines of 16 words where every chunk has one
     b.shift = 2;
     while (b.groups() > (b.shift < 4 ? (unsigned)chunks : most_groups(chunks))) ++b.shift;
+    const unsigned most = (b.groups() + chunks - 1) >> log_chunks, in_window = kLdsWords >> b.shift;  // groups of a chunk, of a window
+    b.windows = min(max((most + in_window - 1) / in_window, 1u), (unsigned)kMaxWindows);
     s_box = b;
     if (w == 0) {
       *box_out = b;
@@ -589,38 +598,52 @@ __global__ void __launch_bounds__(kBoxDealThreads)
           f(cell_of(box, c[u].x, c[u].y >> 1, c[u].z >> 1, c[u].w >> 1));
     }
   };
-  const unsigned to_group = 5 + box.shift;
-  visit([&](unsigned cell) { atomicAdd(&place[chunk_of(cell >> to_group, log_chunks)], 1u); });
+  const unsigned to_group = 5 + box.shift, to_window = kLogLdsWords - box.shift;
+  const int bins = chunks * (int)box.windows;
+  auto bin_of = [&](unsigned cell) {
+    const unsigned group = cell >> to_group;
+    return chunk_of(group, log_chunks) * box.windows + (group >> log_chunks >> to_window);
+  };
+  if (bins > kMaxChunks) {  // (whole tiles of the sums below)
+    for (int i = kMaxChunks + t; i < (bins + kMaxChunks - 1) / kMaxChunks * kMaxChunks; i += kBoxDealThreads) place[i] = 0;
+    __syncthreads();
+  }
+  visit([&](unsigned cell) { atomicAdd(&place[bin_of(cell)], 1u); });
   __syncthreads();
-  constexpr int S = kMaxChunks / kBoxDealThreads;  // counts -> first places, four per thread
+  constexpr int S = kMaxChunks / kBoxDealThreads;  // counts -> first places, four per thread at a time
   static_assert(S == 4, "");
-  const uint4 v = *reinterpret_cast<const uint4*>(place + t * S);
-  const unsigned mine = v.x + v.y + v.z + v.w;
-  unsigned incl = mine;
-  for (int o = 1; o < 64; o <<= 1) {
-    const unsigned up = __shfl_up(incl, o);
-    if (lane >= o) incl += up;
-  }
-  if (lane == 63) wave_sum[wib] = incl;
-  __syncthreads();
-  unsigned at = incl - mine, all = 0;
+  unsigned all = 0;
+  for (int i0 = 0; i0 < bins; i0 += kMaxChunks) {
+    uint4* const mine_at = reinterpret_cast<uint4*>(place + i0 + t * S);
+    const uint4 v = *mine_at;
+    const unsigned mine = v.x + v.y + v.z + v.w;
+    unsigned incl = mine;
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned up = __shfl_up(incl, o);
+      if (lane >= o) incl += up;
+    }
+    if (i0) __syncthreads();
+    if (lane == 63) wave_sum[wib] = incl;
+    __syncthreads();
+    unsigned at = all + incl - mine;
 #pragma unroll
-  for (int i = 0; i < kWaves; ++i) {
-    if (i < wib) at += wave_sum[i];
-    all += wave_sum[i];
+    for (int i = 0; i < kWaves; ++i) {
+      if (i < wib) at += wave_sum[i];
+      all += wave_sum[i];
+    }
+    *mine_at = make_uint4(at, at + v.x, at + v.x + v.y, at + v.x + v.y + v.z);
   }
-  *reinterpret_cast<uint4*>(place + t * S) = make_uint4(at, at + v.x, at + v.x + v.y, at + v.x + v.y + v.z);
   __syncthreads();
-  unsigned* const my_starts = starts + (long long)w * (chunks + 1);
-  for (int i = t; i < chunks; i += kBoxDealThreads) my_starts[i] = place[i];
-  if (t == 0) my_starts[chunks] = all;
+  unsigned* const my_starts = starts + (long long)w * (bins + 1);
+  for (int i = t; i < bins; i += kBoxDealThreads) my_starts[i] = place[i];
+  if (t == 0) my_starts[bins] = all;
   __syncthreads();
   unsigned* const my_entries = entries + (long long)w * per;
-  visit([&](unsigned cell) { my_entries[atomicAdd(&place[chunk_of(cell >> to_group, log_chunks)], 1u)] = cell; });
+  visit([&](unsigned cell) { my_entries[atomicAdd(&place[bin_of(cell)], 1u)] = cell; });
 }
 
 // One workgroup per chunk: its bits in LDS, from there with their prefixes to memory; base[group] = set bits of the group,
-// totals[chunk] of all of them.  A chunk of more than kLdsWords (a sparse box) takes rounds.  Where the box is too large, the coarse points go through the table instead (log_cap 0: it
+// totals[chunk] of all of them.  The windows of a chunk (of a sparse box) one after the other.  Where the box is too large, the coarse points go through the table instead (log_cap 0: it
 // does not fit there).
 __global__ void __launch_bounds__(kBitsThreads)
     k_box_bits(const Box* __restrict__ box_in, const unsigned* __restrict__ entries, const unsigned* __restrict__ starts, int dealers,
@@ -649,34 +672,52 @@ __global__ void __launch_bounds__(kBitsThreads)
     if (t == 0) totals[blockIdx.x] = 0;
     return;
   }
-  int count = 0;
-  if (t < dealers) {
-    const unsigned* const s = starts + (long long)t * (gridDim.x + 1) + blockIdx.x;
-    const unsigned a = s[0], b = s[1];
-    src[t] = a;
-    count = (int)(b - a);
-  }
-  int incl = count;
-  for (int o = 1; o < 64; o <<= 1) {
-    const int up = __shfl_up(incl, o);
-    if (lane >= o) incl += up;
-  }
-  if (lane == 63) wave_sum[wib] = incl;
-  __syncthreads();
-  if (t < kBoxDealers) {
-    for (int i = 0; i < wib; ++i) incl += wave_sum[i];
-    before[t + 1] = incl;
-    if (t == 0) before[0] = 0;
-  }
   unsigned total = 0;  // of this wave's groups
-  const unsigned per_round = kLdsWords >> shift;
-  for (unsigned g0 = 0; g0 < n_groups; g0 += per_round) {
+  const unsigned in_window = kLdsWords >> shift, windows = box.windows;
+  for (unsigned g0 = 0, window = 0; g0 < n_groups; g0 += in_window, ++window) {
+    int count = 0;
+    if (t < dealers) {
+      const unsigned* const s = starts + (long long)t * (gridDim.x * windows + 1) + blockIdx.x * windows + window;
+      const unsigned a = s[0], b = s[1];
+      src[t] = a;
+      count = (int)(b - a);
+    }
+    int incl = count;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int up = __shfl_up(incl, o);
+      if (lane >= o) incl += up;
+    }
+    if (lane == 63) wave_sum[wib] = incl;
     const unsigned w0 = g0 << shift;
-    const int here = (int)(min(per_round, n_groups - g0) << shift);
+    const int here = (int)(min(in_window, n_groups - g0) << shift);
     for (int i = t; i < here / 4; i += kBitsThreads) reinterpret_cast<uint4*>(bits)[i] = make_uint4(0, 0, 0, 0);
     __syncthreads();
+    if (t < kBoxDealers) {
+      for (int i = 0; i < wib; ++i) incl += wave_sum[i];
+      before[t + 1] = incl;
+      if (t == 0) before[0] = 0;
+    }
+    __syncthreads();
     const int rows = before[kBoxDealers];
-    for (int i0 = t; i0 < rows; i0 += U * kBitsThreads) {
+    auto set = [&](unsigned cell) {
+      const unsigned word = cell >> 5, at = ((word >> shift >> log_chunks) << shift | (word & in_group)) - w0;
+      if (at < (unsigned)here) atomicOr(&bits[at], 1u << (cell & 31));
+    };
+    // Many rows (a crowded window): a wave takes a dealer's at a time, which needs no search for the row's dealer.
+    const bool crowded = rows > 64 * kBoxDealers;
+    for (int w = wib; crowded && w < dealers; w += kWaves) {
+      const int n_here = before[w + 1] - before[w];
+      const unsigned* const mine = entries + (long long)w * per + src[w];
+      for (int i0 = lane; i0 < n_here; i0 += U * 64) {
+        unsigned cell[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) cell[u] = i0 + u * 64 < n_here ? mine[i0 + u * 64] : 0u;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (i0 + u * 64 < n_here) set(cell[u]);
+      }
+    }
+    for (int i0 = t; !crowded && i0 < rows; i0 += U * kBitsThreads) {
       int w[U] = {};  // the dealers: before[w] <= i < before[w + 1]
 #pragma unroll
       for (int o = kBoxDealers / 2; o > 0; o >>= 1)
@@ -690,10 +731,8 @@ __global__ void __launch_bounds__(kBitsThreads)
         cell[u] = i < rows ? entries[(long long)w[u] * per + src[w[u]] + (i - before[w[u]])] : 0u;
       }
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const unsigned word = cell[u] >> 5, at = ((word >> shift >> log_chunks) << shift | (word & in_group)) - w0;
-        if (i0 + u * kBitsThreads < rows && at < (unsigned)here) atomicOr(&bits[at], 1u << (cell[u] & 31));
-      }
+      for (int u = 0; u < U; ++u)
+        if (i0 + u * kBitsThreads < rows) set(cell[u]);
     }
     __syncthreads();
     // a wave takes 256 consecutive words at a time, four to a lane: several groups, or a part of one, which it then takes whole
@@ -2285,7 +2324,7 @@ int build_down2(spconv_kmap* km, const int4* rows, int64_t N, int K, hipStream_t
     SPC_TRY(ctl_buf.alloc(sizeof(Ctl)));
     SPC_TRY(own_rows.alloc((size_t)N * 16));
     SPC_TRY(coarse_rows.alloc((size_t)N * 16));
-    SPC_TRY(small.alloc(base_bytes + sizeof(Box) + partial_bytes + ((size_t)chunks + (size_t)dealers * (chunks + 1)) * sizeof(unsigned)));
+    SPC_TRY(small.alloc(base_bytes + sizeof(Box) + partial_bytes + ((size_t)chunks + (size_t)dealers * (chunks * kMaxWindows + 1)) * sizeof(unsigned)));
     SPC_TRY(cells.alloc((size_t)max_words * sizeof(Cells)));
     SPC_TRY(keys.alloc((size_t)N * 8));
     SPC_TRY(side.map.alloc((size_t)most * V * sizeof(int)));

@@ -517,8 +517,9 @@ def test_stride2_masks_by_rows_of_a_wave(sp, K, n_coarse):
     (5000, (256, 64, 8), 1),           # one group of 16 words to a chunk
     (5000, (258, 66, 10), -3),         # two to some
     (26_000, (64, 64, 8), 3),          # groups of four words, hundreds of rows each
-    (30_000, (700, 900, 500), -9),     # chunks of more words than LDS holds, by a part of a round, and by several
-    (80_000, (1016, 1010, 1160), 0),
+    (30_000, (700, 900, 500), -9),     # chunks of more words than LDS holds: two windows,
+    (80_000, (1016, 1010, 1160), 0),   # three,
+    (25_600, (800, 800, 652), 0),      # four
     (40, (60_000, 60_000, 60_000), -30_000), (2000, (1, 65_000, 64_000), -32_768),  # boxes that are left to the table: one
     (16_383, (3000, 3000, 3000), -7), (16_385, (3000, 3000, 3000), 9),              # or many workgroups, the verdict taken late or early,
     (100_000, (4000, 5000, 700), -2000), (150_000, (9000, 9000, 500), 1),           # keys of more than 32 bits
@@ -835,8 +836,8 @@ def _with_far_point(c, axis, cells_per_row):
 @pytest.mark.parametrize("K", [2, 3])
 @pytest.mark.parametrize("shape", ["plane", "wall", "block"])
 def test_stride2_boxes_with_rows_in_a_small_part(sp, K, shape):
-    """Rows that crowd into a part of the box: a plane or a block with one point far from it, a wall whose cells stand at a regular
-    distance (a multiple of a run of groups) from each other."""
+    """Rows that crowd into a part of the box: a plane or a block with one point far from it (more rows to a window than are taken one by
+    one), a wall whose cells stand at a regular distance (a multiple of a run of groups) from each other."""
     g = np.random.default_rng(K)
     if shape == "plane":
         c = np.stack(np.meshgrid([5], np.arange(-120, 120), np.arange(250), indexing="ij"), -1).reshape(-1, 3)
@@ -852,7 +853,7 @@ def test_stride2_boxes_with_rows_in_a_small_part(sp, K, shape):
 
 def test_stride2_build_with_a_far_point_takes_little_longer(sp):
     """A plane of 200,000 rows and one point far from it: the plane's rows are shared among workgroups (in one of them, the build took 5.3
-    times as long as without the point; 1.3 times as it is)."""
+    times as long as without the point; 1.2 to 1.3 times as it is)."""
     import time
     import torch
     c = np.stack(np.meshgrid([0], [0], np.arange(400), np.arange(500), indexing="ij"), -1).reshape(-1, 4).astype(np.int32)
