@@ -1171,7 +1171,9 @@ __device__ __forceinline__ void load_filter(const unsigned* __restrict__ bits, u
 // of which a filter in LDS answered some) and so, us: a scan of 30k rows 28, 17; 60k 36, 25; 100k 44, 28.5; 200k 67, 45; 400k
 // 115, 71; a room of 60k 32, 27; 100k 41.5, 37; 300k 83, 63; 7k rows 18, 14.  What bounds it: round trips behind barriers (the waves of
 // k_probe_buckets wait in 6 of 10 cycles, with 14 reads in flight per CU, 1.6 TB/s and 1 % of the cycles waiting for LDS; a block holds
-// up to 100 rows of a surface, and buckets of 256 rows on average up to 700), and launch and publication, 5 us.
+// up to 100 rows of a surface, and buckets of 256 rows on average up to 700), and launch and publication, 5 us.  Behind the table only on
+// full grids, whose blocks have 512 rows and as many copies, so that few workgroups have all the work: waited builds of cubes of 27k rows 41,
+// 49; 300k 112, 149; 2.1M 711, 556; a full plane of 400k 111, 92.
 constexpr int kBlockBits = 3;      // (16 cells a side: 1.5 copies of a row in place of 2, but buckets of up to 1,800 rows: 300k rows of a room 124 us)
 constexpr int kDealThreads = 512;
 constexpr int kDealers = 256;      // workgroups of k_deal_rows at most
